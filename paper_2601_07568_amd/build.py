@@ -24,21 +24,28 @@ def _hipcc() -> str:
 
 
 # Kernels that wait on their own count of outstanding memory instructions (s_waitcnt vmcnt(n) against copies
-# straight into LDS).  A spill to scratch between such a kernel's first and last copy would add instructions the
-# count does not know (and stores may complete out of order with the loads), so the build looks at the generated code
-# and refuses it.  Scratch traffic before the first copy or after the loop's final wait is harmless.
-COUNTED = {"kernels_gemm.hip": ("k_gemm_t256", "k_gemm_ts"), "kernels_attention.hip": ("k_attn_dl",)}
+# straight into LDS).  A spill to scratch where such counts are used would add instructions the count does not know
+# (and stores may complete out of order with the loads), so the build looks at the generated code and refuses it.
+# The window is from the first to the last copy or, where the kernel waits for everything in front of and behind its
+# loop of matrix instructions ("mfma"), from the first to the last of those.
+COUNTED = {"kernels_gemm.hip": {"k_gemm_tile": "mfma"}, "kernels_attention.hip": {"k_attn_dl": "copies"}}
+
+
+def _is_lds_copy(line: str) -> bool:
+    return "global_load_lds" in line or ("buffer_load" in line and line.split(";")[0].rstrip().endswith(" lds"))
 
 
 def _check_counted_loops(src: str, asm: str) -> None:
     name, body = None, []
+
     def check():
-        if name is None or not any(k in name for k in COUNTED[src]):
+        kind = next((v for k, v in COUNTED[src].items() if name is not None and k in name), None)
+        if kind is None:
             return
-        copies = [i for i, l in enumerate(body) if "global_load_lds" in l]
-        if not copies:
+        marks = [i for i, l in enumerate(body) if (_is_lds_copy(l) if kind == "copies" else "v_mfma" in l)]
+        if not marks:
             return
-        for l in body[copies[0]:copies[-1] + 1]:
+        for l in body[marks[0]:marks[-1] + 1]:
             if "scratch_" in l:
                 raise RuntimeError(f"{src}: kernel {name} spills to scratch between its copies into LDS "
                                    f"({l.strip()}); its explicit memory-instruction counts do not allow that")

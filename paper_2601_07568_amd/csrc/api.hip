@@ -56,8 +56,7 @@ static bool build_map(const dllm_config* c, Workspace* m) {
   m->vpack = take(((size_t)m->tpad * dkv + 64) * es);
   m->cu_pad = take(((size_t)c->max_batch + 1) * 4);
   m->o = take((t_max + 16) * (dq + 128) * es);
-  m->g_bytes = t_max * c->d_ff * 4;
-  m->g = take(m->g_bytes);
+  m->g = take(t_max * c->d_ff * 4);
   m->u = take(t_max * c->d_ff * 4);
   m->h = take((t_max + 16) * ((size_t)c->d_ff + 128) * es);
   m->rope_cos = take(t_max * half * 4);
@@ -143,7 +142,7 @@ extern "C" int dllm_create(dllm_ctx** out, const dllm_config* cfg, const dllm_we
   if (cfg->dtype == DLLM_BF16) {
     // raising two kernels' LDS limits; a failure (e.g. no device in this process) is not an error of the call: the
     // launchers check the flags these leave and take the kernels that need no raised limit
-    const hipError_t e1 = init_gemm_t256();      // without it the 128-row kernels serve every size
+    const hipError_t e1 = init_gemm_tiles();     // without it the 128-row kernels serve every size
     const hipError_t e2 = init_attn_kernels();   // without it every wave of the batch-1 attention writes its own partial
     // such a failure must not surface later as the "last error" of an unrelated launch
     if (e1 != hipSuccess || e2 != hipSuccess) (void)hipGetLastError();
@@ -426,9 +425,8 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
     } else {
       if (big_mfma) {
         ProfScope p(c, s, 2, 2.0 * T * 2.0 * f.d_ff * f.d_model);
-        // (the float gate buffer of the generic path is free here: scratch for the K-split tail tiles)
         TRY(launch_gemm_swiglu(s, c->ws + c->map.xn, L.w_gate, L.w_up, c->ws + c->map.h, T, f.d_ff, f.d_model,
-                               WSP(c, rscale, float), c->rows_dev, WSP(c, g, float), c->map.g_bytes), "gate_up");
+                               WSP(c, rscale, float), c->rows_dev), "gate_up");
       } else {
         TRY(gemm_any(c, s, c->ws + c->map.xn, L.w_gate, c->ws + c->map.g, T, f.d_ff, f.d_model, EPI_STORE_F32, true), "w_gate");
         TRY(gemm_any(c, s, c->ws + c->map.xn, L.w_up, c->ws + c->map.u, T, f.d_ff, f.d_model, EPI_STORE_F32, true), "w_up");

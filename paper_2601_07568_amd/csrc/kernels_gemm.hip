@@ -29,14 +29,14 @@ struct LgArgs {
   void* C3;                // QKV: bfloat16 values
   int N2, tiles_n1, tiles_n2;   // QKV: width of the key/value projections, column tiles of q and of k
   int k_per;               // RESID: K range of one split (multiple of LG_BK); gridDim.y splits
-  int k_splits;            // 256-row kernel: number of K splits (its grid is flat)
+  int k_splits;            // tile kernel: number of K splits (its grid is flat)
+  int group_m;             // tile kernel: most row tiles of a group (order of the work items)
   float* delta;            // RESID: products of splits 1.. go to delta[(split - 1) * delta_stride + m * N + n]
   int64_t delta_stride;
   const int32_t* m_dev;    // optional device row count
   const float* rscale;     // optional [M]: A holds x * gain rounded to bfloat16; the row's normalisation factor
                            // multiplies the float accumulators (every epilogue but RESID, whose input is not a norm's)
   int M, N, K, tiles_m, tiles_n;
-  float* tail;             // 256-row SWIGLU: scratch for the accumulators of K-split tail tiles, or nullptr
   float* part;             // LMSTATS: [rows, n_parts, 4]
   int n_parts;
   int32_t mask_id;
@@ -281,562 +281,431 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(const LgArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// The same products for at least 256 token rows, arranged for one wave per SIMD: a workgroup of 4
-// waves owns a 256 x 256 tile, each wave 128 x 128 of it as 4 x 4 instructions of 32 x 32 x 16 with
-// the 256 accumulator registers in the accumulation file.  Both operands stay row-major in memory
-// and are copied straight into LDS (no register pass) in 32-deep K stages of a 4-stage ring, 16 rows
-// x 64 bytes per wave instruction, the 16-byte pieces of a row xor-ed with bits 2..3 of the row so
-// that a fragment read (32 rows x one piece) touches every bank once.  Per stage a wave issues its
-// share of the copies for three stages ahead and reads the next operands between the products of
-// the current ones; the only wait on memory is "the stage after this one has landed", once per
-// stage, in the middle of the products.
-constexpr int T2_NS = 4, T2_STAGE = 32768, T2_LDS = T2_NS * T2_STAGE;
-#define T2_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
+// The same products for more than 64 token rows.  A workgroup of 4 waves, one per SIMD, owns a tile of 64*TM token
+// rows x 64*TN weight rows, each wave a quarter of it as TM x TN products of 32 x 32 x 16.  Both operands stay
+// row-major in memory and are copied straight into LDS (no register pass) in 64-deep K stages: 64 bfloat16 values are
+// one 128-byte cache line, so a copy instruction fetches 8 whole lines.  (With 32-deep stages every copy asked for
+// half lines: twice the requests to the L2 for the same bytes, 34 M against 17 M on a 1024 x 37888 x 3584 product, and
+// the copies, not the products, set the pace: 0.95 against 1.03 PFLOP/s there, 1.06 against 1.28 at 16384 rows.)
+// LDS holds NSA stages of the activations and NSW of the weights.  The 16-byte pieces of a row are xor-ed with
+// (row / 2) % 8, so the 16 lanes an LDS read serves at a time touch every bank once.
+//
+// The copies run NSA-1 and NSW-1 stages ahead of the products and on into the workgroup's next tile, so neither the
+// ring's fill nor the epilogue's stores leave the memory idle.  Every copy and operand read has its place between two
+// products (sched_barrier keeps it there); the only wait on memory is "the stage after this one has landed", once per
+// stage, together with the barrier that also frees this stage's buffers.
+//
+// The activations are the first operand, so a lane holds one weight row and consecutive registers hold token rows;
+// the weight rows of a wave are dealt to its tiles (LDS row i*32 + c holds feature TN*c + i) so that a lane's TN tiles
+// are TN consecutive features: a row's stores are whole cache lines.  (LMSTATS: weights first, a lane holds one token.)
+typedef __amdgpu_buffer_rsrc_t gt_rsrc;
+typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+#define GT_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
 
-__device__ __forceinline__ void t2_copy16(const void* g, void* l) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                   (__attribute__((address_space(3))) void*)l, 16, 0, 0);
-}
+template <int TM, int TN, int NSA, int NSW>
+struct GtGeom {
+  static_assert(NSA >= 2 && NSA <= NSW, "the weights run at least as far ahead as the activations");
+  static constexpr int BM = 64 * TM, BN = 64 * TN, A_BYTES = BM * 128, W_BYTES = BN * 128;
+  static constexpr int CA = BM / 32, CW = BN / 32;              // copies of a wave and stage (8 rows x 128 bytes each)
+  static constexpr int LDS = NSA * A_BYTES + NSW * W_BYTES;
+  static constexpr int PER_CU = LDS <= 80 * 1024 ? 2 : 1;       // workgroups that fit a CU
+  static constexpr int NPOS = 4 * TM * TN;                      // products of a wave and stage
+  static constexpr int PB = 3 * TM * TN;                        // the barrier comes behind this product
+  // copy c of a stage's group (activations first) goes behind this product, counted on from the barrier that frees
+  // its buffers; positions past the stage's end wrap into the next stage
+  static constexpr int raw_pos(int c) { return PB + 1 + c * (NPOS - 1) / (CA + CW); }
+  static constexpr int pos(int c) { return raw_pos(c) % NPOS; }
+  static constexpr int early() {                                // copies of a group in front of its own stage
+    int n = 0;
+    for (int c = 0; c < CA + CW; ++c) n += raw_pos(c) < NPOS;
+    return n;
+  }
+  // copies issued behind those of stage s+1 that may still be in flight at the barrier in front of stage s+1
+  static constexpr int FLY_A = CW + (NSA - 2) * (CA + CW), FLY_W = (NSW - 2) * (CA + CW);
+  static constexpr int IN_FLIGHT = FLY_A < FLY_W ? FLY_A : FLY_W;
+  static_assert(IN_FLIGHT < 64, "what the memory counter holds");
+};
 
-// The last, partly filled round of the persistent workgroups: when the tiles do not divide by the workgroups, the
-// tiles of the last round are split along K so that every workgroup gets a share of them (at most T2_TAIL_SPLITS
-// shares per tile); their accumulators go to scratch in register order and k_swiglu_tail adds the shares and applies
-// the epilogue.  Derived from the device-resident row count, the same way in both kernels.
-constexpr int T2_TAIL_SPLITS = 3, T2_TAIL_FLOATS = 256 * 256;
-struct T2Tail { int n_full, n_tail, splits; };
-__device__ __forceinline__ T2Tail t2_tail_plan(int n_tiles, int n_wg, bool enabled) {
-  T2Tail t{n_tiles, 0, 1};
-  if (!enabled || n_tiles <= n_wg) return t;
-  const int nf = (n_tiles / n_wg) * n_wg, nt = n_tiles - nf;
-  if (nt == 0) return t;
-  int sp = n_wg / nt;
-  sp = sp > T2_TAIL_SPLITS ? T2_TAIL_SPLITS : sp;
-  if (sp < 2) return t;
-  t.n_full = nf; t.n_tail = nt; t.splits = sp;
-  return t;
-}
-
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_t256(const LgArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char t2_smem[];
-  unsigned char* smem = t2_smem;
-  constexpr int TILE_N = (EPI == LG_SWIGLU) ? 128 : 256;      // output features of a tile
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+template <int EPI, int TM, int TN, int NSA, int NSW>
+__device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
+  using G = GtGeom<TM, TN, NSA, NSW>;
+  constexpr int BM = G::BM, BN = G::BN, CA = G::CA, CW = G::CW;
+  constexpr bool SWIGLU = EPI == LG_SWIGLU, STATS = EPI == LG_LMSTATS;
+  constexpr int TILE_N = SWIGLU ? BN / 2 : BN;                  // output features of a tile
+  static_assert(!SWIGLU || TN % 2 == 0, "gate and up tiles come in pairs");
+  static_assert(!STATS || TN % 2 == 0, "64 columns per partial");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char gt_smem[];
+  unsigned char* const sA = gt_smem;
+  unsigned char* const sW = gt_smem + NSA * G::A_BYTES;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int M = a.M;
   if (a.m_dev) { const int md = *a.m_dev; M = md < M ? md : M; }
   const int N = a.N, K = a.K;
   const int wm = w & 1, wn = w >> 1;
   const int r = lane & 31, h = lane >> 5;
-  // Persistent workgroups, one per CU: the work items (K split, column tile, row tile - row tile
-  // fastest, only row tiles that hold rows) are dealt in contiguous runs to the 8 XCDs (workgroups
-  // go round-robin to XCDs), inside an XCD round-robin to its workgroups, so the row tiles that
-  // share a weight tile run at the same time next to the same L2.
-  const int tiles_m = (M + 255) / 256;
-  const int n_tiles = tiles_m * a.tiles_n;
-  // two passes over the work items, each dealt the same way: the whole tiles (all K splits of the launch), then the
-  // K shares of the tail tiles (SiLU*up launches with scratch only)
-  const T2Tail tp = t2_tail_plan(n_tiles, gridDim.x, EPI == LG_SWIGLU && a.tail != nullptr);
-  const int n_items_a = tp.n_full * a.k_splits, n_items_b = tp.n_tail * tp.splits;
-  const int per_xcd_a = (n_items_a + 7) / 8, per_xcd_b = (n_items_b + 7) / 8;
-  const int step = gridDim.x >> 3;
-  const int iters_a = (per_xcd_a + step - 1) / step, iters_b = (per_xcd_b + step - 1) / step;
-  for (int it = 0; it < iters_a + iters_b; ++it) {
-  const bool is_tail = it >= iters_a;
-  const int iw = (blockIdx.x >> 3) + (is_tail ? it - iters_a : it) * step;
-  const int per_xcd = is_tail ? per_xcd_b : per_xcd_a;
-  const int item = (blockIdx.x & 7) * per_xcd + iw;
-  if (iw >= per_xcd || item >= (is_tail ? n_items_b : n_items_a)) continue;
-  int split, tile;
-  if (is_tail) { split = item / tp.n_tail; tile = tp.n_full + (item - split * tp.n_tail); }
-  else { split = item / tp.n_full; tile = item - split * tp.n_full; }
-  const int tn = tile / tiles_m, tm = tile - tn * tiles_m;
-  const int m0 = tm * 256, n0 = tn * TILE_N;
-  int k_begin = 0, k_end = K;
-  if constexpr (EPI == LG_RESID || EPI == LG_QKV) {
-    k_begin = split * a.k_per;
-    k_end = k_begin + a.k_per < K ? k_begin + a.k_per : K;
-  }
-  if (is_tail) {
-    const int per = ((K / 32) + tp.splits - 1) / tp.splits * 32;
-    k_begin = split * per;
-    k_end = k_begin + per < K ? k_begin + per : K;
-  }
-  // the ring is free once every wave has read the previous item's last operands
-  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  // copies: instruction q of this wave covers rows (w*4 + q%4)*16 .. +15 of the token part (q < 4) or of
-  // the weight part; lane p: row p/4, LDS piece p%4 holds source piece (p%4) ^ ((row>>2)&3)
-  const bf16_t* gsrc[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = (w * 4 + (q & 3)) * 16 + (lane >> 2);
-    const int piece = (lane & 3) ^ ((r >> 2) & 3);
-    if (q < 4) {
-      int row = m0 + r; row = row < M ? row : M - 1;
-      gsrc[q] = a.A + (int64_t)row * K + piece * 8;
-    } else if constexpr (EPI == LG_SWIGLU) {
-      // a wave's four weight tiles are gate, gate, up, up of the same 64 features
-      int row = n0 + (r >> 7) * 64 + ((r >> 5) & 1) * 32 + (r & 31); row = row < N ? row : N - 1;
-      gsrc[q] = (((r >> 6) & 1) ? a.W2 : a.W) + (int64_t)row * K + piece * 8;
-    } else if constexpr (EPI == LG_QKV) {
-      // three projections stacked along the features: q rows [0, N), then k and v with N2 rows each
-      // (all multiples of 256, so a tile belongs to one of them)
-      const int row = n0 + r;
-      const bf16_t* wsel = row < N ? a.W : (row < N + a.N2 ? a.W2 : a.W3);
-      const int lrow = row < N ? row : (row < N + a.N2 ? row - N : row - N - a.N2);
-      gsrc[q] = wsel + (int64_t)lrow * K + piece * 8;
-    } else {
-      int row = n0 + r; row = row < N ? row : N - 1;
-      gsrc[q] = a.W + (int64_t)row * K + piece * 8;
+  // Persistent workgroups: the work items (K split, then groups of at most group_m row tiles, in a group column by
+  // column) are dealt in contiguous runs to the 8 XCDs (workgroups go round-robin to XCDs), inside an XCD round-robin
+  // to its workgroups: what runs at the same time next to one L2 shares its rows and columns (with 64 row tiles and
+  // no groups an XCD's workgroups share one weight tile and nothing else: 1.10 against 1.20 PFLOP/s at K = 18944).
+  const int tiles_m = (M + BM - 1) / BM;
+  const int n_tiles = tiles_m * a.tiles_n, n_items = n_tiles * a.k_splits;
+  const int per_xcd = (n_items + 7) / 8, step = gridDim.x >> 3;
+  const int n_grp = (tiles_m + a.group_m - 1) / a.group_m, gm_full = n_grp > 0 ? (tiles_m + n_grp - 1) / n_grp : 1;
+  struct Item { int split, tm, tn, k_begin, k_end; bool ok; };
+  auto item_at = [&](int it) -> Item {
+    Item t{0, 0, 0, 0, K, false};
+    const int iw = (blockIdx.x >> 3) + it * step;
+    const int item = (blockIdx.x & 7) * per_xcd + iw;
+    if (iw >= per_xcd || item >= n_items) return t;
+    t.split = item / n_tiles;
+    const int tile = item - t.split * n_tiles;
+    const int gi = tile / (gm_full * a.tiles_n), rem = tile - gi * gm_full * a.tiles_n;
+    const int gm = tiles_m - gi * gm_full < gm_full ? tiles_m - gi * gm_full : gm_full;
+    t.tn = rem / gm;
+    t.tm = gi * gm_full + rem - t.tn * gm;
+    t.k_begin = t.split * a.k_per;
+    t.k_end = t.k_begin + a.k_per < K ? t.k_begin + a.k_per : K;
+    t.ok = true;
+    return t;
+  };
+  // descriptors that end with the matrix: rows of a tile past the last one are not read (nor, in the epilogue, written)
+  auto rsrc = [&](const void* base, int64_t bytes) -> gt_rsrc {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+  };
+  auto rsrc_a = [&](const Item& t) -> gt_rsrc {
+    const int rows = M - t.tm * BM < BM ? M - t.tm * BM : BM;
+    return rsrc(a.A + (int64_t)t.tm * BM * K, (int64_t)rows * K * 2);
+  };
+  auto rsrc_w = [&](const Item& t) -> gt_rsrc {
+    const int n0 = t.tn * TILE_N;
+    const bf16_t* base = a.W;
+    int row = n0, rows = N - n0 < TILE_N ? N - n0 : TILE_N;
+    if constexpr (EPI == LG_QKV) {
+      // three projections stacked along the features: q rows [0, N), then k and v with N2 rows each (all multiples of
+      // the tile width, so a tile belongs to one of them)
+      if (n0 >= N) { base = n0 < N + a.N2 ? a.W2 : a.W3; row = n0 < N + a.N2 ? n0 - N : n0 - N - a.N2; }
+      rows = BN;
     }
-  }
-  // fragment reads: lane (r = l%32, h = l/32), k-step s of a stage: piece 2s + h
-  int offA[2], offW[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int slotp = ((2 * ks + h) ^ ((r >> 2) & 3)) * 16;
-    offA[ks] = (wm * 128 + r) * 64 + slotp;
-    offW[ks] = 16384 + (wn * 128 + r) * 64 + slotp;
-  }
-  f32x16 acc[4][4];   // [weight tile][token tile]
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    if constexpr (SWIGLU) {
+      if (w & 1) base = a.W2;                                   // a wave copies gate rows or up rows
+    }
+    return rsrc(base + (int64_t)row * K, (int64_t)rows * K * 2);
+  };
+  Item cur = item_at(0);
+  if (!cur.ok) return;
+  int it_next = 1;
+  Item nxt = item_at(it_next);
+  gt_rsrc ra = rsrc_a(cur), rw = rsrc_w(cur), rna = rsrc_a(nxt.ok ? nxt : cur), rnw = rsrc_w(nxt.ok ? nxt : cur);
+  int ka = cur.k_begin, kw = cur.k_begin, kea = cur.k_end, kew = cur.k_end;
 
-  const int ns = (k_end - k_begin) / 32;      // K ranges are multiples of 32 (checked on the host)
-#define T2_MMA(ks, i, j)                                                                                          \
-  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw[ks][i]),                    \
-                                                      __builtin_bit_cast(bf16x8, fa[ks][j]), acc[i][j], 0, 0, 0)
-  u32x4 fa[2][4], fw[2][4];
+  // copies: instruction q of wave w fills LDS rows (w*C + q)*8 .. +7; lane l holds piece l%8 of row l/8
+  const int l8 = lane >> 3, piece = (lane & 7) ^ (l8 >> 1);     // (odd q: the row's bit 3 flips bit 2 of the piece)
+  constexpr int FS = STATS ? 1 : (SWIGLU ? TN / 2 : TN);        // features between consecutive LDS rows of a tile
+  const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = vA0 ^ 64;
+  const int vW0 = l8 * FS * K * 2 + piece * 16, vW1 = vW0 ^ 64;
+  auto w_row = [&](int q) -> int {                              // weight row of the instruction's first LDS row
+    const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
+    if constexpr (STATS) return R;
+    else if constexpr (SWIGLU) return hw * 16 * TN + (TN / 2) * c + i % (TN / 2);
+    else return hw * 32 * TN + TN * c + i;
+  };
+  auto copy_a = [&](int slot, int q) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(sA + slot * G::A_BYTES + (w * CA + q) * 1024),
+                                             16, (q & 1) ? vA1 : vA0, ka * 2 + q * 16 * K, 0, 0);
+  };
+  auto copy_w = [&](int slot, int q) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (w * CW + q) * 1024),
+                                             16, (q & 1) ? vW1 : vW0, kw * 2 + w_row(q) * 2 * K, 0, 0);
+  };
+  // the copies' next stage: of this item, then of the next one; past the last one the last stage again (never used)
+  auto adv_a = [&]() {
+    ka += 64;
+    if (ka >= kea) {
+      if (nxt.ok) { ra = rna; ka = nxt.k_begin; kea = nxt.k_end; } else ka -= 64;
+    }
+  };
+  auto adv_w = [&]() {
+    kw += 64;
+    if (kw >= kew) {
+      if (nxt.ok) { rw = rnw; kw = nxt.k_begin; kew = nxt.k_end; } else kw -= 64;
+    }
+  };
 #pragma unroll
-  for (int st = 0; st < T2_NS - 1; ++st) {
-    const int kd = k_begin + (st < ns ? st : ns - 1) * 32;
+  for (int s = 0; s < NSW - 1; ++s) {
+    if (s < NSA - 1) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) t2_copy16(gsrc[q] + kd, smem + st * T2_STAGE + (q >> 2) * 16384 + (w * 4 + (q & 3)) * 1024);
+      for (int q = 0; q < CA; ++q) copy_a(s, q);
+      adv_a();
+    }
+#pragma unroll
+    for (int q = 0; q < CW; ++q) copy_w(s, q);
+    adv_w();
   }
-  __builtin_amdgcn_s_waitcnt(T2_VMCNT(8 * (T2_NS - 2)));
+  constexpr int EARLY = G::early();
+  static_assert(EARLY < CA, "the copies in front of their own stage are activations, not all of them");
+#pragma unroll
+  for (int q = 0; q < EARLY; ++q) copy_a(NSA - 1, q);
+  __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));
   __builtin_amdgcn_s_barrier();
+  // operand reads: lane (r, h) of k-step ks takes piece 2*ks + h of row r
+  int oA[4], oW[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    fa[0][j] = *(const u32x4*)(smem + offA[0] + j * 2048);
-    fw[0][j] = *(const u32x4*)(smem + offW[0] + j * 2048);
+  for (int ks = 0; ks < 4; ++ks) {
+    const int p = ((h ^ ((r >> 1) & 7)) * 16) ^ (ks * 32);
+    oA[ks] = (wm * (BM / 2) + r) * 128 + p;
+    oW[ks] = (wn * (BN / 2) + r) * 128 + p;
   }
-  for (int st = 0; st < ns; ++st) {
-    const unsigned char* base = smem + (st % T2_NS) * T2_STAGE;
-    const unsigned char* nbase = smem + ((st + 1) % T2_NS) * T2_STAGE;
-    unsigned char* dbase = smem + ((st + T2_NS - 1) % T2_NS) * T2_STAGE;   // freed by the barrier of the stage before
-    const int sn = st + T2_NS - 1;
-    const int kd = k_begin + (sn < ns ? sn : ns - 1) * 32;                  // past the end: a repeat into a free slot
-    // k-step 0: in the shadow of its products request the ring's next stage and read k-step 1's operands
+  u32x4 fa[2][TM], fw[2][TN];
+  auto rd = [&](int b, int n, const unsigned char* pa, const unsigned char* pw) {   // in the order the products need them
+    if (n == 0) fw[b][0] = *(const u32x4*)pw;
+    else if (n <= TM) fa[b][n - 1] = *(const u32x4*)(pa + (n - 1) * 4096);
+    else fw[b][n - TM] = *(const u32x4*)(pw + (n - TM) * 4096);
+  };
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      __builtin_amdgcn_sched_barrier(0);
-      T2_MMA(0, i, 0); T2_MMA(0, i, 1); T2_MMA(0, i, 2); T2_MMA(0, i, 3);
-      t2_copy16(gsrc[2 * i] + kd, dbase + ((2 * i) >> 2) * 16384 + (w * 4 + ((2 * i) & 3)) * 1024);
-      t2_copy16(gsrc[2 * i + 1] + kd, dbase + ((2 * i + 1) >> 2) * 16384 + (w * 4 + ((2 * i + 1) & 3)) * 1024);
-      fa[1][i] = *(const u32x4*)(base + offA[1] + i * 2048);
-      fw[1][i] = *(const u32x4*)(base + offW[1] + i * 2048);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // k-step 1: wait until every wave's copies of the next stage have landed (all but the two
-    // youngest stages of this wave's own), then read that stage's first operands
+  for (int n = 0; n < TM + TN; ++n) rd(0, n, sA + oA[0], sW + oW[0]);
+  int sa = 0, sw = 0;                                           // buffers of the current stage
+  for (;;) {                                                    // work items
+    f32x16 acc[TN][TM];                                         // [weight tile][token tile]
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      __builtin_amdgcn_sched_barrier(0);
-      T2_MMA(1, i, 0); T2_MMA(1, i, 1); T2_MMA(1, i, 2); T2_MMA(1, i, 3);
-      if (i == 0) {
-        __builtin_amdgcn_s_waitcnt(T2_VMCNT(8 * (T2_NS - 2)));
-        __builtin_amdgcn_s_barrier();
-      }
-      if (i == 1) { fa[0][0] = *(const u32x4*)(nbase + offA[0]); fa[0][1] = *(const u32x4*)(nbase + offA[0] + 2048); fa[0][2] = *(const u32x4*)(nbase + offA[0] + 4096); }
-      if (i == 2) { fa[0][3] = *(const u32x4*)(nbase + offA[0] + 6144); fw[0][0] = *(const u32x4*)(nbase + offW[0]); fw[0][1] = *(const u32x4*)(nbase + offW[0] + 2048); }
-      if (i == 3) { fw[0][2] = *(const u32x4*)(nbase + offW[0] + 4096); fw[0][3] = *(const u32x4*)(nbase + offW[0] + 6144); }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#undef T2_MMA
-  __builtin_amdgcn_s_waitcnt(T2_VMCNT(0));   // the ring's trailing repeats must not outlive the workgroup
-
-  if (EPI == LG_SWIGLU && is_tail) {
-    // a K share of a tail tile: the raw accumulators, in register order (a lane's 16 floats contiguous)
-    float* dst = a.tail + ((int64_t)split * tp.n_tail + (tile - tp.n_full)) * T2_TAIL_FLOATS;
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int j = 0; j < TM; ++j)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        f32x4* d = (f32x4*)(dst + ((((w * 4 + i) * 4 + j) * 64 + lane) << 4));
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    const int ns = (cur.k_end - cur.k_begin) / 64;              // K ranges are multiples of 64, at least two stages
+    for (int st = 0; st < ns; ++st) {
+      const int na = sa + 1 == NSA ? 0 : sa + 1, nw = sw + 1 == NSW ? 0 : sw + 1;
+      const int fa_slot = sa == 0 ? NSA - 1 : sa - 1, fw_slot = sw == 0 ? NSW - 1 : sw - 1;   // the stage before: free
+      const unsigned char *bA = sA + sa * G::A_BYTES, *bW = sW + sw * G::W_BYTES;
+      const unsigned char *cA = sA + na * G::A_BYTES, *cW = sW + nw * G::W_BYTES;
+      if (st == 0) __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));     // the last item's stores are not to count among the copies
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4)
-          d[e4] = f32x4{acc[i][j][e4 * 4], acc[i][j][e4 * 4 + 1], acc[i][j][e4 * 4 + 2], acc[i][j][e4 * 4 + 3]};
-      }
-    continue;
-  }
-  // lane holds token column l%32 of token tile j; features (e/4)*8 + (l/32)*4 + e%4 of weight tile i
-  if constexpr (EPI == LG_LMSTATS) {
+      for (int ks = 0; ks < 4; ++ks) {
+        const int b = ks & 1;
+        const unsigned char* pa = ks < 3 ? bA + oA[(ks + 1) & 3] : cA + oA[0];
+        const unsigned char* pw = ks < 3 ? bW + oW[(ks + 1) & 3] : cW + oW[0];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + wm * 128 + j * 32 + r;
-      const float rs = (a.rscale && m < M) ? a.rscale[m] : 1.0f;
+        for (int i = 0; i < TN; ++i)
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {      // 64 columns per partial
-        // the lane's 32 logits of this partial: maximum first (columns ascend, so the first of equal
-        // maxima is the lowest), then the two sums against it
-        float mx = -DEV_INF;
-        int ix = 0x7fffffff;
+          for (int j = 0; j < TM; ++j) {
+            const int idx = i * TM + j, p = ks * TM * TN + idx;
+            __builtin_amdgcn_sched_barrier(0);
+            acc[i][j] = STATS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw[b][i]), __builtin_bit_cast(bf16x8, fa[b][j]), acc[i][j], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[b][j]), __builtin_bit_cast(bf16x8, fw[b][i]), acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (p == G::PB) {
+              // this wave's copies of the next stage are in and its reads of this one are back (lgkmcnt(0)); behind the
+              // barrier everybody's are
+              __builtin_amdgcn_s_waitcnt(GT_VMCNT(G::IN_FLIGHT) & 0xF0FF);
+              __builtin_amdgcn_s_barrier();
+            }
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+            for (int n = 0; n < TM + TN; ++n)
+              if (n * (TM * TN) / (TM + TN) == idx) rd(b ^ 1, n, pa, pw);
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int i = half * 2 + ii;
-            const int n = n0 + wn * 128 + i * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
-            const float z = acc[i][j][e] * rs;
-            if (n < N && n != a.mask_id && z > mx) { mx = z; ix = n; }
+            for (int c = 0; c < CA + CW; ++c)
+              if (G::pos(c) == p) {
+                if (c < CA) copy_a(p > G::PB ? sa : fa_slot, c);   // behind the barrier: into this stage's own buffer
+                else copy_w(fw_slot, c - CA);
+              }
           }
-        RowStat st;
-        st.init();
-        if (ix != 0x7fffffff) {
-          float se = 0.f, sz = 0.f;
+        if (G::pos(CA - 1) / (TM * TN) == ks) adv_a();
+        if (G::pos(CA + CW - 1) / (TM * TN) == ks) adv_w();
+      }
+      sa = na;
+      sw = nw;
+    }
+
+    const int m0 = cur.tm * BM, n0 = cur.tn * TILE_N, split = cur.split;
+    const int rows = M - m0 < BM ? M - m0 : BM;
+    const gt_rsrc rr = rsrc(a.rscale + m0, (EPI != LG_RESID && a.rscale) ? (int64_t)rows * 4 : 0);
+    if constexpr (STATS) {
+      // lane holds token column l%32 of token tile j; features (e/4)*8 + (l/32)*4 + e%4 of weight tile i
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        const int m = m0 + wm * 32 * TM + j * 32 + r;
+        const float rs = (a.rscale && m < M) ? a.rscale[m] : 1.0f;
+#pragma unroll
+        for (int half = 0; half < TN / 2; ++half) {      // 64 columns per partial
+          // the lane's 32 logits of this partial: maximum first (columns ascend, so the first of equal
+          // maxima is the lowest), then the two sums against it
+          __builtin_amdgcn_sched_barrier(0);
+          const int nb = n0 + wn * 32 * TN + half * 64;
+          float mx = -DEV_INF;
+          int ix = 0x7fffffff;
 #pragma unroll
           for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-              const int i = half * 2 + ii;
-              const int n = n0 + wn * 128 + i * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
-              const float z = acc[i][j][e] * rs;
-              const float ex = (n < N && n != a.mask_id) ? __builtin_amdgcn_exp2f((z - mx) * 1.4426950408889634f) : 0.f;
-              se += ex;
-              sz = fmaf(ex, z, sz);
+              const int n = nb + ii * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+              const float z = acc[half * 2 + ii][j][e] * rs;
+              if (n < N && n != a.mask_id && z > mx) { mx = z; ix = n; }
             }
-          st.m = mx; st.idx = ix; st.s = se; st.t = sz;
-        }
-        const float m2 = __shfl_xor(st.m, 32, 64), s2 = __shfl_xor(st.s, 32, 64), t2 = __shfl_xor(st.t, 32, 64);
-        const int i2 = __shfl_xor(st.idx, 32, 64);
-        st.merge(m2, i2, s2, t2);
-        const int nb = n0 + wn * 128 + half * 64;
-        if (h == 0 && m < M && nb < N) {
-          float* o = a.part + ((int64_t)m * a.n_parts + nb / 64) * 4;
-          *(f32x4*)o = f32x4{st.m, __int_as_float(st.idx), st.s, st.t};
+          RowStat st;
+          st.init();
+          if (ix != 0x7fffffff) {
+            float se = 0.f, sz = 0.f;
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) {
+                const int n = nb + ii * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+                const float z = acc[half * 2 + ii][j][e] * rs;
+                const float ex = (n < N && n != a.mask_id) ? __builtin_amdgcn_exp2f((z - mx) * 1.4426950408889634f) : 0.f;
+                se += ex;
+                sz = fmaf(ex, z, sz);
+              }
+            st.m = mx; st.idx = ix; st.s = se; st.t = sz;
+          }
+          const float m2 = __shfl_xor(st.m, 32, 64), s2 = __shfl_xor(st.s, 32, 64), t2 = __shfl_xor(st.t, 32, 64);
+          const int i2 = __shfl_xor(st.idx, 32, 64);
+          st.merge(m2, i2, s2, t2);
+          if (h == 0 && m < M && nb < N) {
+            float* o = a.part + ((int64_t)m * a.n_parts + nb / 64) * 4;
+            *(f32x4*)o = f32x4{st.m, __int_as_float(st.idx), st.s, st.t};
+          }
         }
       }
-    }
-  } else {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int m = m0 + wm * 128 + j * 32 + r;
-    if (m >= M) continue;
-    const float rs = (EPI != LG_RESID && a.rscale) ? a.rscale[m] : 1.0f;
-    if constexpr (EPI == LG_SWIGLU) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int n = n0 + wn * 64 + i * 32 + e4 * 8 + h * 4;
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float gt = acc[i][j][e4 * 4 + e] * rs;
-            v[e] = gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * (acc[i + 2][j][e4 * 4 + e] * rs);
-          }
-          if (n + 4 <= N) {
-            *(uint2*)((bf16_t*)a.C + (int64_t)m * N + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-          } else {
-            for (int e = 0; e < 4 && n + e < N; ++e) ((bf16_t*)a.C)[(int64_t)m * N + n + e] = f32_to_bf16(v[e]);
-          }
-        }
-    } else if constexpr (EPI == LG_QKV) {
-      // every split stores its partial sums: [split][row][q | k | v] floats
-      const int nt = N + 2 * a.N2;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int n = n0 + wn * 128 + i * 32 + e4 * 8 + h * 4;
-          *(f32x4*)(a.delta + (int64_t)split * a.delta_stride + (int64_t)m * nt + n) =
-              f32x4{acc[i][j][e4 * 4], acc[i][j][e4 * 4 + 1], acc[i][j][e4 * 4 + 2], acc[i][j][e4 * 4 + 3]} * rs;
-        }
     } else {
+      // lane holds weight rows TN*(l%32) .. of its tiles and, in register e, token row (e/4)*8 + (l/32)*4 + e%4
+      const int n = n0 + (SWIGLU ? wn * 16 * TN + (TN / 2) * r : wn * 32 * TN + TN * r);
+      const int nt = EPI == LG_QKV ? N + 2 * a.N2 : N;          // row length of the output
+      constexpr int ES = SWIGLU ? 2 : 4;
+      char* obase;
+      if constexpr (EPI == LG_QKV) obase = (char*)(a.delta + (int64_t)split * a.delta_stride);   // [split][row][q | k | v]
+      else if constexpr (EPI == LG_RESID) obase = (char*)(split == 0 ? (float*)a.C : a.delta + (int64_t)(split - 1) * a.delta_stride);
+      else obase = (char*)a.C;
+      const gt_rsrc ro = rsrc(obase + (int64_t)m0 * nt * ES, (int64_t)rows * nt * ES);
+      const int lrow = wm * 32 * TM + h * 4;
+      const int vo = (lrow * nt + n) * ES;
+      f32x4 rs4 = f32x4{1.f, 1.f, 1.f, 1.f};
+      if (n < nt) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < TM; ++j)
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int n = n0 + wn * 128 + i * 32 + e4 * 8 + h * 4;
-          const f32x4 v = f32x4{acc[i][j][e4 * 4], acc[i][j][e4 * 4 + 1], acc[i][j][e4 * 4 + 2], acc[i][j][e4 * 4 + 3]};
-          const int64_t at = (int64_t)m * N + n;
-          if (n + 4 <= N) {
-            if (split == 0) { f32x4* p = (f32x4*)((float*)a.C + at); *p = *p + v; }
-            else *(f32x4*)(a.delta + (int64_t)(split - 1) * a.delta_stride + at) = v;
-          } else {
-            for (int e = 0; e < 4 && n + e < N; ++e) {
-              if (split == 0) ((float*)a.C)[at + e] += v[e];
-              else a.delta[(int64_t)(split - 1) * a.delta_stride + at + e] = v[e];
+          for (int e = 0; e < 16; ++e) {
+            const int row = j * 32 + (e >> 2) * 8 + (e & 3), so = row * nt * ES;
+            if ((e & 3) == 0) {
+              __builtin_amdgcn_sched_barrier(0);                // four rows at a time: keeps the epilogue out of scratch
+              if (EPI != LG_RESID && a.rscale)
+                rs4 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, lrow * 4, row * 4, 0));
+            }
+            const float rs = rs4[e & 3];
+            if constexpr (SWIGLU) {
+              float v[TN / 2];
+#pragma unroll
+              for (int i = 0; i < TN / 2; ++i) {
+                const float gt = acc[i][j][e] * rs;
+                v[i] = gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * (acc[i + TN / 2][j][e] * rs);
+              }
+              if constexpr (TN == 4) __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(v[0], v[1]), ro, vo, so, 0);
+              else __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v[0]), ro, vo, so, 0);
+            } else {
+              float v[TN];
+#pragma unroll
+              for (int i = 0; i < TN; ++i) v[i] = acc[i][j][e] * rs;
+              if constexpr (TN == 4) {
+                if (EPI == LG_RESID && split == 0) {
+                  const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ro, vo, so, 0));
+#pragma unroll
+                  for (int i = 0; i < 4; ++i) v[i] += x[i];
+                }
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), ro, vo, so, 0);
+              } else if constexpr (TN == 2) {
+                if (EPI == LG_RESID && split == 0) {
+                  const f32x2_t x = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(ro, vo, so, 0));
+                  v[0] += x[0]; v[1] += x[1];
+                }
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2v, f32x2_t{v[0], v[1]}), ro, vo, so, 0);
+              } else {
+                if (EPI == LG_RESID && split == 0) v[0] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, vo, so, 0));
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), ro, vo, so, 0);
+              }
             }
           }
-        }
-    }
-  }
-  }   // store epilogues
-  }   // work items
-}
-
-// The K shares of the tail tiles of a SiLU(gate)*up launch of k_gemm_t256: one workgroup of 64 lanes per (tail tile,
-// wave, gate tile i, token tile j) adds the shares in order, applies the row factor and the activation and stores the
-// 32 x 32 outputs exactly as the fused epilogue would.
-__global__ __launch_bounds__(64) void k_swiglu_tail(const LgArgs a, int n_wg) {
-  int M = a.M;
-  if (a.m_dev) { const int md = *a.m_dev; M = md < M ? md : M; }
-  const int tiles_m = (M + 255) / 256;
-  const T2Tail tp = t2_tail_plan(tiles_m * a.tiles_n, n_wg, true);
-  const int tail = blockIdx.x >> 5, sub = blockIdx.x & 31;
-  if (tail >= tp.n_tail) return;
-  const int w = sub >> 3, i = (sub >> 2) & 1, j = sub & 3, lane = threadIdx.x;
-  const int wm = w & 1, wn = w >> 1, r = lane & 31, h = lane >> 5;
-  const int tile = tp.n_full + tail;
-  const int tn = tile / tiles_m, tm = tile - tn * tiles_m;
-  const int m = tm * 256 + wm * 128 + j * 32 + r;
-  if (m >= M) return;
-  const int N = a.N;
-  float gt[16], up[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) { gt[e] = 0.f; up[e] = 0.f; }
-  for (int sp = 0; sp < tp.splits; ++sp) {
-    const float* src = a.tail + ((int64_t)sp * tp.n_tail + tail) * T2_TAIL_FLOATS;
-    const f32x4* g4 = (const f32x4*)(src + ((((w * 4 + i) * 4 + j) * 64 + lane) << 4));
-    const f32x4* u4 = (const f32x4*)(src + ((((w * 4 + i + 2) * 4 + j) * 64 + lane) << 4));
-#pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {
-      const f32x4 gv = g4[e4], uv = u4[e4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { gt[e4 * 4 + e] += gv[e]; up[e4 * 4 + e] += uv[e]; }
-    }
-  }
-  const float rs = a.rscale ? a.rscale[m] : 1.0f;
-#pragma unroll
-  for (int e4 = 0; e4 < 4; ++e4) {
-    const int n = tn * 128 + wn * 64 + i * 32 + e4 * 8 + h * 4;
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float gg = gt[e4 * 4 + e] * rs;
-      v[e] = gg * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gg)) * (up[e4 * 4 + e] * rs);
-    }
-    if (n + 4 <= N) {
-      *(uint2*)((bf16_t*)a.C + (int64_t)m * N + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-    } else {
-      for (int e = 0; e < 4 && n + e < N; ++e) ((bf16_t*)a.C)[(int64_t)m * N + n + e] = f32_to_bf16(v[e]);
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// 65 .. 255 token rows (a few blocks in flight at small batch): the weights still have to stream from
-// memory once and the products are few, so what counts is bytes in flight and how often the activations
-// are re-read.  A workgroup of 4 waves owns 128 token rows x 64 weight rows; both operands are copied
-// straight into a 4-stage LDS ring of 32-deep K stages (12 KiB each: three workgroups fit a CU), the
-// activations are shared by the waves through LDS, the products are 32 x 32 x 16 ones (wave tile 64 x 32).
-// Row swizzle and operand layout are those of the 256 x 256 kernel.  A wave's 32 weight rows are 16 gate
-// rows followed by the 16 up rows of the same features for SiLU(gate)*up: both land in one lane.  The tile is
-// 128 x 128 where the matrix is wide enough to still fill the chip (gate/up): fewer activation re-reads.
-constexpr int TS_NS = 4;
-
-template <int EPI, int WT>      // WT: 32-row weight tiles per wave (the workgroup's tile is 128 x 64*WT)
-__global__ __launch_bounds__(256) void k_gemm_ts(const LgArgs a) {
-  constexpr int BN = 64 * WT, TS_STAGE = 8192 + BN * 64;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[TS_NS * TS_STAGE];
-  constexpr int TILE_N = (EPI == LG_SWIGLU) ? BN / 2 : BN;    // output features of a tile
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int M = a.M;
-  if (a.m_dev) { const int md = *a.m_dev; M = md < M ? md : M; }
-  const int N = a.N, K = a.K;
-  const int tile = blockIdx.x;
-  const int tn = tile / a.tiles_m, tm = tile - tn * a.tiles_m;
-  const int m0 = tm * 128, n0 = tn * TILE_N;
-  if (m0 >= M) return;
-  const int wm = w & 1, wn = w >> 1;
-  const int r = lane & 31, h = lane >> 5;
-  int k_begin = 0, k_end = K;
-  if constexpr (EPI == LG_RESID || EPI == LG_QKV) {
-    k_begin = blockIdx.y * a.k_per;
-    k_end = k_begin + a.k_per < K ? k_begin + a.k_per : K;
-  }
-  // copies: this wave moves token blocks 2w, 2w+1 (16 rows each) and weight blocks w*WT .. of a stage
-  constexpr int NC = 2 + WT;
-  const bf16_t* gsrc[NC];
-#pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    const int rr = (q < 2 ? (2 * w + q) : (w * WT + q - 2)) * 16 + (lane >> 2);
-    const int piece = (lane & 3) ^ ((rr >> 2) & 3);
-    if (q < 2) {
-      int row = m0 + rr; row = row < M ? row : M - 1;
-      gsrc[q] = a.A + (int64_t)row * K + piece * 8;
-    } else if constexpr (EPI == LG_SWIGLU) {
-      int row = n0 + (rr >> 5) * 16 + (rr & 15); row = row < N ? row : N - 1;     // every 32 rows: 16 gate, 16 up
-      gsrc[q] = (((rr >> 4) & 1) ? a.W2 : a.W) + (int64_t)row * K + piece * 8;
-    } else if constexpr (EPI == LG_QKV) {
-      const int row = n0 + rr;                       // q | k | v stacked, each a multiple of 64 rows
-      const bf16_t* wsel = row < N ? a.W : (row < N + a.N2 ? a.W2 : a.W3);
-      const int lrow = row < N ? row : (row < N + a.N2 ? row - N : row - N - a.N2);
-      gsrc[q] = wsel + (int64_t)lrow * K + piece * 8;
-    } else {
-      int row = n0 + rr; row = row < N ? row : N - 1;
-      gsrc[q] = a.W + (int64_t)row * K + piece * 8;
-    }
-  }
-  auto copy_stage = [&](int slot, int kd) {
-    unsigned char* base = smem + slot * TS_STAGE;
-    t2_copy16(gsrc[0] + kd, base + (2 * w) * 1024);
-    t2_copy16(gsrc[1] + kd, base + (2 * w + 1) * 1024);
-#pragma unroll
-    for (int q = 0; q < WT; ++q) t2_copy16(gsrc[2 + q] + kd, base + 8192 + (w * WT + q) * 1024);
-  };
-  int offA[2], offW[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int slotp = ((2 * ks + h) ^ ((r >> 2) & 3)) * 16;
-    offA[ks] = (wm * 64 + r) * 64 + slotp;
-    offW[ks] = 8192 + (wn * 32 * WT + r) * 64 + slotp;
-  }
-  f32x16 acc[WT][2];   // [weight tile][token tile]
-#pragma unroll
-  for (int i = 0; i < WT; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  const int ns = (k_end - k_begin) / 32;      // K ranges are multiples of 32 (checked on the host)
-#pragma unroll
-  for (int st = 0; st < TS_NS - 1; ++st) copy_stage(st, k_begin + (st < ns ? st : ns - 1) * 32);
-  for (int st = 0; st < ns; ++st) {
-    // this wave's copies of stage st are the oldest of its NC * (NS - 1) outstanding ones
-    __builtin_amdgcn_s_waitcnt(T2_VMCNT(NC * (TS_NS - 2)));
-    __builtin_amdgcn_s_barrier();               // every wave's part of stage st is in; stage st - 1 is free
-    {
-      const int sn = st + TS_NS - 1;
-      copy_stage(sn % TS_NS, k_begin + (sn < ns ? sn : ns - 1) * 32);   // past the end: a repeat into a free slot
-    }
-    const unsigned char* base = smem + (st % TS_NS) * TS_STAGE;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const u32x4 fa0 = *(const u32x4*)(base + offA[ks]), fa1 = *(const u32x4*)(base + offA[ks] + 2048);
-#pragma unroll
-      for (int i = 0; i < WT; ++i) {
-        const u32x4 fw = *(const u32x4*)(base + offW[ks] + i * 2048);
-        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw), __builtin_bit_cast(bf16x8, fa0), acc[i][0], 0, 0, 0);
-        acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw), __builtin_bit_cast(bf16x8, fa1), acc[i][1], 0, 0, 0);
       }
     }
+    if (!nxt.ok) break;
+    cur = nxt;
+    nxt = item_at(++it_next);
+    if (nxt.ok) { rna = rsrc_a(nxt); rnw = rsrc_w(nxt); }
   }
-  __builtin_amdgcn_s_waitcnt(T2_VMCNT(0));   // the ring's trailing repeats must not outlive the workgroup
-
-  // lane holds token column l%32 of token tile j; weight rows (e/4)*8 + (l/32)*4 + e%4 of the wave's tile
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int m = m0 + wm * 64 + j * 32 + r;
-    if (m >= M) continue;
-    const float rs = (EPI != LG_RESID && a.rscale) ? a.rscale[m] : 1.0f;
-    if constexpr (EPI == LG_SWIGLU) {
-#pragma unroll
-      for (int i = 0; i < WT; ++i)
-#pragma unroll
-      for (int e4 = 0; e4 < 2; ++e4) {
-        const int n = n0 + (wn * WT + i) * 16 + e4 * 8 + h * 4;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float gt = acc[i][j][e4 * 4 + e] * rs;
-          v[e] = gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * (acc[i][j][8 + e4 * 4 + e] * rs);
-        }
-        if (n + 4 <= N) {
-          *(uint2*)((bf16_t*)a.C + (int64_t)m * N + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-        } else {
-          for (int e = 0; e < 4 && n + e < N; ++e) ((bf16_t*)a.C)[(int64_t)m * N + n + e] = f32_to_bf16(v[e]);
-        }
-      }
-    } else if constexpr (EPI == LG_QKV) {
-      const int nt = N + 2 * a.N2;
-#pragma unroll
-      for (int i = 0; i < WT; ++i)
-#pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4) {
-        const int n = n0 + (wn * WT + i) * 32 + e4 * 8 + h * 4;
-        *(f32x4*)(a.delta + (int64_t)blockIdx.y * a.delta_stride + (int64_t)m * nt + n) =
-            f32x4{acc[i][j][e4 * 4], acc[i][j][e4 * 4 + 1], acc[i][j][e4 * 4 + 2], acc[i][j][e4 * 4 + 3]} * rs;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < WT; ++i)
-#pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4) {
-        const int n = n0 + (wn * WT + i) * 32 + e4 * 8 + h * 4;
-        const f32x4 v = f32x4{acc[i][j][e4 * 4], acc[i][j][e4 * 4 + 1], acc[i][j][e4 * 4 + 2], acc[i][j][e4 * 4 + 3]};
-        const int64_t at = (int64_t)m * N + n;
-        if (n + 4 <= N) {
-          if (blockIdx.y == 0) { f32x4* p = (f32x4*)((float*)a.C + at); *p = *p + v; }
-          else *(f32x4*)(a.delta + (int64_t)(blockIdx.y - 1) * a.delta_stride + at) = v;
-        } else {
-          for (int e = 0; e < 4 && n + e < N; ++e) {
-            if (blockIdx.y == 0) ((float*)a.C)[at + e] += v[e];
-            else a.delta[(int64_t)(blockIdx.y - 1) * a.delta_stride + at + e] = v[e];
-          }
-        }
-      }
-    }
-  }
+  __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));   // the trailing repeats must not outlive the workgroup
 }
 
-template <int EPI, int WT>
-static hipError_t ts_launch(hipStream_t s, LgArgs a, int k_splits = 1) {
-  constexpr int bn = 64 * WT, tile_n = EPI == LG_SWIGLU ? bn / 2 : bn;
-  a.tiles_m = (a.M + 127) / 128;
-  a.tiles_n = EPI == LG_QKV ? (a.N + 2 * a.N2) / bn : (a.N + tile_n - 1) / tile_n;
-  if (EPI != LG_RESID && EPI != LG_QKV) a.k_per = a.K;
-  const dim3 grid(a.tiles_m * a.tiles_n, k_splits);
-  k_gemm_ts<EPI, WT><<<grid, 256, 0, s>>>(a);
-  return hipGetLastError();
-}
-// rows for which the streaming tiles are the better form: more than the weight-streaming kernels take, fewer
-// than fill 256-row tiles
-static bool ts_usable(int M, int K) {
-  return M > 64 && M < 256 && K % 32 == 0 && K >= 128;
-}
+template <int EPI, int TM, int TN, int NSA, int NSW>
+__global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW>(a); }
 
-// the 256 x 256 form needs the whole ring in LDS: more than the default limit of a kernel
-static bool t2_ready = false;
-static int t2_cus = 256;
-hipError_t init_gemm_t256() {
-  if (t2_ready) return hipSuccess;
-  {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        cus >= 8)
-      t2_cus = cus / 8 * 8;
-  }
-  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_t256<LG_RESID>, hipFuncAttributeMaxDynamicSharedMemorySize, T2_LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_t256<LG_SWIGLU>, hipFuncAttributeMaxDynamicSharedMemorySize, T2_LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_t256<LG_LMSTATS>, hipFuncAttributeMaxDynamicSharedMemorySize, T2_LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_t256<LG_QKV>, hipFuncAttributeMaxDynamicSharedMemorySize, T2_LDS);
-  t2_ready = e == hipSuccess;
+// Rings above the default LDS limit of a kernel: raised once per process.
+static bool gt_ready = false;
+static int gt_cus = 256;
+#define GT_KERNELS(X)                                                                                   \
+  X(LG_SWIGLU, 4, 4, 2, 3) X(LG_SWIGLU, 2, 4, 2, 3) X(LG_SWIGLU, 2, 2, 4, 5)                            \
+  X(LG_RESID, 4, 4, 2, 3) X(LG_RESID, 2, 4, 2, 3) X(LG_RESID, 2, 2, 4, 5) X(LG_RESID, 2, 1, 3, 4)       \
+  X(LG_QKV, 4, 4, 2, 3) X(LG_QKV, 2, 4, 2, 3) X(LG_QKV, 2, 2, 4, 5) X(LG_QKV, 2, 1, 3, 4)               \
+  X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS, 2, 2, 4, 5)
+hipError_t init_gemm_tiles() {
+  if (gt_ready) return hipSuccess;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+      cus >= 8)
+    gt_cus = cus / 8 * 8;
+  hipError_t e = hipSuccess;
+#define X(E, TM, TN, NA, NW)                                                                                       \
+  if (e == hipSuccess)                                                                                             \
+    e = hipFuncSetAttribute((const void*)k_gemm_tile<E, TM, TN, NA, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                            GtGeom<TM, TN, NA, NW>::LDS);
+  GT_KERNELS(X)
+#undef X
+  gt_ready = e == hipSuccess;
   return e;
 }
+// more rows than the weight-streaming kernels take, K in whole 64-deep stages
+static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 64 == 0 && K >= 128; }
 
-template <int EPI>
-static hipError_t t2_launch(hipStream_t s, LgArgs a, int k_splits = 1) {
-  constexpr int tile_n = EPI == LG_SWIGLU ? 128 : 256;
-  a.tiles_m = (a.M + 255) / 256;
-  a.tiles_n = (a.N + tile_n - 1) / tile_n;
-  if (EPI == LG_QKV) a.tiles_n = (a.N + 2 * a.N2) / 256;
+template <int EPI, int TM, int TN, int NSA, int NSW>
+static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1) {
+  using G = GtGeom<TM, TN, NSA, NSW>;
+  constexpr int tile_n = EPI == LG_SWIGLU ? G::BN / 2 : G::BN;
+  a.tiles_m = (a.M + G::BM - 1) / G::BM;
+  a.tiles_n = EPI == LG_QKV ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n;
   a.k_splits = k_splits;
-  if (EPI != LG_RESID && EPI != LG_QKV) a.k_per = a.K;
-  const int items = a.tiles_m * a.tiles_n * k_splits;
-  const int grid = items < t2_cus ? (items + 7) / 8 * 8 : t2_cus;   // one persistent workgroup per CU
-  k_gemm_t256<EPI><<<grid, 256, T2_LDS, s>>>(a);
+  if (k_splits == 1) a.k_per = a.K;
+  a.group_m = 8;
+  const int items = a.tiles_m * a.tiles_n * k_splits, slots = gt_cus * G::PER_CU;
+  k_gemm_tile<EPI, TM, TN, NSA, NSW><<<items < slots ? (items + 7) / 8 * 8 : slots, 256, G::LDS, s>>>(a);
   return hipGetLastError();
 }
-static bool t2_usable(int M, int K) {
-  return t2_ready && M >= 256 && K % 32 == 0 && K >= 128;
+
+// Which tile: the estimate counts rounds of one workgroup per CU in units of a 256 x 256 tile's time.  A 128 x 256 tile
+// costs 0.6 of it (half the products, three quarters of the bytes), a 128 x 128 one 0.33 (copies and products take
+// equally long), a 128 x 64 one 0.22.  Measured against each other (K = 3584 .. 18944, us): 1024 x 37888: 271 / 286 /
+// 297; 256 x 24576: 85 / 55 / 61; 128 x 24576: 85 / 50 / 39; 1024 x 3584 x 3584: 48 (4 K shares) / 38 (2) / 42.
+enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_N = 4 };
+struct GtPlan { GtTile tile; int splits, k_per; };
+// NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile
+static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok) {
+  static const int bm[GT_N] = {256, 128, 128, 128}, bn[GT_N] = {256, 256, 128, 64};
+  static const double unit[GT_N] = {1.0, 0.6, 0.33, 0.22};
+  GtPlan best{GT_128x128, 1, K};
+  double best_t = 1e30;
+  for (int c = 0; c < GT_N; ++c) {
+    if (!((width_ok >> c) & 1u)) continue;
+    const int tiles = ((M + bm[c] - 1) / bm[c]) * ((NW + bn[c] - 1) / bn[c]);
+    for (int sp = 1; sp <= max_splits; ++sp) {
+      if (sp > 1 && (K / sp < 512 || tiles * sp > gt_cus)) break;    // shares long enough to pay for fill and drain
+      const int k_per = ((K + sp - 1) / sp + 63) / 64 * 64;
+      const int n_sp = (K + k_per - 1) / k_per;
+      if (n_sp != sp) continue;
+      const double rounds = (double)((tiles * sp + gt_cus - 1) / gt_cus);
+      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain; a share's [M, NW] floats are written
+      // and read again by the kernel that adds them
+      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + 4.0) + (sp - 1) * (8.0 * M * (double)NW / 4.0e6);
+      if (t < best_t) { best_t = t; best = GtPlan{(GtTile)c, sp, k_per}; }
+    }
+  }
+  return best;
 }
 
 template <int EPI>
@@ -878,69 +747,37 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
   memset(&a, 0, sizeof(a));
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)W; a.C = x; a.M = M; a.N = N; a.K = K;
   a.m_dev = c->rows_dev;
-  if (ts_usable(M, K) && M <= c->map.lg_delta_rows && N == c->cfg.d_model) {
-    // streaming tiles: K split until about three workgroups per CU are in flight
-    const int tiles = ((M + 127) / 128) * ((N + 63) / 64);
-    int splits = 768 / tiles;
-    if (splits > LG_MAX_DELTA + 1) splits = LG_MAX_DELTA + 1;
-    while (splits > 1 && K / splits < 512) --splits;
-    if (splits < 1) splits = 1;
-    a.k_per = ((K + splits - 1) / splits + 31) / 32 * 32;
-    splits = (K + a.k_per - 1) / a.k_per;
-    a.delta = (float*)(c->ws + c->map.delta);
-    a.delta_stride = c->map.lg_delta_stride;
-    *n_delta = splits - 1;
-    return ts_launch<LG_RESID, 1>(s, a, splits);
-  }
-  // short sums over few rows: the 128-row tiles fill the chip better, unless the 256-row tiles' K shares still are
-  // long enough to pay for their fill and drain (measured at K = 4096: 5 row tiles, three shares of 1365, do; 4 row
-  // tiles, four shares of 1024, do not)
-  const int tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
-  int shares256 = tiles256 > 0 ? 256 / tiles256 : 1;
-  shares256 = shares256 > LG_MAX_DELTA + 1 ? LG_MAX_DELTA + 1 : (shares256 < 1 ? 1 : shares256);
-  const bool shares_pay = shares256 > 1 && K / shares256 >= 1280 && M <= c->map.lg_delta_rows && N == c->cfg.d_model;
-  const bool t2 = t2_usable(M, K) && (K >= 8192 || tiles256 >= 192 || shares_pay);
-  const int tiles = t2 ? ((M + 255) / 256) * ((N + 255) / 256) : ((M + 127) / 128) * ((N + LG_BN - 1) / LG_BN);
-  int splits = (t2 ? 256 : 512) / tiles;                      // one 256-row workgroup or two 128-row ones fit a CU
-  if (splits > LG_MAX_DELTA + 1) splits = LG_MAX_DELTA + 1;
-  while (splits > 1 && K / splits < 512) --splits;
-  if (splits < 1 || M > c->map.lg_delta_rows || N != c->cfg.d_model) splits = 1;
-  a.k_per = ((K + splits - 1) / splits + LG_BK - 1) / LG_BK * LG_BK;
-  splits = (K + a.k_per - 1) / a.k_per;
+  const bool can_split = M <= c->map.lg_delta_rows && N == c->cfg.d_model;
   a.delta = (float*)(c->ws + c->map.delta);
   a.delta_stride = c->map.lg_delta_stride;
+  if (gt_usable(M, K)) {
+    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, 0xfu);
+    a.k_per = p.k_per;
+    *n_delta = p.splits - 1;
+    switch (p.tile) {
+      case GT_256x256: return gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, p.splits);
+      case GT_128x256: return gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, p.splits);
+      case GT_128x128: return gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, p.splits);
+      default: return gt_launch<LG_RESID, 2, 1, 3, 4>(s, a, p.splits);
+    }
+  }
+  const int tiles = ((M + 127) / 128) * ((N + LG_BN - 1) / LG_BN);
+  int splits = 512 / tiles;                                   // two workgroups fit a CU
+  if (splits > LG_MAX_DELTA + 1) splits = LG_MAX_DELTA + 1;
+  while (splits > 1 && K / splits < 512) --splits;
+  if (splits < 1 || !can_split) splits = 1;
+  a.k_per = ((K + splits - 1) / splits + LG_BK - 1) / LG_BK * LG_BK;
+  splits = (K + a.k_per - 1) / a.k_per;
   *n_delta = splits - 1;
-  if (t2) return t2_launch<LG_RESID>(s, a, splits);
   return lg_launch<LG_RESID>(s, a, splits);
 }
 
-// The fused q/k/v product on 256-row tiles, its sum over K split to fill the chip: every split leaves
+// The fused q/k/v product on the tile kernel, its sum over K split where that fills the chip: every split leaves
 // [M, dq + 2 dkv] float partial sums (q | k | v) for the rotary kernel to add.  *n_part = 0: not taken.
 hipError_t launch_gemm_qkv_split(dllm_ctx* c, hipStream_t s, const void* A, const void* Wq, const void* Wk, const void* Wv,
                                  int M, int dq, int dkv, int K, int* n_part) {
   *n_part = 0;
-  if (ts_usable(M, K) && M <= c->map.lg_delta_rows && dq % 64 == 0 && dkv % 64 == 0 && c->map.qkvp_stride > 0) {
-    LgArgs a;
-    memset(&a, 0, sizeof(a));
-    a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wq; a.W2 = (const bf16_t*)Wk; a.W3 = (const bf16_t*)Wv;
-    a.M = M; a.N = dq; a.N2 = dkv; a.K = K;
-    a.rscale = WSM(c, rscale, float);
-    a.m_dev = c->rows_dev;
-    const bool wide = dq % 128 == 0 && dkv % 128 == 0 && (dq + 2 * dkv) / 128 >= 64;   // 128 x 128 tiles still fill the chip
-    const int tiles = ((M + 127) / 128) * ((dq + 2 * dkv) / (wide ? 128 : 64));
-    int splits = 768 / tiles;
-    if (splits > LG_QKV_SPLITS) splits = LG_QKV_SPLITS;
-    while (splits > 1 && K / splits < 512) --splits;
-    if (splits < 1) splits = 1;
-    a.k_per = ((K + splits - 1) / splits + 31) / 32 * 32;
-    splits = (K + a.k_per - 1) / a.k_per;
-    a.delta = (float*)(c->ws + c->map.qkvp);
-    a.delta_stride = c->map.qkvp_stride;
-    *n_part = splits;
-    if (wide) return ts_launch<LG_QKV, 2>(s, a, splits);
-    return ts_launch<LG_QKV, 1>(s, a, splits);
-  }
-  if (!t2_usable(M, K) || M > c->map.qkvp_rows || dq % 256 != 0 || dkv % 256 != 0 || c->map.qkvp_stride == 0)
+  if (!gt_usable(M, K) || M > c->map.qkvp_rows || dq % 64 != 0 || dkv % 64 != 0 || c->map.qkvp_stride == 0)
     return hipSuccess;
   LgArgs a;
   memset(&a, 0, sizeof(a));
@@ -948,18 +785,19 @@ hipError_t launch_gemm_qkv_split(dllm_ctx* c, hipStream_t s, const void* A, cons
   a.M = M; a.N = dq; a.N2 = dkv; a.K = K;
   a.rscale = WSM(c, rscale, float);
   a.m_dev = c->rows_dev;
-  const int tiles = ((M + 255) / 256) * ((dq + 2 * dkv) / 256);
-  int splits = 256 / tiles;
-  if (splits > LG_QKV_SPLITS) splits = LG_QKV_SPLITS;
-  while (splits > 1 && K / splits < 1024) --splits;
-  if (splits < 1 || M > c->map.lg_delta_rows) splits = 1;   // the split buffers cover lg_delta_rows rows
-  if (tiles * splits < 128) return hipSuccess;            // too few work items: the 128-row tiles do better
-  a.k_per = ((K + splits - 1) / splits + 31) / 32 * 32;
-  splits = (K + a.k_per - 1) / a.k_per;
+  // a tile belongs to one of the projections; the buffers of a split product cover lg_delta_rows rows
+  const unsigned width_ok = (dq % 256 == 0 && dkv % 256 == 0 ? 0x3u : 0u) | (dq % 128 == 0 && dkv % 128 == 0 ? 0x4u : 0u) | 0x8u;
+  const GtPlan p = gt_plan(M, dq + 2 * dkv, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, width_ok);
+  a.k_per = p.k_per;
   a.delta = (float*)(c->ws + c->map.qkvp);
   a.delta_stride = c->map.qkvp_stride;
-  *n_part = splits;
-  return t2_launch<LG_QKV>(s, a, splits);
+  *n_part = p.splits;
+  switch (p.tile) {
+    case GT_256x256: return gt_launch<LG_QKV, 4, 4, 2, 3>(s, a, p.splits);
+    case GT_128x256: return gt_launch<LG_QKV, 2, 4, 2, 3>(s, a, p.splits);
+    case GT_128x128: return gt_launch<LG_QKV, 2, 2, 4, 5>(s, a, p.splits);
+    default: return gt_launch<LG_QKV, 2, 1, 3, 4>(s, a, p.splits);
+  }
 }
 
 // q32[M,dq], k32[M,dkv] (float) and v[M,dkv] (bfloat16) = A[M,K] times the three projections, one launch
@@ -978,24 +816,18 @@ hipError_t launch_gemm_qkv(hipStream_t s, const void* A, const void* Wq, const v
 
 // h[M,F] = silu(A Wg^T) * (A Wu^T), bfloat16 row-major
 hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, const void* Wu, void* H, int M, int F,
-                              int K, const float* rscale, const int32_t* m_dev, float* tail, size_t tail_bytes) {
+                              int K, const float* rscale, const int32_t* m_dev) {
   LgArgs a;
   memset(&a, 0, sizeof(a));
   a.rscale = rscale;
   a.m_dev = m_dev;
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wg; a.W2 = (const bf16_t*)Wu; a.C = H; a.M = M; a.N = F; a.K = K;
-  if (ts_usable(M, K)) return ts_launch<LG_SWIGLU, 2>(s, a);
-  if (t2_usable(M, K)) {
-    // K-split tail tiles need scratch for one share per workgroup; worth it only if whole rounds come before them
-    const int tiles = ((M + 255) / 256) * ((F + 127) / 128);
-    const bool split_tail = tail != nullptr && tail_bytes >= (size_t)t2_cus * T2_TAIL_FLOATS * sizeof(float) &&
-                            tiles > t2_cus && tiles % t2_cus != 0 && K >= 32 * 8 * T2_TAIL_SPLITS;
-    a.tail = split_tail ? tail : nullptr;
-    hipError_t e = t2_launch<LG_SWIGLU>(s, a);
-    if (e != hipSuccess || !split_tail) return e;
-    a.tiles_n = (F + 127) / 128;
-    k_swiglu_tail<<<(t2_cus - 1) * 32, 64, 0, s>>>(a, t2_cus);
-    return hipGetLastError();
+  if (gt_usable(M, K)) {
+    switch (gt_plan(M, 2 * F, K, 1, 0x7u).tile) {
+      case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a);
+      case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a);
+      default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a);
+    }
   }
   return lg_launch<LG_SWIGLU>(s, a);
 }
@@ -1012,9 +844,8 @@ hipError_t launch_gemm_lmstats(dllm_ctx* c, hipStream_t s, int max_rows, int* n_
   a.n_parts = (f.vocab + 63) / 64;
   a.mask_id = f.mask_id;
   *n_parts_out = a.n_parts;
-  // (65 .. 255 rows stay on the 128 x 128 tiles: 4.3 TB/s at 128 rows, against 2.8 TB/s for the 128 x 64
-  // streaming tiles, whose activation re-reads double the bytes the LM head moves)
-  if (t2_usable(max_rows, a.K)) return t2_launch<LG_LMSTATS>(s, a);
+  if (gt_usable(max_rows, a.K))
+    return max_rows > 128 ? gt_launch<LG_LMSTATS, 4, 4, 2, 3>(s, a) : gt_launch<LG_LMSTATS, 2, 2, 4, 5>(s, a);
   return lg_launch<LG_LMSTATS>(s, a);
 }
 
@@ -1080,13 +911,13 @@ __global__ __launch_bounds__(256) void k_probe_mfma(int iters, int random_bits, 
 }
 
 hipError_t launch_probe_read(hipStream_t s, const void* buf, size_t bytes, void* sink) {
-  k_probe_read<<<t2_cus * 2, 512, 0, s>>>((const u32x4*)buf, bytes / 16, (uint32_t*)sink);
+  k_probe_read<<<gt_cus * 2, 512, 0, s>>>((const u32x4*)buf, bytes / 16, (uint32_t*)sink);
   return hipGetLastError();
 }
 
 // flops of one launch: workgroups * 4 waves * iters * 16 products * 2*32*32*16
 hipError_t launch_probe_mfma(hipStream_t s, int iters, int random_bits, void* sink, double* flops) {
-  const int wgs = t2_cus;
+  const int wgs = gt_cus;
   k_probe_mfma<<<wgs, 256, 0, s>>>(iters, random_bits, (float*)sink);
   *flops = (double)wgs * 4.0 * iters * 16.0 * 2.0 * 32 * 32 * 16;
   return hipGetLastError();
