@@ -446,7 +446,10 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   static_assert(EARLY < CA, "the copies in front of their own stage are activations, not all of them");
 #pragma unroll
   for (int q = 0; q < EARLY; ++q) copy_a(NSA - 1, q);
-  __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));
+  // stage 0 is in: all but the copies behind it
+  constexpr int FILL = (NSA - 1) * CA + (NSW - 1) * CW + EARLY - (CA + CW);
+  static_assert(FILL < 64, "what the memory counter holds");
+  __builtin_amdgcn_s_waitcnt(GT_VMCNT(FILL));
   __builtin_amdgcn_s_barrier();
   // operand reads: lane (r, h) of k-step ks takes piece 2*ks + h of row r
   int oA[4], oW[4];
@@ -479,7 +482,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
       const int fa_slot = sa == 0 ? NSA - 1 : sa - 1, fw_slot = sw == 0 ? NSW - 1 : sw - 1;   // the stage before: free
       const unsigned char *bA = sA + sa * G::A_BYTES, *bW = sW + sw * G::W_BYTES;
       const unsigned char *cA = sA + na * G::A_BYTES, *cW = sW + nw * G::W_BYTES;
-      if (st == 0) __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));     // the last item's stores are not to count among the copies
+      // the last item's loads and stores are not to count among the copies
+      if (st == 0 && it_next > 1) __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const int b = ks & 1;
@@ -579,20 +583,41 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
       const gt_rsrc ro = rsrc(obase + (int64_t)m0 * nt * ES, (int64_t)rows * nt * ES);
       const int lrow = wm * 32 * TM + h * 4;
       const int vo = (lrow * nt + n) * ES;
-      f32x4 rs4 = f32x4{1.f, 1.f, 1.f, 1.f};
       if (n < nt) {
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
+        for (int j = 0; j < TM; ++j) {
+          // what a token tile's 16 rows need is requested together: the row factors, the residual stream
+          __builtin_amdgcn_sched_barrier(0);
+          f32x4 rs4[4];
+          float xv[EPI == LG_RESID ? 16 : 1][TN];
+          if constexpr (EPI == LG_RESID) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              const int so = (j * 32 + (e >> 2) * 8 + (e & 3)) * nt * 4;
+#pragma unroll
+              for (int i = 0; i < TN; ++i) xv[e][i] = 0.f;
+              if (split == 0) {
+                if constexpr (TN == 4) {
+                  const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ro, vo, so, 0));
+#pragma unroll
+                  for (int i = 0; i < 4; ++i) xv[e][i] = x[i];
+                } else if constexpr (TN == 2) {
+                  const f32x2_t x = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(ro, vo, so, 0));
+                  xv[e][0] = x[0]; xv[e][1] = x[1];
+                } else xv[e][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, vo, so, 0));
+              }
+            }
+          } else {
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4)
+              rs4[e4] = a.rscale ? __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, lrow * 4, (j * 32 + e4 * 8) * 4, 0))
+                                 : f32x4{1.f, 1.f, 1.f, 1.f};
+          }
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int row = j * 32 + (e >> 2) * 8 + (e & 3), so = row * nt * ES;
-            if ((e & 3) == 0) {
-              __builtin_amdgcn_sched_barrier(0);                // four rows at a time: keeps the epilogue out of scratch
-              if (EPI != LG_RESID && a.rscale)
-                rs4 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, lrow * 4, row * 4, 0));
-            }
-            const float rs = rs4[e & 3];
+            const int so = (j * 32 + (e >> 2) * 8 + (e & 3)) * nt * ES;
             if constexpr (SWIGLU) {
+              const float rs = rs4[e >> 2][e & 3];
               float v[TN / 2];
 #pragma unroll
               for (int i = 0; i < TN / 2; ++i) {
@@ -604,26 +629,16 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
             } else {
               float v[TN];
 #pragma unroll
-              for (int i = 0; i < TN; ++i) v[i] = acc[i][j][e] * rs;
-              if constexpr (TN == 4) {
-                if (EPI == LG_RESID && split == 0) {
-                  const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ro, vo, so, 0));
-#pragma unroll
-                  for (int i = 0; i < 4; ++i) v[i] += x[i];
-                }
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), ro, vo, so, 0);
-              } else if constexpr (TN == 2) {
-                if (EPI == LG_RESID && split == 0) {
-                  const f32x2_t x = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(ro, vo, so, 0));
-                  v[0] += x[0]; v[1] += x[1];
-                }
-                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2v, f32x2_t{v[0], v[1]}), ro, vo, so, 0);
-              } else {
-                if (EPI == LG_RESID && split == 0) v[0] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, vo, so, 0));
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), ro, vo, so, 0);
+              for (int i = 0; i < TN; ++i) {
+                if constexpr (EPI == LG_RESID) v[i] = xv[e][i] + acc[i][j][e];
+                else v[i] = acc[i][j][e] * rs4[e >> 2][e & 3];
               }
+              if constexpr (TN == 4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), ro, vo, so, 0);
+              else if constexpr (TN == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2v, f32x2_t{v[0], v[1]}), ro, vo, so, 0);
+              else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), ro, vo, so, 0);
             }
           }
+        }
       }
     }
     if (!nxt.ok) break;

@@ -1,0 +1,67 @@
+"""GPU parity of the tile kernel (products of more than 64 rows) at the edges of its tiles: row counts on both sides of
+128 and 256, widths that end inside a tile, K splits with shares of unequal length, and work items that follow each
+other in one workgroup.  The reference is the oracle with bfloat16 storage; the tolerance is that of the layer depth
+(tests/harness.py: logit_tol), for the residual stream per row and for the LM head's statistics as everywhere."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dllm_oracle as O
+from paper_2601_07568_amd import synth
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+W = synth.as_float
+ST = synth.round_bf16
+# d_model 576: nine 64-deep stages, two and a quarter 256-wide tiles; d_ff 1088: 17 stages (K shares of 9 and 8),
+# 2176 gate and up rows; the projections are 512 (q) and 128 (k, v) wide: no 256-wide tile fits k
+EDGE = synth.ModelShape(1, 576, 8, 2, 64, 1088, 1500, 1499, dtype="bf16", lm_head_scale=8.0, name="tile-edges")
+# long K over few columns: four K shares; more items than one round of a workgroup is not possible on few rows
+LONG = synth.ModelShape(1, 256, 2, 2, 128, 4160, 700, 699, dtype="bf16", lm_head_scale=8.0, name="tile-long-k")
+
+
+def run(ms, lens, Q, seed=5, pt=32):
+    w = synth.Weights(ms, seed)
+    B = len(lens)
+    mp = (max(lens) + Q + pt - 1) // pt
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=B * mp, max_batch=B, max_q=Q,
+                        max_tokens=sum(lens))
+    seqs = [synth.random_tokens(ms, seed + i, n) for i, n in enumerate(lens)]
+    blks = [synth.masked_block(ms, seed + 10 + i, Q, max(1, Q // 2)) for i in range(B)]
+    table = eng.i32(H.identity_table(eng, B))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    eng.prefill_kv(eng.i32(np.concatenate(seqs)), eng.i32(cu), table, None, total_tokens=int(cu[-1]), max_seqlen=max(lens))
+    qt, pre = eng.i32(np.stack(blks)), eng.i32(lens)
+    hidden = eng.debug_hidden(qt, pre, table, ms.n_layers, max_prefix_len=max(lens)).cpu().numpy()
+    cand = torch.zeros(B, Q, dtype=torch.int32, device=eng.device)
+    conf = torch.zeros(B, Q, dtype=torch.float32, device=eng.device)
+    ent = torch.zeros(B, Q, dtype=torch.float32, device=eng.device)
+    eng.denoise_step(qt, pre, table, cand, conf, ent, max_prefix_len=max(lens))
+    tol = H.logit_tol("bf16", ms.n_layers, "store")
+    for b in range(B):
+        ck, cv = O.prefill(w, seqs[b], widen=W, store=ST)
+        logits, x = O.forward_cached(w, blks[b], ck, cv, widen=W, store=ST)
+        assert H.rel_err_rows(hidden[b], x).max() <= tol, (b, H.rel_err_rows(hidden[b], x).max())
+        r = {"logits": logits, "cand": O.confidence(logits, ms.mask_id)[0]}
+        H.check_step_outputs(ms, r, blks[b] == ms.mask_id, cand.cpu().numpy()[b], conf.cpu().numpy()[b],
+                             ent.cpu().numpy()[b], "bf16")
+    assert eng.read_status() == 0
+    eng.close()
+
+
+@pytest.mark.parametrize("B,Q", [(1, 65), (1, 127), (2, 64), (3, 43), (1, 255), (4, 64), (1, 257), (3, 171), (8, 97)])
+def test_row_counts_around_the_tiles(B, Q):
+    """65 .. 776 rows: one to seven row tiles, the last one nearly empty, full and just full; prompts of 65 + rows are
+    the no-cache forward on the same tiles."""
+    run(EDGE, [70 + 3 * b for b in range(B)], Q)
+
+
+@pytest.mark.parametrize("B,Q", [(1, 66), (2, 129)])
+def test_k_shares_of_a_long_sum(B, Q):
+    run(LONG, [9 + b for b in range(B)], Q)
+
+
+def test_several_items_per_workgroup():
+    """1600 x 8192 gate and up rows: more tiles than workgroups, the copies of a workgroup run on into its next tile."""
+    wide = synth.ModelShape(1, 128, 2, 1, 64, 8192, 600, 599, dtype="bf16", lm_head_scale=8.0, name="tile-items")
+    run(wide, [40 + b for b in range(16)], 100)
