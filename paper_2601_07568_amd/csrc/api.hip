@@ -63,6 +63,7 @@ static bool build_map(const dllm_config* c, Workspace* m) {
   m->rope_sin = take(t_max * half * 4);
   m->tok_seq = take(t_max * 4);
   m->tok_pos = take(t_max * 4);
+  m->kv_loc = take(t_max * 16);
   m->rows = take((size_t)m->r_max * 4);
   m->lm_part = take((size_t)m->r_max * ((c->vocab + 63) / 64) * 4 * 4);   // finest split: 64 columns per partial
   m->attn_rows = (int64_t)t_step * c->n_q_heads * 8;
@@ -322,6 +323,11 @@ static bool skinny_path(const dllm_ctx* c, const StepGeom& g) {
   return mfma_supported(c) && g.Q > 0 && g.T <= SK_MAX_ROWS && attn_step_supported(c, g);
 }
 
+// bfloat16 models on the matrix-core kernels for many rows
+static bool large_mfma(const dllm_ctx* c) {
+  return c->cfg.dtype == DLLM_BF16 && c->kernel_mode == 0 && c->cfg.d_ff % 4 == 0 && c->cfg.vocab % 4 == 0;
+}
+
 static int run_forward(dllm_ctx* c, hipStream_t s, const StepGeom& g0, int n_layers_run, const HeadOut* head,
                        float* logits_out, float* hidden_out) {
   // the first launches check the device-resident lengths against the host values that size the launches and leave
@@ -332,7 +338,7 @@ static int run_forward(dllm_ctx* c, hipStream_t s, const StepGeom& g0, int n_lay
     TRY(launch_sk_prologue(c, s, g0, n_layers_run > 0 ? c->layers[0].attn_norm : c->final_norm,
                            head ? head->cand : nullptr, head ? head->conf : nullptr, head ? head->entropy : nullptr),
         "prologue");
-  else TRY(launch_token_map(c, s, g0), "token_map");
+  else TRY(launch_token_map(c, s, g0, n_layers_run > 0 && large_mfma(c) && gemm_qkv_rope_wins(c, g0.T)), "token_map");
   StepGeom g = g0;
   if (g.Q > 0) g.prefix_len = WSP(c, len_safe, int32_t);
   else g.cu_seqlens = WSP(c, len_safe, int32_t);
@@ -364,7 +370,8 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   // leaves x * gain of the next norm in fragment order plus partial sums of squares per row, and the consuming
   // GEMM applies the row's normalisation factor to its float accumulators.
   const bool sk = skinny_path(c, g);
-  const bool big_mfma = f.dtype == DLLM_BF16 && c->kernel_mode == 0 && f.d_ff % 4 == 0 && f.vocab % 4 == 0;
+  const bool big_mfma = large_mfma(c);
+  const bool qkv_rope = !sk && big_mfma && gemm_qkv_rope_wins(c, T);   // (the token map has left the rows' K/V places)
   const int ss_groups = (f.d_model + 15) / 16;
   int n_ss = 1;      // partial sums of squares the current skinny-path GEMM input comes with
   if (!sk) {            // (on the weight-streaming path run_forward's prologue launch has done both)
@@ -382,8 +389,14 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
     } else {
       ProfScope p(c, s, 0, 2.0 * T * (dq + 2.0 * dkv) * f.d_model);   // large path: work recorded in flops
       int n_part = 0;
-      if (big_mfma) TRY(launch_gemm_qkv_split(c, s, c->ws + c->map.xn, L.wq, L.wk, L.wv, T, dq, dkv, f.d_model, &n_part), "wqkv");
-      if (n_part > 0) {
+      if (qkv_rope) {
+        const KVView pack = pack_view(c);
+        TRY(launch_gemm_qkv_rope(c, s, c->ws + c->map.xn, L.wq, L.wk, L.wv, T, pool_view(c, g, l), g.Q > 0 ? nullptr : &pack),
+            "wqkv");
+      } else if (big_mfma) TRY(launch_gemm_qkv_split(c, s, c->ws + c->map.xn, L.wq, L.wk, L.wv, T, dq, dkv, f.d_model, &n_part), "wqkv");
+      if (qkv_rope) {
+        // rotated, written
+      } else if (n_part > 0) {
         // q | k | v left as partial sums over K; the rotary kernel adds them
       } else if (big_mfma && f.d_model % 8 == 0 && dq % 4 == 0 && dkv % 4 == 0) {
         TRY(launch_gemm_qkv(s, c->ws + c->map.xn, L.wq, L.wk, L.wv, WSP(c, q32, float), WSP(c, k32, float),
@@ -393,7 +406,7 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
         TRY(gemm_any(c, s, c->ws + c->map.xn, L.wk, c->ws + c->map.k32, T, dkv, f.d_model, EPI_STORE_F32, true), "wk");
         TRY(gemm_any(c, s, c->ws + c->map.xn, L.wv, c->ws + c->map.v, T, dkv, f.d_model, EPI_STORE, true), "wv");
       }
-      TRY(launch_rope_kv(c, s, g, l, n_part), "rope_kv");
+      if (!qkv_rope) TRY(launch_rope_kv(c, s, g, l, n_part), "rope_kv");
     }
     {
       ProfScope p(c, s, 5, 2.0 * 2.0 * dkv * (double)g.max_kv * g.B);

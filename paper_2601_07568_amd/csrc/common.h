@@ -141,6 +141,7 @@ struct Workspace {
   size_t rope_sin;     // float [Tmax, dh/2]
   size_t tok_seq;      // int32 [Tmax]             sequence of each packed token
   size_t tok_pos;      // int32 [Tmax]             position of each token in its sequence
+  size_t kv_loc;       // int4  [Tmax]             where a row's K and V go: pool page (-1: not cached), slot, packed column (-1: none)
   size_t rows;         // int32 [Rmax]             compacted list of LM-head rows
   size_t lm_part;      // float [Rmax, n_vtiles, 4] per-tile (max, argmax, sumexp, sum e*z)
   size_t attn_part;    // float [attn_rows, dh] partial outputs, then [attn_rows, 2] (max, sum) of split-KV units
@@ -211,7 +212,8 @@ struct StepGeom {           // which tokens a forward runs over
   const int32_t* block_table;  // dev [B, max_pages]
 };
 
-hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g);
+// kv_loc: also leave every row's K/V destination in the workspace (and report pages that are not addressable)
+hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool kv_loc);
 // steps of at most 64 rows on the matrix-core path: length checks, token map, rotary table, embedding and (cand != nullptr)
 // the LM head's row list with the fixed outputs of the rows that are not masked, in one launch
 hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, int32_t* cand,
@@ -294,6 +296,11 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
                                    int* n_delta);
 hipError_t launch_gemm_qkv_split(dllm_ctx* c, hipStream_t s, const void* A, const void* Wq, const void* Wk, const void* Wv,
                                  int M, int dq, int dkv, int K, int* n_part);
+bool gemm_qkv_rope_wins(const dllm_ctx* c, int M);
+hipError_t launch_gemm_qkv_rope(dllm_ctx* c, hipStream_t s, const void* A, const void* Wq, const void* Wk, const void* Wv,
+                                int M, const KVView& pool, const KVView* pack);
+KVView pool_view(dllm_ctx* c, const StepGeom& g, int layer);
+KVView pack_view(dllm_ctx* c);
 hipError_t launch_gemm_qkv(hipStream_t s, const void* A, const void* Wq, const void* Wk, const void* Wv, float* q32,
                            float* k32, void* v, int M, int dq, int dkv, int K, const float* rscale,
                            const int32_t* m_dev);

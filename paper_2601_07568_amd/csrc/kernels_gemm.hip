@@ -17,7 +17,7 @@ constexpr int LG_BN = 128, LG_BK = 64;
 // reads stay a permutation of the KiB, and the loader's 16 consecutive lanes (two rows x eight
 // 16-byte columns of a slice) write 16 different bank groups instead of two.
 __device__ __forceinline__ int lg_swz(int g, int ks) { return (4 * g) ^ (2 * ks); }
-enum LgEpi { LG_STORE = 0, LG_STORE_F32 = 1, LG_RESID = 2, LG_SWIGLU = 3, LG_LMSTATS = 4, LG_QKV = 5 };
+enum LgEpi { LG_STORE = 0, LG_STORE_F32 = 1, LG_RESID = 2, LG_SWIGLU = 3, LG_LMSTATS = 4, LG_QKV = 5, LG_ROPE64 = 6, LG_ROPE128 = 7 };
 
 struct LgArgs {
   const bf16_t* A;
@@ -40,6 +40,12 @@ struct LgArgs {
   float* part;             // LMSTATS: [rows, n_parts, 4]
   int n_parts;
   int32_t mask_id;
+  // ROPE64 / ROPE128 (q/k/v product of heads of 64 / 128 channels, rotary embedding and K/V write in the epilogue)
+  const float* rope_cos;   // [M, dh/2]
+  const float* rope_sin;
+  const int4* loc;         // [M] where a row's K and V go: pool page (-1: not cached), slot, packed column (-1: none)
+  bf16_t *pool_k, *pool_v, *pack_k, *pack_v;
+  int page_tokens, tpad;
 };
 
 template <int BM, int EPI>
@@ -330,7 +336,11 @@ template <int EPI, int TM, int TN, int NSA, int NSW>
 __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   using G = GtGeom<TM, TN, NSA, NSW>;
   constexpr int BM = G::BM, BN = G::BN, CA = G::CA, CW = G::CW;
-  constexpr bool SWIGLU = EPI == LG_SWIGLU, STATS = EPI == LG_LMSTATS;
+  constexpr bool SWIGLU = EPI == LG_SWIGLU, STATS = EPI == LG_LMSTATS, ROPE = EPI == LG_ROPE64 || EPI == LG_ROPE128;
+  constexpr bool QKV = EPI == LG_QKV || ROPE;
+  constexpr int DH = EPI == LG_ROPE64 ? 64 : 128;
+  constexpr bool WIDE = EPI == LG_ROPE128 && TN == 4;           // a wave's weight rows are one whole head of 128 channels
+  static_assert(!ROPE || (TM == TN && TN % 2 == 0), "value tiles swap the operands; rotary pairs share a lane");
   constexpr int TILE_N = SWIGLU ? BN / 2 : BN;                  // output features of a tile
   static_assert(!SWIGLU || TN % 2 == 0, "gate and up tiles come in pairs");
   static_assert(!STATS || TN % 2 == 0, "64 columns per partial");
@@ -352,9 +362,9 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   const int n_tiles = tiles_m * a.tiles_n, n_items = n_tiles * a.k_splits;
   const int per_xcd = (n_items + 7) / 8, step = gridDim.x >> 3;
   const int n_grp = (tiles_m + a.group_m - 1) / a.group_m, gm_full = n_grp > 0 ? (tiles_m + n_grp - 1) / n_grp : 1;
-  struct Item { int split, tm, tn, k_begin, k_end; bool ok; };
+  struct Item { int split, tm, tn, k_begin, k_end; bool ok, val; };
   auto item_at = [&](int it) -> Item {
-    Item t{0, 0, 0, 0, K, false};
+    Item t{0, 0, 0, 0, K, false, false};
     const int iw = (blockIdx.x >> 3) + it * step;
     const int item = (blockIdx.x & 7) * per_xcd + iw;
     if (iw >= per_xcd || item >= n_items) return t;
@@ -367,6 +377,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < K ? t.k_begin + a.k_per : K;
     t.ok = true;
+    t.val = ROPE && t.tn * TILE_N >= N + a.N2;                  // a tile of the value projection
     return t;
   };
   // descriptors that end with the matrix: rows of a tile past the last one are not read (nor, in the epilogue, written)
@@ -381,7 +392,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     const int n0 = t.tn * TILE_N;
     const bf16_t* base = a.W;
     int row = n0, rows = N - n0 < TILE_N ? N - n0 : TILE_N;
-    if constexpr (EPI == LG_QKV) {
+    if constexpr (QKV) {
       // three projections stacked along the features: q rows [0, N), then k and v with N2 rows each (all multiples of
       // the tile width, so a tile belongs to one of them)
       if (n0 >= N) { base = n0 < N + a.N2 ? a.W2 : a.W3; row = n0 < N + a.N2 ? n0 - N : n0 - N - a.N2; }
@@ -401,12 +412,18 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
 
   // copies: instruction q of wave w fills LDS rows (w*C + q)*8 .. +7; lane l holds piece l%8 of row l/8
   const int l8 = lane >> 3, piece = (lane & 7) ^ (l8 >> 1);     // (odd q: the row's bit 3 flips bit 2 of the piece)
-  constexpr int FS = STATS ? 1 : (SWIGLU ? TN / 2 : TN);        // features between consecutive LDS rows of a tile
+  // features between consecutive LDS rows of a tile
+  constexpr int FS = STATS ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
   const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = vA0 ^ 64;
   const int vW0 = l8 * FS * K * 2 + piece * 16, vW1 = vW0 ^ 64;
   auto w_row = [&](int q) -> int {                              // weight row of the instruction's first LDS row
     const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
     if constexpr (STATS) return R;
+    // both members of a rotary pair (channels j and j + DH/2 of a head) in one lane, in tiles i and i + 2 (WIDE: two
+    // neighbouring channels per lane) or in tiles 2g and 2g + 1
+    else if constexpr (WIDE) return hw * 128 + (i >> 1) * 64 + 2 * c + (i & 1);
+    else if constexpr (EPI == LG_ROPE128) return (hw >> 1) * 128 + (hw & 1) * 32 + i * 64 + c;
+    else if constexpr (EPI == LG_ROPE64) return hw * 32 * TN + R % (32 * TN);
     else if constexpr (SWIGLU) return hw * 16 * TN + (TN / 2) * c + i % (TN / 2);
     else return hw * 32 * TN + TN * c + i;
   };
@@ -466,7 +483,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     else fw[b][n - TM] = *(const u32x4*)(pw + (n - TM) * 4096);
   };
 #pragma unroll
-  for (int n = 0; n < TM + TN; ++n) rd(0, n, sA + oA[0], sW + oW[0]);
+  for (int n = 0; n < TM + TN; ++n) rd(0, n, cur.val ? sW + oW[0] : sA + oA[0], cur.val ? sA + oA[0] : sW + oW[0]);
   int sa = 0, sw = 0;                                           // buffers of the current stage
   for (;;) {                                                    // work items
     f32x16 acc[TN][TM];                                         // [weight tile][token tile]
@@ -489,6 +506,13 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
         const int b = ks & 1;
         const unsigned char* pa = ks < 3 ? bA + oA[(ks + 1) & 3] : cA + oA[0];
         const unsigned char* pw = ks < 3 ? bW + oW[(ks + 1) & 3] : cW + oW[0];
+        if constexpr (ROPE) {
+          // value tiles: weights first, so that a lane holds one token and a store runs along the keys of a channel
+          const bool sw_ab = ks < 3 || st + 1 < ns || !nxt.ok ? cur.val : nxt.val;
+          const unsigned char* px = pa;
+          pa = sw_ab ? pw : pa;
+          pw = sw_ab ? px : pw;
+        }
 #pragma unroll
         for (int i = 0; i < TN; ++i)
 #pragma unroll
@@ -568,6 +592,159 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
           if (h == 0 && m < M && nb < N) {
             float* o = a.part + ((int64_t)m * a.n_parts + nb / 64) * 4;
             *(f32x4*)o = f32x4{st.m, __int_as_float(st.idx), st.s, st.t};
+          }
+        }
+      }
+    } else if constexpr (ROPE) {
+      const int pt = a.page_tokens, hkv = a.N2 / DH;
+      if (cur.val) {
+        // lane holds token l%32 of token tile i; features (e/4)*8 + (l/32)*4 + e%4 of weight tile j
+        int4 locs[TN];
+        float rss[TN];
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+          const int m = m0 + wm * 32 * TM + i * 32 + r;
+          locs[i] = a.loc[m < M ? m : M - 1];
+          rss[i] = a.rscale ? a.rscale[m < M ? m : M - 1] : 1.0f;
+        }
+        // Four lanes exchange their four tokens' values of four features, so that each holds one feature of four
+        // consecutive tokens and stores 8 bytes along the keys (2-byte stores, one per value and destination, made
+        // this epilogue 30 us long on 256 x 256 tiles); quads whose tokens do not lie side by side store one by one.
+        const int q = lane & 3;
+        constexpr int FQ = WIDE ? 2 : 1;                               // features between consecutive registers
+        const int vf = n0 - N - a.N2 + (WIDE ? wn * 128 + 8 * h : EPI == LG_ROPE128 ? (wn >> 1) * 128 + (wn & 1) * 32 + 4 * h : wn * 32 * TN + 4 * h);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+          __builtin_amdgcn_sched_barrier(0);
+          const int m = m0 + wm * 32 * TM + i * 32 + r;
+          const bool in = m < M;
+          const int page = in ? locs[i].x : -1, slot = locs[i].y, col = in ? locs[i].z : -1;
+          const float rs = rss[i];
+          // the quad's first token, and whether the others follow it
+          const int page0 = __builtin_amdgcn_mov_dpp(page, 0x00, 0xf, 0xf, true), slot0 = __builtin_amdgcn_mov_dpp(slot, 0x00, 0xf, 0xf, true);
+          const int col0 = __builtin_amdgcn_mov_dpp(col, 0x00, 0xf, 0xf, true);
+          const unsigned long long okp = __builtin_amdgcn_ballot_w64(page >= 0 && page == page0 && slot == slot0 + q);
+          const unsigned long long okk = __builtin_amdgcn_ballot_w64(col >= 0 && col == col0 + q);
+          const bool runp = ((okp >> (lane & ~3)) & 15) == 15, runk = ((okk >> (lane & ~3)) & 15) == 15;
+          bf16_t* const pool4 = a.pool_v + ((int64_t)page0 * a.N2 + vf + q * FQ) * pt + slot0;
+          bf16_t* const pack4 = a.pack_v + (int64_t)(vf + q * FQ) * a.tpad + col0;
+          bf16_t* const pool1 = a.pool_v + ((int64_t)page * a.N2 + vf) * pt + slot;
+          bf16_t* const pack1 = a.pack_v + (int64_t)vf * a.tpad + col;
+#pragma unroll
+          for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+              // feature of register e4*4: the weight rows lie in LDS as for the rotary pairs
+              const int f = WIDE ? (j >> 1) * 64 + 16 * e4 + (j & 1) : (EPI == LG_ROPE128 ? j * 64 : j * 32) + e4 * 8;
+              const uint32_t p01 = pack_bf16x2(acc[i][j][e4 * 4] * rs, acc[i][j][e4 * 4 + 1] * rs);
+              const uint32_t p23 = pack_bf16x2(acc[i][j][e4 * 4 + 2] * rs, acc[i][j][e4 * 4 + 3] * rs);
+              const uint32_t o01 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p01, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+              const uint32_t o23 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p23, 0xB1, 0xf, 0xf, true);
+              const uint32_t x = (q & 1) ? (o01 >> 16) | (p01 & 0xffff0000u) : (p01 & 0xffffu) | (o01 << 16);
+              const uint32_t y = (q & 1) ? (o23 >> 16) | (p23 & 0xffff0000u) : (p23 & 0xffffu) | (o23 << 16);
+              const uint32_t z = (uint32_t)__builtin_amdgcn_mov_dpp((int)((q & 2) ? x : y), 0x4E, 0xf, 0xf, true);   // lane ^ 2
+              const u32x2v four = (q & 2) ? u32x2v{z, y} : u32x2v{x, z};
+              if (runp) __builtin_memcpy(pool4 + (int64_t)f * pt, &four, 8);
+              if (runk) __builtin_memcpy(pack4 + (int64_t)f * a.tpad, &four, 8);
+              if (!runp && page >= 0) {
+                bf16_t* o = pool1 + (int64_t)f * pt;
+                o[0] = (bf16_t)p01; o[(int64_t)FQ * pt] = (bf16_t)(p01 >> 16);
+                o[(int64_t)2 * FQ * pt] = (bf16_t)p23; o[(int64_t)3 * FQ * pt] = (bf16_t)(p23 >> 16);
+              }
+              if (!runk && col >= 0) {
+                bf16_t* o = pack1 + (int64_t)f * a.tpad;
+                o[0] = (bf16_t)p01; o[(int64_t)FQ * a.tpad] = (bf16_t)(p01 >> 16);
+                o[(int64_t)2 * FQ * a.tpad] = (bf16_t)p23; o[(int64_t)3 * FQ * a.tpad] = (bf16_t)(p23 >> 16);
+              }
+            }
+        }
+      } else {
+        // lane holds weight rows l%32 of its tiles and, in register e, token row (e/4)*8 + (l/32)*4 + e%4
+        const bool is_q = n0 < N;
+        const int lrow = wm * 32 * TM + h * 4;
+        // first channel pair of the lane (of head `head` of its projection) and its place in the projection's rows
+        const int f0 = (is_q ? n0 : n0 - N) + (EPI == LG_ROPE128 && TN == 2 ? (wn >> 1) * 128 : wn * 32 * TN);
+        const int j0 = WIDE ? 2 * r : (EPI == LG_ROPE128 ? (wn & 1) * 32 + r : r);
+        const int head = f0 / DH;
+        const gt_rsrc rc = rsrc(a.rope_cos + (int64_t)m0 * (DH / 2), (int64_t)rows * (DH / 2) * 4);
+        const gt_rsrc rn = rsrc(a.rope_sin + (int64_t)m0 * (DH / 2), (int64_t)rows * (DH / 2) * 4);
+        const gt_rsrc rl = rsrc(a.loc + m0, (int64_t)rows * 16);
+        const gt_rsrc rq = rsrc((bf16_t*)a.C + (int64_t)m0 * N, (int64_t)rows * N * 2);
+        const int vc = (lrow * (DH / 2) + j0) * 4, vq = (lrow * N + f0 + j0) * 2;
+        constexpr int G2 = TN / 2;                              // channel pairs of a lane
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+          // what 16 rows need is requested together
+          __builtin_amdgcn_sched_barrier(0);
+          f32x4 rs4[4];
+          float cs[16][WIDE ? 2 : 1], sn[16][WIDE ? 2 : 1];
+          const u32x4 locs = __builtin_amdgcn_raw_buffer_load_b128(rl, (wm * 32 * TM + r) * 16, j * 32 * 16, 0);   // row j*32 + l%32
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4)
+            rs4[e4] = a.rscale ? __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, lrow * 4, (j * 32 + e4 * 8) * 4, 0))
+                               : f32x4{1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int so = (j * 32 + (e >> 2) * 8 + (e & 3)) * (DH / 2) * 4;
+            if constexpr (WIDE) {
+              const f32x2_t c2 = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rc, vc, so, 0));
+              const f32x2_t s2 = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rn, vc, so, 0));
+              cs[e][0] = c2[0]; cs[e][1] = c2[1]; sn[e][0] = s2[0]; sn[e][1] = s2[1];
+            } else {
+              cs[e][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, vc, so, 0));
+              sn[e][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rn, vc, so, 0));
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int row = j * 32 + (e >> 2) * 8 + (e & 3);
+            const float rs = rs4[e >> 2][e & 3];
+            float lo[G2], hi[G2];
+#pragma unroll
+            for (int g = 0; g < G2; ++g) {
+              const float x = (WIDE ? acc[g][j][e] : acc[2 * g][j][e]) * rs, y = (WIDE ? acc[g + 2][j][e] : acc[2 * g + 1][j][e]) * rs;
+              const float c = cs[e][WIDE ? g : 0], s = sn[e][WIDE ? g : 0];
+              lo[g] = x * c - y * s;
+              hi[g] = y * c + x * s;
+            }
+            if (is_q) {
+              const int so = row * N * 2;
+              if constexpr (WIDE) {
+                __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(lo[0], lo[1]), rq, vq, so, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(hi[0], hi[1]), rq, vq + DH, so, 0);
+              } else {
+#pragma unroll
+                for (int g = 0; g < G2; ++g) {
+                  __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(lo[g]), rq, vq + g * DH * 2, so, 0);
+                  __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(hi[g]), rq, vq + g * DH * 2 + DH, so, 0);
+                }
+              }
+            } else if (m0 + lrow + row < M) {
+              auto of_row = [&](uint32_t v) -> int {            // the value lane `row within the tile` holds
+                const int ln = (e >> 2) * 8 + (e & 3);
+                const int v0 = __builtin_amdgcn_readlane((int)v, ln), v1 = __builtin_amdgcn_readlane((int)v, ln + 4);
+                return h ? v1 : v0;
+              };
+              const int slot = of_row(locs[1]);
+#pragma unroll
+              for (int dst = 0; dst < 2; ++dst) {
+                const int at = of_row(dst == 0 ? locs[0] : locs[2]);
+                if (at < 0) continue;
+                bf16_t* kp = dst == 0 ? a.pool_k + (((int64_t)at * hkv + head) * pt + slot) * DH + j0
+                                      : a.pack_k + ((int64_t)head * a.tpad + at) * DH + j0;
+                const int64_t hstep = (int64_t)(dst == 0 ? pt : a.tpad) * DH;     // to the same row of the next head
+                if constexpr (WIDE) {
+                  *(uint32_t*)kp = pack_bf16x2(lo[0], lo[1]);
+                  *(uint32_t*)(kp + DH / 2) = pack_bf16x2(hi[0], hi[1]);
+                } else {
+#pragma unroll
+                  for (int g = 0; g < G2; ++g) {
+                    kp[g * hstep] = f32_to_bf16(lo[g]);
+                    kp[g * hstep + DH / 2] = f32_to_bf16(hi[g]);
+                  }
+                }
+              }
+            }
           }
         }
       }
@@ -658,6 +835,8 @@ static int gt_cus = 256;
 #define GT_KERNELS(X)                                                                                   \
   X(LG_SWIGLU, 4, 4, 2, 3) X(LG_SWIGLU, 2, 4, 2, 3) X(LG_SWIGLU, 2, 2, 4, 5)                            \
   X(LG_RESID, 4, 4, 2, 3) X(LG_RESID, 2, 4, 2, 3) X(LG_RESID, 2, 2, 4, 5) X(LG_RESID, 2, 1, 3, 4)       \
+  X(LG_ROPE64, 2, 2, 4, 5) X(LG_ROPE64, 2, 2, 2, 3)                            \
+  X(LG_ROPE128, 4, 4, 2, 3) X(LG_ROPE128, 2, 2, 4, 5) X(LG_ROPE128, 2, 2, 2, 3)                         \
   X(LG_QKV, 4, 4, 2, 3) X(LG_QKV, 2, 4, 2, 3) X(LG_QKV, 2, 2, 4, 5) X(LG_QKV, 2, 1, 3, 4)               \
   X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS, 2, 2, 4, 5)
 hipError_t init_gemm_tiles() {
@@ -684,7 +863,8 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1) {
   using G = GtGeom<TM, TN, NSA, NSW>;
   constexpr int tile_n = EPI == LG_SWIGLU ? G::BN / 2 : G::BN;
   a.tiles_m = (a.M + G::BM - 1) / G::BM;
-  a.tiles_n = EPI == LG_QKV ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n;
+  constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128;
+  a.tiles_n = qkv ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n;
   a.k_splits = k_splits;
   if (k_splits == 1) a.k_per = a.K;
   a.group_m = 8;
@@ -698,13 +878,14 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1) {
 // equally long), a 128 x 64 one 0.22.  Measured against each other (K = 3584 .. 18944, us): 1024 x 37888: 271 / 286 /
 // 297; 256 x 24576: 85 / 55 / 61; 128 x 24576: 85 / 50 / 39; 1024 x 3584 x 3584: 48 (4 K shares) / 38 (2) / 42.
 enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_N = 4 };
-struct GtPlan { GtTile tile; int splits, k_per; };
+struct GtPlan { GtTile tile; int splits, k_per; double us; };
 // NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile
-static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok) {
+// fold_us_per_share: what each share behind the first costs (written here, read by the kernel that adds it)
+static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok, double fold_us_per_share) {
   static const int bm[GT_N] = {256, 128, 128, 128}, bn[GT_N] = {256, 256, 128, 64};
-  static const double unit[GT_N] = {1.0, 0.6, 0.33, 0.22};
-  GtPlan best{GT_128x128, 1, K};
-  double best_t = 1e30;
+  // (up to 256 rows a 128-row tile waits for its weights, which no other row tile has brought in)
+  const double unit[GT_N] = {1.0, 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22};
+  GtPlan best{GT_128x128, 1, K, 1e30};
   for (int c = 0; c < GT_N; ++c) {
     if (!((width_ok >> c) & 1u)) continue;
     const int tiles = ((M + bm[c] - 1) / bm[c]) * ((NW + bn[c] - 1) / bn[c]);
@@ -714,10 +895,9 @@ static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok) {
       const int n_sp = (K + k_per - 1) / k_per;
       if (n_sp != sp) continue;
       const double rounds = (double)((tiles * sp + gt_cus - 1) / gt_cus);
-      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain; a share's [M, NW] floats are written
-      // and read again by the kernel that adds them
-      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + 4.0) + (sp - 1) * (8.0 * M * (double)NW / 4.0e6);
-      if (t < best_t) { best_t = t; best = GtPlan{(GtTile)c, sp, k_per}; }
+      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain
+      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + 4.0) + (sp - 1) * fold_us_per_share;
+      if (t < best.us) best = GtPlan{(GtTile)c, sp, k_per, t};
     }
   }
   return best;
@@ -766,7 +946,7 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
   a.delta = (float*)(c->ws + c->map.delta);
   a.delta_stride = c->map.lg_delta_stride;
   if (gt_usable(M, K)) {
-    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, 0xfu);
+    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, 0xfu, 1.0 + 8.0 * M * (double)N / 4.0e6);
     a.k_per = p.k_per;
     *n_delta = p.splits - 1;
     switch (p.tile) {
@@ -802,7 +982,7 @@ hipError_t launch_gemm_qkv_split(dllm_ctx* c, hipStream_t s, const void* A, cons
   a.m_dev = c->rows_dev;
   // a tile belongs to one of the projections; the buffers of a split product cover lg_delta_rows rows
   const unsigned width_ok = (dq % 256 == 0 && dkv % 256 == 0 ? 0x3u : 0u) | (dq % 128 == 0 && dkv % 128 == 0 ? 0x4u : 0u) | 0x8u;
-  const GtPlan p = gt_plan(M, dq + 2 * dkv, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, width_ok);
+  const GtPlan p = gt_plan(M, dq + 2 * dkv, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, width_ok, 1.0 + 8.0 * M * (dq + 2.0 * dkv) / 4.0e6);
   a.k_per = p.k_per;
   a.delta = (float*)(c->ws + c->map.qkvp);
   a.delta_stride = c->map.qkvp_stride;
@@ -813,6 +993,50 @@ hipError_t launch_gemm_qkv_split(dllm_ctx* c, hipStream_t s, const void* A, cons
     case GT_128x128: return gt_launch<LG_QKV, 2, 2, 4, 5>(s, a, p.splits);
     default: return gt_launch<LG_QKV, 2, 1, 3, 4>(s, a, p.splits);
   }
+}
+
+// The fused q/k/v product with the rotary embedding and the K/V write in its epilogue (heads of 64 or 128 channels,
+// projections that are whole 128-row tiles): the float projections never reach memory and the rotary kernel's launch is
+// saved, but the sum over K cannot be split.
+static bool qkv_rope_usable(const dllm_ctx* c, int M) {
+  const dllm_config& f = c->cfg;
+  return gt_usable(M, f.d_model) && (f.n_q_heads * f.head_dim) % 128 == 0 && (f.n_kv_heads * f.head_dim) % 128 == 0;
+}
+// Taken unless the split product and the rotary kernel behind it are quicker by the estimate (the rotary kernel: about
+// 10 us and its operands at 2.5 TB/s).  Measured, product + rotary
+// kernel against this one (us): 15348 rows x 4608 x 3584: 464 + 278 / 513; 1184 x 12288 x 4096: 107 + 38 / 128; 1024 x
+// 4608 x 3584: 42 + 21 / 61; 211 x 12288 x 4096: 43 + 13 / 48; 128 rows there: 33 + 15 / 52 (96 workgroups), not taken.
+bool gemm_qkv_rope_wins(const dllm_ctx* c, int M) {
+  if (!qkv_rope_usable(c, M)) return false;
+  const dllm_config& f = c->cfg;
+  const int dq = f.n_q_heads * f.head_dim, dkv = f.n_kv_heads * f.head_dim, nw = dq + 2 * dkv, K = f.d_model;
+  const bool w256 = dq % 256 == 0 && dkv % 256 == 0;
+  const GtPlan fused = gt_plan(M, nw, K, 1, (w256 && f.head_dim == 128 ? 0x1u : 0u) | 0x4u, 0.0);
+  const GtPlan split = gt_plan(M, nw, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, (w256 ? 0x3u : 0u) | 0xcu, 0.0);
+  return fused.us <= split.us + 10.0 + (4.0 * split.splits + 2.0) * M * (double)nw / 2.5e6;
+}
+hipError_t launch_gemm_qkv_rope(dllm_ctx* c, hipStream_t s, const void* A, const void* Wq, const void* Wk, const void* Wv,
+                                int M, const KVView& pool, const KVView* pack) {
+  const dllm_config& f = c->cfg;
+  const int dq = f.n_q_heads * f.head_dim, dkv = f.n_kv_heads * f.head_dim, K = f.d_model;
+  LgArgs a;
+  memset(&a, 0, sizeof(a));
+  a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wq; a.W2 = (const bf16_t*)Wk; a.W3 = (const bf16_t*)Wv;
+  a.M = M; a.N = dq; a.N2 = dkv; a.K = K;
+  a.C = WSM(c, q, bf16_t);
+  a.rscale = WSM(c, rscale, float);
+  a.m_dev = c->rows_dev;
+  a.rope_cos = WSM(c, rope_cos, float); a.rope_sin = WSM(c, rope_sin, float);
+  a.loc = WSM(c, kv_loc, int4);
+  a.pool_k = (bf16_t*)pool.k; a.pool_v = (bf16_t*)pool.v; a.page_tokens = pool.page_tokens;
+  if (pack) { a.pack_k = (bf16_t*)pack->k; a.pack_v = (bf16_t*)pack->v; a.tpad = pack->tpad; }
+  const bool dh64 = f.head_dim == 64, w256 = dq % 256 == 0 && dkv % 256 == 0 && !dh64;
+  const GtPlan p = gt_plan(M, dq + 2 * dkv, K, 1, (w256 ? 0x1u : 0u) | 0x4u, 0.0);
+  if (p.tile == GT_256x256) return gt_launch<LG_ROPE128, 4, 4, 2, 3>(s, a);
+  // one tile per CU: the deep ring; more: two workgroups per CU
+  if (((M + 127) / 128) * ((dq + 2 * dkv) / 128) <= gt_cus)
+    return dh64 ? gt_launch<LG_ROPE64, 2, 2, 4, 5>(s, a) : gt_launch<LG_ROPE128, 2, 2, 4, 5>(s, a);
+  return dh64 ? gt_launch<LG_ROPE64, 2, 2, 2, 3>(s, a) : gt_launch<LG_ROPE128, 2, 2, 2, 3>(s, a);
 }
 
 // q32[M,dq], k32[M,dkv] (float) and v[M,dkv] (bfloat16) = A[M,K] times the three projections, one launch
@@ -838,7 +1062,7 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
   a.m_dev = m_dev;
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wg; a.W2 = (const bf16_t*)Wu; a.C = H; a.M = M; a.N = F; a.K = K;
   if (gt_usable(M, K)) {
-    switch (gt_plan(M, 2 * F, K, 1, 0x7u).tile) {
+    switch (gt_plan(M, 2 * F, K, 1, 0x7u, 0.0).tile) {
       case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a);
       case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a);
       default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a);

@@ -89,23 +89,39 @@ __global__ void k_seq_check(int T, int B, int Q, int max_len, const int32_t* pre
 
 // token map: sequence and position of every row of the forward, from the checked lengths.  Rows of a packed forward
 // past the last sequence's end and padding rows of a step have no position (-1): nothing of theirs is cached or attended.
+// loc != nullptr: also where the row's K and V go in every layer - the page and slot of the pool (page -1: the row is
+// not cached or its page is not addressable) and the column of the packed scratch (-1: none).
 __global__ void k_token_map(int T, int B, int Q, const int32_t* len_safe, int32_t* tok_seq, int32_t* tok_pos,
-                            const int32_t* q_valid) {
+                            const int32_t* q_valid, int4* loc, KVView pool, const int32_t* cu_pad, const int32_t* n_cache,
+                            int32_t* status) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= T) return;
+  int b, pos;
   if (Q > 0) {
-    int b = t / Q;
-    tok_seq[t] = b;
+    b = t / Q;
     // padding rows of a step (past q_valid of their sequence; q_valid < 0: the whole sequence) have no position
-    tok_pos[t] = (q_valid && (t - b * Q) >= q_valid[b]) ? -1 : len_safe[b] + (t - b * Q);
+    pos = (q_valid && (t - b * Q) >= q_valid[b]) ? -1 : len_safe[b] + (t - b * Q);
   } else {
     int lo = 0, hi = B;  // largest b with cu[b] <= t
     while (hi - lo > 1) {
       int mid = (lo + hi) >> 1;
       if (len_safe[mid] <= t) lo = mid; else hi = mid;
     }
-    tok_seq[t] = lo;
-    tok_pos[t] = t < len_safe[lo + 1] ? t - len_safe[lo] : -1;
+    b = lo;
+    pos = t < len_safe[lo + 1] ? t - len_safe[lo] : -1;
+  }
+  tok_seq[t] = b;
+  tok_pos[t] = pos;
+  if (loc) {
+    int4 l = make_int4(-1, 0, -1, 0);
+    if (pos >= 0 && (n_cache == nullptr || pos < n_cache[b])) {
+      const int pi = pos / pool.page_tokens;
+      const int page = pi < pool.max_pages ? pool.table[(int64_t)b * pool.max_pages + pi] : -1;
+      if (page >= 0 && page < pool.n_pages) { l.x = page; l.y = pos - pi * pool.page_tokens; }
+      else atomicOr(status, DLLM_STATUS_BAD_PAGE);
+    }
+    if (cu_pad && pos >= 0) l.z = cu_pad[b] + pos;
+    loc[t] = l;
   }
 }
 
@@ -728,7 +744,7 @@ __global__ void k_set_i32(int32_t* p, int n, int32_t v) {
 #define WS(c, field, type) ((type*)((c)->ws + (c)->map.field))
 #define IS_BF16(c) ((c)->cfg.dtype == DLLM_BF16)
 
-hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g) {
+hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool kv_loc) {
   const bool live = g.Q > 0 && g.n_live != nullptr;
   k_seq_check<<<1, 256, 0, s>>>(g.T, g.B, g.Q, g.Q > 0 ? g.max_kv - g.Q : g.max_kv, g.prefix_len, g.cu_seqlens,
                                 WS(c, len_safe, int32_t), WS(c, cu_pad, int32_t), g.Q > 0 ? g.q_valid : nullptr,
@@ -738,7 +754,9 @@ hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g) {
   if (e != hipSuccess) return e;
   const int32_t* qv = g.Q > 0 ? (live ? WS(c, q_valid_eff, int32_t) : g.q_valid) : nullptr;
   k_token_map<<<(g.T + 255) / 256, 256, 0, s>>>(g.T, g.B, g.Q, WS(c, len_safe, int32_t), WS(c, tok_seq, int32_t),
-                                                WS(c, tok_pos, int32_t), qv);
+                                                WS(c, tok_pos, int32_t), qv, kv_loc ? WS(c, kv_loc, int4) : nullptr,
+                                                pool_view(c, g, 0), g.Q > 0 ? nullptr : WS(c, cu_pad, int32_t),
+                                                g.Q > 0 ? nullptr : g.n_cache, WS(c, status, int32_t));
   return hipGetLastError();
 }
 
@@ -855,7 +873,7 @@ hipError_t launch_gemm_generic(dllm_ctx* c, hipStream_t s, const void* A, const 
   return hipGetLastError();
 }
 
-static KVView pool_view(dllm_ctx* c, const StepGeom& g, int layer) {
+KVView pool_view(dllm_ctx* c, const StepGeom& g, int layer) {
   const dllm_config& f = c->cfg;
   const size_t slab = kv_slab_elems(f) * elem_size(f);
   KVView kv;
@@ -872,7 +890,7 @@ static KVView pool_view(dllm_ctx* c, const StepGeom& g, int layer) {
   return kv;
 }
 
-static KVView pack_view(dllm_ctx* c) {
+KVView pack_view(dllm_ctx* c) {
   const dllm_config& f = c->cfg;
   KVView kv;
   kv.k = c->ws + c->map.kpack;

@@ -65,3 +65,32 @@ def test_several_items_per_workgroup():
     """1600 x 8192 gate and up rows: more tiles than workgroups, the copies of a workgroup run on into its next tile."""
     wide = synth.ModelShape(1, 128, 2, 1, 64, 8192, 600, 599, dtype="bf16", lm_head_scale=8.0, name="tile-items")
     run(wide, [40 + b for b in range(16)], 100)
+
+
+@pytest.mark.parametrize("ms", [EDGE, LONG], ids=["head-dim-64", "head-dim-128"])
+@pytest.mark.parametrize("lens,n_cache,pt", [([129, 70, 31], [129, 64, 0], 32), ([67], [66], 24), ([300, 3, 5, 150], [299, 3, 2, 150], 64)])
+def test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt):
+    """The q/k/v product writes K and V itself: packed sequences that start anywhere in a tile, positions that are not
+    cached, pages of 24 tokens (four tokens of a value row may end a page).  Slots past n_cache stay as they were."""
+    w = synth.Weights(ms, 3)
+    B = len(lens)
+    mp = (max(lens) + pt - 1) // pt
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=B * mp, max_batch=B, max_q=32,
+                        max_tokens=sum(lens))
+    perm = np.random.default_rng(1).permutation(B * mp)
+    table = H.identity_table(eng, B, perm)
+    seqs = [synth.random_tokens(ms, 20 + i, n) for i, n in enumerate(lens)]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    eng.kv_pool.view(torch.bfloat16).fill_(7.0)
+    eng.prefill_kv(eng.i32(np.concatenate(seqs)), eng.i32(cu), eng.i32(table), eng.i32(n_cache), total_tokens=int(cu[-1]),
+                   max_seqlen=max(lens))
+    for b in range(B):
+        ck, cv = O.prefill(w, seqs[b], widen=W, store=ST)
+        for which, ref in ((0, ck[0]), (1, cv[0])):
+            got = H.gather_cache(eng, table[b], lens[b], 0, which)
+            n = n_cache[b]
+            # one bfloat16 rounding of a float sum against one of the exact sum: neighbours in bfloat16 at most (2^-7)
+            assert np.abs(got[:n] - ref[:n]).max(initial=0.0) <= 2.0 ** -7 * np.abs(ref).max(), (b, which)
+            assert (got[n:] == 7.0).all(), (b, which)
+    assert eng.read_status() == 0
+    eng.close()
