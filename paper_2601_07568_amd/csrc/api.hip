@@ -148,6 +148,13 @@ extern "C" int dllm_create(dllm_ctx** out, const dllm_config* cfg, const dllm_we
     // such a failure must not surface later as the "last error" of an unrelated launch
     if (e1 != hipSuccess || e2 != hipSuccess) (void)hipGetLastError();
   }
+  uintptr_t low = (uintptr_t)kv_pool | (uintptr_t)c->tok_emb | (uintptr_t)c->final_norm | (uintptr_t)c->lm_head;
+  for (int l = 0; l < cfg->n_layers; ++l) {
+    const dllm_layer_w& L = c->layers[l];
+    low |= (uintptr_t)L.attn_norm | (uintptr_t)L.wq | (uintptr_t)L.wk | (uintptr_t)L.wv | (uintptr_t)L.wo | (uintptr_t)L.mlp_norm |
+           (uintptr_t)L.w_gate | (uintptr_t)L.w_up | (uintptr_t)L.w_down;
+  }
+  c->f32_aligned = (low & 15) == 0;
   *out = c;
   return DLLM_OK;
 }
@@ -333,7 +340,7 @@ static int run_forward(dllm_ctx* c, hipStream_t s, const StepGeom& g0, int n_lay
   // the first launches check the device-resident lengths against the host values that size the launches and leave
   // clamped copies in the workspace: every kernel after them addresses memory with those
   // (one launch together with the token map, the rotary table and the embedding on the weight-streaming path)
-  const bool pro = skinny_path(c, g0);
+  const bool pro = skinny_path(c, g0) || s32_supported(c, g0);
   if (pro)
     TRY(launch_sk_prologue(c, s, g0, n_layers_run > 0 ? c->layers[0].attn_norm : c->final_norm,
                            head ? head->cand : nullptr, head ? head->conf : nullptr, head ? head->entropy : nullptr),
@@ -370,22 +377,26 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   // leaves x * gain of the next norm in fragment order plus partial sums of squares per row, and the consuming
   // GEMM applies the row's normalisation factor to its float accumulators.
   const bool sk = skinny_path(c, g);
+  // float denoise steps of as few rows: the same chain of launches, the gain applied by the consuming product
+  const bool s32 = s32_supported(c, g), few = sk || s32;
   const bool big_mfma = large_mfma(c);
   const bool qkv_rope = !sk && big_mfma && gemm_qkv_rope_wins(c, T);   // (the token map has left the rows' K/V places)
   const int ss_groups = (f.d_model + 15) / 16;
   int n_ss = 1;      // partial sums of squares the current skinny-path GEMM input comes with
-  if (!sk) {            // (on the weight-streaming path run_forward's prologue launch has done both)
+  if (!few) {           // (on the few-row paths run_forward's prologue launch has done both)
     TRY(launch_embed(c, s, g), "embed");
     TRY(launch_rope_table(c, s, g), "rope_table");
   }
   int pending = 0;   // open residual sums (K splits of the last residual projection) not yet added to x
   for (int l = 0; l < n_layers_run; ++l) {
     const dllm_layer_w& L = c->layers[l];
-    if (!sk) TRY(launch_rmsnorm(c, s, L.attn_norm, T, nullptr, nullptr, 0, pending), "rmsnorm");
+    if (!few) TRY(launch_rmsnorm(c, s, L.attn_norm, T, nullptr, nullptr, 0, pending), "rmsnorm");
     pending = 0;
     if (sk) {
       ProfScope p(c, s, 0, 2.0 * (dq + 2.0 * dkv) * f.d_model);
       TRY(launch_sk_qkv(c, s, g, l, attention_view(c, g, l), n_ss), "qkv");
+    } else if (s32) {
+      TRY(launch_s32_qkv(c, s, g, l, attention_view(c, g, l), n_ss), "qkv");
     } else {
       ProfScope p(c, s, 0, 2.0 * T * (dq + 2.0 * dkv) * f.d_model);   // large path: work recorded in flops
       int n_part = 0;
@@ -410,12 +421,16 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
     }
     {
       ProfScope p(c, s, 5, 2.0 * 2.0 * dkv * (double)g.max_kv * g.B);
-      if (attn_step_supported(c, g)) TRY(launch_attn_step(c, s, g, attention_view(c, g, l), sk), "attention");
+      if (s32) TRY(launch_s32_attn(c, s, g, attention_view(c, g, l)), "attention");
+      else if (attn_step_supported(c, g)) TRY(launch_attn_step(c, s, g, attention_view(c, g, l), sk), "attention");
       else TRY(launch_attention_generic(c, s, g, l), "attention");
     }
     if (sk) {
       ProfScope p(c, s, 1, 2.0 * dq * f.d_model);
       TRY(launch_sk_resid(c, s, c->ws + c->map.o, c->packed_layers[l].wo, T, f.d_model, dq, L.mlp_norm), "wo");
+      n_ss = ss_groups;
+    } else if (s32) {
+      TRY(launch_s32_resid(c, s, WSP(c, o, float), L.wo, T, dq), "wo");
       n_ss = ss_groups;
     } else {
       ProfScope p(c, s, 1, 2.0 * T * (double)dq * f.d_model);
@@ -423,7 +438,7 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
         TRY(launch_gemm_resid_split(c, s, c->ws + c->map.o, L.wo, WSP(c, x, float), T, f.d_model, dq, &pending), "wo");
       else TRY(gemm_any(c, s, c->ws + c->map.o, L.wo, c->ws + c->map.x, T, f.d_model, dq, EPI_RESID), "wo");
     }
-    if (!sk) TRY(launch_rmsnorm(c, s, L.mlp_norm, T, nullptr, nullptr, 0, pending), "rmsnorm");
+    if (!few) TRY(launch_rmsnorm(c, s, L.mlp_norm, T, nullptr, nullptr, 0, pending), "rmsnorm");
     pending = 0;
     if (sk) {
       {
@@ -435,6 +450,9 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
       const void* gain_next = l + 1 < n_layers_run ? c->layers[l + 1].attn_norm : c->final_norm;
       TRY(launch_sk_resid(c, s, c->ws + c->map.h, c->packed_layers[l].w_down, T, f.d_model, f.d_ff, gain_next),
           "w_down");
+    } else if (s32) {
+      TRY(launch_s32_swiglu(c, s, l, T, n_ss), "swiglu");
+      TRY(launch_s32_resid(c, s, WSP(c, h, float), L.w_down, T, f.d_ff), "w_down");
     } else {
       if (big_mfma) {
         ProfScope p(c, s, 2, 2.0 * T * 2.0 * f.d_ff * f.d_model);
@@ -459,6 +477,8 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   if (logits_out) {
     if (sk) {
       TRY(launch_sk_f32(c, s, c->ws + c->map.xn, c->packed_lm_head, logits_out, T, f.vocab, f.d_model, n_ss), "lm_head");
+    } else if (s32) {
+      TRY(launch_s32_logits(c, s, logits_out, T, n_ss), "lm_head");
     } else {
       TRY(launch_rmsnorm(c, s, c->final_norm, T, nullptr, nullptr, 0, pending), "final_norm");
       pending = 0;
@@ -467,8 +487,8 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   }
   if (head) {
     const int max_rows = T < c->map.r_max ? T : (int)c->map.r_max;
-    if (!sk) TRY(launch_mask_rows(c, s, g, head->cand, head->conf, head->entropy), "mask_rows");
-    if (!sk) {
+    if (!few) TRY(launch_mask_rows(c, s, g, head->cand, head->conf, head->entropy), "mask_rows");
+    if (!few) {
       TRY(launch_rmsnorm(c, s, c->final_norm, max_rows, WSP(c, rows, int32_t), WSP(c, status, int32_t) + 1, 0, pending),
           "final_norm");
       pending = 0;
@@ -477,11 +497,13 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
     if (sk) {
       ProfScope p(c, s, 4, 2.0 * f.vocab * f.d_model);
       TRY(launch_sk_lmstats(c, s, T, n_ss, &n_parts), "lm_head");
+    } else if (s32) {
+      TRY(launch_s32_lmstats(c, s, T, n_ss, &n_parts), "lm_head");
     } else if (big_mfma) {
       ProfScope p(c, s, 4, 2.0 * max_rows * (double)f.vocab * f.d_model);   // upper bound: max_rows rows
       TRY(launch_gemm_lmstats(c, s, max_rows, &n_parts), "lm_head");
     } else TRY(launch_lm_head_generic(c, s, max_rows), "lm_head");
-    TRY(launch_lm_merge(c, s, max_rows, n_parts, head->cand, head->conf, head->entropy, sk), "lm_merge");
+    TRY(launch_lm_merge(c, s, max_rows, n_parts, head->cand, head->conf, head->entropy, few), "lm_merge");
   }
   return DLLM_OK;
 }

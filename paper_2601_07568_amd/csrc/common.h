@@ -177,6 +177,7 @@ struct dllm_ctx {
   char* ws;
   dllm::Workspace map;
   int kernel_mode;
+  int f32_aligned;           // float models: every weight and the pool are 16-byte aligned (the few-row kernels load that wide)
   const int32_t* rows_dev;   // during a step with a live count: device count of rows the large GEMMs compute; else nullptr
   char hip_error[256];
   // per-kernel event timing (dllm_profile_*)
@@ -214,7 +215,7 @@ struct StepGeom {           // which tokens a forward runs over
 
 // kv_loc: also leave every row's K/V destination in the workspace (and report pages that are not addressable)
 hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool kv_loc);
-// steps of at most 64 rows on the matrix-core path: length checks, token map, rotary table, embedding and (cand != nullptr)
+// steps of at most 64 rows on the matrix-core paths: length checks, token map, rotary table, embedding and (cand != nullptr)
 // the LM head's row list with the fixed outputs of the rows that are not masked, in one launch
 hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, int32_t* cand,
                               float* conf, float* entropy);
@@ -275,7 +276,7 @@ hipError_t launch_copy_f32(hipStream_t s, const float* src, float* dst, size_t n
 hipError_t launch_gather_rows(hipStream_t s, int B, int row_len, const int32_t* index, const int32_t* n_index,
                               const int32_t* src, int32_t* dst, int32_t fill, bool scatter);
 
-// ---- launchers implemented in kernels_skinny.hip / kernels_attention.hip / kernels_gemm.hip (bf16, matrix cores) --
+// ---- launchers implemented in kernels_skinny.hip / _attention.hip / _gemm.hip (bf16, matrix cores) ------
 bool mfma_supported(const dllm_ctx* c);
 size_t packed_weight_bytes(int N, int K);
 hipError_t launch_pack_weight(hipStream_t s, const void* W, void* P, int N, int K);
@@ -309,6 +310,15 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
 hipError_t launch_gemm_lmstats(dllm_ctx* c, hipStream_t s, int max_rows, int* n_parts_out);
 hipError_t launch_probe_read(hipStream_t s, const void* buf, size_t bytes, void* sink);
 hipError_t launch_probe_mfma(hipStream_t s, int iters, int random_bits, void* sink, double* flops);
+// float models, steps of at most 64 rows (kernels_f32.hip).  The rows' sums of squares go from launch to launch as on the
+// bfloat16 weight-streaming path: n_ss partials per row.
+bool s32_supported(const dllm_ctx* c, const StepGeom& g);
+hipError_t launch_s32_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int layer, const KVView& pool, int n_ss);
+hipError_t launch_s32_attn(dllm_ctx* c, hipStream_t s, const StepGeom& g, const KVView& kv);
+hipError_t launch_s32_resid(dllm_ctx* c, hipStream_t s, const float* A, const void* W, int M, int K);
+hipError_t launch_s32_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_ss);
+hipError_t launch_s32_logits(dllm_ctx* c, hipStream_t s, float* out, int M, int n_ss);
+hipError_t launch_s32_lmstats(dllm_ctx* c, hipStream_t s, int M, int n_ss, int* n_parts_out);
 bool attn_step_supported(const dllm_ctx* c, const StepGeom& g);
 hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const KVView& kv, bool frag_out);
 

@@ -526,10 +526,12 @@ static void sk_row_scale(dllm_ctx* c, SkArgs& a, int n_ss) {
 // the checks of the device-resident lengths (workgroup 0 writes the clamped copies, the live-row count and the status
 // bit, exactly as k_seq_check does; every workgroup derives its own sequence's values the same way), the row's
 // sequence and position (k_token_map), its rotary table entries (k_rope_table) and its embedding: x[t] = E[token[t]] in float, x * gain of the first norm in
-// fragment order as the first GEMM's input, the row's sum of squares as its single partial.
-__global__ __launch_bounds__(256) void k_sk_prologue(int T, int B, int Q, int max_len, int d, int vocab, int mt, int half,
+// fragment order as the first GEMM's input (bfloat16 models; the float kernels apply the gain themselves), the row's
+// sum of squares as its single partial.
+template <typename T>
+__global__ __launch_bounds__(256) void k_sk_prologue(int n_rows, int B, int Q, int max_len, int d, int vocab, int mt, int half,
                                                      double log2_base, const int32_t* tokens, const int32_t* prefix_len,
-                                                     const int32_t* q_valid, const int32_t* n_live, const bf16_t* emb,
+                                                     const int32_t* q_valid, const int32_t* n_live, const T* emb,
                                                      const bf16_t* gain, float* x, bf16_t* xg, float* ss, int ss_stride,
                                                      int32_t* len_safe, int32_t* q_valid_eff, int32_t* tok_seq,
                                                      int32_t* tok_pos, float* cs, float* sn, int32_t* status,
@@ -558,7 +560,7 @@ __global__ __launch_bounds__(256) void k_sk_prologue(int T, int B, int Q, int ma
     if (cand && threadIdx.x < 64) {
       const int r = threadIdx.x;
       bool flag = false;
-      if (r < T) {
+      if (r < n_rows) {
         const int b2 = r / Q, j2 = r - b2 * Q;
         const bool hq = n_live != nullptr || q_valid != nullptr;
         const int qv2 = n_live ? (b2 < nl ? (q_valid ? q_valid[b2] : Q) : -1) : (q_valid ? q_valid[b2] : Q);
@@ -602,8 +604,15 @@ __global__ __launch_bounds__(256) void k_sk_prologue(int T, int B, int Q, int ma
     if (threadIdx.x == 0) atomicOr(status, DLLM_STATUS_BAD_TOKEN);
     tok = 0;
   }
-  const bf16_t* row = emb + (int64_t)tok * d;
+  const T* row = emb + (int64_t)tok * d;
   float sq = 0.f;
+  if constexpr (sizeof(T) == 4) {
+    for (int u = threadIdx.x; u < (d >> 2); u += 256) {
+      const float4 v = *(const float4*)(row + 4 * u);
+      *(float4*)(x + (int64_t)t * d + 4 * u) = v;
+      sq = fmaf(v.x, v.x, sq); sq = fmaf(v.y, v.y, sq); sq = fmaf(v.z, v.z, sq); sq = fmaf(v.w, v.w, sq);
+    }
+  } else
   for (int u = threadIdx.x; u < (d >> 3); u += 256) {          // 16-byte units: 8 channels
     const uint4 ev = *(const uint4*)(row + 8 * u), gv = *(const uint4*)(gain + 8 * u);
     const uint32_t ew[4] = {ev.x, ev.y, ev.z, ev.w}, gw[4] = {gv.x, gv.y, gv.z, gv.w};
@@ -633,13 +642,17 @@ hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, con
                               float* conf, float* entropy) {
   const dllm_config& f = c->cfg;
   const bool live = g.n_live != nullptr;
-  k_sk_prologue<<<g.T, 256, 0, s>>>(g.T, g.B, g.Q, g.max_kv - g.Q, f.d_model, f.vocab, (g.T + 15) / 16, f.head_dim / 2,
-                                    log2((double)f.rope_base), g.tokens, g.prefix_len, g.q_valid, live ? g.n_live : nullptr,
-                                    (const bf16_t*)c->tok_emb, (const bf16_t*)gain, WSM(c, x, float), WSM(c, xn, bf16_t),
-                                    WSM(c, ss, float), sk_ss_stride(c), WSM(c, len_safe, int32_t),
-                                    WSM(c, q_valid_eff, int32_t), WSM(c, tok_seq, int32_t), WSM(c, tok_pos, int32_t),
-                                    WSM(c, rope_cos, float), WSM(c, rope_sin, float), WSM(c, status, int32_t),
-                                    f.mask_id, (int)c->map.r_max, WSM(c, rows, int32_t), cand, conf, entropy);
+#define PROLOGUE(TYPE)                                                                                                   \
+  k_sk_prologue<TYPE><<<g.T, 256, 0, s>>>(g.T, g.B, g.Q, g.max_kv - g.Q, f.d_model, f.vocab, (g.T + 15) / 16, f.head_dim / 2, \
+                                    log2((double)f.rope_base), g.tokens, g.prefix_len, g.q_valid, live ? g.n_live : nullptr, \
+                                    (const TYPE*)c->tok_emb, (const bf16_t*)gain, WSM(c, x, float), WSM(c, xn, bf16_t), \
+                                    WSM(c, ss, float), sk_ss_stride(c), WSM(c, len_safe, int32_t), \
+                                    WSM(c, q_valid_eff, int32_t), WSM(c, tok_seq, int32_t), WSM(c, tok_pos, int32_t), \
+                                    WSM(c, rope_cos, float), WSM(c, rope_sin, float), WSM(c, status, int32_t), \
+                                    f.mask_id, (int)c->map.r_max, WSM(c, rows, int32_t), cand, conf, entropy)
+  if (f.dtype == DLLM_BF16) PROLOGUE(bf16_t);
+  else PROLOGUE(float);
+#undef PROLOGUE
   return hipGetLastError();
 }
 
