@@ -383,14 +383,15 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   const bool qkv_rope = !sk && big_mfma && gemm_qkv_rope_wins(c, T);   // (the token map has left the rows' K/V places)
   const int ss_groups = (f.d_model + 15) / 16;
   int n_ss = 1;      // partial sums of squares the current skinny-path GEMM input comes with
+  bool normed = false;  // the first layer's norm came with the embedding
   if (!few) {           // (on the few-row paths run_forward's prologue launch has done both)
-    TRY(launch_embed(c, s, g), "embed");
+    TRY(launch_embed(c, s, g, n_layers_run > 0 ? c->layers[0].attn_norm : nullptr, &normed), "embed");
     TRY(launch_rope_table(c, s, g), "rope_table");
   }
   int pending = 0;   // open residual sums (K splits of the last residual projection) not yet added to x
   for (int l = 0; l < n_layers_run; ++l) {
     const dllm_layer_w& L = c->layers[l];
-    if (!few) TRY(launch_rmsnorm(c, s, L.attn_norm, T, nullptr, nullptr, 0, pending), "rmsnorm");
+    if (!few && !(l == 0 && normed)) TRY(launch_rmsnorm(c, s, L.attn_norm, T, nullptr, nullptr, 0, pending), "rmsnorm");
     pending = 0;
     if (sk) {
       ProfScope p(c, s, 0, 2.0 * (dq + 2.0 * dkv) * f.d_model);

@@ -219,7 +219,8 @@ hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool 
 // the LM head's row list with the fixed outputs of the rows that are not masked, in one launch
 hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, int32_t* cand,
                               float* conf, float* entropy);
-hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g);
+// gain: of the norm that reads the embeddings, or nullptr; *normed: that norm has been applied in the same launch
+hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed);
 hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g);
 // out[T or n_rows, d] = rmsnorm(x[row]) * gain; rows == nullptr: identity row map, n = T
 // frag_mt > 0: write in fragment order for frag_mt 16-row tiles (bfloat16 only)

@@ -760,8 +760,98 @@ hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool 
   return hipGetLastError();
 }
 
-hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g) {
+// Row-major bfloat16 output (d % 4 == 0): one workgroup per row, NV groups of four elements per thread.  With few rows
+// the launch is a chain of memory round trips (as two passes over the row, the second re-reading what the first wrote,
+// it took 9.5 us at 128 rows of 4096; a trivial launch takes 4.6), so everything a thread needs - its part of the row, of
+// the open K shares of the last residual projection, of the gain - is requested before anything is used.
+// EMB: the rows come from the embedding table (the first norm of a forward): x is written, not read.
+template <int NV, bool EMB>
+__global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x, const bf16_t* gain, bf16_t* out,
+                                                      const int32_t* rows, const int32_t* n_rows_dev, const float* delta,
+                                                      int n_delta, int64_t delta_stride, float* rscale,
+                                                      const int32_t* live_rows, const bf16_t* emb, const int32_t* tokens,
+                                                      int vocab, int32_t* status) {
+  __shared__ float red[16];
+  const int r = blockIdx.x;
+  const bool live = !live_rows || r < *live_rows;
+  if (!EMB && !live) return;
+  int src = r;
+  if (rows) {
+    if (r >= *n_rows_dev) return;
+    src = rows[r];
+  }
+  const int n4 = d >> 2;
+  float4* xr = (float4*)(x + (int64_t)src * d);
+  const uint2* erow = nullptr;
+  if constexpr (EMB) {
+    int tok = tokens[r];
+    if (tok < 0 || tok >= vocab) {
+      if (threadIdx.x == 0) atomicOr(status, DLLM_STATUS_BAD_TOKEN);
+      tok = 0;
+    }
+    erow = (const uint2*)(emb + (int64_t)tok * d);
+  }
+  float4 v[NV];
+  uint2 gq[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int i = threadIdx.x + 256 * k, ic = i < n4 ? i : n4 - 1;
+    if constexpr (EMB) {
+      const uint2 e = erow[ic];
+      v[k] = make_float4(__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
+                         __uint_as_float(e.y & 0xffff0000u));
+    } else {
+      v[k] = xr[ic];
+    }
+    gq[k] = ((const uint2*)gain)[ic];
+  }
+  for (int sd = 0; sd < n_delta; ++sd) {      // open K splits of the last residual projection, added in split order
+    const float4* dr = (const float4*)(delta + sd * delta_stride + (int64_t)src * d);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int i = threadIdx.x + 256 * k;
+      const float4 dv = dr[i < n4 ? i : n4 - 1];
+      v[k].x += dv.x; v[k].y += dv.y; v[k].z += dv.z; v[k].w += dv.w;
+    }
+  }
+  float ss = 0.f;
+  uint2* orow = (uint2*)(out + (int64_t)r * d);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int i = threadIdx.x + 256 * k;
+    if (i >= n4) continue;
+    ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
+    if (EMB || n_delta > 0) xr[i] = v[k];
+    if (!live) continue;
+    const float g0 = bf16_to_f32((bf16_t)(gq[k].x & 0xffff)), g1 = bf16_to_f32((bf16_t)(gq[k].x >> 16));
+    const float g2 = bf16_to_f32((bf16_t)(gq[k].y & 0xffff)), g3 = bf16_to_f32((bf16_t)(gq[k].y >> 16));
+    orow[i] = make_uint2((uint32_t)f32_to_bf16(v[k].x * g0) | ((uint32_t)f32_to_bf16(v[k].y * g1) << 16),
+                         (uint32_t)f32_to_bf16(v[k].z * g2) | ((uint32_t)f32_to_bf16(v[k].w * g3) << 16));
+  }
+  if (!live) return;
+  ss = block_sum(ss, red);
+  // the output is x * gain; the row factor goes to rscale[r] and multiplies the consuming GEMM's accumulators
+  if (threadIdx.x == 0) rscale[r] = 1.0f / sqrtf(ss / (float)d + eps);
+}
+
+// one workgroup of 256 threads holds a row in registers
+static bool rmsnorm_row4_usable(const dllm_ctx* c) { return IS_BF16(c) && c->cfg.d_model % 4 == 0 && c->cfg.d_model <= 16384; }
+
+hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed) {
   const dllm_config& f = c->cfg;
+  *normed = false;
+  if (gain && rmsnorm_row4_usable(c)) {
+    *normed = true;
+#define ROW4(NV) k_rmsnorm_row4<NV, true><<<g.T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,      \
+                     WS(c, xn, bf16_t), nullptr, nullptr, nullptr, 0, 0, WS(c, rscale, float), c->rows_dev,               \
+                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t))
+    if (f.d_model <= 2048) ROW4(2);
+    else if (f.d_model <= 4096) ROW4(4);
+    else if (f.d_model <= 8192) ROW4(8);
+    else ROW4(16);
+#undef ROW4
+    return hipGetLastError();
+  }
   if (IS_BF16(c))
     k_embed<bf16_t><<<g.T, 256, 0, s>>>(f.d_model, f.vocab, g.tokens, (const bf16_t*)c->tok_emb,
                                         WS(c, x, float), WS(c, status, int32_t));
@@ -778,47 +868,6 @@ hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g) {
                                                WS(c, tok_pos, int32_t), WS(c, rope_cos, float),
                                                WS(c, rope_sin, float));
   return hipGetLastError();
-}
-
-// row-major bfloat16 output, four elements per thread and pass (d % 4 == 0)
-__global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x, const bf16_t* gain, bf16_t* out,
-                                                      const int32_t* rows, const int32_t* n_rows_dev, const float* delta,
-                                                      int n_delta, int64_t delta_stride, float* rscale,
-                                                      const int32_t* live_rows) {
-  __shared__ float red[16];
-  const int r = blockIdx.x;
-  if (live_rows && r >= *live_rows) return;
-  int src = r;
-  if (rows) {
-    if (r >= *n_rows_dev) return;
-    src = rows[r];
-  }
-  float4* xr = (float4*)(x + (int64_t)src * d);
-  const int n4 = d >> 2;
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < n4; i += 256) {
-    float4 v = xr[i];
-    if (n_delta > 0) {      // open K splits of the last residual projection, added in split order
-      for (int sd = 0; sd < n_delta; ++sd) {
-        const float4 dv = ((const float4*)(delta + sd * delta_stride + (int64_t)src * d))[i];
-        v.x += dv.x; v.y += dv.y; v.z += dv.z; v.w += dv.w;
-      }
-      xr[i] = v;
-    }
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-  }
-  ss = block_sum(ss, red);
-  // the output is x * gain; the row factor goes to rscale[r] and multiplies the consuming GEMM's accumulators
-  if (threadIdx.x == 0) rscale[r] = 1.0f / sqrtf(ss / (float)d + eps);
-  uint2* orow = (uint2*)(out + (int64_t)r * d);
-  for (int i = threadIdx.x; i < n4; i += 256) {   // a thread re-reads only what it wrote itself
-    const float4 v = xr[i];
-    const uint2 gq = ((const uint2*)gain)[i];
-    const float g0 = bf16_to_f32((bf16_t)(gq.x & 0xffff)), g1 = bf16_to_f32((bf16_t)(gq.x >> 16));
-    const float g2 = bf16_to_f32((bf16_t)(gq.y & 0xffff)), g3 = bf16_to_f32((bf16_t)(gq.y >> 16));
-    orow[i] = make_uint2((uint32_t)f32_to_bf16(v.x * g0) | ((uint32_t)f32_to_bf16(v.y * g1) << 16),
-                         (uint32_t)f32_to_bf16(v.z * g2) | ((uint32_t)f32_to_bf16(v.w * g3) << 16));
-  }
 }
 
 __global__ void k_fold_delta(int64_t n, float* x, const float* delta, int n_delta, int64_t delta_stride) {
@@ -842,10 +891,16 @@ hipError_t launch_fold_delta(dllm_ctx* c, hipStream_t s, int T, int n_delta, boo
 hipError_t launch_rmsnorm(dllm_ctx* c, hipStream_t s, const void* gain, int T, const int32_t* rows,
                           const int32_t* n_rows_dev, int frag_mt, int n_delta) {
   const dllm_config& f = c->cfg;
-  if (IS_BF16(c) && f.d_model % 4 == 0)
-    k_rmsnorm_row4<<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain, WS(c, xn, bf16_t), rows,
-                                     n_rows_dev, WS(c, delta, float), n_delta, c->map.lg_delta_stride, WS(c, rscale, float),
-                                     rows ? nullptr : c->rows_dev);
+  if (rmsnorm_row4_usable(c)) {
+#define ROW4(NV) k_rmsnorm_row4<NV, false><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,        \
+                     WS(c, xn, bf16_t), rows, n_rows_dev, WS(c, delta, float), n_delta, c->map.lg_delta_stride,           \
+                     WS(c, rscale, float), rows ? nullptr : c->rows_dev, nullptr, nullptr, 0, nullptr)
+    if (f.d_model <= 2048) ROW4(2);
+    else if (f.d_model <= 4096) ROW4(4);
+    else if (f.d_model <= 8192) ROW4(8);
+    else ROW4(16);
+#undef ROW4
+  }
   else if (IS_BF16(c))
     k_rmsnorm<bf16_t><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,
                                         WS(c, xn, bf16_t), rows, n_rows_dev, 0, WS(c, delta, float), n_delta,
