@@ -31,6 +31,7 @@ struct LgArgs {
   int k_per;               // RESID: K range of one split (multiple of LG_BK); gridDim.y splits
   int k_splits;            // tile kernel: number of K splits (its grid is flat)
   int group_m;             // tile kernel: most row tiles of a group (order of the work items)
+  int tn0;                 // tile kernel: its first column tile
   float* delta;            // RESID: products of splits 1.. go to delta[(split - 1) * delta_stride + m * N + n]
   int64_t delta_stride;
   const int32_t* m_dev;    // optional device row count
@@ -374,6 +375,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     const int gm = tiles_m - gi * gm_full < gm_full ? tiles_m - gi * gm_full : gm_full;
     t.tn = rem / gm;
     t.tm = gi * gm_full + rem - t.tn * gm;
+    t.tn += a.tn0;
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < K ? t.k_begin + a.k_per : K;
     t.ok = true;
@@ -858,13 +860,15 @@ hipError_t init_gemm_tiles() {
 // more rows than the weight-streaming kernels take, K in whole 64-deep stages
 static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 64 == 0 && K >= 128; }
 
+// the column tiles [tn0, tn0 + n_tn) of a product (n_tn 0: all of them)
 template <int EPI, int TM, int TN, int NSA, int NSW>
-static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1) {
+static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 = 0, int n_tn = 0) {
   using G = GtGeom<TM, TN, NSA, NSW>;
   constexpr int tile_n = EPI == LG_SWIGLU ? G::BN / 2 : G::BN;
   a.tiles_m = (a.M + G::BM - 1) / G::BM;
   constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128;
-  a.tiles_n = qkv ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n;
+  a.tiles_n = n_tn ? n_tn : (qkv ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n) - tn0;
+  a.tn0 = tn0;
   a.k_splits = k_splits;
   if (k_splits == 1) a.k_per = a.K;
   a.group_m = 8;
@@ -901,6 +905,20 @@ static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok, d
     }
   }
   return best;
+}
+
+// A last round of 256 x 256 tiles that fills few of the CUs takes as long as a whole one.  Returns how many column tiles
+// the whole rounds hold (0: none, or not worth it) when those and then the remaining columns as a launch of smaller
+// tiles, which spread over the chip, are estimated shorter than `one_us`, all columns in one launch.  The second launch
+// costs its boundary and a fill of its own, 6 us.  (592 tiles of a 1024 x 37888 x 3584 product: 256 -> 185 + 55 us;
+// 15348 x 3584 products of K = 3584 and 18944, 840 tiles: 1075 -> 1007 us on average.  The cut in
+// one launch, its remainder as a second loop of the same kernel, costs the main loop registers: 313 us.)
+static int gt_whole_rounds(int M, int NW, int K, unsigned rest_ok, double one_us) {
+  const int tiles_m = (M + 255) / 256, tiles_n = (NW + 255) / 256, rounds = tiles_m * tiles_n / gt_cus;
+  const int n_tn = rounds * gt_cus / tiles_m;
+  if (rounds < 1 || n_tn < 1 || n_tn >= tiles_n) return 0;
+  const double us = rounds * (1.6 * (K / 64) + 4.0) + gt_plan(M, NW - n_tn * 256, K, 1, rest_ok, 0.0).us + 6.0;
+  return us < one_us ? n_tn : 0;
 }
 
 template <int EPI>
@@ -949,6 +967,15 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
     const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, 0xfu, 1.0 + 8.0 * M * (double)N / 4.0e6);
     a.k_per = p.k_per;
     *n_delta = p.splits - 1;
+    const int n_tn = gt_whole_rounds(M, N, K, 0x6u, p.us);
+    if (n_tn > 0) {
+      *n_delta = 0;
+      a.k_per = K;
+      const hipError_t e = gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, 1, 0, n_tn);
+      if (e != hipSuccess) return e;
+      return gt_plan(M, N - n_tn * 256, K, 1, 0x6u, 0.0).tile == GT_128x256 ? gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, 1, n_tn)
+                                                                            : gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, 1, 2 * n_tn);
+    }
     switch (p.tile) {
       case GT_256x256: return gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, p.splits);
       case GT_128x256: return gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, p.splits);
@@ -1062,7 +1089,15 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
   a.m_dev = m_dev;
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wg; a.W2 = (const bf16_t*)Wu; a.C = H; a.M = M; a.N = F; a.K = K;
   if (gt_usable(M, K)) {
-    switch (gt_plan(M, 2 * F, K, 1, 0x7u, 0.0).tile) {
+    const GtPlan p = gt_plan(M, 2 * F, K, 1, 0x7u, 0.0);
+    const int n_tn = gt_whole_rounds(M, 2 * F, K, 0x6u, p.us);
+    if (n_tn > 0) {
+      const hipError_t e = gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, 0, n_tn);
+      if (e != hipSuccess) return e;
+      return gt_plan(M, 2 * F - n_tn * 256, K, 1, 0x6u, 0.0).tile == GT_128x256 ? gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a, 1, n_tn)
+                                                                                : gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a, 1, 2 * n_tn);
+    }
+    switch (p.tile) {
       case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a);
       case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a);
       default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a);

@@ -67,6 +67,17 @@ def test_several_items_per_workgroup():
     run(wide, [40 + b for b in range(16)], 100)
 
 
+@pytest.mark.parametrize("ms,B,Q", [
+    # gate and up of 1016 rows: 64 column tiles of 256 in one whole round, two and a half left
+    (synth.ModelShape(1, 768, 2, 2, 64, 8512, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-ff"), 8, 127),
+    # down of 8217 rows: 7 of the 8 column tiles in one whole round, the last row tile of 25 rows
+    (synth.ModelShape(1, 2048, 2, 1, 64, 768, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-out"), 83, 99),
+], ids=["gate-up", "down"])
+def test_columns_behind_the_whole_rounds(ms, B, Q):
+    """Products whose last columns are a launch of smaller tiles behind whole rounds of 256 x 256 ones."""
+    run(ms, [5 + b % 3 for b in range(B)], Q)
+
+
 @pytest.mark.parametrize("ms", [EDGE, LONG], ids=["head-dim-64", "head-dim-128"])
 @pytest.mark.parametrize("lens,n_cache,pt", [([129, 70, 31], [129, 64, 0], 32), ([67], [66], 24), ([300, 3, 5, 150], [299, 3, 2, 150], 64)])
 def test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt):
