@@ -32,6 +32,7 @@ struct LgArgs {
   int k_splits;            // tile kernel: number of K splits (its grid is flat)
   int group_m;             // tile kernel: most row tiles of a group (order of the work items)
   int tn0;                 // tile kernel: its first column tile
+  int k_rot;               // tile kernel: a column tile's sum begins this many stages after its left neighbour's (0: all at 0)
   float* delta;            // RESID: products of splits 1.. go to delta[(split - 1) * delta_stride + m * N + n]
   int64_t delta_stride;
   const int32_t* m_dev;    // optional device row count
@@ -363,9 +364,9 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   const int n_tiles = tiles_m * a.tiles_n, n_items = n_tiles * a.k_splits;
   const int per_xcd = (n_items + 7) / 8, step = gridDim.x >> 3;
   const int n_grp = (tiles_m + a.group_m - 1) / a.group_m, gm_full = n_grp > 0 ? (tiles_m + n_grp - 1) / n_grp : 1;
-  struct Item { int split, tm, tn, k_begin, k_end; bool ok, val; };
+  struct Item { int split, tm, tn, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
-    Item t{0, 0, 0, 0, K, false, false};
+    Item t{0, 0, 0, 0, K, 0, false, false};
     const int iw = (blockIdx.x >> 3) + it * step;
     const int item = (blockIdx.x & 7) * per_xcd + iw;
     if (iw >= per_xcd || item >= n_items) return t;
@@ -378,6 +379,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     t.tn += a.tn0;
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < K ? t.k_begin + a.k_per : K;
+    t.k_first = t.k_begin + (t.tn * a.k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
     t.ok = true;
     t.val = ROPE && t.tn * TILE_N >= N + a.N2;                  // a tile of the value projection
     return t;
@@ -410,7 +412,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   int it_next = 1;
   Item nxt = item_at(it_next);
   gt_rsrc ra = rsrc_a(cur), rw = rsrc_w(cur), rna = rsrc_a(nxt.ok ? nxt : cur), rnw = rsrc_w(nxt.ok ? nxt : cur);
-  int ka = cur.k_begin, kw = cur.k_begin, kea = cur.k_end, kew = cur.k_end;
+  int ka = cur.k_first, kw = cur.k_first, kba = cur.k_begin, kbw = cur.k_begin, kea = cur.k_end, kew = cur.k_end;
+  int ksa = ka, ksw = kw;                                       // where the item's stages begin and, having wrapped, end
 
   // copies: instruction q of wave w fills LDS rows (w*C + q)*8 .. +7; lane l holds piece l%8 of row l/8
   const int l8 = lane >> 3, piece = (lane & 7) ^ (l8 >> 1);     // (odd q: the row's bit 3 flips bit 2 of the piece)
@@ -429,25 +432,38 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     else if constexpr (SWIGLU) return hw * 16 * TN + (TN / 2) * c + i % (TN / 2);
     else return hw * 32 * TN + TN * c + i;
   };
+  // One wave issues an instruction in about 5 cycles, and a stage of the smaller tiles has few products to issue others
+  // beside (128 x 128: 16 of 165 instructions): there every copy keeps its own offset instead of adding it up each time.
+  // (256 x 4096 x 12288: 45 -> 41 us; the 256 x 256 tiles have no registers left for it.)
+  constexpr bool VO = TM * TN < 16;
+  int vA[VO ? CA : 1], vW[VO ? CW : 1];
+  if constexpr (VO) {
+#pragma unroll
+    for (int q = 0; q < CA; ++q) vA[q] = ((q & 1) ? vA1 : vA0) + q * 16 * K;
+#pragma unroll
+    for (int q = 0; q < CW; ++q) vW[q] = ((q & 1) ? vW1 : vW0) + w_row(q) * 2 * K;
+  }
   auto copy_a = [&](int slot, int q) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(sA + slot * G::A_BYTES + (w * CA + q) * 1024),
-                                             16, (q & 1) ? vA1 : vA0, ka * 2 + q * 16 * K, 0, 0);
+                                             16, VO ? vA[q] : (q & 1) ? vA1 : vA0, VO ? ka * 2 : ka * 2 + q * 16 * K, 0, 0);
   };
   auto copy_w = [&](int slot, int q) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (w * CW + q) * 1024),
-                                             16, (q & 1) ? vW1 : vW0, kw * 2 + w_row(q) * 2 * K, 0, 0);
+                                             16, VO ? vW[q] : (q & 1) ? vW1 : vW0, VO ? kw * 2 : kw * 2 + w_row(q) * 2 * K, 0, 0);
   };
   // the copies' next stage: of this item, then of the next one; past the last one the last stage again (never used)
   auto adv_a = [&]() {
-    ka += 64;
-    if (ka >= kea) {
-      if (nxt.ok) { ra = rna; ka = nxt.k_begin; kea = nxt.k_end; } else ka -= 64;
+    ka = ka + 64 < kea ? ka + 64 : kba;
+    if (ka == ksa) {
+      if (nxt.ok) { ra = rna; ka = ksa = nxt.k_first; kba = nxt.k_begin; kea = nxt.k_end; }
+      else ka = (ka > kba ? ka : kea) - 64;
     }
   };
   auto adv_w = [&]() {
-    kw += 64;
-    if (kw >= kew) {
-      if (nxt.ok) { rw = rnw; kw = nxt.k_begin; kew = nxt.k_end; } else kw -= 64;
+    kw = kw + 64 < kew ? kw + 64 : kbw;
+    if (kw == ksw) {
+      if (nxt.ok) { rw = rnw; kw = ksw = nxt.k_first; kbw = nxt.k_begin; kew = nxt.k_end; }
+      else kw = (kw > kbw ? kw : kew) - 64;
     }
   };
 #pragma unroll
@@ -869,6 +885,11 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
   constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128;
   a.tiles_n = n_tn ? n_tn : (qkv ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n) - tn0;
   a.tn0 = tn0;
+  // Workgroups that run in step would all ask for the same 128 bytes of rows a power of two apart, which are few memory
+  // channels: 4.5 against 6.4 TB/s of plain reads with rows of 8 KiB.  Column tiles next to each other begin 11 stages
+  // apart instead.  With more rows the activations no longer stay in the L2, which the column tiles share only in step.
+  // (128 rows: 24576 x 4096 53.6 -> 51.7 us, 12288 x 4096 33.5 -> 30.9; a whole pass of 128 rows 782 -> 746 us.)
+  a.k_rot = a.M <= 256 ? 11 : 0;
   a.k_splits = k_splits;
   if (k_splits == 1) a.k_per = a.K;
   a.group_m = 8;
