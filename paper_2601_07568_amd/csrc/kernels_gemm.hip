@@ -3,7 +3,8 @@
 
 // ==========================================================================================
 // Large-M bfloat16 GEMM on the matrix cores: C[M,N] = A[M,K] * W[N,K]^T (both K-contiguous).
-// A workgroup of 4 waves computes a BM x 128 tile (BM = 256 or 128 token rows; waves 2x2, each
+// Below, k_gemm_tile: more than 64 rows, K a multiple of 64.  First k_gemm_mfma, which takes the rest: a
+// workgroup of 4 waves computes a BM x 128 tile (BM = 128 token rows; waves 2x2, each
 // BM/2 x 64), 64-deep K slices are staged through LDS in fragment order (every operand read is 64
 // lanes x 16 contiguous bytes, no bank conflicts), double-buffered in LDS and double-buffered in
 // registers on the way there, so two slices are in flight from memory while a third is multiplied.
@@ -32,7 +33,6 @@ struct LgArgs {
   int k_splits;            // tile kernel: number of K splits (its grid is flat)
   int group_m;             // tile kernel: most row tiles of a group (order of the work items)
   int tn0;                 // tile kernel: its first column tile
-  int k_rot;               // tile kernel: a column tile's sum begins this many stages after its left neighbour's (0: all at 0)
   float* delta;            // RESID: products of splits 1.. go to delta[(split - 1) * delta_stride + m * N + n]
   int64_t delta_stride;
   const int32_t* m_dev;    // optional device row count
@@ -364,6 +364,13 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   const int n_tiles = tiles_m * a.tiles_n, n_items = n_tiles * a.k_splits;
   const int per_xcd = (n_items + 7) / 8, step = gridDim.x >> 3;
   const int n_grp = (tiles_m + a.group_m - 1) / a.group_m, gm_full = n_grp > 0 ? (tiles_m + n_grp - 1) / n_grp : 1;
+  // Workgroups that run in step would all ask for the same 128 bytes of rows a power of two apart, which are few memory
+  // channels: 4.5 against 6.4 TB/s of plain reads with rows of 8 KiB.  Neighbouring columns of 256 weight rows begin 11
+  // stages apart instead.  With more rows the activations no longer stay in the L2, which the column tiles share only in step.
+  // (128 rows: 24576 x 4096 53.6 -> 51.7 us, 12288 x 4096 33.5 -> 30.9; a whole pass of 128 rows 782 -> 746 us.)  By the rows
+  // there are and not the host's bound, by weight rows and not tiles, so that a call with a device-resident total, which
+  // may take other tiles, sums as the sized call does.
+  const int k_rot = M <= 256 ? 11 : 0;
   struct Item { int split, tm, tn, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
     Item t{0, 0, 0, 0, K, 0, false, false};
@@ -379,7 +386,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     t.tn += a.tn0;
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < K ? t.k_begin + a.k_per : K;
-    t.k_first = t.k_begin + (t.tn * a.k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
+    t.k_first = t.k_begin + (t.tn * BN / 256 * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
     t.ok = true;
     t.val = ROPE && t.tn * TILE_N >= N + a.N2;                  // a tile of the value projection
     return t;
@@ -885,11 +892,6 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
   constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128;
   a.tiles_n = n_tn ? n_tn : (qkv ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n) - tn0;
   a.tn0 = tn0;
-  // Workgroups that run in step would all ask for the same 128 bytes of rows a power of two apart, which are few memory
-  // channels: 4.5 against 6.4 TB/s of plain reads with rows of 8 KiB.  Column tiles next to each other begin 11 stages
-  // apart instead.  With more rows the activations no longer stay in the L2, which the column tiles share only in step.
-  // (128 rows: 24576 x 4096 53.6 -> 51.7 us, 12288 x 4096 33.5 -> 30.9; a whole pass of 128 rows 782 -> 746 us.)
-  a.k_rot = a.M <= 256 ? 11 : 0;
   a.k_splits = k_splits;
   if (k_splits == 1) a.k_per = a.K;
   a.group_m = 8;
