@@ -526,9 +526,9 @@ def large_batch(args, torch, np, synth, Engine, dev, steps, warmup):
     roofline = None
     if dom:
         a = kern[dom]["TFLOPs"]
-        traffic = pmc_traffic("denoise_step_c5_hbm_traffic_pmc.txt", f"k_gemm_t256({dom})") if args.layers is None else None
+        traffic = pmc_traffic("denoise_step_c5_hbm_traffic_pmc.txt", f"k_gemm_tile({dom})") if args.layers is None else None
         roofline = {"bound": "mfma", "step_frac_of_mfma_peak": flops / (ms_per_step * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS,
-                    "kernel": f"k_gemm_t256 ({dom})", "achieved": a, "peak": MFMA_PEAK_TFLOPS,
+                    "kernel": f"k_gemm_tile ({dom})", "achieved": a, "peak": MFMA_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": a / MFMA_PEAK_TFLOPS, "traffic": traffic, "avg_us": kern[dom]["avg_us"]}
     eng.close()
     return {"metric": "denoise_steps_per_s", "value": steps / elapsed, "unit": "steps/s", "n_gpus": 1,

@@ -497,9 +497,13 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
     int n_parts = c->map.n_vtiles;
     if (sk) {
       ProfScope p(c, s, 4, 2.0 * f.vocab * f.d_model);
-      TRY(launch_sk_lmstats(c, s, T, n_ss, &n_parts), "lm_head");
+      TRY(launch_sk_lmstats(c, s, c->ws + c->map.xn, T, n_ss, &n_parts), "lm_head");
     } else if (s32) {
       TRY(launch_s32_lmstats(c, s, T, n_ss, &n_parts), "lm_head");
+    } else if (big_mfma && sk_head_supported(c, max_rows)) {
+      TRY(launch_sk_head_rows(c, s, max_rows), "head_rows");
+      ProfScope p(c, s, 4, 2.0 * max_rows * (double)f.vocab * f.d_model);
+      TRY(launch_sk_lmstats(c, s, c->ws + c->map.h, max_rows, 1, &n_parts), "lm_head");
     } else if (big_mfma) {
       ProfScope p(c, s, 4, 2.0 * max_rows * (double)f.vocab * f.d_model);   // upper bound: max_rows rows
       TRY(launch_gemm_lmstats(c, s, max_rows, &n_parts), "lm_head");

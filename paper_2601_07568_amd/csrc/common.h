@@ -289,7 +289,9 @@ hipError_t launch_sk_f32(dllm_ctx* c, hipStream_t s, const void* A, const void* 
                          int n_ss);
 hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int layer, const KVView& pool, int n_ss);
 hipError_t launch_sk_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_ss);
-hipError_t launch_sk_lmstats(dllm_ctx* c, hipStream_t s, int T, int n_ss, int* n_parts_out);
+hipError_t launch_sk_lmstats(dllm_ctx* c, hipStream_t s, const void* X, int T, int n_ss, int* n_parts_out);
+bool sk_head_supported(const dllm_ctx* c, int max_rows);
+hipError_t launch_sk_head_rows(dllm_ctx* c, hipStream_t s, int max_rows);
 hipError_t launch_gemm_mfma(hipStream_t s, const void* A, const void* W, void* C, int M, int N, int K, Epi epi,
                             const float* rscale = nullptr, const int32_t* m_dev = nullptr);
 hipError_t init_attn_kernels();   // once per process (raises a kernel's LDS limit)

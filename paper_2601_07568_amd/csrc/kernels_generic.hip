@@ -1,6 +1,6 @@
 // Generic kernels of the denoise-step path: any shape, float or bfloat16 storage, scalar FMA
-// arithmetic in float.  They are the whole path for float models and the fallback for bfloat16
-// shapes the matrix-core kernels do not take; the small bookkeeping kernels (token map, rotary
+// arithmetic in float.  They are the path of float models outside the steps of few rows and the fallback for
+// bfloat16 shapes the matrix-core kernels do not take; the small bookkeeping kernels (token map, rotary
 // table, row compaction, statistics merge, unmask) are shared by both.
 #include "common.h"
 #include <math.h>

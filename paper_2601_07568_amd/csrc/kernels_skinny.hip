@@ -703,11 +703,40 @@ hipError_t launch_sk_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_
   return sk_launch_mt<2, SK_NW, SK_SWIGLU>(s, a, (f.d_ff + 15) / 16);
 }
 
-// LM head on all rows of the step (ws.xn holds x * final gain) -> per-64-column softmax statistics of every row;
-// the merge picks the masked ones.  If no row is masked (device count) nothing is computed.
-hipError_t launch_sk_lmstats(dllm_ctx* c, hipStream_t s, int T, int n_ss, int* n_parts_out) {
+// The compacted rows of a forward of many tokens (ws.xn row-major x * gain, ws.rscale their factors) as the
+// weight-streaming LM head reads them: fragment order in ws.h (free behind the last layer), and the sum of squares that
+// the factor came from.  One workgroup per row; a launch of 5 us.  A refresh of 1184 tokens with the outputs of 32 rows:
+// LM head 263 us on 128 x 128 tiles, 211 + 5 here.
+__global__ __launch_bounds__(256) void k_sk_head_rows(int d, int mt, int ss_stride, float inv_d, float eps, const int32_t* n_rows,
+                                                      const bf16_t* xn, const float* rscale, bf16_t* X, float* ss) {
+  const int row = blockIdx.x;
+  if (row >= *n_rows) return;
+  const int d_pad = (d + SK_KB - 1) / SK_KB * SK_KB;
+  for (int k = threadIdx.x * 8; k < d_pad; k += 256 * 8)
+    *(u32x4*)(X + frag_offset(row, k, mt)) = k < d ? *(const u32x4*)(xn + (int64_t)row * d + k) : u32x4{0, 0, 0, 0};
+  if (threadIdx.x == 0) {
+    const double r = rscale[row];
+    ss[(int64_t)row * ss_stride] = (float)((1.0 / (r * r) - (double)eps) / (double)inv_d);
+  }
+}
+// LM heads of at most 64 rows behind a forward of many tokens: the packed weights stream faster than tiles of mostly
+// padding rows read them
+bool sk_head_supported(const dllm_ctx* c, int max_rows) {
+  return mfma_supported(c) && max_rows <= 64 && c->cfg.d_ff >= c->cfg.d_model;
+}
+hipError_t launch_sk_head_rows(dllm_ctx* c, hipStream_t s, int max_rows) {
   const dllm_config& f = c->cfg;
-  SkArgs a = sk_base(c->ws + c->map.xn, T, f.d_model);
+  k_sk_head_rows<<<max_rows, 256, 0, s>>>(f.d_model, (max_rows + 15) / 16, sk_ss_stride(c), 1.0f / (float)f.d_model, f.rms_eps,
+                                          WSM(c, status, int32_t) + 1, WSM(c, xn, bf16_t), WSM(c, rscale, float), WSM(c, h, bf16_t),
+                                          WSM(c, ss, float));
+  return hipGetLastError();
+}
+
+// LM head on all rows of the step (X holds x * final gain) -> per-64-column softmax statistics of every row;
+// the merge picks the masked ones.  If no row is masked (device count) nothing is computed.
+hipError_t launch_sk_lmstats(dllm_ctx* c, hipStream_t s, const void* X, int T, int n_ss, int* n_parts_out) {
+  const dllm_config& f = c->cfg;
+  SkArgs a = sk_base(X, T, f.d_model);
   sk_row_scale(c, a, n_ss);
   a.n_lm_rows = WSM(c, status, int32_t) + 1;
   a.W0 = (const bf16_t*)c->packed_lm_head;

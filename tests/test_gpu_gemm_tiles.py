@@ -105,3 +105,29 @@ def test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt):
             assert (got[n:] == 7.0).all(), (b, which)
     assert eng.read_status() == 0
     eng.close()
+
+
+@pytest.mark.parametrize("ms,lens,Q,n_masked", [(EDGE, [80], 32, 1), (EDGE, [75, 90], 32, 17), (LONG, [70], 64, 64)],
+                         ids=["one-row", "seventeen-rows-k-576", "sixty-four-rows"])
+def test_few_head_rows_behind_a_forward_of_many(ms, lens, Q, n_masked):
+    """Outputs of a refresh with at most 64 rows of the LM head (which then reads the packed weights): every sequence's
+    last Q tokens, n_masked of them masked, against the forward without cache."""
+    w = synth.Weights(ms, 7)
+    B, pt = len(lens), 32
+    mp = (max(lens) + pt - 1) // pt
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=B * mp, max_batch=B, max_q=Q, max_tokens=sum(lens))
+    seqs = [np.concatenate([synth.random_tokens(ms, 40 + i, n - Q), synth.masked_block(ms, 50 + i, Q, n_masked)])
+            for i, n in enumerate(lens)]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cand = torch.zeros(sum(lens), dtype=torch.int32, device=eng.device)
+    conf, ent = (torch.zeros(sum(lens), dtype=torch.float32, device=eng.device) for _ in range(2))
+    eng.refresh_cache(eng.i32(np.concatenate(seqs)), eng.i32(cu), eng.i32(H.identity_table(eng, B)), eng.i32([n - Q for n in lens]),
+                      cand, conf, ent, total_tokens=int(cu[-1]), max_seqlen=max(lens))
+    for b, n in enumerate(lens):
+        full, _, _, _ = O.forward_full(w, seqs[b], widen=W, store=ST)
+        rows = slice(int(cu[b]) + n - Q, int(cu[b]) + n)
+        r = {"logits": full[n - Q:], "cand": O.confidence(full[n - Q:], ms.mask_id)[0]}
+        H.check_step_outputs(ms, r, seqs[b][n - Q:] == ms.mask_id, cand.cpu().numpy()[rows], conf.cpu().numpy()[rows],
+                             ent.cpu().numpy()[rows], "bf16")
+    assert eng.read_status() == 0
+    eng.close()
