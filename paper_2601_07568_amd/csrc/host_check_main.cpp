@@ -5,8 +5,10 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <utility>
 #include <vector>
 #include "../../include/dllm.h"
+#include "gemm_ring.h"
 
 static int failures = 0;
 #define EXPECT(call, want)                                                            \
@@ -24,7 +26,55 @@ static dllm_config tiny_cfg() {
   return c;
 }
 
+// The tile kernel's copies against what it multiplies.  Ring of `ring` buffers of one operand, `nsw` of the weights (the
+// deeper ring, by which a launch is sized); item i has `stages` + i % 3 stages and starts at stage i % (their number).
+// Every workgroup's copies are issued as the kernel issues them - ring - 1 stages in front of its first item, then one per
+// stage, each followed by a step of the cursor that knows the item behind the one being multiplied and no other - and the
+// stage a copy fetched has to be the one that is multiplied from its buffer.  Returns the number of wrong stages and of
+// items that are not multiplied exactly once.
+static int ring_errors(int ring, int nsw, int stages, int n_items, int slots) {
+  struct It { int id, k_first, k_begin, k_end; bool ok; };
+  const int n_wg = dllm::gt_workgroups(n_items, slots, stages, nsw);
+  auto item = [&](int wg, int it) {
+    const int id = dllm::gt_item(wg, n_wg, it, n_items), n = stages + (id < 0 ? 0 : id) % 3;
+    return It{id, (id < 0 ? 0 : id) % n * 64, 0, n * 64, id >= 0};
+  };
+  int errors = 0;
+  std::vector<int> seen(n_items, 0);
+  for (int wg = 0; wg < n_wg; ++wg) {
+    It cur = item(wg, 0);
+    if (!cur.ok) continue;
+    int it = 1, from = cur.id, k = cur.k_first, first = cur.k_first, begin = cur.k_begin, end = cur.k_end;
+    It nxt = item(wg, it);
+    std::vector<std::pair<int, int>> copied;                  // (item, k) of every copy, in order
+    auto copy = [&]() {
+      copied.push_back({from, k});
+      GT_ADVANCE(k, first, begin, end, nxt, from = nxt.id);
+    };
+    for (int s = 0; s < ring - 1; ++s) copy();
+    for (size_t at = 0;;) {
+      for (int s = 0, n = cur.k_end / 64; s < n; ++s, ++at) {
+        copy();
+        if (copied[at] != std::make_pair(cur.id, (cur.k_first / 64 + s) % n * 64)) ++errors;
+      }
+      ++seen[cur.id];
+      if (!nxt.ok) break;
+      cur = nxt;
+      nxt = item(wg, ++it);
+    }
+  }
+  for (int n : seen) errors += n != 1;
+  return errors;
+}
+
 int main() {
+  const int rings[][2] = {{2, 3}, {3, 4}, {4, 5}};
+  for (const auto& r : rings)
+    for (int stages = 2; stages <= 8; ++stages)
+      for (int n_items = 1; n_items <= 48; ++n_items) {       // on 8 places: up to six items after each other
+        EXPECT(ring_errors(r[0], r[1], stages, n_items, 8), 0);
+        EXPECT(ring_errors(r[1], r[1], stages, n_items, 8), 0);
+      }
   void* const p = (void*)0x3000;          // stands for device memory; the host never reads it
   int32_t* const ip = (int32_t*)p;
   float* const fp = (float*)p;

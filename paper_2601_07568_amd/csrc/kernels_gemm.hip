@@ -1,5 +1,6 @@
 // bfloat16 matrix-core (MFMA) kernels for gfx950: GEMMs over many token rows.
 #include "mfma_common.h"
+#include "gemm_ring.h"
 
 // ==========================================================================================
 // Large-M bfloat16 GEMM on the matrix cores: C[M,N] = A[M,K] * W[N,K]^T (both K-contiguous).
@@ -356,13 +357,11 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   const int N = a.N, K = a.K;
   const int wm = w & 1, wn = w >> 1;
   const int r = lane & 31, h = lane >> 5;
-  // Persistent workgroups: the work items (K split, then groups of at most group_m row tiles, in a group column by
-  // column) are dealt in contiguous runs to the 8 XCDs (workgroups go round-robin to XCDs), inside an XCD round-robin
-  // to its workgroups: what runs at the same time next to one L2 shares its rows and columns (with 64 row tiles and
-  // no groups an XCD's workgroups share one weight tile and nothing else: 1.10 against 1.20 PFLOP/s at K = 18944).
+  // Persistent workgroups: the work items are K splits, in a split groups of at most group_m row tiles, in a group column
+  // by column, in the order of gt_item: what runs at the same time next to one L2 shares its rows and columns (with 64 row
+  // tiles and no groups an XCD's workgroups share one weight tile and nothing else: 1.10 against 1.20 PFLOP/s at K = 18944).
   const int tiles_m = (M + BM - 1) / BM;
   const int n_tiles = tiles_m * a.tiles_n, n_items = n_tiles * a.k_splits;
-  const int per_xcd = (n_items + 7) / 8, step = gridDim.x >> 3;
   const int n_grp = (tiles_m + a.group_m - 1) / a.group_m, gm_full = n_grp > 0 ? (tiles_m + n_grp - 1) / n_grp : 1;
   // Workgroups that run in step would all ask for the same 128 bytes of rows a power of two apart, which are few memory
   // channels: 4.5 against 6.4 TB/s of plain reads with rows of 8 KiB.  Neighbouring columns of 256 weight rows begin 11
@@ -374,9 +373,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   struct Item { int split, tm, tn, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
     Item t{0, 0, 0, 0, K, 0, false, false};
-    const int iw = (blockIdx.x >> 3) + it * step;
-    const int item = (blockIdx.x & 7) * per_xcd + iw;
-    if (iw >= per_xcd || item >= n_items) return t;
+    const int item = gt_item(blockIdx.x, gridDim.x, it, n_items);
+    if (item < 0) return t;
     t.split = item / n_tiles;
     const int tile = item - t.split * n_tiles;
     const int gi = tile / (gm_full * a.tiles_n), rem = tile - gi * gm_full * a.tiles_n;
@@ -458,21 +456,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (w * CW + q) * 1024),
                                              16, VO ? vW[q] : (q & 1) ? vW1 : vW0, VO ? kw * 2 : kw * 2 + w_row(q) * 2 * K, 0, 0);
   };
-  // the copies' next stage: of this item, then of the next one; past the last one the last stage again (never used)
-  auto adv_a = [&]() {
-    ka = ka + 64 < kea ? ka + 64 : kba;
-    if (ka == ksa) {
-      if (nxt.ok) { ra = rna; ka = ksa = nxt.k_first; kba = nxt.k_begin; kea = nxt.k_end; }
-      else ka = (ka > kba ? ka : kea) - 64;
-    }
-  };
-  auto adv_w = [&]() {
-    kw = kw + 64 < kew ? kw + 64 : kbw;
-    if (kw == ksw) {
-      if (nxt.ok) { rw = rnw; kw = ksw = nxt.k_first; kbw = nxt.k_begin; kew = nxt.k_end; }
-      else kw = (kw > kbw ? kw : kew) - 64;
-    }
-  };
+  auto adv_a = [&]() { GT_ADVANCE(ka, ksa, kba, kea, nxt, ra = rna); };
+  auto adv_w = [&]() { GT_ADVANCE(kw, ksw, kbw, kew, nxt, rw = rnw); };
 #pragma unroll
   for (int s = 0; s < NSW - 1; ++s) {
     if (s < NSA - 1) {
@@ -518,7 +503,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
       for (int j = 0; j < TM; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    const int ns = (cur.k_end - cur.k_begin) / 64;              // K ranges are multiples of 64, at least two stages
+    // K ranges are multiples of 64: at least two stages, and where another item follows at least NSW (gt_workgroups)
+    const int ns = (cur.k_end - cur.k_begin) / 64;
     for (int st = 0; st < ns; ++st) {
       const int na = sa + 1 == NSA ? 0 : sa + 1, nw = sw + 1 == NSW ? 0 : sw + 1;
       const int fa_slot = sa == 0 ? NSA - 1 : sa - 1, fw_slot = sw == 0 ? NSW - 1 : sw - 1;   // the stage before: free
@@ -895,8 +881,9 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
   a.k_splits = k_splits;
   if (k_splits == 1) a.k_per = a.K;
   a.group_m = 8;
-  const int items = a.tiles_m * a.tiles_n * k_splits, slots = gt_cus * G::PER_CU;
-  k_gemm_tile<EPI, TM, TN, NSA, NSW><<<items < slots ? (items + 7) / 8 * 8 : slots, 256, G::LDS, s>>>(a);
+  const int last_k = a.K - (k_splits - 1) * a.k_per;            // the last share is the shortest
+  const int wgs = gt_workgroups(a.tiles_m * a.tiles_n * k_splits, gt_cus * G::PER_CU, (last_k < a.k_per ? last_k : a.k_per) / 64, NSW);
+  k_gemm_tile<EPI, TM, TN, NSA, NSW><<<wgs, 256, G::LDS, s>>>(a);
   return hipGetLastError();
 }
 

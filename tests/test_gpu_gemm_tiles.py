@@ -67,6 +67,26 @@ def test_several_items_per_workgroup():
     run(wide, [40 + b for b in range(16)], 100)
 
 
+def _short(name, d, hq, hkv, ff, vocab):
+    return synth.ModelShape(1, d, hq, hkv, 64, ff, vocab, vocab - 1, dtype="bf16", lm_head_scale=8.0, name=name)
+
+
+@pytest.mark.parametrize("ms,lens,Q", [
+    # LM head of 256 x 128256 on 128 x 128 tiles: 1002 of them, K of four stages behind a ring of five
+    (_short("short-head", 256, 2, 2, 256, 128256), [33, 40, 47], 32),
+    # LM head of 128 x 131072 for 304 rows on 256 x 256 tiles: 1024 of them, two stages behind a ring of three
+    (_short("short-head-256", 128, 2, 2, 128, 131072), [20 + b for b in range(19)], 32),
+    # gate and up of 1600 x 32768, K of two stages: 896 tiles of 256 x 256
+    (_short("short-gate-up", 128, 2, 1, 16384, 600), [40 + b for b in range(16)], 100),
+    # q/k/v of 256 + 2 * 64 rows, K of three stages behind a ring of four: 128 x 64 tiles, and their ring of two a CU
+    (_short("short-qkv", 192, 4, 1, 256, 600), [700 + b for b in range(32)], 8),
+], ids=["head-k256", "head-k128", "gate-up-k128", "qkv-k192"])
+def test_short_sums_with_more_than_two_tiles_per_workgroup(ms, lens, Q):
+    """Sums shorter than the rings of copies with a third and further tile for every place on the chip (what the copies
+    fetch for them is checked for all rings on the host: csrc/host_check_main.cpp)."""
+    run(ms, lens, Q)
+
+
 @pytest.mark.parametrize("ms,B,Q", [
     # gate and up of 1016 rows: 64 column tiles of 256 in one whole round, two and a half left
     (synth.ModelShape(1, 768, 2, 2, 64, 8512, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-ff"), 8, 127),
