@@ -63,7 +63,7 @@ static bool build_map(const dllm_config* c, Workspace* m) {
   m->rope_sin = take(t_max * half * 4);
   m->tok_seq = take(t_max * 4);
   m->tok_pos = take(t_max * 4);
-  m->kv_loc = take(t_max * 16);
+  m->kv_loc = m->q32;   // a forward uses one or the other (16 bytes a token of at least 256), so no call needs more workspace for it
   m->rows = take((size_t)m->r_max * 4);
   m->lm_part = take((size_t)m->r_max * ((c->vocab + 63) / 64) * 4 * 4);   // finest split: 64 columns per partial
   m->attn_rows = (int64_t)t_step * c->n_q_heads * 8;

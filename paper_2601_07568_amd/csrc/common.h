@@ -141,7 +141,8 @@ struct Workspace {
   size_t rope_sin;     // float [Tmax, dh/2]
   size_t tok_seq;      // int32 [Tmax]             sequence of each packed token
   size_t tok_pos;      // int32 [Tmax]             position of each token in its sequence
-  size_t kv_loc;       // int4  [Tmax]             where a row's K and V go: pool page (-1: not cached), slot, packed column (-1: none)
+  size_t kv_loc;       // int4  [Tmax]             where a row's K and V go: pool page (-1: not cached), slot, packed column (-1: none);
+                       // in q32's place: read by the q/k/v product with the rotary embedding in it, which leaves no float q
   size_t rows;         // int32 [Rmax]             compacted list of LM-head rows
   size_t lm_part;      // float [Rmax, n_vtiles, 4] per-tile (max, argmax, sumexp, sum e*z)
   size_t attn_part;    // float [attn_rows, dh] partial outputs, then [attn_rows, 2] (max, sum) of split-KV units

@@ -54,6 +54,16 @@ def test_sizes_and_config_validation():
     assert L.dllm_workspace_bytes(C.byref(cfg_for(ms))) == 0
 
 
+def test_largest_float_context_of_the_static_step():
+    """The workspace of the two-layer float model with the most prefill tokens that dllm_denoise_step_static takes, byte for
+    byte: a field that is added to the map must not push a caller's context out of the fixed array."""
+    L = B.lib()
+    kw = dict(page_tokens=64, max_pages_per_seq=8, n_pages=8, max_batch=1, max_q=1)
+    size = L.dllm_workspace_bytes(C.byref(cfg_for(synth.TINY, max_tokens=3469, **kw)))
+    assert size == 67108608 <= L.dllm_static_scratch_bytes()
+    assert L.dllm_workspace_bytes(C.byref(cfg_for(synth.TINY, max_tokens=3470, **kw))) > L.dllm_static_scratch_bytes()
+
+
 def test_create_rejects_nulls_and_small_buffers():
     L = B.lib()
     cfg = cfg_for(synth.TINY)
