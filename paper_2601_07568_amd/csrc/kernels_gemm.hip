@@ -4,7 +4,7 @@
 
 // ==========================================================================================
 // Large-M bfloat16 GEMM on the matrix cores: C[M,N] = A[M,K] * W[N,K]^T (both K-contiguous).
-// Below, k_gemm_tile: more than 64 rows, K a multiple of 64.  First k_gemm_mfma, which takes the rest: a
+// Below, k_gemm_tile: more than 64 rows, K a multiple of 32.  First k_gemm_mfma, which takes the rest: a
 // workgroup of 4 waves computes a BM x 128 tile (BM = 128 token rows; waves 2x2, each
 // BM/2 x 64), 64-deep K slices are staged through LDS in fragment order (every operand read is 64
 // lanes x 16 contiguous bytes, no bank conflicts), double-buffered in LDS and double-buffered in
@@ -335,7 +335,9 @@ struct GtGeom {
   static_assert(IN_FLIGHT < 64, "what the memory counter holds");
 };
 
-template <int EPI, int TM, int TN, int NSA, int NSW>
+// HALF: K is 32 more than a multiple of 64.  The last stage's upper 32 come from past the end of the row, so their copies
+// are sent out of the descriptor, which leaves zeros in LDS; an instruction more per copy (a form of its own for it).
+template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF>
 __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   using G = GtGeom<TM, TN, NSA, NSW>;
   constexpr int BM = G::BM, BN = G::BN, CA = G::CA, CW = G::CW;
@@ -354,7 +356,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int M = a.M;
   if (a.m_dev) { const int md = *a.m_dev; M = md < M ? md : M; }
-  const int N = a.N, K = a.K;
+  const int N = a.N, K = a.K, k_all = HALF ? K + 32 : K;        // k_all: in whole stages
   const int wm = w & 1, wn = w >> 1;
   const int r = lane & 31, h = lane >> 5;
   // Persistent workgroups: the work items are K splits, in a split groups of at most group_m row tiles, in a group column
@@ -372,7 +374,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   const int k_rot = M <= 256 ? 11 : 0;
   struct Item { int split, tm, tn, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
-    Item t{0, 0, 0, 0, K, 0, false, false};
+    Item t{0, 0, 0, 0, k_all, 0, false, false};
     const int item = gt_item(blockIdx.x, gridDim.x, it, n_items);
     if (item < 0) return t;
     t.split = item / n_tiles;
@@ -383,7 +385,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     t.tm = gi * gm_full + rem - t.tn * gm;
     t.tn += a.tn0;
     t.k_begin = t.split * a.k_per;
-    t.k_end = t.k_begin + a.k_per < K ? t.k_begin + a.k_per : K;
+    t.k_end = t.k_begin + a.k_per < k_all ? t.k_begin + a.k_per : k_all;
     t.k_first = t.k_begin + (t.tn * BN / 256 * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
     t.ok = true;
     t.val = ROPE && t.tn * TILE_N >= N + a.N2;                  // a tile of the value projection
@@ -424,8 +426,9 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   const int l8 = lane >> 3, piece = (lane & 7) ^ (l8 >> 1);     // (odd q: the row's bit 3 flips bit 2 of the piece)
   // features between consecutive LDS rows of a tile
   constexpr int FS = STATS ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
-  const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = vA0 ^ 64;
-  const int vW0 = l8 * FS * K * 2 + piece * 16, vW1 = vW0 ^ 64;
+  const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = HALF ? vA0 + (piece < 4 ? 64 : -64) : vA0 ^ 64;
+  const int vW0 = l8 * FS * K * 2 + piece * 16, vW1 = HALF ? vW0 + (piece < 4 ? 64 : -64) : vW0 ^ 64;
+  const int out0 = piece < 4 ? 0 : 0x40000000, out1 = piece < 4 ? 0x40000000 : 0;   // HALF: added in the last stage (even, odd q)
   auto w_row = [&](int q) -> int {                              // weight row of the instruction's first LDS row
     const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
     if constexpr (STATS) return R;
@@ -448,13 +451,14 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
 #pragma unroll
     for (int q = 0; q < CW; ++q) vW[q] = ((q & 1) ? vW1 : vW0) + w_row(q) * 2 * K;
   }
+  auto past = [&](int k, int q) -> int { return HALF && k + 64 > K ? ((q & 1) ? out1 : out0) : 0; };
   auto copy_a = [&](int slot, int q) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(sA + slot * G::A_BYTES + (w * CA + q) * 1024),
-                                             16, VO ? vA[q] : (q & 1) ? vA1 : vA0, VO ? ka * 2 : ka * 2 + q * 16 * K, 0, 0);
+                                             16, (VO ? vA[q] : (q & 1) ? vA1 : vA0) + past(ka, q), VO ? ka * 2 : ka * 2 + q * 16 * K, 0, 0);
   };
   auto copy_w = [&](int slot, int q) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (w * CW + q) * 1024),
-                                             16, VO ? vW[q] : (q & 1) ? vW1 : vW0, VO ? kw * 2 : kw * 2 + w_row(q) * 2 * K, 0, 0);
+                                             16, (VO ? vW[q] : (q & 1) ? vW1 : vW0) + past(kw, q), VO ? kw * 2 : kw * 2 + w_row(q) * 2 * K, 0, 0);
   };
   auto adv_a = [&]() { GT_ADVANCE(ka, ksa, kba, kea, nxt, ra = rna); };
   auto adv_w = [&]() { GT_ADVANCE(kw, ksw, kbw, kew, nxt, rw = rnw); };
@@ -837,8 +841,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));   // the trailing repeats must not outlive the workgroup
 }
 
-template <int EPI, int TM, int TN, int NSA, int NSW>
-__global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW>(a); }
+template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF = false>
+__global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW, HALF>(a); }
 
 // Rings above the default LDS limit of a kernel: raised once per process.
 static bool gt_ready = false;
@@ -850,6 +854,18 @@ static int gt_cus = 256;
   X(LG_ROPE128, 4, 4, 2, 3) X(LG_ROPE128, 2, 2, 4, 5) X(LG_ROPE128, 2, 2, 2, 3)                         \
   X(LG_QKV, 4, 4, 2, 3) X(LG_QKV, 2, 4, 2, 3) X(LG_QKV, 2, 2, 4, 5) X(LG_QKV, 2, 1, 3, 4)               \
   X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS, 2, 2, 4, 5)
+// the forms that are also built for K of 32 more than a multiple of 64
+template <int EPI, int TM, int TN>
+constexpr bool GT_HALF = (TM == TN || TN == 1) && EPI != LG_ROPE64 && EPI != LG_ROPE128;
+template <int EPI, int TM, int TN, int NSA, int NSW>
+static hipError_t gt_raise_lds() {
+  constexpr int lds = GtGeom<TM, TN, NSA, NSW>::LDS;
+  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if constexpr (GT_HALF<EPI, TM, TN>)
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  return e;
+}
 hipError_t init_gemm_tiles() {
   if (gt_ready) return hipSuccess;
   int dev = 0, cus = 0;
@@ -857,17 +873,17 @@ hipError_t init_gemm_tiles() {
       cus >= 8)
     gt_cus = cus / 8 * 8;
   hipError_t e = hipSuccess;
-#define X(E, TM, TN, NA, NW)                                                                                       \
-  if (e == hipSuccess)                                                                                             \
-    e = hipFuncSetAttribute((const void*)k_gemm_tile<E, TM, TN, NA, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                            GtGeom<TM, TN, NA, NW>::LDS);
+#define X(E, TM, TN, NA, NW) if (e == hipSuccess) e = gt_raise_lds<E, TM, TN, NA, NW>();
   GT_KERNELS(X)
 #undef X
   gt_ready = e == hipSuccess;
   return e;
 }
-// more rows than the weight-streaming kernels take, K in whole 64-deep stages
-static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 64 == 0 && K >= 128; }
+// more rows than the weight-streaming kernels take, K in whole or half 64-deep stages (two layers of 3616 channels, d_ff
+// 18976, us, k_gemm_mfma / this kernel: 97 rows 658 / 432, 700 rows 1438 / 892, 3000 rows 5508 / 3226)
+static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 32 == 0 && K >= 128; }
+// of a mask of tiles (bit per GtTile) those that are built for this K
+static unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0x2u; }
 
 // the column tiles [tn0, tn0 + n_tn) of a product (n_tn 0: all of them)
 template <int EPI, int TM, int TN, int NSA, int NSW>
@@ -879,10 +895,18 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
   a.tiles_n = n_tn ? n_tn : (qkv ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n) - tn0;
   a.tn0 = tn0;
   a.k_splits = k_splits;
-  if (k_splits == 1) a.k_per = a.K;
+  const int k_all = (a.K + 63) / 64 * 64;
+  if (k_splits == 1) a.k_per = k_all;
   a.group_m = 8;
-  const int last_k = a.K - (k_splits - 1) * a.k_per;            // the last share is the shortest
+  const int last_k = k_all - (k_splits - 1) * a.k_per;          // the last share is the shortest
   const int wgs = gt_workgroups(a.tiles_m * a.tiles_n * k_splits, gt_cus * G::PER_CU, (last_k < a.k_per ? last_k : a.k_per) / 64, NSW);
+  if constexpr (GT_HALF<EPI, TM, TN>) {
+    if (a.K != k_all) {
+      k_gemm_tile<EPI, TM, TN, NSA, NSW, true><<<wgs, 256, G::LDS, s>>>(a);
+      return hipGetLastError();
+    }
+  }
+  if (a.K != k_all) return hipErrorInvalidValue;
   k_gemm_tile<EPI, TM, TN, NSA, NSW><<<wgs, 256, G::LDS, s>>>(a);
   return hipGetLastError();
 }
@@ -893,7 +917,7 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
 // 297; 256 x 24576: 85 / 55 / 61; 128 x 24576: 85 / 50 / 39; 1024 x 3584 x 3584: 48 (4 K shares) / 38 (2) / 42.
 enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_N = 4 };
 struct GtPlan { GtTile tile; int splits, k_per; double us; };
-// NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile
+// NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile that its widths allow
 // fold_us_per_share: what each share behind the first costs (written here, read by the kernel that adds it)
 static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok, double fold_us_per_share) {
   static const int bm[GT_N] = {256, 128, 128, 128}, bn[GT_N] = {256, 256, 128, 64};
@@ -901,7 +925,7 @@ static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok, d
   const double unit[GT_N] = {1.0, 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22};
   GtPlan best{GT_128x128, 1, K, 1e30};
   for (int c = 0; c < GT_N; ++c) {
-    if (!((width_ok >> c) & 1u)) continue;
+    if (!((gt_built(K, width_ok) >> c) & 1u)) continue;
     const int tiles = ((M + bm[c] - 1) / bm[c]) * ((NW + bn[c] - 1) / bn[c]);
     for (int sp = 1; sp <= max_splits; ++sp) {
       if (sp > 1 && (K / sp < 512 || tiles * sp > gt_cus)) break;    // shares long enough to pay for fill and drain
@@ -1037,7 +1061,7 @@ hipError_t launch_gemm_qkv_split(dllm_ctx* c, hipStream_t s, const void* A, cons
 // saved, but the sum over K cannot be split.
 static bool qkv_rope_usable(const dllm_ctx* c, int M) {
   const dllm_config& f = c->cfg;
-  return gt_usable(M, f.d_model) && (f.n_q_heads * f.head_dim) % 128 == 0 && (f.n_kv_heads * f.head_dim) % 128 == 0;
+  return gt_usable(M, f.d_model) && f.d_model % 64 == 0 && (f.n_q_heads * f.head_dim) % 128 == 0 && (f.n_kv_heads * f.head_dim) % 128 == 0;
 }
 // Taken unless the split product and the rotary kernel behind it are quicker by the estimate (the rotary kernel: about
 // 10 us and its operands at 2.5 TB/s).  Measured, product + rotary

@@ -87,6 +87,24 @@ def test_short_sums_with_more_than_two_tiles_per_workgroup(ms, lens, Q):
     run(ms, lens, Q)
 
 
+HALF = synth.ModelShape(1, 544, 8, 2, 64, 1120, 1500, 1499, dtype="bf16", lm_head_scale=8.0, name="tile-half-stage")
+
+
+@pytest.mark.parametrize("ms,lens,Q", [
+    (HALF, [70], 65), (HALF, [90], 127), (HALF, [33, 40, 47], 43), (HALF, [300], 257), (HALF, [20 + b for b in range(8)], 97),
+    # K shares of the down projection: 65.5 stages
+    (synth.ModelShape(1, 288, 2, 2, 128, 4192, 700, 699, dtype="bf16", lm_head_scale=8.0, name="half-stage-long-k"), [9, 10], 129),
+    # gate and up of 1016 rows in whole rounds of 256 x 256 tiles and a rest of 128 x 128 ones
+    (synth.ModelShape(1, 800, 2, 2, 64, 8544, 600, 599, dtype="bf16", lm_head_scale=8.0, name="half-stage-wide-ff"), [5 + b for b in range(8)], 127),
+    # two and a half stages and more than two tiles per workgroup
+    (_short("half-stage-short", 160, 2, 1, 16416, 600), [40 + b for b in range(16)], 100),
+], ids=["65", "127", "129", "257", "776", "k-shares", "whole-rounds", "short"])
+def test_k_of_half_a_stage_more(ms, lens, Q):
+    """d_model and d_ff 32 more than a multiple of 64: the last stage of a sum is half empty."""
+    assert ms.d_model % 64 == 32 and ms.d_ff % 64 == 32
+    run(ms, lens, Q)
+
+
 @pytest.mark.parametrize("ms,B,Q", [
     # gate and up of 1016 rows: 64 column tiles of 256 in one whole round, two and a half left
     (synth.ModelShape(1, 768, 2, 2, 64, 8512, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-ff"), 8, 127),
