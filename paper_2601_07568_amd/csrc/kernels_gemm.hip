@@ -19,7 +19,8 @@ constexpr int LG_BN = 128, LG_BK = 64;
 // reads stay a permutation of the KiB, and the loader's 16 consecutive lanes (two rows x eight
 // 16-byte columns of a slice) write 16 different bank groups instead of two.
 __device__ __forceinline__ int lg_swz(int g, int ks) { return (4 * g) ^ (2 * ks); }
-enum LgEpi { LG_STORE = 0, LG_STORE_F32 = 1, LG_RESID = 2, LG_SWIGLU = 3, LG_LMSTATS = 4, LG_QKV = 5, LG_ROPE64 = 6, LG_ROPE128 = 7 };
+enum LgEpi { LG_STORE = 0, LG_STORE_F32 = 1, LG_RESID = 2, LG_SWIGLU = 3, LG_LMSTATS = 4, LG_QKV = 5, LG_ROPE64 = 6, LG_ROPE128 = 7,
+             LG_LMSTATS_X = 8 };   // (tile kernel: LMSTATS with expf)
 
 struct LgArgs {
   const bf16_t* A;
@@ -341,7 +342,7 @@ template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF>
 __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   using G = GtGeom<TM, TN, NSA, NSW>;
   constexpr int BM = G::BM, BN = G::BN, CA = G::CA, CW = G::CW;
-  constexpr bool SWIGLU = EPI == LG_SWIGLU, STATS = EPI == LG_LMSTATS, ROPE = EPI == LG_ROPE64 || EPI == LG_ROPE128;
+  constexpr bool SWIGLU = EPI == LG_SWIGLU, STATS = EPI == LG_LMSTATS || EPI == LG_LMSTATS_X, ROPE = EPI == LG_ROPE64 || EPI == LG_ROPE128;
   constexpr bool QKV = EPI == LG_QKV || ROPE;
   constexpr int DH = EPI == LG_ROPE64 ? 64 : 128;
   constexpr bool WIDE = EPI == LG_ROPE128 && TN == 4;           // a wave's weight rows are one whole head of 128 channels
@@ -595,7 +596,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
               for (int e = 0; e < 16; ++e) {
                 const int n = nb + ii * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
                 const float z = acc[half * 2 + ii][j][e] * rs;
-                const float ex = (n < N && n != a.mask_id) ? __builtin_amdgcn_exp2f((z - mx) * 1.4426950408889634f) : 0.f;
+                const float ex = !(n < N && n != a.mask_id) ? 0.f : EPI == LG_LMSTATS_X ? expf(z - mx)
+                                                                : __builtin_amdgcn_exp2f((z - mx) * 1.4426950408889634f);
                 se += ex;
                 sz = fmaf(ex, z, sz);
               }
@@ -853,7 +855,7 @@ static int gt_cus = 256;
   X(LG_ROPE64, 2, 2, 4, 5) X(LG_ROPE64, 2, 2, 2, 3)                            \
   X(LG_ROPE128, 4, 4, 2, 3) X(LG_ROPE128, 2, 2, 4, 5) X(LG_ROPE128, 2, 2, 2, 3)                         \
   X(LG_QKV, 4, 4, 2, 3) X(LG_QKV, 2, 4, 2, 3) X(LG_QKV, 2, 2, 4, 5) X(LG_QKV, 2, 1, 3, 4)               \
-  X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS, 2, 2, 4, 5)
+  X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS_X, 4, 4, 2, 3) X(LG_LMSTATS_X, 2, 2, 4, 5)
 // the forms that are also built for K of 32 more than a multiple of 64
 template <int EPI, int TM, int TN>
 constexpr bool GT_HALF = (TM == TN || TN == 1) && EPI != LG_ROPE64 && EPI != LG_ROPE128;
@@ -1152,8 +1154,13 @@ hipError_t launch_gemm_lmstats(dllm_ctx* c, hipStream_t s, int max_rows, int* n_
   a.n_parts = (f.vocab + 63) / 64;
   a.mask_id = f.mask_id;
   *n_parts_out = a.n_parts;
-  if (gt_usable(max_rows, a.K))
-    return max_rows > 128 ? gt_launch<LG_LMSTATS, 4, 4, 2, 3>(s, a) : gt_launch<LG_LMSTATS, 2, 2, 4, 5>(s, a);
+  // Below 256 rows the exponentials are expf's (relative error 8e-8 at most): the hardware's 2^((z - max) log2 e) is off by up
+  // to 4e-6 at z - max = -80.  It is left to the calls of many rows, where it has always been and expf would cost 5 % of the
+  // head and more (152064 x 3584, us: 512 rows 525 / 557, 1024 rows 1004 / 1068).
+  if (gt_usable(max_rows, a.K)) {
+    if (max_rows >= 256) return gt_launch<LG_LMSTATS, 4, 4, 2, 3>(s, a);
+    return max_rows > 128 ? gt_launch<LG_LMSTATS_X, 4, 4, 2, 3>(s, a) : gt_launch<LG_LMSTATS_X, 2, 2, 4, 5>(s, a);
+  }
   return lg_launch<LG_LMSTATS>(s, a);
 }
 
