@@ -489,8 +489,9 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   if (head) {
     const int max_rows = T < c->map.r_max ? T : (int)c->map.r_max;
     if (!few) TRY(launch_mask_rows(c, s, g, head->cand, head->conf, head->entropy), "mask_rows");
+    const bool sk_head = !few && big_mfma && sk_head_supported(c, max_rows);
     if (!few) {
-      TRY(launch_rmsnorm(c, s, c->final_norm, max_rows, WSP(c, rows, int32_t), WSP(c, status, int32_t) + 1, 0, pending),
+      TRY(launch_rmsnorm(c, s, c->final_norm, max_rows, WSP(c, rows, int32_t), WSP(c, status, int32_t) + 1, 0, pending, sk_head),
           "final_norm");
       pending = 0;
     }
@@ -500,10 +501,10 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
       TRY(launch_sk_lmstats(c, s, c->ws + c->map.xn, T, n_ss, &n_parts), "lm_head");
     } else if (s32) {
       TRY(launch_s32_lmstats(c, s, T, n_ss, &n_parts), "lm_head");
-    } else if (big_mfma && sk_head_supported(c, max_rows)) {
+    } else if (sk_head) {
       TRY(launch_sk_head_rows(c, s, max_rows), "head_rows");
       ProfScope p(c, s, 4, 2.0 * max_rows * (double)f.vocab * f.d_model);
-      TRY(launch_sk_lmstats(c, s, c->ws + c->map.h, max_rows, 1, &n_parts), "lm_head");
+      TRY(launch_sk_lmstats(c, s, c->ws + c->map.h, max_rows, 0, &n_parts), "lm_head");
     } else if (big_mfma) {
       ProfScope p(c, s, 4, 2.0 * max_rows * (double)f.vocab * f.d_model);   // upper bound: max_rows rows
       TRY(launch_gemm_lmstats(c, s, max_rows, &n_parts), "lm_head");

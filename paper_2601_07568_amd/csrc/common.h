@@ -194,6 +194,8 @@ inline size_t elem_size(const dllm_config& c) { return c.dtype == DLLM_BF16 ? 2 
 inline size_t kv_slab_elems(const dllm_config& c) {
   return (size_t)c.n_pages * c.n_kv_heads * c.page_tokens * c.head_dim;
 }
+// floats between the rows of ws.ss: room for a partial sum of squares per 16 columns of d_model
+inline int ss_row_stride(const dllm_ctx* c) { return ((c->cfg.d_model + 15) / 16 + 3) / 4 * 4; }
 constexpr int LM_TILE_N = 512;      // vocabulary columns per LM-head partial
 constexpr int ATTN_MAX_SPLITS = 64;
 
@@ -226,8 +228,9 @@ hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g);
 // out[T or n_rows, d] = rmsnorm(x[row]) * gain; rows == nullptr: identity row map, n = T
 // frag_mt > 0: write in fragment order for frag_mt 16-row tiles (bfloat16 only)
 // n_delta > 0 (fragment path only): first add the open residual sums delta_0 .. to x
+// keep_mean (at most 64 rows, d_model as sk_head_supported allows it): also leave the rows' mean squares in ws.ss
 hipError_t launch_rmsnorm(dllm_ctx* c, hipStream_t s, const void* gain, int T, const int32_t* rows,
-                          const int32_t* n_rows_dev, int frag_mt, int n_delta);
+                          const int32_t* n_rows_dev, int frag_mt, int n_delta, bool keep_mean = false);
 hipError_t launch_fold_delta(dllm_ctx* c, hipStream_t s, int T, int n_delta, bool frag_path);
 constexpr int LG_QKV_SPLITS = 3;       // large path: most K splits of the fused q/k/v product
 constexpr int LG_MAX_DELTA = 3;        // large path: a residual projection is split over K at most 4 ways
@@ -290,6 +293,7 @@ hipError_t launch_sk_f32(dllm_ctx* c, hipStream_t s, const void* A, const void* 
                          int n_ss);
 hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int layer, const KVView& pool, int n_ss);
 hipError_t launch_sk_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_ss);
+// n_ss 0: ws.ss holds the rows' mean squares
 hipError_t launch_sk_lmstats(dllm_ctx* c, hipStream_t s, const void* X, int T, int n_ss, int* n_parts_out);
 bool sk_head_supported(const dllm_ctx* c, int max_rows);
 hipError_t launch_sk_head_rows(dllm_ctx* c, hipStream_t s, int max_rows);

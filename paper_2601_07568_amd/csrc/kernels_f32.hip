@@ -429,8 +429,6 @@ bool s32_supported(const dllm_ctx* c, const StepGeom& g) {
          f.d_ff % 4 == 0 && f.page_tokens % 4 == 0;
 }
 
-static int s32_ss_stride(const dllm_ctx* c) { return ((c->cfg.d_model + 15) / 16 + 3) / 4 * 4; }
-
 static S32Args s32_base(dllm_ctx* c, const float* X, int M, int K, const void* gain, int n_ss) {
   S32Args a;
   memset(&a, 0, sizeof(a));
@@ -438,7 +436,7 @@ static S32Args s32_base(dllm_ctx* c, const float* X, int M, int K, const void* g
   a.gain = (const float*)gain;
   if (gain) a.ss_in = WSM(c, ss, float);
   a.n_ss = n_ss;
-  a.ss_stride = s32_ss_stride(c);
+  a.ss_stride = ss_row_stride(c);
   a.inv_d = 1.0f / (float)c->cfg.d_model;
   a.eps = c->cfg.rms_eps;
   return a;

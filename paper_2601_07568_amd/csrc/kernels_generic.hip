@@ -770,7 +770,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x
                                                       const int32_t* rows, const int32_t* n_rows_dev, const float* delta,
                                                       int n_delta, int64_t delta_stride, float* rscale,
                                                       const int32_t* live_rows, const bf16_t* emb, const int32_t* tokens,
-                                                      int vocab, int32_t* status) {
+                                                      int vocab, int32_t* status, float* mean_out, int ss_stride) {
   __shared__ float red[16];
   const int r = blockIdx.x;
   const bool live = !live_rows || r < *live_rows;
@@ -831,7 +831,11 @@ __global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x
   if (!live) return;
   ss = block_sum(ss, red);
   // the output is x * gain; the row factor goes to rscale[r] and multiplies the consuming GEMM's accumulators
-  if (threadIdx.x == 0) rscale[r] = 1.0f / sqrtf(ss / (float)d + eps);
+  if (threadIdx.x == 0) {
+    const float mean = ss / (float)d;
+    rscale[r] = 1.0f / sqrtf(mean + eps);
+    if (mean_out) mean_out[(int64_t)r * ss_stride] = mean;
+  }
 }
 
 // one workgroup of 256 threads holds a row in registers
@@ -844,7 +848,7 @@ hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const voi
     *normed = true;
 #define ROW4(NV) k_rmsnorm_row4<NV, true><<<g.T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,      \
                      WS(c, xn, bf16_t), nullptr, nullptr, nullptr, 0, 0, WS(c, rscale, float), c->rows_dev,               \
-                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t))
+                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t), nullptr, 0)
     if (f.d_model <= 2048) ROW4(2);
     else if (f.d_model <= 4096) ROW4(4);
     else if (f.d_model <= 8192) ROW4(8);
@@ -889,12 +893,13 @@ hipError_t launch_fold_delta(dllm_ctx* c, hipStream_t s, int T, int n_delta, boo
 // the output is x * gain rounded to bfloat16 and the row factors go to ws.rscale (the consuming GEMMs multiply their
 // float accumulators by them); float models: the output is the normalised row.
 hipError_t launch_rmsnorm(dllm_ctx* c, hipStream_t s, const void* gain, int T, const int32_t* rows,
-                          const int32_t* n_rows_dev, int frag_mt, int n_delta) {
+                          const int32_t* n_rows_dev, int frag_mt, int n_delta, bool keep_mean) {
   const dllm_config& f = c->cfg;
   if (rmsnorm_row4_usable(c)) {
 #define ROW4(NV) k_rmsnorm_row4<NV, false><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,        \
                      WS(c, xn, bf16_t), rows, n_rows_dev, WS(c, delta, float), n_delta, c->map.lg_delta_stride,           \
-                     WS(c, rscale, float), rows ? nullptr : c->rows_dev, nullptr, nullptr, 0, nullptr)
+                     WS(c, rscale, float), rows ? nullptr : c->rows_dev, nullptr, nullptr, 0, nullptr,           \
+                     keep_mean ? WS(c, ss, float) : nullptr, ss_row_stride(c))
     if (f.d_model <= 2048) ROW4(2);
     else if (f.d_model <= 4096) ROW4(4);
     else if (f.d_model <= 8192) ROW4(8);

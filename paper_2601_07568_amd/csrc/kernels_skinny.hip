@@ -493,9 +493,6 @@ static SkArgs sk_base(const void* X, int M, int K) {
   return a;
 }
 
-// partial sums of squares per row: one per 16-column tile of d_model; rows are ss_stride floats apart
-static int sk_ss_stride(const dllm_ctx* c) { return ((c->cfg.d_model + 15) / 16 + 3) / 4 * 4; }
-
 // Residual projection x += A * W^T: one workgroup of 16 waves per 16-column tile, the waves split K.  Its epilogue
 // prepares the next GEMM's input (x * gain_next in fragment order, sums of squares per row): no RMSNorm launch.
 // A workgroup re-reads all of A from the L2 (twice its weight bytes); that costs less than exchanging partial
@@ -509,7 +506,7 @@ hipError_t launch_sk_resid(dllm_ctx* c, hipStream_t s, const void* A, const void
   a.gain_next = (const bf16_t*)gain_next;
   a.xg_out = WSM(c, xn, bf16_t);
   a.ss_out = WSM(c, ss, float);
-  a.ss_stride = sk_ss_stride(c);
+  a.ss_stride = ss_row_stride(c);
   return sk_launch_mt<1, SK_NW_RESID, SK_RESID>(s, a, (N + 15) / 16);
 }
 
@@ -517,7 +514,7 @@ hipError_t launch_sk_resid(dllm_ctx* c, hipStream_t s, const void* A, const void
 static void sk_row_scale(dllm_ctx* c, SkArgs& a, int n_ss) {
   a.ss_in = WSM(c, ss, float);
   a.n_ss = n_ss;
-  a.ss_stride = sk_ss_stride(c);
+  a.ss_stride = ss_row_stride(c);
   a.inv_d = 1.0f / (float)c->cfg.d_model;
   a.eps = c->cfg.rms_eps;
 }
@@ -646,7 +643,7 @@ hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, con
   k_sk_prologue<TYPE><<<g.T, 256, 0, s>>>(g.T, g.B, g.Q, g.max_kv - g.Q, f.d_model, f.vocab, (g.T + 15) / 16, f.head_dim / 2, \
                                     log2((double)f.rope_base), g.tokens, g.prefix_len, g.q_valid, live ? g.n_live : nullptr, \
                                     (const TYPE*)c->tok_emb, (const bf16_t*)gain, WSM(c, x, float), WSM(c, xn, bf16_t), \
-                                    WSM(c, ss, float), sk_ss_stride(c), WSM(c, len_safe, int32_t), \
+                                    WSM(c, ss, float), ss_row_stride(c), WSM(c, len_safe, int32_t), \
                                     WSM(c, q_valid_eff, int32_t), WSM(c, tok_seq, int32_t), WSM(c, tok_pos, int32_t), \
                                     WSM(c, rope_cos, float), WSM(c, rope_sin, float), WSM(c, status, int32_t), \
                                     f.mask_id, (int)c->map.r_max, WSM(c, rows, int32_t), cand, conf, entropy)
@@ -703,21 +700,17 @@ hipError_t launch_sk_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_
   return sk_launch_mt<2, SK_NW, SK_SWIGLU>(s, a, (f.d_ff + 15) / 16);
 }
 
-// The compacted rows of a forward of many tokens (ws.xn row-major x * gain, ws.rscale their factors) as the
-// weight-streaming LM head reads them: fragment order in ws.h (free behind the last layer), and the sum of squares that
-// the factor came from.  One workgroup per row; a launch of 5 us.  A refresh of 1184 tokens with the outputs of 32 rows:
-// LM head 263 us on 128 x 128 tiles, 211 + 5 here.
-__global__ __launch_bounds__(256) void k_sk_head_rows(int d, int mt, int ss_stride, float inv_d, float eps, const int32_t* n_rows,
-                                                      const bf16_t* xn, const float* rscale, bf16_t* X, float* ss) {
+// The compacted rows of a forward of many tokens (ws.xn row-major x * gain; the norm has left their mean squares in
+// ws.ss, from which the head's kernel takes the very factor that the norm computed) as the weight-streaming LM head reads them: fragment order in ws.h (free behind the last layer).  One workgroup per
+// row; a launch of 5 us.  A refresh of 1184 tokens with the outputs of 32 rows: LM head 263 us on 128 x 128 tiles, 211 + 5
+// here; one layer and the head at 300 tokens and 4 / 32 / 64 rows: 0.78 / 0.80 / 0.84 of the time on the 8B shape, 0.63 /
+// 0.64 / 0.70 on the 7B shape, 0.60 / 0.66 / 0.75 at 1024 channels, 0.72 / 0.74 / 0.81 at 256 x 40000.
+__global__ __launch_bounds__(256) void k_sk_head_rows(int d, int mt, const int32_t* n_rows, const bf16_t* xn, bf16_t* X) {
   const int row = blockIdx.x;
   if (row >= *n_rows) return;
   const int d_pad = (d + SK_KB - 1) / SK_KB * SK_KB;
   for (int k = threadIdx.x * 8; k < d_pad; k += 256 * 8)
     *(u32x4*)(X + frag_offset(row, k, mt)) = k < d ? *(const u32x4*)(xn + (int64_t)row * d + k) : u32x4{0, 0, 0, 0};
-  if (threadIdx.x == 0) {
-    const double r = rscale[row];
-    ss[(int64_t)row * ss_stride] = (float)((1.0 / (r * r) - (double)eps) / (double)inv_d);
-  }
 }
 // LM heads of at most 64 rows behind a forward of many tokens: the packed weights stream faster than tiles of mostly
 // padding rows read them
@@ -726,9 +719,8 @@ bool sk_head_supported(const dllm_ctx* c, int max_rows) {
 }
 hipError_t launch_sk_head_rows(dllm_ctx* c, hipStream_t s, int max_rows) {
   const dllm_config& f = c->cfg;
-  k_sk_head_rows<<<max_rows, 256, 0, s>>>(f.d_model, (max_rows + 15) / 16, sk_ss_stride(c), 1.0f / (float)f.d_model, f.rms_eps,
-                                          WSM(c, status, int32_t) + 1, WSM(c, xn, bf16_t), WSM(c, rscale, float), WSM(c, h, bf16_t),
-                                          WSM(c, ss, float));
+  k_sk_head_rows<<<max_rows, 256, 0, s>>>(f.d_model, (max_rows + 15) / 16, WSM(c, status, int32_t) + 1, WSM(c, xn, bf16_t),
+                                          WSM(c, h, bf16_t));
   return hipGetLastError();
 }
 
@@ -737,7 +729,8 @@ hipError_t launch_sk_head_rows(dllm_ctx* c, hipStream_t s, int max_rows) {
 hipError_t launch_sk_lmstats(dllm_ctx* c, hipStream_t s, const void* X, int T, int n_ss, int* n_parts_out) {
   const dllm_config& f = c->cfg;
   SkArgs a = sk_base(X, T, f.d_model);
-  sk_row_scale(c, a, n_ss);
+  sk_row_scale(c, a, n_ss > 0 ? n_ss : 1);
+  if (n_ss == 0) a.inv_d = 1.0f;
   a.n_lm_rows = WSM(c, status, int32_t) + 1;
   a.W0 = (const bf16_t*)c->packed_lm_head;
   a.N0 = f.vocab;

@@ -169,3 +169,39 @@ def test_few_head_rows_behind_a_forward_of_many(ms, lens, Q, n_masked):
                              ent.cpu().numpy()[rows], "bf16")
     assert eng.read_status() == 0
     eng.close()
+
+
+def test_few_head_rows_scale_by_the_norms_own_factor():
+    """The LM head's outputs behind a forward of many tokens and behind a denoise step run through the same kernel; with no
+    layers, 256 channels and embeddings of small whole numbers (every sum of squares and every product exact) the row
+    factor is all that could differ, and must not by a bit."""
+    ms = synth.ModelShape(0, 256, 2, 2, 64, 256, 512, 511, dtype="bf16", lm_head_scale=8.0, name="head-only")
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(11)
+    g = {"tok_emb": torch.randint(-9, 10, (512, 256), generator=gen, device=dev).to(torch.bfloat16),
+         "lm_head": torch.randn(512, 256, generator=gen, device=dev).mul_(0.2).to(torch.bfloat16),
+         "final_norm": torch.ones(256, device=dev, dtype=torch.bfloat16)}
+    from paper_2601_07568_amd.binding import Engine
+    eng = Engine(ms, None, page_tokens=16, max_pages_per_seq=2, n_pages=2, max_batch=1, max_q=8, max_tokens=24, device_weights=(g, []))
+    table, zero = eng.i32([[0, 1]]), eng.i32([0])
+    q = torch.full((1, 8), ms.mask_id, dtype=torch.int32, device=dev)
+    for _ in range(64):
+        g["tok_emb"][ms.mask_id] = torch.randint(-9, 10, (256,), generator=gen, device=dev).to(torch.bfloat16)
+        out = []
+        for many in (False, True):
+            cand = torch.zeros(24, dtype=torch.int32, device=dev)
+            conf, ent = (torch.zeros(24, dtype=torch.float32, device=dev) for _ in range(2))
+            if many:
+                toks = torch.cat([torch.arange(16, dtype=torch.int32, device=dev), q[0]])
+                eng.refresh_cache(toks, eng.i32([0, 24]), table, eng.i32([16]), cand, conf, ent, total_tokens=24, max_seqlen=24)
+                out.append((cand[16:], conf[16:], ent[16:]))
+            else:
+                c1, f1, e1 = cand[:8].view(1, 8), conf[:8].view(1, 8), ent[:8].view(1, 8)
+                eng.denoise_step(q, zero, table, c1, f1, e1, max_prefix_len=0)
+                out.append((c1[0], f1[0], e1[0]))
+        for a, b in zip(*out):
+            assert torch.equal(a, b), (a, b)
+        assert 0.0 < float(out[0][1][0]) < 1.0
+    assert eng.read_status() == 0
+    eng.close()
