@@ -397,6 +397,7 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
       ProfScope p(c, s, 0, 2.0 * (dq + 2.0 * dkv) * f.d_model);
       TRY(launch_sk_qkv(c, s, g, l, attention_view(c, g, l), n_ss), "qkv");
     } else if (s32) {
+      ProfScope p(c, s, 0, 2.0 * T * (dq + 2.0 * dkv) * f.d_model);   // (work of the float paths: in flops)
       TRY(launch_s32_qkv(c, s, g, l, attention_view(c, g, l), n_ss), "qkv");
     } else {
       ProfScope p(c, s, 0, 2.0 * T * (dq + 2.0 * dkv) * f.d_model);   // large path: work recorded in flops
@@ -431,6 +432,7 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
       TRY(launch_sk_resid(c, s, c->ws + c->map.o, c->packed_layers[l].wo, T, f.d_model, dq, L.mlp_norm), "wo");
       n_ss = ss_groups;
     } else if (s32) {
+      ProfScope p(c, s, 1, 2.0 * T * (double)dq * f.d_model);
       TRY(launch_s32_resid(c, s, WSP(c, o, float), L.wo, T, dq), "wo");
       n_ss = ss_groups;
     } else {
@@ -453,6 +455,7 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
           "w_down");
     } else if (s32) {
       TRY(launch_s32_swiglu(c, s, l, T, n_ss), "swiglu");
+      ProfScope p(c, s, 3, 2.0 * T * (double)f.d_ff * f.d_model);
       TRY(launch_s32_resid(c, s, WSP(c, h, float), L.w_down, T, f.d_ff), "w_down");
     } else {
       if (big_mfma) {

@@ -60,3 +60,22 @@ def test_float_step_around_the_tiles(ms, lens, Q, pt):
         eng.denoise_step(qt[:1, :n0].contiguous(), pre[:1], dt[:1], c3, f3, None, max_prefix_len=lens[0])
         assert torch.equal(c2[0, :n0], c3[0]) and torch.equal(f2[0, :n0], f3[0])
     eng.close()
+
+
+def test_profile_of_a_float_step_records_what_the_generic_kernels_record():
+    """dllm_profile_read after a step on the few-row kernels: launches and work of every class as on the generic ones."""
+    ms = synth.TINY
+    eng = H.make_engine(ms, synth.Weights(ms, 1), page_tokens=16, max_pages_per_seq=4, n_pages=4, max_batch=1, max_q=32)
+    table, zero = eng.i32(H.identity_table(eng, 1)), eng.i32([0])
+    q = eng.i32([synth.masked_block(ms, 3, 32, 16)])
+    cand = torch.zeros(1, 32, dtype=torch.int32, device=eng.device)
+    conf = torch.zeros(1, 32, dtype=torch.float32, device=eng.device)
+    got = []
+    for mode in (1, 0):
+        eng.set_kernel_mode(mode)
+        eng.profile_enable(True)
+        eng.denoise_step(q, zero, table, cand, conf, None, max_prefix_len=0)
+        got.append([eng.profile_read(cls)[::2] for cls in range(6)])
+        eng.profile_enable(False)
+    assert got[0] == got[1] and got[1][0][0] == got[1][5][0] == ms.n_layers, got
+    eng.close()
