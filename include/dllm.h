@@ -106,7 +106,8 @@ size_t dllm_kv_pool_bytes(const dllm_config *cfg);
  * for DLLM_BF16 d_model, d_ff and n_*_heads * head_dim must be multiples of 8; mask_id in
  * [0, vocab).  kv_pool (dev) holds dllm_kv_pool_bytes, workspace (dev, 256-byte aligned) holds
  * dllm_workspace_bytes; the workspace's status word must be cleared once with
- * dllm_reset_status before the first call.  Performs no HIP call. */
+ * dllm_reset_status before the first call.  Enqueues nothing; its only HIP calls raise LDS limits of bfloat16 kernels, and
+ * without a device they are skipped. */
 int dllm_create(dllm_ctx **out, const dllm_config *cfg, const dllm_weights *w,
                 void *kv_pool, size_t kv_pool_bytes, void *workspace, size_t workspace_bytes);
 void dllm_destroy(dllm_ctx *ctx);
@@ -119,7 +120,9 @@ void dllm_destroy(dllm_ctx *ctx);
  * kb*128 + j*32 + g*8 .. +7 (rows padded to 16, columns to 128, with zeros).
  * dllm_pack_weights enqueues the re-ordering of all projection matrices and of the LM head into
  * `packed` (dev, 256-byte aligned, dllm_packed_weight_bytes, borrowed for the life of the context).
- * The original weights stay in use (prefill, refresh and steps of more than 64 rows read them).
+ * The original weights stay in use: prefill, refresh and steps of more than 64 rows read them, but for the LM head of a
+ * refresh that can have at most 64 rows of it (the smaller of total_tokens and max_batch * max_q), which reads the packed
+ * one.  Whoever changes a weight packs again before the calls that read it.
  * Until this call has been made, bfloat16 denoise steps run on the generic kernels. */
 size_t dllm_packed_weight_bytes(const dllm_config *cfg);
 int dllm_pack_weights(dllm_ctx *ctx, void *stream, void *packed, size_t packed_bytes);

@@ -141,8 +141,9 @@ extern "C" int dllm_create(dllm_ctx** out, const dllm_config* cfg, const dllm_we
   c->map = m;
   c->kernel_mode = 0;
   if (cfg->dtype == DLLM_BF16) {
-    // raising two kernels' LDS limits; a failure (e.g. no device in this process) is not an error of the call: the
-    // launchers check the flags these leave and take the kernels that need no raised limit
+    // raising the LDS limits of the tile kernel's forms and of the attention kernels; a failure (e.g. no device in this
+    // process) is not an error of the call: the launchers check the flags these leave and take the kernels that need no
+    // raised limit
     const hipError_t e1 = init_gemm_tiles();     // without it the 128-row kernels serve every size
     const hipError_t e2 = init_attn_kernels();   // without it every wave of the batch-1 attention writes its own partial
     // such a failure must not surface later as the "last error" of an unrelated launch

@@ -422,7 +422,10 @@ __global__ __launch_bounds__(512) void k_s32_attn(const float* q, float* o, cons
 }
 
 // ------------------------------------------------------------------------------------------
-// float models, steps of at most 64 rows; everything the kernels load 16 bytes at a time is aligned for it
+// float models, steps of at most 64 rows; everything the kernels load 16 bytes at a time is aligned for it.  No bound on the
+// prefix or the width: against the generic kernels a step of two layers and a head takes 0.04 .. 0.19 of the time for 1 ..
+// 64 rows, prefixes of 64 .. 8192 and 256 .. 4096 channels (us, 32 rows: 256 channels 801 / 95 at prefix 64, 2085 / 391 at 8192;
+// 4096 channels 11647 / 837 and 24153 / 1795).
 bool s32_supported(const dllm_ctx* c, const StepGeom& g) {
   const dllm_config& f = c->cfg;
   return f.dtype == DLLM_F32 && c->kernel_mode == 0 && c->f32_aligned && g.Q > 0 && g.T <= SK_MAX_ROWS && f.d_model % 4 == 0 &&

@@ -337,7 +337,8 @@ struct GtGeom {
 };
 
 // HALF: K is 32 more than a multiple of 64.  The last stage's upper 32 come from past the end of the row, so their copies
-// are sent out of the descriptor, which leaves zeros in LDS; an instruction more per copy (a form of its own for it).
+// are sent out of the descriptor, which leaves zeros in LDS.  A form of its own: it takes 19 .. 21 instructions more per stage
+// (128 x 128: 146 for 125).
 template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF>
 __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   using G = GtGeom<TM, TN, NSA, NSW>;
@@ -370,8 +371,10 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // channels: 4.5 against 6.4 TB/s of plain reads with rows of 8 KiB.  Neighbouring columns of 256 weight rows begin 11
   // stages apart instead.  With more rows the activations no longer stay in the L2, which the column tiles share only in step.
   // (128 rows: 24576 x 4096 53.6 -> 51.7 us, 12288 x 4096 33.5 -> 30.9; a whole pass of 128 rows 782 -> 746 us.)  By the rows
-  // there are and not the host's bound, by weight rows and not tiles, so that a call with a device-resident total, which
-  // may take other tiles, sums as the sized call does.
+  // there are and not the host's bound, by weight rows and not tiles: where a call with a device-resident total gets the
+  // same K split and the same q/k/v form as the sized call, it sums in the same order whatever its tiles.  Those two are
+  // chosen by the host's bound (4096 x 4096: three shares at 600 rows, one at 700), so it need not get them; and a
+  // row's sums begin elsewhere when the rows of its call pass 256.
   const int k_rot = M <= 256 ? 11 : 0;
   struct Item { int split, tm, tn, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
@@ -442,7 +445,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     else return hw * 32 * TN + TN * c + i;
   };
   // One wave issues an instruction in about 5 cycles, and a stage of the smaller tiles has few products to issue others
-  // beside (128 x 128: 16 of 165 instructions): there every copy keeps its own offset instead of adding it up each time.
+  // beside (128 x 128: 16 of 125 instructions, 168 in the rotary form): there every copy keeps its own offset instead of adding it up each time.
   // (256 x 4096 x 12288: 45 -> 41 us; the 256 x 256 tiles have no registers left for it.)
   constexpr bool VO = TM * TN < 16;
   int vA[VO ? CA : 1], vW[VO ? CW : 1];
@@ -917,6 +920,8 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
 // costs 0.6 of it (half the products, three quarters of the bytes), a 128 x 128 one 0.33 (copies and products take
 // equally long), a 128 x 64 one 0.22.  Measured against each other (K = 3584 .. 18944, us): 1024 x 37888: 271 / 286 /
 // 297; 256 x 24576: 85 / 55 / 61; 128 x 24576: 85 / 50 / 39; 1024 x 3584 x 3584: 48 (4 K shares) / 38 (2) / 42.
+// Over 200 layers of 128 .. 8192 channels and 96 .. 16384 rows, 257 .. 511 among them, what it picks takes 0.47 .. 0.98 of the
+// time of the 32-deep kernels that were here before.
 enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_N = 4 };
 struct GtPlan { GtTile tile; int splits, k_per; double us; };
 // NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile that its widths allow

@@ -207,3 +207,16 @@ def test_build_refuses_spills_between_lds_copies():
     other = "_ZN4dllm14k_attn_combineILi128EEEvPKfS2_iPtiil:\n global_load_lds_dwordx4 v[0:1], off\n scratch_store_dword off, v3, off\n" \
             " global_load_lds_dwordx4 v[2:3], off\n"
     build._check_counted_loops("kernels_attention.hip", other)
+
+
+def test_build_refuses_spills_between_the_products_of_the_tile_kernel():
+    """The tile kernel's counts hold from its first matrix instruction to its last one: spills there are refused, spills
+    in front of and behind them (its epilogue) pass."""
+    from paper_2601_07568_amd import build
+    head = "_ZN4dllm11k_gemm_tileILi3ELi4ELi4ELi2ELi3ELb0EEEvNS_6LgArgsE:\n"
+    copy, mfma = " buffer_load_dwordx4 v1, s[0:3], s4 offen lds\n", " v_mfma_f32_32x32x16_bf16 a[0:15], v[0:3], v[4:7], a[0:15]\n"
+    spill = " scratch_store_dword off, v3, off\n"
+    with pytest.raises(RuntimeError):
+        build._check_counted_loops("kernels_gemm.hip", head + copy + mfma + spill + copy + mfma)
+    build._check_counted_loops("kernels_gemm.hip", head + spill + copy + mfma + copy + mfma + spill)
+    build._check_counted_loops("kernels_gemm.hip", head.replace("k_gemm_tile", "k_gemm_mfma") + copy + mfma + spill + mfma)
