@@ -598,13 +598,21 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
 #pragma unroll
               for (int e = 0; e < 16; ++e) {
                 const int n = nb + ii * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
-                const float z = acc[half * 2 + ii][j][e] * rs;
+                // (a weight of 0 does not leave out an infinite logit)
+                const float z = n != a.mask_id ? acc[half * 2 + ii][j][e] * rs : 0.f;
                 const float ex = !(n < N && n != a.mask_id) ? 0.f : EPI == LG_LMSTATS_X ? expf(z - mx)
                                                                 : __builtin_amdgcn_exp2f((z - mx) * 1.4426950408889634f);
                 se += ex;
                 sz = fmaf(ex, z, sz);
               }
             st.m = mx; st.idx = ix; st.s = se; st.t = sz;
+          } else {
+            // No logit above -inf: nothing to add, but a row of NaNs has to show.  The lane's first columns (one of them may
+            // be the mask token's) stand for all of them.
+            const int n = nb + h * 4;
+            const float z0 = acc[half * 2][j][0] * rs, z1 = acc[half * 2][j][1] * rs;
+            const bool b0 = n < N && n != a.mask_id && z0 != z0, b1 = n + 1 < N && n + 1 != a.mask_id && z1 != z1;
+            if (b0 || b1) { st.m = st.s = st.t = b0 ? z0 : z1; st.idx = b0 ? n : n + 1; }
           }
           const float m2 = __shfl_xor(st.m, 32, 64), s2 = __shfl_xor(st.s, 32, 64), t2 = __shfl_xor(st.t, 32, 64);
           const int i2 = __shfl_xor(st.idx, 32, 64);

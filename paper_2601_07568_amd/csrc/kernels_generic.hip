@@ -635,7 +635,7 @@ __global__ __launch_bounds__(256) void k_lm_head(const T* __restrict__ A, const 
 // one wavefront per compacted row: merge the per-tile statistics and emit the outputs
 __global__ __launch_bounds__(256) void k_lm_merge(const float* part, int n_vtiles, const int32_t* rows,
                                                   const int32_t* n_rows_dev, int32_t* cand, float* conf,
-                                                  float* entropy, int by_token) {
+                                                  float* entropy, int by_token, int32_t mask_id) {
   // 256 threads per row; a thread's partials are fetched eight at a time before they are merged, so the
   // loads of a batch are in flight together; lanes, then waves, merge in a fixed order
   __shared__ float4 wst[4];
@@ -667,7 +667,9 @@ __global__ __launch_bounds__(256) void k_lm_merge(const float* part, int n_vtile
     st.init();
     for (int w = 0; w < 4; ++w) st.merge(wst[w].x, __float_as_int(wst[w].y), wst[w].z, wst[w].w);
     const int t = rows[r];
-    cand[t] = st.idx;
+    // a row without a logit above -inf has no distribution: the confidence is NaN, the candidate some token id
+    if (st.s == 0.f) st.s = __builtin_nanf("");
+    cand[t] = st.idx != 0x7fffffff ? st.idx : (mask_id == 0 ? 1 : 0);
     conf[t] = 1.0f / st.s;
     if (entropy) entropy[t] = (st.m + logf(st.s)) - st.t / st.s;
   }
@@ -1053,7 +1055,8 @@ hipError_t launch_lm_head_generic(dllm_ctx* c, hipStream_t s, int max_rows) {
 hipError_t launch_lm_merge(dllm_ctx* c, hipStream_t s, int max_rows, int n_parts, int32_t* cand, float* conf,
                            float* entropy, bool by_token) {
   k_lm_merge<<<max_rows, 256, 0, s>>>(WS(c, lm_part, float), n_parts, WS(c, rows, int32_t),
-                                     WS(c, status, int32_t) + 1, cand, conf, entropy, by_token ? 1 : 0);
+                                     WS(c, status, int32_t) + 1, cand, conf, entropy, by_token ? 1 : 0,
+                                     c->cfg.mask_id);
   return hipGetLastError();
 }
 

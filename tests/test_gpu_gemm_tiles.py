@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from oracle import dllm_oracle as O
-from paper_2601_07568_amd import synth
+from paper_2601_07568_amd import binding, synth
 from tests import harness as H
 
 pytestmark = pytest.mark.gpu
@@ -204,4 +204,43 @@ def test_few_head_rows_scale_by_the_norms_own_factor():
             assert torch.equal(a, b), (a, b)
         assert 0.0 < float(out[0][1][0]) < 1.0
     assert eng.read_status() == 0
+    eng.close()
+
+
+@pytest.mark.parametrize("ms,Q", [(EDGE, 16), (EDGE, 32), (EDGE, 43), (EDGE, 120), (HALF, 43), (synth.TINY, 16)],
+                         ids=["48-rows", "96-rows", "129-rows", "360-rows", "half-stage", "float-48-rows"])
+def test_rows_that_are_not_finite_stay_to_themselves(ms, Q):
+    """Infinities in one sequence (an embedding only it uses) and in the LM head's column of the mask token, which takes no
+    part in the distribution, leave the other sequences' outputs as they are, bit for bit: also where the end of a row is
+    copied next to the beginning of another.  The sequence itself, all NaN, reports confidences that no threshold accepts
+    and candidates that are token ids."""
+    w = synth.Weights(ms, 6)
+    B, pt = 3, 16
+    mp = (Q + pt - 1) // pt
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=B * mp, max_batch=B, max_q=Q)
+    table, zero = eng.i32(H.identity_table(eng, B)), eng.i32([0] * B)
+    odd = 17
+    q = np.stack([synth.masked_block(ms, 20 + b, Q, Q // 2) for b in range(B)])
+    q[q == odd] = odd + 1
+    q[1, 0] = q[1, -1] = odd
+    out = []
+    for poison in (False, True):
+        if poison:
+            eng.g["tok_emb"][odd] = float("inf")
+            eng.g["lm_head"][ms.mask_id] = float("inf")
+            if ms.dtype == "bf16":
+                off = (-eng.packed.data_ptr()) % 256
+                eng._check(binding.lib().dllm_pack_weights(eng.ctx, eng._stream(), eng.packed.data_ptr() + off, eng.packed.numel() - 256))
+        cand = torch.zeros(B, Q, dtype=torch.int32, device=eng.device)
+        conf, ent = (torch.zeros(B, Q, dtype=torch.float32, device=eng.device) for _ in range(2))
+        eng.denoise_step(eng.i32(q), zero, table, cand, conf, ent, max_prefix_len=0)
+        hidden = eng.debug_hidden(eng.i32(q), zero, table, ms.n_layers, max_prefix_len=0)
+        out.append((cand, conf, ent, hidden))
+    for a, b in zip(*out):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[2], b[2])
+    cand, conf, _, hidden = out[1]
+    masked = torch.from_numpy(q[1] == ms.mask_id).to(eng.device)
+    assert torch.isfinite(hidden[::2]).all() and not torch.isfinite(hidden[1]).any()
+    assert torch.isnan(conf[1][masked]).all() and torch.isfinite(out[0][1]).all()
+    assert ((cand[1] >= 0) & (cand[1] < ms.vocab)).all() and (cand[1][masked] != ms.mask_id).all()
     eng.close()
