@@ -1,6 +1,7 @@
 // Host-side exercise of the C ABI for a sanitizer build (AddressSanitizer + UndefinedBehaviorSanitizer on the host
 // code only): every entry point is driven through its argument validation, the workspace map and the context
-// life cycle with device pointers that are never dereferenced on the host.  No GPU is needed: nothing is launched.
+// life cycle with device pointers that are never dereferenced on the host, and the order in which the tile kernel's copies
+// and products run through their work (gemm_ring.h) is checked.  No GPU is needed: nothing is launched.
 // Exit status 0 = every call returned what it should; the sanitizers abort the process on a finding.
 #include <stdio.h>
 #include <stdlib.h>

@@ -184,7 +184,7 @@ def test_host_side_code_under_address_and_undefined_behaviour_sanitizers():
     """The library's host code (argument validation, workspace map, context life cycle, launch geometry up to the
     first launch) compiled with AddressSanitizer + UndefinedBehaviorSanitizer on the host side only and driven by
     csrc/host_check_main.cpp through every entry point, without a GPU: the sanitizers abort on a finding, the
-    driver counts wrong return codes."""
+    driver counts wrong return codes, and stages and tiles that the tile kernel's copies would fetch out of order."""
     import subprocess
     exe = build.build_host_check()
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)

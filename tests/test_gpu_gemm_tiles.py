@@ -62,7 +62,8 @@ def test_k_shares_of_a_long_sum(B, Q):
 
 
 def test_several_items_per_workgroup():
-    """1600 x 8192 gate and up rows: more tiles than workgroups, the copies of a workgroup run on into its next tile."""
+    """1600 rows x 2 * 8192 gate and up rows: 448 tiles of 256 x 256 on 256 places, a second one for most of them (a third
+    and further: test_short_sums_with_more_than_two_tiles_per_workgroup)."""
     wide = synth.ModelShape(1, 128, 2, 1, 64, 8192, 600, 599, dtype="bf16", lm_head_scale=8.0, name="tile-items")
     run(wide, [40 + b for b in range(16)], 100)
 
