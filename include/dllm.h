@@ -147,7 +147,8 @@ int dllm_prefill_kv(dllm_ctx *ctx, void *stream, int B, int total_tokens, int ma
  * excluded) is reduced on the fly -- the logits are never stored --
  * to cand_token = arg max (lowest id on ties), conf = its softmax probability, and optionally
  * entropy (nats).  Rows that are not masked get cand_token = their own token, conf = 1,
- * entropy = 0.
+ * entropy = 0.  A masked row whose logits are all NaN, or none of which is above -infinity, gets
+ * conf = NaN (dllm_unmask ranks it last) and some token id other than mask_id.
  *   q_tokens dev int32 [B, Q]    prefix_len dev int32 [B]    block_table dev int32 [B, max_pages_per_seq]
  *   cand_token dev int32 [B, Q]  conf dev float [B, Q]       entropy dev float [B, Q] or NULL
  *   max_prefix_len (host) >= every prefix_len[b]; it only sizes the launch. */
