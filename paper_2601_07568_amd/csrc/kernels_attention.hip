@@ -1,5 +1,6 @@
 // bfloat16 matrix-core (MFMA) kernels for gfx950: attention.
 #include "mfma_common.h"
+#include <type_traits>
 
 namespace dllm {
 
@@ -413,549 +414,478 @@ __global__ __launch_bounds__(512) void k_attn_combine(const float* part_o, const
 }
 
 // ------------------------------------------------------------------------------------------
-// The same attention for many query rows per KV head (grouped-query models at large batch, and
-// every no-cache forward): the waves of a workgroup are row groups of 32 rows that all need the
-// same keys, so each 64-key block of K and V^T is fetched from memory once per workgroup, by all
-// threads together, and laid out in LDS in operand order (every fragment read is 64 lanes x 16
-// bytes of one KiB; inside the KiB the row index is xor-ed with the piece's column so that the
-// loader's consecutive lanes, which walk along a row, hit different banks); two LDS buffers, the
-// next block in flight in registers while the current one is multiplied.  Arithmetic, masking and
-// outputs are those of k_attn_step.
-template <int DH, int NW, bool PAGED, bool FAST>
-__global__ __launch_bounds__(NW * 64) void k_attn_lds(const AttnArgs a) {
-  constexpr int KK = DH / 32, DT = DH / 16, QT = 2;
-  constexpr int KP = DH / 8;                 // 16-byte pieces of a K row
-  constexpr int KPB = 64 * KP, VPB = DH * 8; // pieces of a 64-key block: K rows, V^T channel rows
-  constexpr int NP = KPB + VPB, nthr = NW * 64, MAXP = NP / nthr;
-  static_assert(KPB % nthr == 0 && VPB % nthr == 0, "a thread's i-th piece is K for all threads or V for all");
-  __shared__ u32x4 sk[2][2][2][KK][64];      // [buffer][32-key half][tile][k-step][lane]
-  __shared__ u32x4 sv[2][2][DT][64];         // [buffer][32-key half][channel tile][lane]
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
-  const int c = lane & 15, g = lane >> 4;
-  const int rg = blockIdx.y * a.n_rg_wg + w;
-  const int unit = blockIdx.x;
-  const int b = blockIdx.z / a.Hkv, kvh = blockIdx.z - b * a.Hkv;
-  const int G = a.Hq / a.Hkv;
-  const int row_base = PAGED ? b * a.Q : a.cu[b];
-  const int n_q = PAGED ? a.Q : a.cu[b + 1] - a.cu[b];
-  const int R = n_q * G;
-  const int kv_len = PAGED ? a.prefix_len[b] + (a.q_valid ? min(max(a.q_valid[b], 0), a.Q) : a.Q) : n_q;
-  const bool active = w < a.n_rg_wg && rg * 16 * QT < R;     // waves beyond the rows only help loading
-  if (blockIdx.y * a.n_rg_wg * 16 * QT >= R) return;         // whole workgroup beyond this sequence's rows
-  if (PAGED && a.q_valid && a.q_valid[b] < 0) return;        // the sequence is not part of this call
-  const KVView& kv = a.kv;
-  const int sh = a.pt_shift, pt = 1 << sh;                   // page size (a power of two)
-  const bf16_t* kslab = (const bf16_t*)kv.k;
-  const bf16_t* vslab = (const bf16_t*)kv.v;
-  const int32_t* table = PAGED ? kv.table + (int64_t)b * kv.max_pages : nullptr;
-  const int64_t pcol = PAGED ? 0 : kv.cu_pad[b];
-  bool bad = false;
-
-  u32x4 qf[QT][KK];
-  int64_t row_out[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    int r = rg * 16 * QT + t * 16 + c;
-    const bool ok = active && r < R;
-    if (!ok) r = 0;
-    const int hg = r / n_q, j = r - hg * n_q;
-    const int64_t ro = (int64_t)(row_base + j) * a.Hq + kvh * G + hg;
-    row_out[t] = ok ? ro : -1;
-    const bf16_t* qp = a.q + ro * DH + g * 8;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[t][kk] = *(const u32x4*)(qp + kk * 32);
-  }
-
-  // ---- cooperative loader.  Piece p = tid + i * nthr of a 64-key block: a 16-byte column of a K
-  // row (i-th pieces below KPB) or eight keys of a V^T channel row.  No branch anywhere on the
-  // way to a load, and the page ids of a block are fetched one block earlier than its data, so a
-  // wave never waits on two dependent memory round trips.
-  auto piece_key = [&](int i, int kb64) -> int {              // first key the piece addresses (clamped into the sequence)
-    const int p = tid + i * nthr;
-    if (i * nthr < KPB) {
-      const int key = (kb64 << 6) + p / KP;
-      return key < kv_len ? key : kv_len - 1;                   // masked at the scores
-    }
-    const int key = (kb64 << 6) + ((p - KPB) & 7) * 8;
-    return key < kv_len ? key : (kv_len - 1) & ~7;              // zeroed when it is put into LDS
-  };
-  // FAST: a 64-key block lies inside one page (page size a multiple of 64) or in the packed scratch, so
-  // its K rows are 64 * DH contiguous elements and its V^T rows 64 contiguous keys per channel: one
-  // base per block (wave-uniform) plus a per-thread constant.  Rows past the sequence end are read
-  // as they are (inside the page, or inside the workspace) and masked or zeroed later.
-  int koff[MAXP];
-#pragma unroll
-  for (int i = 0; i < MAXP; ++i) {
-    const int p = tid + i * nthr;
-    if (i * nthr < KPB) koff[i] = p * 8;
-    else koff[i] = ((p - KPB) >> 3) * (PAGED ? pt : kv.tpad) + ((p - KPB) & 7) * 8;
-  }
-  auto fetch_pages = [&](int (&pg)[MAXP], int kb64) {
-    if constexpr (PAGED && FAST) {
-      const int pi = (kb64 << 6) >> sh;
-      const int v = table[pi < kv.max_pages ? pi : kv.max_pages - 1];
-      pg[0] = pi < kv.max_pages ? v : -1;
-    } else if constexpr (PAGED) {
-#pragma unroll
-      for (int i = 0; i < MAXP; ++i) {
-        const int pi = piece_key(i, kb64) >> sh;
-        const int v = table[pi < kv.max_pages ? pi : kv.max_pages - 1];
-        pg[i] = pi < kv.max_pages ? v : -1;
-      }
-    }
-  };
-  auto issue = [&](u32x4 (&reg)[MAXP], const int (&pg)[MAXP], int kb64, uint32_t& vbad) {
-    vbad = 0;
-    if constexpr (FAST) {
-      const int k0 = kb64 << 6;
-      int64_t kb, vb;
-      if constexpr (PAGED) {
-        const int page = __builtin_amdgcn_readfirstlane(pg[0]);
-        const bool ok = (uint32_t)page < (uint32_t)kv.n_pages;
-        bad |= !ok;
-        vbad = ok ? 0u : 0xffffffffu;
-        const int64_t rows = (((int64_t)(ok ? page : 0) * kv.n_kv_heads + kvh) << sh);
-        kb = (rows + (k0 & (pt - 1))) * DH;
-        vb = rows * DH + (k0 & (pt - 1));
-      } else {
-        kb = ((int64_t)kvh * kv.tpad + pcol + k0) * DH;
-        vb = (int64_t)kvh * DH * kv.tpad + pcol + k0;
-      }
-      const bf16_t* kp = kslab + kb;
-      const bf16_t* vp = vslab + vb;
-#pragma unroll
-      for (int i = 0; i < MAXP; ++i) reg[i] = *(const u32x4*)((i * nthr < KPB ? kp : vp) + koff[i]);
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < MAXP; ++i) {
-      const int p = tid + i * nthr;
-      const int key = piece_key(i, kb64);
-      int64_t off;
-      if (i * nthr < KPB) {
-        const int pc = p % KP;
-        if constexpr (PAGED) {
-          const bool ok = (uint32_t)pg[i] < (uint32_t)kv.n_pages;
-          bad |= !ok;
-          off = ((((int64_t)(ok ? pg[i] : 0) * kv.n_kv_heads + kvh) << sh) + (key & (pt - 1))) * DH + pc * 8;
-        } else {
-          off = ((int64_t)kvh * kv.tpad + pcol + key) * DH + pc * 8;
-        }
-        reg[i] = *(const u32x4*)(kslab + off);
-      } else {
-        const int ch = (p - KPB) >> 3;
-        if constexpr (PAGED) {
-          const bool ok = (uint32_t)pg[i] < (uint32_t)kv.n_pages;
-          bad |= !ok;
-          vbad |= ok ? 0u : (1u << i);
-          off = ((((int64_t)(ok ? pg[i] : 0) * kv.n_kv_heads + kvh) * DH + ch) << sh) + (key & (pt - 1));
-        } else {
-          off = ((int64_t)kvh * DH + ch) * kv.tpad + pcol + key;
-        }
-        reg[i] = *(const u32x4*)(vslab + off);
-      }
-    }
-  };
-  // V^T elements of keys beyond the sequence (or of a page that is not addressable) become zero
-  // here: their probability is zero, and zero times whatever the pool holds there must stay zero
-  auto commit = [&](const u32x4 (&reg)[MAXP], int buf, int kb64, uint32_t vbad) {
-    u32x4* dk = &sk[buf][0][0][0][0];
-    u32x4* dv = &sv[buf][0][0][0];
-    const bool fix = (kb64 << 6) + 64 > kv_len || __builtin_amdgcn_ballot_w64(vbad != 0) != 0;
-#pragma unroll
-    for (int i = 0; i < MAXP; ++i) {
-      const int p = tid + i * nthr;
-      if (i * nthr < KPB) {
-        const int r = p / KP, pc = p - r * KP;
-        const int half = r >> 5, r32 = r & 31, aa = r32 >> 3, bb = r32 & 7;
-        const int tt = bb >> 2, cc = 4 * aa + (bb & 3);         // key 8a+b of a half sits in tile b/4, row 4a + b%4
-        dk[(((half * 2 + tt) * KK + (pc >> 2)) * 64) + (pc & 3) * 16 + (cc ^ (4 * (pc & 3)) ^ (pc >> 2))] = reg[i];
-      } else {
-        const int q = p - KPB, ch = q >> 3, kg = q & 7;
-        u32x4 v = reg[i];
-        if (fix) {                                              // only a sequence's last block, or a bad page
-          int valid = kv_len - ((kb64 << 6) + kg * 8);          // elements of this piece inside the sequence
-          if (vbad & (1u << i)) valid = 0;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            uint32_t x = v[e];
-            x = valid > 2 * e + 1 ? x : (x & 0x0000ffffu);
-            x = valid > 2 * e ? x : 0u;
-            v[e] = x;
-          }
-        }
-        dv[(((kg >> 2) * DT + (ch >> 4)) * 64) + (kg & 3) * 16 + ((ch & 15) ^ (4 * (kg & 3)) ^ (2 * (kg >> 2)))] = v;
-      }
-    }
-  };
-
-  f32x4 oacc[DT][QT];
-#pragma unroll
-  for (int d = 0; d < DT; ++d)
-#pragma unroll
-    for (int t = 0; t < QT; ++t) oacc[d][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run[QT], l_run[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) { m_run[t] = -DEV_INF; l_run[t] = 0.f; }
-
-  // One 64-key block.  The waves of a workgroup leave the block's barrier in the same phase, so the
-  // pipes (LDS, matrix, vector) only overlap where one wave's instruction order lets them: all K
-  // fragments of the block are requested first, the scores of both 32-key halves are issued back to
-  // back, and each half's V^T fragments are requested before its softmax (vector arithmetic, no LDS: its
-  // reductions are row swaps), which runs while the matrix pipe still works on the other half.  A half beyond the sequence is multiplied like any
-  // other: its scores are masked to -inf (the running maximum is finite after the first half) and its
-  // V^T columns are zero in LDS.
-  auto compute = [&](int buf, int kb64) {
-    const int k0 = kb64 << 6;
-    const int lk = lane ^ (4 * g);
-    u32x4 kf[2][2][KK];
-#pragma unroll
-    for (int half = 0; half < 2; ++half)
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) kf[half][tt][kk] = sk[buf][half][tt][kk][lk ^ kk];
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 s[2][2][QT];
-#pragma unroll
-    for (int half = 0; half < 2; ++half)
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-#pragma unroll
-        for (int t = 0; t < QT; ++t) s[half][tt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-          for (int t = 0; t < QT; ++t) s[half][tt][t] = mfma16(kf[half][tt][kk], qf[t][kk], s[half][tt][t]);
-      }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      u32x4 vf[DT];
-#pragma unroll
-      for (int d = 0; d < DT; ++d) vf[d] = sv[buf][half][d][lk ^ (2 * half)];
-      __builtin_amdgcn_sched_barrier(0);
-      u32x4 pf[QT], pl[QT];
-      attn_softmax_block<DT, QT>(s[half], k0 + half * 32, kv_len, g, a.scale_log2, m_run, l_run, oacc, pf, pl);
-#pragma unroll
-      for (int d = 0; d < DT; ++d) {
-#pragma unroll
-        for (int t = 0; t < QT; ++t) oacc[d][t] = mfma16(vf[d], pf[t], oacc[d][t]);
-#pragma unroll
-        for (int t = 0; t < QT; ++t) oacc[d][t] = mfma16(vf[d], pl[t], oacc[d][t]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  const int nkb = (kv_len + 63) >> 6;
-  if (unit < nkb) {
-    const int last = unit + ((nkb - 1 - unit) / a.n_units) * a.n_units;
-    u32x4 reg[MAXP];
-    int pg[MAXP];
-    uint32_t vbad;
-    fetch_pages(pg, unit);
-    issue(reg, pg, unit, vbad);
-    {
-      const int nxt = unit + a.n_units;
-      fetch_pages(pg, nxt <= last ? nxt : last);
-    }
-    commit(reg, 0, unit, vbad);
-    int buf = 0;
-    for (int kb = unit; kb < nkb; kb += a.n_units) {
-      __syncthreads();
-      int nxt = kb + a.n_units;
-      nxt = nxt <= last ? nxt : last;
-      int nxt2 = nxt + a.n_units;
-      nxt2 = nxt2 <= last ? nxt2 : last;
-      issue(reg, pg, nxt, vbad);          // its page ids arrived during the previous block
-      fetch_pages(pg, nxt2);
-      if (active) compute(buf, kb);
-      commit(reg, buf ^ 1, nxt, vbad);
-      buf ^= 1;
-    }
-  }
-
-  if (active) {
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      float l = l_run[t];
-      l += __shfl_xor(l, 16, 64);
-      l += __shfl_xor(l, 32, 64);
-      if (row_out[t] < 0) continue;
-      if (a.n_units == 1) {
-        const float inv = l > 0.f ? 1.0f / l : 0.f;
-        const int64_t ro = row_out[t];
-        const int tok = (int)(ro / a.Hq), head = (int)(ro - (int64_t)tok * a.Hq);
-#pragma unroll
-        for (int d = 0; d < DT; ++d) {
-          const int ch = d * 16 + 4 * g;
-          const int64_t at = a.out_mt > 0 ? frag_offset(tok, head * DH + ch, a.out_mt) : ro * DH + ch;
-          *(uint2*)(a.o + at) = make_uint2(
-              (uint32_t)f32_to_bf16(oacc[d][t][0] * inv) | ((uint32_t)f32_to_bf16(oacc[d][t][1] * inv) << 16),
-              (uint32_t)f32_to_bf16(oacc[d][t][2] * inv) | ((uint32_t)f32_to_bf16(oacc[d][t][3] * inv) << 16));
-        }
-        continue;
-      }
-      const int64_t slot = row_out[t] * a.n_units + unit;
-      float* po = a.part_o + slot * DH + 4 * g;
-#pragma unroll
-      for (int d = 0; d < DT; ++d) *(f32x4*)(po + d * 16) = oacc[d][t];
-      if (g == 0) { a.part_ml[slot * 2] = m_run[t]; a.part_ml[slot * 2 + 1] = l; }
-    }
-  }
-  if (bad) atomicOr(a.status, DLLM_STATUS_BAD_PAGE);
-}
-
-// ------------------------------------------------------------------------------------------
-// The staged attention with the K and V^T blocks copied from memory straight into LDS (no register pass,
-// no LDS stores from registers - those cost bank conflicts whatever the layout - and no registers held
-// for data in flight).  A 64-key block is NF one-KiB operand fragments (lane l's 16 bytes at byte 16 l);
-// one copy instruction of a wave fills one fragment, each lane fetching the 16 bytes its slot holds: for
-// a K fragment (half, tile tt, k-step kk) row 8(c/4) + c%4 + 4tt of the half, bytes 64 kk + 16 g ..,
-// for a V^T fragment (half, channel tile d) channel 16 d + c, keys 8g .. 8g+7 of the half (c = l%16,
-// g = l/16).  NB buffers form a ring with NB-1 blocks in flight; the only wait on memory is "the block
-// about to be multiplied has landed", once per block, before the barrier that also frees the oldest
-// buffer.  Needs blocks that never straddle a page (page size a multiple of 64) or the packed scratch.
-// The page ids of the sequence are copied into LDS once; rows of a block past the sequence end are read
-// as they lie in the page (or workspace) and the V^T columns of such keys are zeroed in LDS before use,
-// as are those of a block whose page id is not addressable.
+// The same attention for many query rows per KV head (grouped-query models at large batch, and every no-cache
+// forward).  The eight waves of a workgroup are row groups of 32 query rows that all need the same keys, so each 64-key
+// block of K and V^T is copied from memory into LDS once per workgroup, straight (no register pass).
+//
+// A block is 64 K rows and DH V^T rows of 64 keys, row-major; one copy instruction of a wave fills one KiB of whole
+// 128-byte lines, its 16-byte pieces xor-ed with the row so that the 16 lanes an LDS read serves at a time touch every
+// bank once.  NB = 4 buffers form a ring: two blocks are in flight while the products read three (below); the only
+// wait on memory is "the next block has landed", once per block, together with the barrier that frees the oldest
+// buffer.  The page ids of the sequence lie in LDS; keys past the sequence end are read as they lie in the page (or
+// workspace), their scores are masked and their V^T columns zeroed in LDS before use, as are those of keys whose page
+// id is not addressable.
+//
+// What bounds it: a 32-key half costs a wave 24 products of 32 x 32 x 16 (8 of scores, 16 of V^T P^T: P enters as a
+// bfloat16 pair hi + lo) = 768 cycles of its SIMD's matrix pipe and about 600 cycles of vector work (16 exponentials
+// of 8 cycles, the pair split).  Run one behind the other they add up, and the waves leave each barrier in the same
+// phase: the kernel that did so took 2.3 times the products' time.  Here every wave runs them side by side: while it
+// takes the exponentials of half u, its matrix instructions are the scores of half u+1 and V^T P^T of half u-1, one
+// product and a few vector instructions in turn (sched_barrier keeps the order), LDS reads 4 .. 8 products ahead.
+// (us, the kernel before it with 16 x 16 x 32 products / this one: 32 sequences of up to 8192 keys, 4 key heads of 7 x 32
+// rows 219 / 191; 8 prompts of up to 2048 tokens, 4 key heads 902 / 665; 1184 tokens, 32 heads 75 / 67.  The chip's clock
+// follows the products' power: 24 of them on random operands, with as many vector instructions as here between them,
+// take two waves of a SIMD 0.94 us, on zeros 0.70.)
+//
+// 32 x 32 x 16 layouts (lane l, r = l % 32, h = l / 32): A holds row r, B column r, each the 8 k-elements 8h .. 8h+7;
+// D holds column r, rows (e/4)*8 + 4h + e%4.  A row r of a score product is given key 16(r/16) + 8(r/4%2) + 4(r/8%2)
+// + r%4 of the half, so that registers 8s .. 8s+7 of D are keys 16s + 8h .. +7 of the lane's query: the B operand of
+// step s of V^T P^T as it stands.
+//
+// The running maximum (log2 units) is an integer and moves only when a score exceeds it by more than DL_SLACK: weights
+// reach 2^DL_SLACK, which neither the float sums nor the bfloat16 pairs mind, and the accumulators, the sums and the
+// weights that still wait for their product are then scaled by a power of two, which is exact.
 #define DL_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
-template <int DH, int NW, bool PAGED>
-__global__ __launch_bounds__(NW * 64) void k_attn_dl(const AttnArgs a) {
-  constexpr int KK = DH / 32, DT = DH / 16, QT = 2;
-  constexpr int NB = NW >= 8 ? 3 : 2;
-  constexpr int NKF = 4 * KK, NVF = 2 * DT, NF = NKF + NVF, FPW = NF / NW;
-  static_assert(NF % NW == 0 && NKF % FPW == 0, "a wave's i-th fragment is K for all of a wave or V^T for all");
-  constexpr int BLK = NF * 1024, nthr = NW * 64;
+constexpr float DL_SLACK = 8.0f;
+// the value is computed here: neither earlier nor where it is used
+template <typename T>
+__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
+template <typename T, typename U>
+__device__ __forceinline__ void pin(T& x, U& y) { asm volatile("" : "+v"(x), "+v"(y)); }
+constexpr int DL_NB = 4;
+// PG: 0 packed scratch; 1 paged, a 64-key block lies inside a page; 2 paged, smaller pages (a power of two of at least 8)
+template <int DH, int PG>
+__device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
+  constexpr int KK = DH / 16, DT = DH / 32, NM = KK + 4 * DT;   // score steps, channel tiles, products per half
+  constexpr int NB = DL_NB, NW = 8;
+  constexpr int NKF = DH / 8, NVF = DH / 8, NF = NKF + NVF, FPW = NF / NW;   // KiB of K, of V^T; copies of a wave
+  static_assert(NKF % FPW == 0, "a wave's copies are K for all of a wave or V^T for all");
+  constexpr int BLK = NF * 1024, nthr = NW * 64, KROW = DH * 2;
   extern __shared__ __attribute__((aligned(1024))) unsigned char dl_smem[];
   int32_t* s_pg = (int32_t*)(dl_smem + NB * BLK);
   const int tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
-  const int c = lane & 15, g = lane >> 4;
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 31, h = lane >> 5;
   const int rg = blockIdx.y * a.n_rg_wg + w;
   const int unit = blockIdx.x;
   const int b = blockIdx.z / a.Hkv, kvh = blockIdx.z - b * a.Hkv;
   const int G = a.Hq / a.Hkv;
-  const int row_base = PAGED ? b * a.Q : a.cu[b];
-  const int n_q = PAGED ? a.Q : a.cu[b + 1] - a.cu[b];
+  const int row_base = PG ? b * a.Q : a.cu[b];
+  const int n_q = PG ? a.Q : a.cu[b + 1] - a.cu[b];
   const int R = n_q * G;
-  const int kv_len = PAGED ? a.prefix_len[b] + (a.q_valid ? min(max(a.q_valid[b], 0), a.Q) : a.Q) : n_q;
-  const bool active = w < a.n_rg_wg && rg * 16 * QT < R;     // waves beyond the rows only help loading
-  if (blockIdx.y * a.n_rg_wg * 16 * QT >= R) return;         // whole workgroup beyond this sequence's rows
-  if (PAGED && a.q_valid && a.q_valid[b] < 0) return;        // the sequence is not part of this call
+  const int kv_len = PG ? a.prefix_len[b] + (a.q_valid ? min(max(a.q_valid[b], 0), a.Q) : a.Q) : n_q;
+  const bool active = w < a.n_rg_wg && rg * 32 < R;   // waves beyond the rows only help loading
+  if (blockIdx.y * a.n_rg_wg * 32 >= R) return;              // whole workgroup beyond this sequence's rows
+  if (PG && a.q_valid && a.q_valid[b] < 0) return;           // the sequence is not part of this call
   const KVView& kv = a.kv;
   const int sh = a.pt_shift, pt = 1 << sh;
   const bf16_t* kslab = (const bf16_t*)kv.k;
   const bf16_t* vslab = (const bf16_t*)kv.v;
-  const int64_t pcol = PAGED ? 0 : kv.cu_pad[b];
-  bool bad = false;
+  const int64_t pcol = PG ? 0 : kv.cu_pad[b];
+  uint32_t bad = 0;
   const int nkb = (kv_len + 63) >> 6;
 
   int np = 0;
-  if constexpr (PAGED) {
+  const int32_t* const table = PG ? kv.table + (int64_t)b * kv.max_pages : nullptr;
+  if constexpr (PG != 0) {
     np = (kv_len + pt - 1) >> sh;
     np = np < a.pg_cap ? np : a.pg_cap;
     np = np < kv.max_pages ? np : kv.max_pages;
-    const int32_t* table = kv.table + (int64_t)b * kv.max_pages;
-    for (int i = tid; i < np; i += nthr) s_pg[i] = table[i];
   }
 
-  u32x4 qf[QT][KK];
-  int64_t row_out[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    int r = rg * 16 * QT + t * 16 + c;
-    const bool ok = active && r < R;
-    if (!ok) r = 0;
-    const int hg = r / n_q, j = r - hg * n_q;
-    const int64_t ro = (int64_t)(row_base + j) * a.Hq + kvh * G + hg;
-    row_out[t] = ok ? ro : -1;
-    const bf16_t* qp = a.q + ro * DH + g * 8;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[t][kk] = *(const u32x4*)(qp + kk * 32);
-  }
-  __syncthreads();                                            // page ids are in LDS (and the q loads have landed)
-
-  // this lane's source offsets (elements from the block's K or V^T base) for the wave's FPW fragments
-  int foff[FPW];
+  // this lane's source offsets (bytes from the block's K or V^T base) for the wave's copies; with small pages the
+  // key (from the block's first) and the offset from its page's K row or V^T column
+  const bool wave_k = w * FPW < NKF;
+  int foff[FPW], fkey[PG == 2 ? FPW : 1];
 #pragma unroll
   for (int i = 0; i < FPW; ++i) {
     const int f = w * FPW + i;
+    int key, off;
     if (f < NKF) {
-      const int half = f / (2 * KK), tt = (f / KK) & 1, kk = f % KK;
-      foff[i] = (half * 32 + 8 * (c >> 2) + (c & 3) + 4 * tt) * DH + (kk * 4 + g) * 8;
+      constexpr int PR = DH / 8;                              // 16-byte pieces of a K row
+      key = f * (64 / PR) + lane / PR;
+      const int swz = DH == 128 ? key & 15 : (key >> 1) & 7;
+      off = (PG == 2 ? 0 : key * DH) + (((lane % PR) ^ swz) * 8);
     } else {
-      const int fv = f - NKF, half = fv / DT, d = fv % DT;
-      foff[i] = (d * 16 + c) * (PAGED ? pt : kv.tpad) + half * 32 + g * 8;
+      const int ch = (f - NKF) * 8 + (lane >> 3);
+      key = ((lane & 7) ^ ((ch >> 1) & 7)) * 8;
+      off = ch * (PG ? pt : kv.tpad) + (PG == 2 ? 0 : key);
     }
+    foff[i] = PG == 2 ? off : off * 2;                        // (small pages: elements)
+    if constexpr (PG == 2) fkey[i] = key;
   }
-  const bool wave_k = w * FPW < NKF;
-  uint32_t badbuf = 0;                                        // buffers whose block came from a page id out of range
+  uint32_t badbuf = 0;                                        // buffers with keys from a page id out of range
   auto page_of = [&](int kb64) -> int {
-    if constexpr (!PAGED) return 0;
+    if constexpr (PG != 1) return 0;
     const int pi = (kb64 << 6) >> sh;
     return pi < np ? s_pg[pi] : -1;
   };
-  auto issue = [&](int kb64, int buf, int page_v) {
+  // The block being copied, as a descriptor that ends with it.  (The form of the copies that goes through a flat address
+  // makes the compiler wait for all LDS reads wherever it waits for one; small pages, whose keys lie wherever their page
+  // does, have only that.)
+  const bf16_t* src = nullptr;
+  __amdgpu_buffer_rsrc_t rsrc;
+  auto copy_base = [&](int kb64, int buf, int page_v) {
     const int k0 = kb64 << 6;
     int64_t kb, vb;
-    if constexpr (PAGED) {
+    if constexpr (PG == 1) {
       const int page = __builtin_amdgcn_readfirstlane(page_v);
       const bool ok = (uint32_t)page < (uint32_t)kv.n_pages;
-      bad |= !ok;
-      badbuf = ok ? (badbuf & ~(1u << buf)) : (badbuf | (1u << buf));
+      const uint32_t miss = ok ? 0u : 1u;
+      bad |= miss;
+      badbuf = (badbuf & ~(1u << buf)) | (miss << buf);
       const int64_t rows = (((int64_t)(ok ? page : 0) * kv.n_kv_heads + kvh) << sh);
       kb = (rows + (k0 & (pt - 1))) * DH;
       vb = rows * DH + (k0 & (pt - 1));
-    } else {
+    } else if constexpr (PG == 0) {
       kb = ((int64_t)kvh * kv.tpad + pcol + k0) * DH;
       vb = (int64_t)kvh * DH * kv.tpad + pcol + k0;
+    } else {
+      kb = vb = 0;
+      badbuf &= ~(1u << buf);
     }
-    const bf16_t* src = wave_k ? kslab + kb : vslab + vb;
-    unsigned char* dst = dl_smem + buf * BLK + w * FPW * 1024;
+    if constexpr (PG == 2) src = wave_k ? kslab : vslab;
+    else {
+      const int bytes = wave_k ? 64 * KROW : ((DH - 1) * (PG ? pt : kv.tpad) + 64) * 2;
+      rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(wave_k ? kslab + kb : vslab + vb), 0, bytes, 0x00020000);
+    }
+  };
+  auto copy = [&](int kb64, int buf, int i) {
+    void* const dst = dl_smem + buf * BLK + (w * FPW + i) * 1024;
+    if constexpr (PG == 2) {
+      const int key = (kb64 << 6) + fkey[i], pi = key >> sh;
+      const int page = s_pg[pi < np ? pi : 0];
+      const bool ok = pi < np && (uint32_t)page < (uint32_t)kv.n_pages;
+      if (!ok && key < kv_len) { bad = 1; badbuf |= 1u << buf; }
+      const int64_t rows = (((int64_t)(ok ? page : 0) * kv.n_kv_heads + kvh) << sh);
+      const bf16_t* p = src + rows * DH + (wave_k ? (key & (pt - 1)) * DH : (key & (pt - 1))) + foff[i];
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    } else {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, foff[i], 0, 0, 0);
+    }
+  };
+  const int last = unit < nkb ? unit + ((nkb - 1 - unit) / a.n_units) * a.n_units : unit;
+  auto clampb = [&](int kb) { return kb <= last ? kb : last; };
+  // the ring's first blocks (past the end: repeats of the last block into buffers nobody reads); their page ids come
+  // straight from the table, so that the copies are on their way before anything else is waited for
+  auto first_blocks = [&]() {
 #pragma unroll
-    for (int i = 0; i < FPW; ++i)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + foff[i]),
-                                       (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, 0, 0);
+    for (int j = 0; j < NB - 1; ++j) {
+      const int kb = clampb(unit + j * a.n_units), pi = (kb << 6) >> sh;
+      copy_base(kb, j, PG == 1 && pi < np ? table[pi] : -1);
+#pragma unroll
+      for (int i = 0; i < FPW; ++i) copy(kb, j, i);
+    }
+  };
+  if (PG != 2 && unit < nkb) first_blocks();
+  if constexpr (PG != 0)
+    for (int i = tid; i < np; i += nthr) s_pg[i] = table[i];
+
+  u32x4 qf[KK];               // B operand: column r = the lane's query
+  int64_t row_out;            // its (token * Hq + head), -1 if beyond R
+  {
+    int rr = rg * 32 + r;
+    const bool ok = active && rr < R;
+    if (!ok) rr = 0;
+    const int hg = rr / n_q, j = rr - hg * n_q;
+    const int64_t ro = (int64_t)(row_base + j) * a.Hq + kvh * G + hg;
+    row_out = ok ? ro : -1;
+    const bf16_t* qp = a.q + ro * DH + h * 8;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) qf[kk] = *(const u32x4*)(qp + kk * 16);
+  }
+  // the buffer in front of block 0 stands for the half in front of the first: its weights are zero, its V^T as well
+  {
+    u32x4* vb = (u32x4*)(dl_smem + (NB - 1) * BLK + NKF * 1024);
+    for (int q = tid; q < NVF * 64; q += nthr) vb[q] = u32x4{0, 0, 0, 0};
+  }
+  __syncthreads();                                            // page ids are in LDS
+
+  // zeroes the V^T columns of keys past the sequence end and of keys without a page
+  auto fix_tail = [&](int kb64, int buf) {
+    bool any = (kb64 << 6) + 64 > kv_len;
+    if constexpr (PG == 1) any |= (badbuf >> buf) & 1u;
+    if constexpr (PG == 2) {
+      for (int p = (kb64 << 6) >> sh; p <= ((kb64 << 6) + 63) >> sh; ++p) any |= p >= np || (uint32_t)s_pg[p] >= (uint32_t)kv.n_pages;
+    }
+    if (!any) return;
+    u32x4* vb = (u32x4*)(dl_smem + buf * BLK + NKF * 1024);
+    for (int q = tid; q < NVF * 64; q += nthr) {
+      const int key = (kb64 << 6) + ((q & 7) ^ ((q >> 4) & 7)) * 8;
+      int valid = kv_len - key;
+      if constexpr (PG == 1) valid = ((badbuf >> buf) & 1u) ? 0 : valid;
+      if constexpr (PG == 2) {
+        const int pi = key >> sh;
+        if (pi >= np || (uint32_t)s_pg[pi] >= (uint32_t)kv.n_pages) valid = 0;
+      }
+      if (valid < 8) {
+        u32x4 v = vb[q];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          uint32_t x = v[e];
+          x = valid > 2 * e + 1 ? x : (x & 0x0000ffffu);
+          x = valid > 2 * e ? x : 0u;
+          v[e] = x;
+        }
+        vb[q] = v;
+      }
+    }
   };
 
-  f32x4 oacc[DT][QT];
+  f32x16 oacc[DT];
 #pragma unroll
   for (int d = 0; d < DT; ++d)
 #pragma unroll
-    for (int t = 0; t < QT; ++t) oacc[d][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run[QT], l_run[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) { m_run[t] = -DEV_INF; l_run[t] = 0.f; }
+    for (int e = 0; e < 16; ++e) oacc[d][e] = 0.f;
+  float m_run = -DEV_INF, l_run = 0.f, l_odd = 0.f;
+  const float scl = a.scale_log2;
 
-  // One 64-key block; the instruction order lets one wave's LDS reads, matrix and vector work overlap
-  // (the waves of a workgroup leave the barrier in the same phase): all K fragments are requested first,
-  // the scores of both halves issued back to back, each half's V^T fragments requested before its
-  // softmax (no LDS traffic: its reductions are row swaps), which runs while the matrix pipe still works.
-  auto compute = [&](int buf, int kb64) {
-    const int k0 = kb64 << 6;
-    const u32x4* fk = (const u32x4*)(dl_smem + buf * BLK) + lane;
-    const u32x4* fv = fk + NKF * 64;
-    u32x4 kf[2][2][KK];
+  struct Wts { u32x4 hi[2], lo[2]; };                         // weights of a half: B operands of its two steps
+  f32x16 sc, sn;                                              // scores of the current half, of the next
+  Wts pa, pb;
+  u32x4 kf[4], v0[DT], v1[DT];
+  int ka[KK], va[4];                                          // LDS addresses: K by step, V^T by 16-key step of the block
+  // key of score row r, and the swizzle of its LDS row
+  const int kr = 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3);
+  const int k_lane = kr * KROW + ((h ^ (DH == 128 ? kr & 15 : (kr >> 1) & 7)) * 16);
+  const int v_lane = NKF * 1024 + r * 128 + ((h ^ ((r >> 1) & 7)) * 16);
+  // (addresses in LDS as such: with an offset to dl_smem every read adds it)
+  typedef __attribute__((address_space(3))) unsigned char lds_u8;
+  const int lds0 = (int)(uintptr_t)(lds_u8*)dl_smem;
+  auto k_addr = [&](int buf) {
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
+    for (int kk = 0; kk < KK; ++kk) ka[kk] = (lds0 + buf * BLK + k_lane) ^ (kk * 32);
+  };
+  auto v_addr = [&](int buf) {
 #pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
+    for (int x = 0; x < 4; ++x) va[x] = (lds0 + buf * BLK + v_lane) ^ (x * 32);
+  };
+  auto rd = [&](int at) -> u32x4 { return *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(uint32_t)at; };
+  auto mm = [&](u32x4 x, u32x4 y, f32x16 c) -> f32x16 {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
+  };
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  // in front of half k0's exponentials: mask, and now and then the new scale (mx: the scores' maximum, one per half wave)
+  auto settle = [&](f32x16& s, float mx, int k0, Wts& open) {
+    if (k0 + 32 > kv_len) {                               // only a sequence's last block has keys to mask
+      mx = -DEV_INF;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) kf[half][tt][kk] = fk[((half * 2 + tt) * KK + kk) * 64];
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 s[2][2][QT];
-#pragma unroll
-    for (int half = 0; half < 2; ++half)
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-#pragma unroll
-        for (int t = 0; t < QT; ++t) s[half][tt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-          for (int t = 0; t < QT; ++t) s[half][tt][t] = mfma16(kf[half][tt][kk], qf[t][kk], s[half][tt][t]);
+      for (int e = 0; e < 16; ++e) {
+        if (k0 + 16 * (e >> 3) + 8 * h + (e & 7) >= kv_len) s[e] = -DEV_INF;
+        mx = fmaxf(mx, s[e]);
       }
-    __builtin_amdgcn_sched_barrier(0);
+    }
+    const uint32_t mi = __float_as_uint(mx);
+    const u32x2_t sw = __builtin_amdgcn_permlane32_swap(mi, mi, false, false);
+    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scl;
+    if (__builtin_amdgcn_ballot_w64(mx > m_run + DL_SLACK) != 0) {
+      const float m_new = fmaxf(m_run, ceilf(mx));
+      const float f = __builtin_amdgcn_ldexpf(1.0f, (int)fmaxf(m_run - m_new, -200.0f));
+      m_run = m_new;
+      l_run *= f;
+      l_odd *= f;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      u32x4 vf[DT];
+      for (int d = 0; d < DT; ++d)
 #pragma unroll
-      for (int d = 0; d < DT; ++d) vf[d] = fv[(half * DT + d) * 64];
-      __builtin_amdgcn_sched_barrier(0);
-      u32x4 pf[QT], pl[QT];
-      attn_softmax_block<DT, QT>(s[half], k0 + half * 32, kv_len, g, a.scale_log2, m_run, l_run, oacc, pf, pl);
+        for (int e = 0; e < 16; ++e) oacc[d][e] *= f;
+      auto scale2 = [&](uint32_t v) -> uint32_t {
+        return (__float_as_uint(__uint_as_float(v << 16) * f) >> 16) | (__float_as_uint(__uint_as_float(v & 0xffff0000u) * f) & 0xffff0000u);
+      };
 #pragma unroll
-      for (int d = 0; d < DT; ++d) {
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int t = 0; t < QT; ++t) oacc[d][t] = mfma16(vf[d], pf[t], oacc[d][t]);
-#pragma unroll
-        for (int t = 0; t < QT; ++t) oacc[d][t] = mfma16(vf[d], pl[t], oacc[d][t]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+        for (int e = 0; e < 4; ++e) { open.hi[x][e] = scale2(open.hi[x][e]); open.lo[x][e] = scale2(open.lo[x][e]); }
     }
   };
+  // One half: the exponentials of s -> pn beside the scores of the next half (K fragments at ka + HN, four of them read)
+  // -> so and V^T P^T of the one before (po; V^T steps 2*HP, 2*HP+1 of the block at va, the first one's fragments read).
+  // `mid` runs behind product 2*KK - 1; behind it the fragments that the next call starts with are read: K half HN2,
+  // V^T step 2*HP2.  tail(i), i < FPW: copies in the remaining places.
+  auto half_step = [&](auto hn_, auto hp_, auto hn2_, auto hp2_, f32x16& s, f32x16& so, Wts& pn, const Wts& po, auto&& mid, auto&& tail) {
+    constexpr int HN = decltype(hn_)::value, HP = decltype(hp_)::value, HN2 = decltype(hn2_)::value, HP2 = decltype(hp2_)::value;
+    // 24 steps, three per pair of scores, about five instruction slots each.  (pin: sched_barrier does not hold plain
+    // arithmetic in its place; nothing reads the weights before the next half, so all of it would move there.)
+    float x0 = 0.f, x1 = 0.f, e0 = 0.f, e1 = 0.f, g0 = 0.f, g1 = 0.f;
+    uint32_t hi = 0;
+    auto vec = [&](int st) {
+      const int i = st / 3, ph = st % 3;
+      if (ph == 0) {
+        pin(s);
+        x0 = fmaf(s[2 * i], scl, -m_run);
+        x1 = fmaf(s[2 * i + 1], scl, -m_run);
+      }
+      if (ph == 1) {
+        pin(x0, x1);
+        e0 = __builtin_amdgcn_exp2f(x0);
+        e1 = __builtin_amdgcn_exp2f(x1);
+      }
+      if (ph == 2) {
+        pin(e0, e1);
+        l_run += e0;
+        l_odd += e1;
+        pin(l_run, l_odd);
+        hi = pack_bf16x2(e0, e1);
+        g0 = e0; g1 = e1;
+        pn.hi[i >> 2][i & 3] = hi;
+      }
+      // the pair before: what its first bfloat16 numbers leave
+      if ((ph == 0 && i > 0) || st == 23) {
+        const int q = st == 23 ? 7 : i - 1;
+        pin(hi);
+        uint32_t lo = pack_bf16x2(g0 - __uint_as_float(hi << 16), g1 - __uint_as_float(hi & 0xffff0000u));
+        pin(lo);
+        pn.lo[q >> 2][q & 3] = lo;
+      }
+    };
+    // the maximum of the next half's scores, in the last products' places
+    float t0 = 0.f, t1 = 0.f, t2 = 0.f, t3 = 0.f;
+    auto top = [&](int st) {
+      auto max3 = [](float a, float b, float c) { return fmaxf(fmaxf(a, b), c); };
+      if (st == 0) { pin(so); t0 = max3(so[0], so[1], so[2]); t1 = max3(so[3], so[4], so[5]); }
+      if (st == 1) { pin(t1); t2 = max3(so[6], so[7], so[8]); t3 = max3(so[9], so[10], so[11]); }
+      if (st == 2) { pin(t2); t0 = max3(t0, t1, t2); t3 = max3(t3, so[12], so[13]); }
+      if (st == 3) { pin(t3); t3 = max3(t3, so[14], so[15]); pin(t3); }
+      if (st == 4) { t0 = fmaxf(t0, t3); pin(t0); }
+    };
+#pragma unroll
+    for (int idx = 0; idx < NM; ++idx) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (idx < 2 * KK && (idx & 1) == 0) {
+        const int kk = idx / 2;
+        so = mm(kf[kk & 3], qf[kk], kk == 0 ? zero16 : so);
+      } else {
+        const int j = idx < 2 * KK ? idx / 2 : idx - KK, x = j / (2 * DT), lo = (j / DT) & 1, d = j % DT;
+        oacc[d] = mm(x ? v1[d] : v0[d], lo ? po.lo[x] : po.hi[x], oacc[d]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int st = 0; st < 24; ++st)
+        if (st * NM / 24 == idx) vec(st);
+#pragma unroll
+      for (int st = 0; st < 5; ++st)
+        if (2 * KK + (NM - 2 * KK) / 4 + st * (NM - 2 * KK) / 8 == idx) top(st);
+      // reads: K fragments 4 .. of this half into the places just used, V^T of the second step
+      if (idx < 2 * KK && (idx & 1) == 0 && idx / 2 + 4 < KK) kf[(idx / 2) & 3] = rd(ka[(idx / 2 + 4) % KK] + HN * 32 * KROW);
+      if (idx >= KK && idx < KK + DT) v1[idx - KK] = rd(va[2 * HP + 1] + (idx - KK) * 4096);
+      if (idx == 2 * KK - 1) mid();
+      if (idx >= 2 * KK) {
+        constexpr int NR = 4 + DT, SL = NM - 2 * KK;
+#pragma unroll
+        for (int n = 0; n < NR; ++n)
+          if (2 * KK + n * SL / NR == idx) {
+            const int q = n / 2;
+            if (n < 2 * DT && (n & 1)) v0[q % DT] = rd(va[2 * HP2] + (q % DT) * 4096);
+            else { const int k2 = n < 2 * DT ? q : n - DT; kf[k2 & 3] = rd(ka[k2 % KK] + HN2 * 32 * KROW); }
+          }
+#pragma unroll
+        for (int i = 0; i < FPW; ++i)
+          if (2 * KK + i * SL / FPW == idx) tail(i);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    return t0;
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
 
   if (unit < nkb) {          // (a unit without keys still writes its empty partial below)
-    const int last = unit + ((nkb - 1 - unit) / a.n_units) * a.n_units;
-    auto clampb = [&](int kb) { return kb <= last ? kb : last; };
-    // the ring's first NB-1 blocks (past the end: repeats of the last block into buffers nobody reads)
-#pragma unroll
-    for (int j = 0; j < NB - 1; ++j) {
-      const int kb = clampb(unit + j * a.n_units);
-      issue(kb, j, page_of(kb));
-    }
+    if (PG == 2) first_blocks();
     int pg_next = page_of(clampb(unit + (NB - 1) * a.n_units));
+    // the first block has landed; with everything in front of it (PG 2), or with the q loads that were issued behind it
+    if constexpr (PG == 2) __builtin_amdgcn_s_waitcnt(DL_VMCNT(2 * FPW));
+    else __builtin_amdgcn_s_waitcnt(DL_VMCNT(0));
+    __builtin_amdgcn_s_barrier();
+    fix_tail(unit, 0);        // read behind the barrier inside the loop
     int buf = 0;
-    for (int kb = unit; kb < nkb; kb += a.n_units) {
-      // (the count is exact only while the loop issues no other vector memory instruction: no spills to scratch,
-      // which the build's resource report shows)
-      __builtin_amdgcn_s_waitcnt(DL_VMCNT((NB - 2) * FPW));   // this wave's copies of block kb have landed
-      __builtin_amdgcn_s_barrier();                            // everybody's have; the previous block's buffer is free
-      const int nbuf = buf == 0 ? NB - 1 : buf - 1;            // (buf + NB - 1) % NB: the buffer of the block before
-      const int kn = clampb(kb + (NB - 1) * a.n_units);
-      issue(kn, nbuf, pg_next);
-      pg_next = page_of(clampb(kb + NB * a.n_units));
-      if ((kb << 6) + 64 > kv_len || ((badbuf >> buf) & 1u)) {
-        // zero the V^T columns of keys past the sequence end (all keys of a block without a page)
-        const bool nopage = (badbuf >> buf) & 1u;
-        u32x4* vb = (u32x4*)(dl_smem + buf * BLK + NKF * 1024);
-        for (int q = tid; q < NVF * 64; q += nthr) {
-          const int half = (q >> 6) / DT, gg = (q & 63) >> 4;
-          const int valid = nopage ? 0 : kv_len - ((kb << 6) + half * 32 + gg * 8);
-          if (valid < 8) {
-            u32x4 v = vb[q];
+    float mx = -DEV_INF;
+    if (active) {
+      k_addr(0);
+      v_addr(NB - 1);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              uint32_t x = v[e];
-              x = valid > 2 * e + 1 ? x : (x & 0x0000ffffu);
-              x = valid > 2 * e ? x : 0u;
-              v[e] = x;
-            }
-            vb[q] = v;
-          }
-        }
-        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
+      for (int x = 0; x < 2; ++x) pa.hi[x] = pa.lo[x] = pb.hi[x] = pb.lo[x] = u32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) sc = mm(rd(ka[kk]), qf[kk], kk == 0 ? zero16 : sc);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) kf[x] = rd(ka[x % KK] + 32 * KROW);
+#pragma unroll
+      for (int d = 0; d < DT; ++d) v0[d] = u32x4{0, 0, 0, 0};
+    }
+    for (int kb = unit; kb < nkb; kb += a.n_units) {
+      const int nbuf = buf == 0 ? NB - 1 : buf - 1;            // (buf + NB - 1) % NB: the buffer of the block before
+      const int buf1 = buf + 1 == NB ? 0 : buf + 1;
+      const int kn = clampb(kb + (NB - 1) * a.n_units);
+      if (kb != unit) fix_tail(kb, buf);
+      // (the counts are exact only while the loop issues no other vector memory instruction: no spills to scratch,
+      // which the build's resource report shows)
+      auto turn = [&]() {
+        __builtin_amdgcn_s_waitcnt(DL_VMCNT(FPW) & 0xF0FF);   // this wave's copies of the next block have landed, its reads are back
+        __builtin_amdgcn_s_barrier();                          // everybody's; the buffer of the block before is free
+        copy_base(kn, nbuf, pg_next);
+      };
+      if (active) {
+        settle(sc, mx, kb << 6, pb);
+        mx = half_step(I1{}, I1{}, I0{}, I0{}, sc, sn, pa, pb, [&]() { turn(); k_addr(buf1); v_addr(buf); }, [&](int i) { copy(kn, nbuf, i); });
+        pg_next = page_of(clampb(kb + NB * a.n_units));
+        settle(sn, mx, (kb << 6) + 32, pa);
+        mx = half_step(I0{}, I0{}, I1{}, I1{}, sn, sc, pb, pa, [&]() {}, [&](int) {});
+      } else {
+        turn();
+#pragma unroll
+        for (int i = 0; i < FPW; ++i) copy(kn, nbuf, i);
+        pg_next = page_of(clampb(kb + NB * a.n_units));
       }
-      if (active) compute(buf, kb);
-      buf = buf + 1 == NB ? 0 : buf + 1;
+      buf = buf1;
     }
     __builtin_amdgcn_s_waitcnt(DL_VMCNT(0));   // the trailing repeats must not outlive the workgroup
+    if (active) {
+#pragma unroll
+      for (int d = 0; d < DT; ++d) v1[d] = rd(va[3] + d * 4096);
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int d = 0; d < DT; ++d) {
+          oacc[d] = mm(x ? v1[d] : v0[d], pb.hi[x], oacc[d]);
+          oacc[d] = mm(x ? v1[d] : v0[d], pb.lo[x], oacc[d]);
+        }
+    }
   }
 
   if (active) {
+    // lane holds query column r, channels 32d + 8(e/4) + 4h + e%4
+    float l = l_run + l_odd;
+    l += __shfl_xor(l, 32, 64);
+    if (row_out < 0) {
+    } else if (a.n_units == 1) {
+      const float inv = l > 0.f ? 1.0f / l : 0.f;
+      const int tok = (int)(row_out / a.Hq), head = (int)(row_out - (int64_t)tok * a.Hq);
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      float l = l_run[t];
-      l += __shfl_xor(l, 16, 64);
-      l += __shfl_xor(l, 32, 64);
-      if (row_out[t] < 0) continue;
-      if (a.n_units == 1) {
-        const float inv = l > 0.f ? 1.0f / l : 0.f;
-        const int64_t ro = row_out[t];
-        const int tok = (int)(ro / a.Hq), head = (int)(ro - (int64_t)tok * a.Hq);
+      for (int d = 0; d < DT; ++d)
 #pragma unroll
-        for (int d = 0; d < DT; ++d) {
-          const int ch = d * 16 + 4 * g;
-          const int64_t at = a.out_mt > 0 ? frag_offset(tok, head * DH + ch, a.out_mt) : ro * DH + ch;
-          *(uint2*)(a.o + at) = make_uint2(
-              (uint32_t)f32_to_bf16(oacc[d][t][0] * inv) | ((uint32_t)f32_to_bf16(oacc[d][t][1] * inv) << 16),
-              (uint32_t)f32_to_bf16(oacc[d][t][2] * inv) | ((uint32_t)f32_to_bf16(oacc[d][t][3] * inv) << 16));
+        for (int e4 = 0; e4 < 4; ++e4) {
+          const int ch = d * 32 + e4 * 8 + 4 * h;
+          const int64_t at = a.out_mt > 0 ? frag_offset(tok, head * DH + ch, a.out_mt) : row_out * DH + ch;
+          *(uint2*)(a.o + at) = make_uint2(pack_bf16x2(oacc[d][e4 * 4] * inv, oacc[d][e4 * 4 + 1] * inv),
+                                           pack_bf16x2(oacc[d][e4 * 4 + 2] * inv, oacc[d][e4 * 4 + 3] * inv));
         }
-        continue;
-      }
-      const int64_t slot = row_out[t] * a.n_units + unit;
-      float* po = a.part_o + slot * DH + 4 * g;
+    } else {
+      const int64_t slot = row_out * a.n_units + unit;
+      float* po = a.part_o + slot * DH + 4 * h;
 #pragma unroll
-      for (int d = 0; d < DT; ++d) *(f32x4*)(po + d * 16) = oacc[d][t];
-      if (g == 0) { a.part_ml[slot * 2] = m_run[t]; a.part_ml[slot * 2 + 1] = l; }
+      for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4)
+          *(f32x4*)(po + d * 32 + e4 * 8) = f32x4{oacc[d][e4 * 4], oacc[d][e4 * 4 + 1], oacc[d][e4 * 4 + 2], oacc[d][e4 * 4 + 3]};
+      if (h == 0) { a.part_ml[slot * 2] = m_run; a.part_ml[slot * 2 + 1] = l; }
     }
   }
   if (bad) atomicOr(a.status, DLLM_STATUS_BAD_PAGE);
 }
+
+template <int DH, int PG>
+__global__ __launch_bounds__(512) void k_attn_dl(const AttnArgs a) { attn_dl_body<DH, PG>(a); }
 
 bool attn_step_supported(const dllm_ctx* c, const StepGeom& g) {
   const dllm_config& f = c->cfg;
@@ -966,16 +896,15 @@ bool attn_step_supported(const dllm_ctx* c, const StepGeom& g) {
 // Attention of a denoise step (paged pool) or of a no-cache forward (packed scratch).
 // merging four waves' partial results takes a little more LDS than a kernel gets by default
 static bool attn_merge_ready = false;
-constexpr int DL_LDS_MAX = 128 * 1024;          // ring of k_attn_dl plus its copy of a sequence's page ids
+constexpr int DL_LDS_MAX = 160 * 1024;          // ring of k_attn_dl plus its copy of a sequence's page ids
 hipError_t init_attn_kernels() {
   if (attn_merge_ready) return hipSuccess;
   hipError_t e = hipFuncSetAttribute((const void*)k_attn_step<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
   if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_attn_step<64, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-#define DL_ATTR(DHV, NWV, PG)                                                                                     \
+#define DL_ATTR(DHV, PG)                                                                                          \
   if (e == hipSuccess)                                                                                            \
-    e = hipFuncSetAttribute((const void*)k_attn_dl<DHV, NWV, PG>, hipFuncAttributeMaxDynamicSharedMemorySize, DL_LDS_MAX)
-  DL_ATTR(128, 8, true); DL_ATTR(128, 8, false); DL_ATTR(128, 4, true); DL_ATTR(128, 4, false);
-  DL_ATTR(64, 8, true); DL_ATTR(64, 8, false); DL_ATTR(64, 4, true); DL_ATTR(64, 4, false);
+    e = hipFuncSetAttribute((const void*)k_attn_dl<DHV, PG>, hipFuncAttributeMaxDynamicSharedMemorySize, DL_LDS_MAX)
+  DL_ATTR(128, 0); DL_ATTR(128, 1); DL_ATTR(128, 2); DL_ATTR(64, 0); DL_ATTR(64, 1); DL_ATTR(64, 2);
 #undef DL_ATTR
   attn_merge_ready = e == hipSuccess;
   return e;
@@ -993,7 +922,10 @@ hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const
     pt_shift = -1;
     for (int sft = 3; sft < 31; ++sft) if (f.page_tokens == (1 << sft)) pt_shift = sft;
   }
-  const bool staged = n_rg >= 4 && pt_shift >= 0;   // K/V staged in LDS, up to 8 row groups per workgroup
+  // many rows per KV head: K and V staged in LDS, up to 8 row groups per workgroup, if the ring and the page ids fit
+  const int pg_cap = g.Q > 0 ? (g.max_kv + f.page_tokens - 1) / f.page_tokens : 0;
+  const size_t dl_lds = (size_t)DL_NB * (f.head_dim / 4) * 1024 + (size_t)pg_cap * sizeof(int32_t);
+  const bool staged = n_rg >= 4 && pt_shift >= 0 && attn_merge_ready && dl_lds <= (size_t)DL_LDS_MAX;
   const int rg_cap = staged ? 8 : 4;                           // the register-direct kernel runs at most 4 waves
   const int n_rg_wg = n_rg < rg_cap ? n_rg : rg_cap;
   const int n_chunks = (n_rg + n_rg_wg - 1) / n_rg_wg;
@@ -1038,29 +970,17 @@ hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const
   dim3 grid((unsigned)(units / kspl), n_chunks, g.B * f.n_kv_heads);
   const int threads = 64 * n_rg_wg * kspl;
   if (staged) {
-    // many rows per kv head: K/V staged once per workgroup in LDS (at least 4 waves load)
-    const bool paged = g.Q > 0;
-    const bool fast = !paged || a.pt_shift >= 6;     // a 64-key block never straddles pages
-    // blocks inside one page (or the packed scratch): straight-to-LDS copies, if the ring and the sequence's
-    // page ids fit; otherwise the loader that goes through registers
-    a.pg_cap = paged ? (g.max_kv + f.page_tokens - 1) / f.page_tokens : 0;
-    const size_t ring = (size_t)(n_rg_wg <= 4 ? 2 : 3) * (size_t)(f.head_dim / 4) * 1024;   // NB buffers of head_dim/4 one-KiB fragments
-    const size_t dl_lds = ring + (size_t)a.pg_cap * sizeof(int32_t);
-    const bool direct = fast && attn_merge_ready && dl_lds <= (size_t)DL_LDS_MAX;
-#define ATTN_LDS(DHV, NWV)                                                                                 \
-  do {                                                                                                     \
-    if (direct && paged) k_attn_dl<DHV, NWV, true><<<grid, NWV * 64, dl_lds, s>>>(a);                      \
-    else if (direct) k_attn_dl<DHV, NWV, false><<<grid, NWV * 64, dl_lds, s>>>(a);                         \
-    else if (!paged) k_attn_lds<DHV, NWV, false, true><<<grid, NWV * 64, 0, s>>>(a);                       \
-    else if (fast) k_attn_lds<DHV, NWV, true, true><<<grid, NWV * 64, 0, s>>>(a);                          \
-    else k_attn_lds<DHV, NWV, true, false><<<grid, NWV * 64, 0, s>>>(a);                                   \
+    a.pg_cap = pg_cap;
+    const int pg = g.Q == 0 ? 0 : (pt_shift >= 6 ? 1 : 2);
+#define ATTN_DL(DHV)                                                            \
+  do {                                                                          \
+    if (pg == 0) k_attn_dl<DHV, 0><<<grid, 512, dl_lds, s>>>(a);                \
+    else if (pg == 1) k_attn_dl<DHV, 1><<<grid, 512, dl_lds, s>>>(a);           \
+    else k_attn_dl<DHV, 2><<<grid, 512, dl_lds, s>>>(a);                        \
   } while (0)
-    if (f.head_dim == 128) {
-      if (n_rg_wg <= 4) ATTN_LDS(128, 4); else ATTN_LDS(128, 8);
-    } else {
-      if (n_rg_wg <= 4) ATTN_LDS(64, 4); else ATTN_LDS(64, 8);
-    }
-#undef ATTN_LDS
+    if (f.head_dim == 128) ATTN_DL(128);
+    else ATTN_DL(64);
+#undef ATTN_DL
   } else {
     const size_t lds = kspl > 1 ? (size_t)kspl * (2 * QT * 16 * sizeof(float) + (size_t)(f.head_dim / 16) * QT * 64 * 16) : 0;
     if (f.head_dim == 128) k_attn_step<128, QT><<<grid, threads, lds, s>>>(a);

@@ -1,0 +1,63 @@
+"""GPU parity of the bfloat16 attention kernels at the edges of their key blocks, over caches that stress the running
+softmax: keys whose scores grow along the sequence by far more than the kernels let the running maximum lag behind, and
+pool slots past every sequence's end that hold NaN.  The reference is the oracle with bfloat16 storage on the same
+cache; the tolerance is that of a one-layer model (tests/harness.py: logit_tol)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dllm_oracle as O
+from paper_2601_07568_amd import synth
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+W = synth.as_float
+ST = synth.round_bf16
+
+
+def shape(hq, hkv, dh):
+    return synth.ModelShape(1, 256, hq, hkv, dh, 512, 700, 699, dtype="bf16", lm_head_scale=8.0, name=f"attn-{hq}-{hkv}-{dh}")
+
+
+# 7 and 4 heads a key head: seven and four groups of 32 query rows at 32 rows a sequence, one per wave; 1: the few-row
+# kernels
+SHAPES = {"g7-128": shape(7, 1, 128), "g4-128": shape(8, 2, 128), "g7-64": shape(7, 1, 64), "g8-64": shape(8, 1, 64),
+          "g1-128": shape(2, 2, 128), "g1-64": shape(3, 3, 64)}
+# prefixes: keys (prefix + rows) on both sides of 32 and 64, inside and past a page, several blocks per workgroup
+LENS = {32: [0, 1, 31, 33, 95, 97, 480, 1500], 40: [0, 23, 24, 25, 88, 300], 64: [0, 63, 65, 700], 100: [28, 29, 155, 400]}
+
+
+@pytest.mark.parametrize("name,Q,pt", [("g7-128", 32, 64), ("g7-128", 32, 8), ("g7-128", 40, 32), ("g4-128", 32, 128), ("g4-128", 64, 16),
+                                       ("g7-64", 32, 64), ("g8-64", 40, 8), ("g8-64", 64, 256), ("g1-128", 32, 64), ("g1-128", 40, 24),
+                                       ("g1-128", 64, 32), ("g1-128", 100, 64), ("g1-64", 100, 16)])
+@pytest.mark.parametrize("ramp", [1.0, 60.0])
+def test_key_block_edges_growing_scores_and_nan_slots(name, Q, pt, ramp):
+    ms, lens = SHAPES[name], LENS[Q]
+    B = len(lens)
+    w = synth.Weights(ms, 3)
+    mp = (max(lens) + Q + pt - 1) // pt + 1
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=B * mp, max_batch=B, max_q=Q, max_tokens=0)
+    rng = np.random.default_rng(17)
+    table = H.identity_table(eng, B, perm=rng.permutation(B * mp))
+    eng.kv_pool.view(torch.bfloat16).fill_(float("nan"))
+    ks, vs = eng.kv_slab(0, 0), eng.kv_slab(0, 1)
+    cache = []
+    for b, n in enumerate(lens):
+        size = np.geomspace(1.0, ramp, max(n, 1))[:n, None, None]
+        k = ST(rng.standard_normal((n, ms.n_kv_heads, ms.head_dim)) * size)
+        v = ST(rng.standard_normal((n, ms.n_kv_heads, ms.head_dim)))
+        for p0 in range(0, n, pt):
+            m = min(pt, n - p0)
+            page = int(table[b, p0 // pt])
+            ks[page, :, :m] = torch.as_tensor(np.asarray(k[p0:p0 + m]).transpose(1, 0, 2).copy()).to(eng.device, torch.bfloat16)
+            vs[page, :, :m] = torch.as_tensor(np.asarray(v[p0:p0 + m]).transpose(1, 0, 2).copy()).to(eng.device, torch.bfloat16)
+        cache.append(([k], [v]))
+    blks = [synth.masked_block(ms, 30 + b, Q, Q // 2) for b in range(B)]
+    hidden = eng.debug_hidden(eng.i32(np.stack(blks)), eng.i32(lens), eng.i32(table), 1, max_prefix_len=max(lens)).cpu().numpy()
+    tol = H.logit_tol("bf16", 1, "store")
+    for b in range(B):
+        _, x = O.forward_cached(w, blks[b], *cache[b], widen=W, store=ST, want_logits=False)
+        err = H.rel_err_rows(hidden[b], x).max()
+        assert err <= tol, (lens[b], err)
+    assert eng.read_status() == 0
+    eng.close()
