@@ -2,9 +2,9 @@
 //
 // Skinny GEMM (at most 64 activation rows): the step is bound by streaming each weight once from
 // HBM, so a workgroup owns a few 16-row tiles of the weight matrix for the whole K extent, its
-// waves split K among themselves in interleaved 128-element blocks, every lane pulls 16-byte
-// pieces of its weight row straight into registers (64 contiguous bytes per row and instruction,
-// one block prefetched ahead), and the partial tiles are summed through LDS in a fixed order.
+// waves split K among themselves in interleaved stages of one or two 32-element steps, every load
+// of a wave is a contiguous KiB of the packed weights or of the activations straight into registers
+// (one or two stages ahead), and the partial tiles are summed through LDS in a fixed order.
 // The epilogue of the summed tile is the fusion point: residual add, rotary embedding + KV-cache
 // write, SiLU*up, or the softmax statistics of the LM head (the logits never reach memory).
 //
@@ -40,6 +40,7 @@ struct SkArgs {
   const float* ss_in;
   int n_ss, ss_stride;
   float inv_d, eps;
+  const float* rscale;      // more than 64 rows: the factors themselves
   // RESID (residual projection x += X W0^T): a workgroup owns 16 columns for the whole of K, adds its tile to the
   // residual stream, writes x * gain_next in fragment order as the next GEMM's input and the rows' sums of squares
   // over its 16 columns to ss_out[row * ss_stride + workgroup].
@@ -102,9 +103,9 @@ template <int NT, int EPI>
 __device__ inline void sk_tile_rows(const SkArgs& a, int wg, const bf16_t* (&wbase)[NT], int (&row0)[NT],
                                     int (&nrows)[NT]) {
   if constexpr (EPI == SK_QKV) {
-    // NT == 3: tiles 0 and 1 are the two halves of rotary pair-tile wg (rows h*dh + j0 .. and the same
-    // + dh/2) of Wq or Wk, tile 2 is 16-row tile wg of Wv: pair tiles and value tiles are handed out
-    // together so that the grid is max(pair tiles, value tiles) equal workgroups
+    // Tiles 0 and 1 are the two halves of rotary pair-tile wg (rows h*dh + j0 .. and the same + dh/2) of Wq or Wk.
+    // NT == 3: tile 2 is 16-row tile wg of Wv: pair tiles and value tiles are handed out together so that the grid is
+    // max(pair tiles, value tiles) equal workgroups.  NT == 2: the workgroups behind the pair tiles take two tiles of Wv.
     const int half = a.dh >> 1, per_head = half / 16;
     const int n_pairs = a.n_q_wg + a.n_k_wg;
     const int pw = wg < n_pairs ? wg : n_pairs - 1;            // clamped: the result is dropped
@@ -117,9 +118,18 @@ __device__ inline void sk_tile_rows(const SkArgs& a, int wg, const bf16_t* (&wba
       nrows[t] = isq ? a.N0 : a.N1;
       row0[t] = h * a.dh + j0 + t * half;
     }
-    wbase[NT - 1] = a.W2;
-    nrows[NT - 1] = a.N2;
-    row0[NT - 1] = wg * 16;                                    // beyond N2: clamped by the caller, dropped below
+    if constexpr (NT == 3) {
+      wbase[NT - 1] = a.W2;
+      nrows[NT - 1] = a.N2;
+      row0[NT - 1] = wg * 16;                                  // beyond N2: clamped by the caller, dropped below
+    } else if (wg >= n_pairs) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        wbase[t] = a.W2;
+        nrows[t] = a.N2;
+        row0[t] = ((wg - n_pairs) * 2 + t) * 16;
+      }
+    }
   } else if constexpr (EPI == SK_SWIGLU) {
     // NT = 2*P: tiles 0..P-1 are P consecutive 16-row tiles of the gate matrix, tiles P..2P-1 the same rows of up
 #pragma unroll
@@ -134,18 +144,18 @@ __device__ inline void sk_tile_rows(const SkArgs& a, int wg, const bf16_t* (&wba
   }
 }
 
-// (second launch bound: at least 4 waves per SIMD, i.e. two 8-wave workgroups per CU, so that one
-// workgroup's prologue and reduction overlap the other's streaming)
-template <int NT, int MT, int NW, int EPI>
-__global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 && MT >= 3) ? 2 : 1)) void k_skinny(const SkArgs a) {
-  // weight bytes in flight per wave: two stages of NT*JB KiB; with three or four activation tiles the
-  // shorter stage keeps the registers of three stages within a wave's share
-  constexpr int JB = (MT >= 3) ? 1 : 2;
+// JB: matrix-instruction steps of a pipeline stage, D: stages that registers hold.  TPC: weight tiles whose partial sums go through LDS together.
+template <int NT, int MT, int NW, int EPI, int JB, int TPC, int D, int WPS>
+__global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   constexpr bool SCALED = (EPI != SK_RESID);
   constexpr int RPW = (MT * 16 + NW - 1) / NW;          // rows per wave when the row scales are summed
-  __shared__ float red[NW][NT][MT][4][64];
+  // partial tiles go through LDS in chunks of TPC weight tiles and MC activation tiles
+  constexpr int NCH = NT / TPC, MCH = NW * TPC * MT <= 144 ? 1 : 2, MC = (MT + MCH - 1) / MCH;
+  static_assert(NT % TPC == 0 && (EPI != SK_LMSTATS || (TPC == 4 && MCH == 1)), "64 columns per partial of the LM head");
+  constexpr int NBUF = NCH * MCH > 1 && NW * TPC * MC <= 64 ? 2 : 1;   // (of 64 KiB at most)
+  __shared__ float red_buf[NBUF][NW][TPC][MC][4][64];
   __shared__ float lmst[EPI == SK_LMSTATS ? MT : 1][4][16][4];
-  __shared__ float rs[64];                              // row scale of the activations
+  __shared__ float rs[MT * 16 < 64 ? 64 : MT * 16];     // row scale of the activations
   __shared__ float ssq[EPI == SK_RESID ? MT : 1][4][64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
@@ -180,33 +190,47 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
     xres = a.x[ok ? (int64_t)tok * a.N0 + n : 0];
     gres = bf16_to_f32(a.gain_next[ok ? n : 0]);
   }
-  // QKV with one epilogue item per thread: what that item needs besides the sums - the row's position, its rotary
-  // factors, the page of its cache slot - is requested now and arrives while the weights stream
-  constexpr bool QKV_PRE = EPI == SK_QKV && MT * 256 <= NW * 64;
-  float pcs = 0.f, psn = 0.f;
-  int ppos = -1, ppage = -1;
-  if constexpr (QKV_PRE) {
-    const int m = tid >> 8, iq = (tid >> 6) & 3;
-    const int tok = m * 16 + c;
-    if (m < MT && tok < M) {
-      ppos = a.tok_pos[tok];
-      if (wg < a.n_q_wg + a.n_k_wg) {
-        const int hj = row0[0] + 4 * g + iq;
-        const int j = hj - (hj / a.dh) * a.dh;
-        const int half = a.dh >> 1;
-        pcs = a.rope_cos[(int64_t)tok * half + j];
-        psn = a.rope_sin[(int64_t)tok * half + j];
+  // QKV: what a thread's epilogue items need besides the sums - the rows' positions, their rotary factors - is requested
+  // before the weights, the pages of their cache slots (which depend on the positions) behind the first weights: a wave
+  // that waited for the positions first would start its stream a round trip late.  Addresses are clamped, not branched.
+  constexpr int IPT = EPI == SK_QKV ? (MC * 256 + NW * 64 - 1) / (NW * 64) : 1;   // items of a thread and chunk
+  float pcs[MCH][IPT], psn[MCH][IPT];
+  int ppos[MCH][IPT], pseq[MCH][IPT], ppage[MCH][IPT];
+  if constexpr (EPI == SK_QKV) {
+#pragma unroll
+    for (int mc = 0; mc < MCH; ++mc)
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const int item = tid + k * NW * 64, iq = (item >> 6) & 3;
+        int tok = (mc * MC + (item >> 8)) * 16 + c;
+        tok = tok < M ? tok : M - 1;
+        const int hj = row0[0] + 4 * g + iq, half = a.dh >> 1;
+        int j = hj - (hj / a.dh) * a.dh;
+        j = j < half ? j : 0;                                   // (a value row's is not used)
+        ppos[mc][k] = a.tok_pos[tok];
+        pseq[mc][k] = a.tok_seq[tok];
+        pcs[mc][k] = a.rope_cos[(int64_t)tok * half + j];
+        psn[mc][k] = a.rope_sin[(int64_t)tok * half + j];
       }
-      const int pi = ppos >= 0 ? ppos / a.pool.page_tokens : a.pool.max_pages;
-      if (pi < a.pool.max_pages) ppage = a.pool.table[(int64_t)a.tok_seq[tok] * a.pool.max_pages + pi];
-    }
   }
-  // kv_locate for that item from the values fetched above
-  auto locate_pre = [&](int h, int64_t& k_off, int64_t& v_off, int& v_stride) -> bool {
+  auto fetch_pages = [&]() {
+    if constexpr (EPI == SK_QKV) {
+#pragma unroll
+      for (int mc = 0; mc < MCH; ++mc)
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          const int pos = ppos[mc][k], pi = pos >= 0 ? pos / a.pool.page_tokens : a.pool.max_pages;
+          const int page = a.pool.table[(int64_t)pseq[mc][k] * a.pool.max_pages + (pi < a.pool.max_pages ? pi : a.pool.max_pages - 1)];
+          ppage[mc][k] = pi < a.pool.max_pages ? page : -1;
+        }
+    }
+  };
+  // kv_locate from a position and its page
+  auto locate = [&](int pos, int page, int h, int64_t& k_off, int64_t& v_off, int& v_stride) -> bool {
     const KVView& kv = a.pool;
-    if (ppos < 0 || ppage < 0 || ppage >= kv.n_pages) return false;
-    const int slot = ppos - (ppos / kv.page_tokens) * kv.page_tokens;
-    const int64_t ph = (int64_t)ppage * kv.n_kv_heads + h;
+    if (pos < 0 || page < 0 || page >= kv.n_pages) return false;
+    const int slot = pos - (pos / kv.page_tokens) * kv.page_tokens;
+    const int64_t ph = (int64_t)page * kv.n_kv_heads + h;
     k_off = (ph * kv.page_tokens + slot) * kv.head_dim;
     v_off = ph * kv.head_dim * kv.page_tokens + slot;
     v_stride = kv.page_tokens;
@@ -224,7 +248,9 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
   // row's factor.  Called once the first weight stages are on their way: the partials come from the L2, the
   // weights from memory, so the wave waits no longer for them than it would for the weights alone.
   auto row_scales = [&]() {
-    if constexpr (SCALED) {
+    if constexpr (SCALED && MT > 4) {
+      if (tid < MT * 16) rs[tid] = a.rscale[tid < M ? tid : M - 1];
+    } else if constexpr (SCALED) {
       if (a.ss_in) {
         float4 ssv[RPW];
         const int idc = 4 * lane < a.ss_stride - 4 ? 4 * lane : a.ss_stride - 4;
@@ -251,7 +277,7 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
     }
   };
 
-  // Software pipeline over this wave's stages (w, w+NW, ...): two stages are in flight while a third
+  // Software pipeline over this wave's stages (w, w+NW, ...): D - 1 stages are in flight while another
   // is multiplied.  No load sits inside a branch of the steady-state loop (a branch around a load
   // makes the compiler wait for every outstanding load at the join); the drain is straight-line code.
   constexpr int SKB = JB * 32;                        // k-elements per stage
@@ -260,27 +286,39 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
   const int n_w = n_full > ws ? (n_full - ws + NW - 1) / NW : 0;
 #define SK_LD(F, I) sk_load<NT, MT, JB, false>(F, wt, xf, ws + (I) * NW, g, K)
 #define SK_MM(F) sk_mma<NT, MT, JB>(F, acc)
-  if (n_w <= 1) {
-    SkFrag<NT, MT, JB> f0;
-    if (n_w == 1) SK_LD(f0, 0);
+  if (n_w == 0) {
+    fetch_pages();
     row_scales();
-    if (n_w == 1) SK_MM(f0);
   } else {
-    SkFrag<NT, MT, JB> f0, f1, f2;
-    SK_LD(f0, 0);
-    SK_LD(f1, 1);
+    SkFrag<NT, MT, JB> f[D];
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j) SK_LD(f[j], j < n_w ? j : n_w - 1);
+    fetch_pages();
     row_scales();
-    int i = 0;
-    while (i + 4 < n_w) {          // stages i .. i+4 exist
-      SK_LD(f2, i + 2); SK_MM(f0);
-      SK_LD(f0, i + 3); SK_MM(f1);
-      SK_LD(f1, i + 4); SK_MM(f2);
-      i += 3;
-    }
-    switch (n_w - i) {             // 2, 3 or 4 stages left; f0 = stage i, f1 = stage i+1 in flight
-      case 2: SK_MM(f0); SK_MM(f1); break;
-      case 3: SK_LD(f2, i + 2); SK_MM(f0); SK_MM(f1); SK_MM(f2); break;
-      default: SK_LD(f2, i + 2); SK_MM(f0); SK_LD(f0, i + 3); SK_MM(f1); SK_MM(f2); SK_MM(f0); break;
+    if (n_w < D - 1) {
+#pragma unroll
+      for (int j = 0; j < D - 2; ++j)
+        if (j < n_w) SK_MM(f[j]);
+    } else {
+      int i = 0;
+      while (i + 2 * D - 2 < n_w) {          // stages i .. i + 2D - 2 exist, the first D - 1 of them are in flight
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          SK_LD(f[(j + D - 1) % D], i + j + D - 1);
+          SK_MM(f[j]);
+        }
+        i += D;
+      }
+      const int left = n_w - i;              // D - 1 .. 2D - 2
+#pragma unroll
+      for (int r = D - 1; r <= 2 * D - 2; ++r)
+        if (left == r) {
+#pragma unroll
+          for (int j = 0; j < 2 * D - 2; ++j) {
+            if (j + D - 1 < r) SK_LD(f[(j + D - 1) % D], i + j + D - 1);
+            if (j < r) SK_MM(f[j % D]);
+          }
+        }
     }
   }
 #undef SK_LD
@@ -291,14 +329,24 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
     sk_mma<NT, MT, JB>(ft, acc);
   }
 
-  // sum the waves' partial tiles in wave order
+  // Sum the waves' partial tiles in wave order, a chunk at a time (SWIGLU: gate tiles and the up tiles of the same rows).
+  // Two buffers in turn: a chunk's barrier also says that every thread is done with the chunk before the last.
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
+  for (int chunk = 0; chunk < NCH * MCH; ++chunk) {
+  const int ch = chunk / MCH, mc = chunk % MCH;
+  auto& red = red_buf[chunk & (NBUF - 1)];
+  if (NBUF == 1 && chunk > 0) __syncthreads();
+  auto tile_of = [&](int u) { return EPI == SK_SWIGLU ? (u < TPC / 2 ? ch * (TPC / 2) + u : NT / 2 + ch * (TPC / 2) + u - TPC / 2) : ch * TPC + u; };
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+  for (int u = 0; u < TPC; ++u)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) red[w][t][m][i][lane] = acc[t][m][i];
+    for (int m = 0; m < MC; ++m)
+      if (mc * MC + m < MT) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[w][u][m][i][lane] = acc[tile_of(u)][mc * MC + m][i];
+      }
   __syncthreads();
+  const int n_items = (MT - mc * MC < MC ? MT - mc * MC : MC) * 256;
 
   if constexpr (EPI == SK_RESID) {
     // ---- residual projection: x += tile; next GEMM's input x * gain; sums of squares of the 16 columns per row
@@ -333,14 +381,17 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
     return;
   }
 
-  for (int item = tid; item < MT * 256; item += NW * 64) {
+#pragma unroll
+  for (int k = 0; k < (MC * 256 + NW * 64 - 1) / (NW * 64); ++k) {
+    const int item = tid + k * NW * 64;
+    if (item >= n_items) break;
     const int m = item >> 8, i = (item >> 6) & 3, ln = item & 63;
-    const int tok = m * 16 + (ln & 15);
+    const int tok = (mc * MC + m) * 16 + (ln & 15);
     const int fr = 4 * (ln >> 4) + i;          // row inside the 16-row tile
-    float val[NT];
+    float val[TPC];
     const float rsc = SCALED ? rs[tok] : 1.0f;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+    for (int t = 0; t < TPC; ++t) {
       float s = 0.f;
 #pragma unroll
       for (int ww = 0; ww < NW; ++ww) s += red[ww][t][m][i][ln];
@@ -349,17 +400,17 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
     const bool tok_ok = tok < M;
     if constexpr (EPI == SK_F32) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int n = row0[t] + fr;
+      for (int t = 0; t < TPC; ++t) {
+        const int n = row0[tile_of(t)] + fr;
         if (tok_ok && n < a.N0) a.out_f32[(int64_t)tok * a.N0 + n] = val[t];
       }
     } else if constexpr (EPI == SK_SWIGLU) {
 #pragma unroll
-      for (int t = 0; t < NT / 2; ++t) {
-        const int n = row0[t] + fr;
+      for (int t = 0; t < TPC / 2; ++t) {
+        const int n = row0[tile_of(t)] + fr;
         if (tok_ok && n < a.N0) {
           const float gt = val[t];
-          a.out_bf16[frag_offset(tok, n, MT)] = f32_to_bf16(gt / (1.0f + expf(-gt)) * val[t + NT / 2]);
+          a.out_bf16[frag_offset(tok, n, MT)] = f32_to_bf16(gt / (1.0f + expf(-gt)) * val[t + TPC / 2]);
         }
       }
     } else if constexpr (EPI == SK_QKV) {
@@ -369,8 +420,7 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
           const int half = a.dh >> 1;
           const int hj = row0[0] + fr;                 // h*dh + j, j < half
           const int h = hj / a.dh, j = hj - h * a.dh;
-          const float cs = QKV_PRE ? pcs : a.rope_cos[(int64_t)tok * half + j];
-          const float sn = QKV_PRE ? psn : a.rope_sin[(int64_t)tok * half + j];
+          const float cs = pcs[mc][k], sn = psn[mc][k];
           const float v0 = val[0], v1 = val[1];
           const bf16_t r0 = f32_to_bf16(v0 * cs - v1 * sn), r1 = f32_to_bf16(v1 * cs + v0 * sn);
           if (isq) {
@@ -379,31 +429,32 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
           } else {
             int64_t ko, vo;
             int vs;
-            const int pos = QKV_PRE ? ppos : a.tok_pos[tok];
-            if (pos < 0) {
+            if (ppos[mc][k] < 0) {
               // a padding row: nothing of it is cached
-            } else if (QKV_PRE ? locate_pre(h, ko, vo, vs) : kv_locate(a.pool, a.tok_seq[tok], pos, h, ko, vo, vs)) {
+            } else if (locate(ppos[mc][k], ppage[mc][k], h, ko, vo, vs)) {
               a.pool_k[ko + j] = r0;
               a.pool_k[ko + j + half] = r1;
             } else atomicOr(a.status, DLLM_STATUS_BAD_PAGE);
           }
         }
-        const int n = row0[NT - 1] + fr;               // value row
-        if (n < a.N2) {
-          const int h = n / a.dh, ch = n - h * a.dh;
-          int64_t ko, vo;
-          int vs;
-          const int pos = QKV_PRE ? ppos : a.tok_pos[tok];
-          if (pos >= 0 && (QKV_PRE ? locate_pre(h, ko, vo, vs) : kv_locate(a.pool, a.tok_seq[tok], pos, h, ko, vo, vs)))
-            a.pool_v[vo + (int64_t)ch * vs] = f32_to_bf16(val[NT - 1]);
+        if (NT == 3 || wg >= a.n_q_wg + a.n_k_wg) {
+#pragma unroll
+          for (int t = NT == 3 ? 2 : 0; t < NT; ++t) {
+            const int n = row0[t] + fr;                // value row
+            if (n >= a.N2) continue;
+            const int h = n / a.dh, cn = n - h * a.dh;
+            int64_t ko, vo;
+            int vs;
+            if (locate(ppos[mc][k], ppage[mc][k], h, ko, vo, vs)) a.pool_v[vo + (int64_t)cn * vs] = f32_to_bf16(val[t]);
+          }
         }
       }
     } else if constexpr (EPI == SK_LMSTATS) {
       RowStat st;
       st.init();
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int n = row0[t] + fr;
+      for (int t = 0; t < TPC; ++t) {
+        const int n = row0[tile_of(t)] + fr;
         if (n < a.N0 && n != a.mask_id) st.merge(val[t], n, 1.0f, val[t]);
       }
       // same token: lanes ln, ln^16, ln^32, ln^48 of this wave, then the four values of i
@@ -423,7 +474,7 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
     __syncthreads();
     if (tid < MT * 16) {
       const int m = tid >> 4, cc = tid & 15, tok = m * 16 + cc;
-      if (tok < M) {
+      if (tok < M && wg * NCH + ch < a.n_parts) {
         RowStat st;
         st.init();
 #pragma unroll
@@ -431,24 +482,53 @@ __global__ __launch_bounds__(NW * 64, (NT + MT == 4 && NW == 8) ? 4 : ((NW == 4 
           const float* p = &lmst[m][i][cc][0];
           st.merge(p[0], __float_as_int(p[1]), p[2], p[3]);
         }
-        float* o = a.part + ((int64_t)tok * a.n_parts + wg) * 4;
+        float* o = a.part + ((int64_t)tok * a.n_parts + wg * NCH + ch) * 4;
         o[0] = st.m; o[1] = __int_as_float(st.idx); o[2] = st.s; o[3] = st.t;
       }
     }
   }
+  }   // chunks
+}
+
+// Pipeline of a form.  What a wave has in flight beyond two stages brings nothing (D 3 -> 4 .. 8: -1 .. +5 % where the
+// registers last, up to twice the time where they do not), so stages are as short and as few as keep a wave's registers
+// in its share: 8 waves of 6 tiles x 64 rows with two stages (178 registers) 42.4 us where 4 waves with three take 47.1.
+template <int NT, int MT, int NW, int EPI>
+struct SkCfg {
+  static constexpr bool WIDE = EPI == SK_SWIGLU && NT == 6;
+  static constexpr int JB = (MT >= 3 || (EPI == SK_SWIGLU && MT == 2) || (EPI == SK_QKV && NT == 2)) ? 1 : 2;
+  static constexpr int D = (WIDE && MT >= 3) || (EPI == SK_SWIGLU && MT == 4) || (EPI == SK_QKV && MT >= 7) ? 2
+                           : (EPI == SK_QKV && NT == 2 && MT <= 2) ? 5 : 3;
+  static constexpr int TPC = EPI == SK_SWIGLU ? 2 : NT;
+  // waves per SIMD that the registers are to allow: two 8-wave workgroups per CU for the narrow gate/up form, so that one
+  // workgroup's prologue and reduction overlap the other's streaming
+  static constexpr int WPS = NW == 16 || (EPI == SK_SWIGLU && NT == 2) ? 4 : (NW == 4 && MT <= 2) ? 1 : 2;
+};
+template <int NT, int MT, int NW, int EPI>
+static hipError_t sk_go(hipStream_t s, const SkArgs& a, int grid) {
+  using C = SkCfg<NT, MT, NW, EPI>;
+  k_skinny<NT, MT, NW, EPI, C::JB, C::TPC, C::D, C::WPS><<<grid, NW * 64, 0, s>>>(a);
+  return hipGetLastError();
 }
 
 template <int NT, int NW, int EPI>
 static hipError_t sk_launch_mt(hipStream_t s, const SkArgs& a, int grid) {
   const int mt = (a.M + 15) / 16;
   switch (mt) {
-    case 1: k_skinny<NT, 1, NW, EPI><<<grid, NW * 64, 0, s>>>(a); break;
-    case 2: k_skinny<NT, 2, NW, EPI><<<grid, NW * 64, 0, s>>>(a); break;
-    case 3: k_skinny<NT, 3, NW, EPI><<<grid, NW * 64, 0, s>>>(a); break;
-    case 4: k_skinny<NT, 4, NW, EPI><<<grid, NW * 64, 0, s>>>(a); break;
-    default: return hipErrorInvalidValue;
+    case 1: return sk_go<NT, 1, NW, EPI>(s, a, grid);
+    case 2: return sk_go<NT, 2, NW, EPI>(s, a, grid);
+    case 3: return sk_go<NT, 3, NW, EPI>(s, a, grid);
+    case 4: return sk_go<NT, 4, NW, EPI>(s, a, grid);
   }
-  return hipGetLastError();
+  if constexpr (EPI == SK_QKV) {
+    switch (mt) {
+      case 5: return sk_go<NT, 5, NW, EPI>(s, a, grid);
+      case 6: return sk_go<NT, 6, NW, EPI>(s, a, grid);
+      case 7: return sk_go<NT, 7, NW, EPI>(s, a, grid);
+      case 8: return sk_go<NT, 8, NW, EPI>(s, a, grid);
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
 // ---- weight packing ---------------------------------------------------------------------------
@@ -669,7 +749,8 @@ hipError_t launch_sk_f32(dllm_ctx* c, hipStream_t s, const void* A, const void* 
 hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int layer, const KVView& pool, int n_ss) {
   const dllm_config& f = c->cfg;
   SkArgs a = sk_base(c->ws + c->map.xn, g.T, f.d_model);
-  sk_row_scale(c, a, n_ss);
+  if (g.T > SK_MAX_ROWS) a.rscale = WSM(c, rscale, float);
+  else sk_row_scale(c, a, n_ss);
   const dllm_layer_w& P = c->packed_layers[layer];
   a.W0 = (const bf16_t*)P.wq; a.W1 = (const bf16_t*)P.wk; a.W2 = (const bf16_t*)P.wv;
   a.N0 = f.n_q_heads * f.head_dim; a.N1 = a.N2 = f.n_kv_heads * f.head_dim;
@@ -682,7 +763,11 @@ hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int laye
   a.tok_seq = WSM(c, tok_seq, int32_t); a.tok_pos = WSM(c, tok_pos, int32_t);
   a.pool_k = (bf16_t*)pool.k; a.pool_v = (bf16_t*)pool.v; a.pool = pool;
   a.status = WSM(c, status, int32_t);
-  const int n_pairs = a.n_q_wg + a.n_k_wg, n_vt = (a.N2 + 15) / 16;
+  const int n_pairs = a.n_q_wg + a.n_k_wg, n_vt = (a.N2 + 15) / 16, apart = n_pairs + (n_vt + 1) / 2;
+  // Value tiles in workgroups of their own where all then still run at once (few key heads: 128 pair tiles and 32 value
+  // tiles took 128 workgroups of three tiles, most of them with one to throw away: 16.0 -> 13.1 us at 32 rows of 3584,
+  // 21.4 -> 19.0 at 64, 27.8 -> 24.3 at 128).
+  if (apart <= 256) return sk_launch_mt<2, SK_NW, SK_QKV>(s, a, apart);
   return sk_launch_mt<3, SK_NW, SK_QKV>(s, a, n_pairs > n_vt ? n_pairs : n_vt);
 }
 
@@ -695,9 +780,14 @@ hipError_t launch_sk_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_
   a.W0 = (const bf16_t*)P.w_gate; a.W1 = (const bf16_t*)P.w_up;
   a.N0 = f.d_ff;
   a.out_bf16 = WSM(c, h, bf16_t);
-  // (three tile pairs per workgroup -- 256 equal workgroups at F = 12288, a third of the activation reads --
-  // measured no faster than one: 40.8 against 41.7 us)
-  return sk_launch_mt<2, SK_NW, SK_SWIGLU>(s, a, (f.d_ff + 15) / 16);
+  // Three tile pairs per workgroup read the activations a third as often.  With one pair those reads are as many bytes as
+  // the weights at 32 rows and twice as many at 64, and although the L2 serves them their time adds to the stream's (a
+  // stream of 200 MB from memory with 0 / 200 / 400 / 800 MB from the L2 beside it: 32 / 37 / 46 / 64 us).  F = 12288,
+  // K = 4096, us, one pair / three: 32 rows 40.0 / 38.1, 48 rows 46.4 / 40.4, 64 rows 59.2 / 42.4; F = 18944, K = 3584: 57.1 /
+  // 55.1, -, 82.1 / 68.3; 16 rows 36.3 / 36.7 and 48.1 / 51.3, hence one there; and one where three would leave CUs idle.
+  const int pairs = (f.d_ff + 15) / 16;
+  if (M > 16 && pairs >= 3 * 192) return sk_launch_mt<6, SK_NW, SK_SWIGLU>(s, a, (pairs + 2) / 3);
+  return sk_launch_mt<2, SK_NW, SK_SWIGLU>(s, a, pairs);
 }
 
 // The compacted rows of a forward of many tokens (ws.xn row-major x * gain; the norm has left their mean squares in

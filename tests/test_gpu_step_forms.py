@@ -1,0 +1,30 @@
+"""GPU parity of the weight-streaming kernels' forms that the small models of the other tests do not reach: gate/up with
+three tile pairs per workgroup (d_ff of at least 9216), the q/k/v product with the value tiles beside the rotary pairs
+(many heads) and in workgroups of their own (few key heads), at row counts on both sides of every 16-row tile and at sums
+with no, one and several stages per wave and a ragged end.  Reference and tolerance as in test_gpu_gemm_tiles.py."""
+import pytest
+
+from paper_2601_07568_amd import synth
+from tests.test_gpu_gemm_tiles import run
+
+pytestmark = pytest.mark.gpu
+
+
+def shape(d, hq, hkv, dh, ff, vocab=600):
+    return synth.ModelShape(1, d, hq, hkv, dh, ff, vocab, vocab - 1, dtype="bf16", lm_head_scale=8.0, name=f"forms-{d}-{hq}-{hkv}-{ff}")
+
+
+# 577 tile pairs: the last workgroup has one of three; d_model 104: no whole 128, a ragged last stage
+WIDE = shape(104, 2, 2, 64, 9232)
+# 33 stages of 32: one to five a wave; 580 pairs
+DEEP = shape(1056, 4, 1, 64, 9280)
+# 192 pair tiles and 192 value tiles (three tiles per workgroup)
+HEADS = shape(136, 24, 24, 128, 320)
+# 72 pair tiles, 8 value tiles in four workgroups
+GROUPED = shape(264, 17, 1, 128, 320)
+
+
+@pytest.mark.parametrize("B,Q", [(1, 7), (1, 17), (1, 32), (3, 11), (1, 48), (7, 7), (2, 32)])
+@pytest.mark.parametrize("ms", [WIDE, DEEP, HEADS, GROUPED], ids=["wide", "deep", "heads", "grouped"])
+def test_rows_of_a_step(ms, B, Q):
+    run(ms, [40 + 9 * b for b in range(B)], Q)
