@@ -336,6 +336,18 @@ static bool large_mfma(const dllm_ctx* c) {
   return c->cfg.dtype == DLLM_BF16 && c->kernel_mode == 0 && c->cfg.d_ff % 4 == 0 && c->cfg.vocab % 4 == 0;
 }
 
+// Steps of 65 .. 128 rows: the q/k/v product with its rotary embedding and K/V write still comes from the packed weights
+// (the other products are quicker on the tile kernel).  12288 x 4096, us, the split tile product + the rotary kernel behind
+// it / this one: 128 rows 32 + 16 / 35, 96 rows 30 on this one, 80 rows 28; at 256 rows a workgroup's accumulators no
+// longer fit its registers.
+static bool sk_qkv_rows(const dllm_ctx* c, const StepGeom& g) {
+  return mfma_supported(c) && large_mfma(c) && g.Q > 0 && g.T > SK_MAX_ROWS && g.T <= SK_QKV_ROWS;
+}
+// the q/k/v product of many rows with the rotary embedding in it
+static bool tile_qkv_rope(const dllm_ctx* c, const StepGeom& g) {
+  return large_mfma(c) && !sk_qkv_rows(c, g) && gemm_qkv_rope_wins(c, g.T);
+}
+
 static int run_forward(dllm_ctx* c, hipStream_t s, const StepGeom& g0, int n_layers_run, const HeadOut* head,
                        float* logits_out, float* hidden_out) {
   // the first launches check the device-resident lengths against the host values that size the launches and leave
@@ -346,7 +358,7 @@ static int run_forward(dllm_ctx* c, hipStream_t s, const StepGeom& g0, int n_lay
     TRY(launch_sk_prologue(c, s, g0, n_layers_run > 0 ? c->layers[0].attn_norm : c->final_norm,
                            head ? head->cand : nullptr, head ? head->conf : nullptr, head ? head->entropy : nullptr),
         "prologue");
-  else TRY(launch_token_map(c, s, g0, n_layers_run > 0 && large_mfma(c) && gemm_qkv_rope_wins(c, g0.T)), "token_map");
+  else TRY(launch_token_map(c, s, g0, n_layers_run > 0 && tile_qkv_rope(c, g0)), "token_map");
   StepGeom g = g0;
   if (g.Q > 0) g.prefix_len = WSP(c, len_safe, int32_t);
   else g.cu_seqlens = WSP(c, len_safe, int32_t);
@@ -381,21 +393,23 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   // float denoise steps of as few rows: the same chain of launches, the gain applied by the consuming product
   const bool s32 = s32_supported(c, g), few = sk || s32;
   const bool big_mfma = large_mfma(c);
-  const bool qkv_rope = !sk && big_mfma && gemm_qkv_rope_wins(c, T);   // (the token map has left the rows' K/V places)
+  const bool sk_qkv = !sk && sk_qkv_rows(c, g);
+  const int qkv_mt = sk_qkv ? (T + 15) / 16 : 0;               // its input is in fragment order
+  const bool qkv_rope = !sk && tile_qkv_rope(c, g);   // (the token map has left the rows' K/V places)
   const int ss_groups = (f.d_model + 15) / 16;
   int n_ss = 1;      // partial sums of squares the current skinny-path GEMM input comes with
   bool normed = false;  // the first layer's norm came with the embedding
   if (!few) {           // (on the few-row paths run_forward's prologue launch has done both)
-    TRY(launch_embed(c, s, g, n_layers_run > 0 ? c->layers[0].attn_norm : nullptr, &normed), "embed");
+    TRY(launch_embed(c, s, g, n_layers_run > 0 ? c->layers[0].attn_norm : nullptr, &normed, qkv_mt), "embed");
     TRY(launch_rope_table(c, s, g), "rope_table");
   }
   int pending = 0;   // open residual sums (K splits of the last residual projection) not yet added to x
   for (int l = 0; l < n_layers_run; ++l) {
     const dllm_layer_w& L = c->layers[l];
-    if (!few && !(l == 0 && normed)) TRY(launch_rmsnorm(c, s, L.attn_norm, T, nullptr, nullptr, 0, pending), "rmsnorm");
+    if (!few && !(l == 0 && normed)) TRY(launch_rmsnorm(c, s, L.attn_norm, T, nullptr, nullptr, qkv_mt, pending), "rmsnorm");
     pending = 0;
-    if (sk) {
-      ProfScope p(c, s, 0, 2.0 * (dq + 2.0 * dkv) * f.d_model);
+    if (sk || sk_qkv) {
+      ProfScope p(c, s, 0, 2.0 * (dq + 2.0 * dkv) * f.d_model * (sk ? 1 : T));   // bytes; many rows: flops
       TRY(launch_sk_qkv(c, s, g, l, attention_view(c, g, l), n_ss), "qkv");
     } else if (s32) {
       ProfScope p(c, s, 0, 2.0 * T * (dq + 2.0 * dkv) * f.d_model);   // (work of the float paths: in flops)

@@ -222,8 +222,8 @@ hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool 
 // the LM head's row list with the fixed outputs of the rows that are not masked, in one launch
 hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, int32_t* cand,
                               float* conf, float* entropy);
-// gain: of the norm that reads the embeddings, or nullptr; *normed: that norm has been applied in the same launch
-hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed);
+// gain: of the norm that reads the embeddings, or nullptr; *normed: that norm has been applied in the same launch (frag_mt as below)
+hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed, int frag_mt = 0);
 hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g);
 // out[T or n_rows, d] = rmsnorm(x[row]) * gain; rows == nullptr: identity row map, n = T
 // frag_mt > 0: write in fragment order for frag_mt 16-row tiles (bfloat16 only)
@@ -286,6 +286,7 @@ bool mfma_supported(const dllm_ctx* c);
 size_t packed_weight_bytes(int N, int K);
 hipError_t launch_pack_weight(hipStream_t s, const void* W, void* P, int N, int K);
 constexpr int SK_MAX_ROWS = 64;   // the skinny (weight-streaming) kernels take at most this many rows
+constexpr int SK_QKV_ROWS = 128;  // ... their q/k/v product this many
 KVView attention_view(dllm_ctx* c, const StepGeom& g, int layer);
 // n_ss: partial sums of squares per row the GEMM input comes with (1 after the embedding, d_model / 64 after a
 // residual projection)

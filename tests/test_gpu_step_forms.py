@@ -1,7 +1,8 @@
 """GPU parity of the weight-streaming kernels' forms that the small models of the other tests do not reach: gate/up with
 three tile pairs per workgroup (d_ff of at least 9216), the q/k/v product with the value tiles beside the rotary pairs
-(many heads) and in workgroups of their own (few key heads), at row counts on both sides of every 16-row tile and at sums
-with no, one and several stages per wave and a ragged end.  Reference and tolerance as in test_gpu_gemm_tiles.py."""
+(many heads) and in workgroups of their own (few key heads), the latter also at 65 .. 128 rows behind a norm that writes in
+fragment order, at row counts on both sides of every 16-row tile and at sums with no, one and several stages per wave and a
+ragged end.  Reference and tolerance as in test_gpu_gemm_tiles.py."""
 import pytest
 
 from paper_2601_07568_amd import synth
@@ -27,4 +28,10 @@ GROUPED = shape(264, 17, 1, 128, 320)
 @pytest.mark.parametrize("B,Q", [(1, 7), (1, 17), (1, 32), (3, 11), (1, 48), (7, 7), (2, 32)])
 @pytest.mark.parametrize("ms", [WIDE, DEEP, HEADS, GROUPED], ids=["wide", "deep", "heads", "grouped"])
 def test_rows_of_a_step(ms, B, Q):
+    run(ms, [40 + 9 * b for b in range(B)], Q)
+
+
+@pytest.mark.parametrize("B,Q", [(1, 65), (1, 80), (3, 27), (1, 96), (1, 111), (4, 32), (1, 129)])
+@pytest.mark.parametrize("ms", [DEEP, HEADS, GROUPED], ids=["deep", "heads", "grouped"])
+def test_qkv_of_65_to_128_rows(ms, B, Q):
     run(ms, [40 + 9 * b for b in range(B)], Q)
