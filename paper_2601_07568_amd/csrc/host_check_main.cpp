@@ -69,7 +69,7 @@ static int ring_errors(int ring, int nsw, int stages, int n_items, int slots) {
 }
 
 int main() {
-  const int rings[][2] = {{2, 3}, {3, 4}, {4, 5}};
+  const int rings[][2] = {{2, 3}, {3, 4}, {4, 5}, {3, 3}, {4, 4}, {5, 5}};
   for (const auto& r : rings)
     for (int stages = 2; stages <= 8; ++stages)
       for (int n_items = 1; n_items <= 48; ++n_items) {       // on 8 places: up to six items after each other

@@ -312,10 +312,11 @@ typedef __amdgpu_buffer_rsrc_t gt_rsrc;
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 #define GT_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
 
-template <int TM, int TN, int NSA, int NSW>
+// WM: waves along the token rows (the others lie along the weight rows)
+template <int TM, int TN, int NSA, int NSW, int WM = 2>
 struct GtGeom {
   static_assert(NSA >= 2 && NSA <= NSW, "the weights run at least as far ahead as the activations");
-  static constexpr int BM = 64 * TM, BN = 64 * TN, A_BYTES = BM * 128, W_BYTES = BN * 128;
+  static constexpr int BM = 32 * WM * TM, BN = 32 * (4 / WM) * TN, A_BYTES = BM * 128, W_BYTES = BN * 128;
   static constexpr int CA = BM / 32, CW = BN / 32;              // copies of a wave and stage (8 rows x 128 bytes each)
   static constexpr int LDS = NSA * A_BYTES + NSW * W_BYTES;
   static constexpr int PER_CU = LDS <= 80 * 1024 ? 2 : 1;       // workgroups that fit a CU
@@ -339,9 +340,9 @@ struct GtGeom {
 // HALF: K is 32 more than a multiple of 64.  The last stage's upper 32 come from past the end of the row, so their copies
 // are sent out of the descriptor, which leaves zeros in LDS.  A form of its own: it takes 19 .. 21 instructions more per stage
 // (128 x 128: 146 for 125).
-template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF>
+template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF, int WM>
 __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
-  using G = GtGeom<TM, TN, NSA, NSW>;
+  using G = GtGeom<TM, TN, NSA, NSW, WM>;
   constexpr int BM = G::BM, BN = G::BN, CA = G::CA, CW = G::CW;
   constexpr bool SWIGLU = EPI == LG_SWIGLU, STATS = EPI == LG_LMSTATS || EPI == LG_LMSTATS_X, ROPE = EPI == LG_ROPE64 || EPI == LG_ROPE128;
   constexpr bool QKV = EPI == LG_QKV || ROPE;
@@ -349,7 +350,9 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   constexpr bool WIDE = EPI == LG_ROPE128 && TN == 4;           // a wave's weight rows are one whole head of 128 channels
   static_assert(!ROPE || (TM == TN && TN % 2 == 0), "value tiles swap the operands; rotary pairs share a lane");
   constexpr int TILE_N = SWIGLU ? BN / 2 : BN;                  // output features of a tile
-  static_assert(!SWIGLU || TN % 2 == 0, "gate and up tiles come in pairs");
+  // gate and up tiles come in pairs; of an odd number the last holds 16 gate rows and the same 16 up rows
+  constexpr bool ODD = SWIGLU && TN % 2 == 1;
+  static_assert((WM == 2 || ODD) && !(ODD && HALF), "other layouts of the waves are built for odd gate/up tiles alone");
   static_assert(!STATS || TN % 2 == 0, "64 columns per partial");
   extern __shared__ __attribute__((aligned(1024))) unsigned char gt_smem[];
   unsigned char* const sA = gt_smem;
@@ -359,7 +362,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   int M = a.M;
   if (a.m_dev) { const int md = *a.m_dev; M = md < M ? md : M; }
   const int N = a.N, K = a.K, k_all = HALF ? K + 32 : K;        // k_all: in whole stages
-  const int wm = w & 1, wn = w >> 1;
+  const int wm = w % WM, wn = w / WM;
   const int r = lane & 31, h = lane >> 5;
   // Persistent workgroups: the work items are K splits, in a split groups of at most group_m row tiles, in a group column
   // by column, in the order of gt_item: what runs at the same time next to one L2 shares its rows and columns (with 64 row
@@ -371,7 +374,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // channels: 4.5 against 6.4 TB/s of plain reads with rows of 8 KiB.  Neighbouring columns of 256 weight rows begin 11
   // stages apart instead.  With more rows the activations no longer stay in the L2, which the column tiles share only in step.
   // (128 rows: 24576 x 4096 53.6 -> 51.7 us, 12288 x 4096 33.5 -> 30.9; a whole pass of 128 rows 782 -> 746 us.)  By the rows
-  // there are and not the host's bound, by weight rows and not tiles: where a call with a device-resident total gets the
+  // there are and not the host's bound, by weight rows and not tiles (gate/up: by 1920 features, which tiles of every width end
+  // at; per tile 43.9 us and so 44.9 for 128 x 24576 x 4096 on 128 x 96 tiles, 59.7 and 58.9 at 256 rows): where a call with a device-resident total gets the
   // same K split and the same q/k/v form as the sized call, it sums in the same order whatever its tiles.  Those two are
   // chosen by the host's bound (4096 x 4096: three shares at 600 rows, one at 700), so it need not get them; and a
   // row's sums begin elsewhere when the rows of its call pass 256.
@@ -390,7 +394,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     t.tn += a.tn0;
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < k_all ? t.k_begin + a.k_per : k_all;
-    t.k_first = t.k_begin + (t.tn * BN / 256 * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
+    t.k_first = t.k_begin + ((SWIGLU ? t.tn * TILE_N / 1920 : t.tn * BN / 256) * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
     t.ok = true;
     t.val = ROPE && t.tn * TILE_N >= N + a.N2;                  // a tile of the value projection
     return t;
@@ -414,7 +418,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
       rows = BN;
     }
     if constexpr (SWIGLU) {
-      if (w & 1) base = a.W2;                                   // a wave copies gate rows or up rows
+      if (ODD ? w >> 1 : w & 1) base = a.W2;                    // a wave copies gate rows or up rows
     }
     return rsrc(base + (int64_t)row * K, (int64_t)rows * K * 2);
   };
@@ -429,11 +433,19 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // copies: instruction q of wave w fills LDS rows (w*C + q)*8 .. +7; lane l holds piece l%8 of row l/8
   const int l8 = lane >> 3, piece = (lane & 7) ^ (l8 >> 1);     // (odd q: the row's bit 3 flips bit 2 of the piece)
   // features between consecutive LDS rows of a tile
-  constexpr int FS = STATS ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
+  constexpr int FS = STATS || ODD ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
   const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = HALF ? vA0 + (piece < 4 ? 64 : -64) : vA0 ^ 64;
   const int vW0 = l8 * FS * K * 2 + piece * 16, vW1 = HALF ? vW0 + (piece < 4 ? 64 : -64) : vW0 ^ 64;
   const int out0 = piece < 4 ? 0 : 0x40000000, out1 = piece < 4 ? 0x40000000 : 0;   // HALF: added in the last stage (even, odd q)
+  // ODD: waves 0 and 1 copy the gate rows, waves 2 and 3 the up rows, eight at a time in the order of the features; a wave's
+  // first 4*(TN/2) eights are its whole tiles, the other two its half of the last
+  auto odd_lds = [&](int q) -> int {                            // LDS row of the instruction's first row
+    constexpr int PER = 2 * TN, P = TN / 2;
+    const int gu = (w & 1) * CW + q, hw = gu / PER, u = gu - hw * PER, up = w >> 1;
+    return hw * 32 * TN + (u < 4 * P ? (up * P + (u >> 2)) * 32 + (u & 3) * 8 : 2 * P * 32 + up * 16 + (u - 4 * P) * 8);
+  };
   auto w_row = [&](int q) -> int {                              // weight row of the instruction's first LDS row
+    if constexpr (ODD) return ((w & 1) * CW + q) * 8;
     const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
     if constexpr (STATS) return R;
     // both members of a rotary pair (channels j and j + DH/2 of a head) in one lane, in tiles i and i + 2 (WIDE: two
@@ -453,7 +465,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
 #pragma unroll
     for (int q = 0; q < CA; ++q) vA[q] = ((q & 1) ? vA1 : vA0) + q * 16 * K;
 #pragma unroll
-    for (int q = 0; q < CW; ++q) vW[q] = ((q & 1) ? vW1 : vW0) + w_row(q) * 2 * K;
+    for (int q = 0; q < CW; ++q) vW[q] = ((ODD ? (odd_lds(q) >> 3) & 1 : q & 1) ? vW1 : vW0) + w_row(q) * 2 * K;
   }
   auto past = [&](int k, int q) -> int { return HALF && k + 64 > K ? ((q & 1) ? out1 : out0) : 0; };
   auto copy_a = [&](int slot, int q) {
@@ -461,7 +473,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
                                              16, (VO ? vA[q] : (q & 1) ? vA1 : vA0) + past(ka, q), VO ? ka * 2 : ka * 2 + q * 16 * K, 0, 0);
   };
   auto copy_w = [&](int slot, int q) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (w * CW + q) * 1024),
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (ODD ? odd_lds(q) * 128 : (w * CW + q) * 1024)),
                                              16, (VO ? vW[q] : (q & 1) ? vW1 : vW0) + past(kw, q), VO ? kw * 2 : kw * 2 + w_row(q) * 2 * K, 0, 0);
   };
   auto adv_a = [&]() { GT_ADVANCE(ka, ksa, kba, kea, nxt, ra = rna); };
@@ -491,8 +503,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int p = ((h ^ ((r >> 1) & 7)) * 16) ^ (ks * 32);
-    oA[ks] = (wm * (BM / 2) + r) * 128 + p;
-    oW[ks] = (wn * (BN / 2) + r) * 128 + p;
+    oA[ks] = (wm * (BM / WM) + r) * 128 + p;
+    oW[ks] = (wn * (BN / (4 / WM)) + r) * 128 + p;
   }
   u32x4 fa[2][TM], fw[2][TN];
   auto rd = [&](int b, int n, const unsigned char* pa, const unsigned char* pw) {   // in the order the products need them
@@ -776,6 +788,43 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
           }
         }
       }
+    } else if constexpr (ODD) {
+      // Lane holds gate and up rows l%32 of tiles i and TN/2 + i; of the last tile the lanes with l%32 < 16 hold gate rows and the
+      // others the up rows of the same features: two registers (two token rows) exchange their halves, and each lane has one row.
+      constexpr int P = TN / 2;
+      const gt_rsrc ro = rsrc((char*)a.C + (int64_t)m0 * N * 2, (int64_t)rows * N * 2);
+      const int lrow = wm * 32 * TM + h * 4, nw = n0 + wn * 16 * TN;
+      auto act = [](float gt, float up, float rs) -> uint32_t {
+        gt *= rs;
+        return f32_to_bf16(gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt)) * (up * rs));
+      };
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 rs4[4];
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4)
+          rs4[e4] = a.rscale ? __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, lrow * 4, (j * 32 + e4 * 8) * 4, 0))
+                             : f32x4{1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          const int n = nw + i * 32 + r;
+          if (n >= N) continue;
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)act(acc[i][j][e], acc[P + i][j][e], rs4[e >> 2][e & 3]), ro, (lrow * N + n) * 2,
+                                                  (j * 32 + (e >> 2) * 8 + (e & 3)) * N * 2, 0);
+        }
+        const int n = nw + P * 32 + (r & 15), odd = r >> 4;
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          const u32x2_t x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[TN - 1][j][e]), __float_as_uint(acc[TN - 1][j][e + 1]), false, false);
+          const float rs = odd ? rs4[e >> 2][(e & 3) + 1] : rs4[e >> 2][e & 3];
+          const uint32_t v = act(__uint_as_float(x[0]), __uint_as_float(x[1]), rs);
+          if (n < N)
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, ro, ((lrow + odd) * N + n) * 2, (j * 32 + (e >> 2) * 8 + (e & 3)) * N * 2, 0);
+        }
+      }
     } else {
       // lane holds weight rows TN*(l%32) .. of its tiles and, in register e, token row (e/4)*8 + (l/32)*4 + e%4
       const int n = n0 + (SWIGLU ? wn * 16 * TN + (TN / 2) * r : wn * 32 * TN + TN * r);
@@ -854,8 +903,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));   // the trailing repeats must not outlive the workgroup
 }
 
-template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF = false>
-__global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW, HALF>(a); }
+template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF = false, int WM = 2>
+__global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW, HALF, WM>(a); }
 
 // Rings above the default LDS limit of a kernel: raised once per process.
 static bool gt_ready = false;
@@ -867,14 +916,16 @@ static int gt_cus = 256;
   X(LG_ROPE128, 4, 4, 2, 3) X(LG_ROPE128, 2, 2, 4, 5) X(LG_ROPE128, 2, 2, 2, 3)                         \
   X(LG_QKV, 4, 4, 2, 3) X(LG_QKV, 2, 4, 2, 3) X(LG_QKV, 2, 2, 4, 5) X(LG_QKV, 2, 1, 3, 4)               \
   X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS_X, 4, 4, 2, 3) X(LG_LMSTATS_X, 2, 2, 4, 5)
+// gate/up in tiles of an odd number of 32 weight rows, all four waves along the token rows
+#define GT_ODD_KERNELS(X) X(1, 3, 5, 5) X(1, 5, 4, 4) X(2, 3, 3, 3) X(2, 5, 3, 3)
 // the forms that are also built for K of 32 more than a multiple of 64
 template <int EPI, int TM, int TN>
 constexpr bool GT_HALF = (TM == TN || TN == 1) && EPI != LG_ROPE64 && EPI != LG_ROPE128;
-template <int EPI, int TM, int TN, int NSA, int NSW>
+template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2>
 static hipError_t gt_raise_lds() {
-  constexpr int lds = GtGeom<TM, TN, NSA, NSW>::LDS;
-  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if constexpr (GT_HALF<EPI, TM, TN>)
+  constexpr int lds = GtGeom<TM, TN, NSA, NSW, WM>::LDS;
+  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, false, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if constexpr (WM == 2 && GT_HALF<EPI, TM, TN>)
     if (e == hipSuccess)
       e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   return e;
@@ -889,6 +940,9 @@ hipError_t init_gemm_tiles() {
 #define X(E, TM, TN, NA, NW) if (e == hipSuccess) e = gt_raise_lds<E, TM, TN, NA, NW>();
   GT_KERNELS(X)
 #undef X
+#define X(TM, TN, NA, NW) if (e == hipSuccess) e = gt_raise_lds<LG_SWIGLU, TM, TN, NA, NW, 4>();
+  GT_ODD_KERNELS(X)
+#undef X
   gt_ready = e == hipSuccess;
   return e;
 }
@@ -896,12 +950,12 @@ hipError_t init_gemm_tiles() {
 // 18976, us, k_gemm_mfma / this kernel: 97 rows 658 / 432, 700 rows 1438 / 892, 3000 rows 5508 / 3226)
 static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 32 == 0 && K >= 128; }
 // of a mask of tiles (bit per GtTile) those that are built for this K
-static unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0x2u; }
+static unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0xf2u; }
 
 // the column tiles [tn0, tn0 + n_tn) of a product (n_tn 0: all of them)
-template <int EPI, int TM, int TN, int NSA, int NSW>
+template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2>
 static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 = 0, int n_tn = 0) {
-  using G = GtGeom<TM, TN, NSA, NSW>;
+  using G = GtGeom<TM, TN, NSA, NSW, WM>;
   constexpr int tile_n = EPI == LG_SWIGLU ? G::BN / 2 : G::BN;
   a.tiles_m = (a.M + G::BM - 1) / G::BM;
   constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128;
@@ -913,31 +967,40 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
   a.group_m = 8;
   const int last_k = k_all - (k_splits - 1) * a.k_per;          // the last share is the shortest
   const int wgs = gt_workgroups(a.tiles_m * a.tiles_n * k_splits, gt_cus * G::PER_CU, (last_k < a.k_per ? last_k : a.k_per) / 64, NSW);
-  if constexpr (GT_HALF<EPI, TM, TN>) {
+  if constexpr (WM == 2 && GT_HALF<EPI, TM, TN>) {
     if (a.K != k_all) {
       k_gemm_tile<EPI, TM, TN, NSA, NSW, true><<<wgs, 256, G::LDS, s>>>(a);
       return hipGetLastError();
     }
   }
   if (a.K != k_all) return hipErrorInvalidValue;
-  k_gemm_tile<EPI, TM, TN, NSA, NSW><<<wgs, 256, G::LDS, s>>>(a);
+  k_gemm_tile<EPI, TM, TN, NSA, NSW, false, WM><<<wgs, 256, G::LDS, s>>>(a);
   return hipGetLastError();
 }
 
 // Which tile: the estimate counts rounds of one workgroup per CU in units of a 256 x 256 tile's time.  A 128 x 256 tile
 // costs 0.6 of it (half the products, three quarters of the bytes), a 128 x 128 one 0.33 (copies and products take
-// equally long), a 128 x 64 one 0.22.  Measured against each other (K = 3584 .. 18944, us): 1024 x 37888: 271 / 286 /
+// equally long), a 128 x 64 one 0.22, a 256 x 160 one 0.80, a 256 x 96 one 0.54, a 128 x 160 one 0.45.  Measured against each other (K = 3584 .. 18944, us): 1024 x 37888: 271 / 286 /
 // 297; 256 x 24576: 85 / 55 / 61; 128 x 24576: 85 / 50 / 39; 1024 x 3584 x 3584: 48 (4 K shares) / 38 (2) / 42.
 // Over 200 layers of 128 .. 8192 channels and 96 .. 16384 rows, 257 .. 511 among them, what it picks takes 0.47 .. 0.98 of the
 // time of the 32-deep kernels that were here before.
-enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_N = 4 };
+//
+// The odd widths are gate/up's alone: one round of one tile per CU decides there up to about 500 rows, and 128 and 256
+// columns seldom make one (256 CUs; 24576 gate and up rows: 256 tiles of 96, 37888: 237 of 160).  Measured, the best of the
+// even tiles / these, us: 24576 x 4096: 128 rows 47.9 / 44.2 (128 x 96), 211 rows 59.3 / 56.9 and 256 rows 61.5 / 59.8 (256 x
+// 96), 300 rows 101 / 84 (128 x 160); 37888 x 3584: 65 rows 61.7 / 53.3 and 128 rows 67.3 / 58.4 (128 x 160), 211 rows
+// 83.5 / 71.8 and 256 rows 87.6 / 74.9 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its weights are all from
+// memory and two thirds of the CUs ask for them.
+enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_N = 8 };
+constexpr unsigned GT_ODD_TILES = 0xf0u;
 struct GtPlan { GtTile tile; int splits, k_per; double us; };
 // NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile that its widths allow
 // fold_us_per_share: what each share behind the first costs (written here, read by the kernel that adds it)
 static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok, double fold_us_per_share) {
-  static const int bm[GT_N] = {256, 128, 128, 128}, bn[GT_N] = {256, 256, 128, 64};
+  static const int bm[GT_N] = {256, 128, 128, 128, 128, 128, 256, 256}, bn[GT_N] = {256, 256, 128, 64, 96, 160, 96, 160};
   // (up to 256 rows a 128-row tile waits for its weights, which no other row tile has brought in)
-  const double unit[GT_N] = {1.0, 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22};
+  const double unit[GT_N] = {1.0, M <= 128 && (width_ok & GT_ODD_TILES) ? 0.68 : 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22,
+                             M <= 128 ? 0.39 : 0.45, M <= 128 ? 0.60 : 0.45, 0.54, 0.80};
   GtPlan best{GT_128x128, 1, K, 1e30};
   for (int c = 0; c < GT_N; ++c) {
     if (!((gt_built(K, width_ok) >> c) & 1u)) continue;
@@ -1138,7 +1201,7 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
   a.m_dev = m_dev;
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wg; a.W2 = (const bf16_t*)Wu; a.C = H; a.M = M; a.N = F; a.K = K;
   if (gt_usable(M, K)) {
-    const GtPlan p = gt_plan(M, 2 * F, K, 1, 0x7u, 0.0);
+    const GtPlan p = gt_plan(M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0);
     const int n_tn = gt_whole_rounds(M, 2 * F, K, 0x6u, p.us);
     if (n_tn > 0) {
       const hipError_t e = gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, 0, n_tn);
@@ -1149,6 +1212,10 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
     switch (p.tile) {
       case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a);
       case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a);
+      case GT_128x96: return gt_launch<LG_SWIGLU, 1, 3, 5, 5, 4>(s, a);
+      case GT_128x160: return gt_launch<LG_SWIGLU, 1, 5, 4, 4, 4>(s, a);
+      case GT_256x96: return gt_launch<LG_SWIGLU, 2, 3, 3, 3, 4>(s, a);
+      case GT_256x160: return gt_launch<LG_SWIGLU, 2, 5, 3, 3, 4>(s, a);
       default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a);
     }
   }

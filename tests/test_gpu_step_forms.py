@@ -35,3 +35,12 @@ def test_rows_of_a_step(ms, B, Q):
 @pytest.mark.parametrize("ms", [DEEP, HEADS, GROUPED], ids=["deep", "heads", "grouped"])
 def test_qkv_of_65_to_128_rows(ms, B, Q):
     run(ms, [40 + 9 * b for b in range(B)], Q)
+
+
+# gate/up in tiles of 96 and 160 weight rows: 24704 rows end inside a tile of either (on 256 CUs the first is taken for them up
+# to 256 rows), 37888 rows take the second; a sum of three stages is shorter than its ring, one of eight longer.  300 rows: a
+# second row tile, two items for some workgroups
+@pytest.mark.parametrize("rows", [(1, 65), (1, 128), (3, 43), (1, 160), (2, 128), (3, 100)])
+@pytest.mark.parametrize("d,ff", [(192, 12352), (512, 12352), (192, 18944)])
+def test_gate_up_in_odd_tiles(d, ff, rows):
+    run(shape(d, 2, 2, 64, ff), [5 + b for b in range(rows[0])], rows[1])
