@@ -348,6 +348,11 @@ static bool tile_qkv_rope(const dllm_ctx* c, const StepGeom& g) {
   return large_mfma(c) && !sk_qkv_rows(c, g) && gemm_qkv_rope_wins(c, g.T);
 }
 
+// steps off the few-row paths whose first launch is launch_step_prologue
+static bool step_prologue(const dllm_ctx* c, const StepGeom& g, int n_layers_run) {
+  return g.Q > 0 && n_layers_run > 0 && step_prologue_usable(c);
+}
+
 static int run_forward(dllm_ctx* c, hipStream_t s, const StepGeom& g0, int n_layers_run, const HeadOut* head,
                        float* logits_out, float* hidden_out) {
   // the first launches check the device-resident lengths against the host values that size the launches and leave
@@ -357,6 +362,9 @@ static int run_forward(dllm_ctx* c, hipStream_t s, const StepGeom& g0, int n_lay
   if (pro)
     TRY(launch_sk_prologue(c, s, g0, n_layers_run > 0 ? c->layers[0].attn_norm : c->final_norm,
                            head ? head->cand : nullptr, head ? head->conf : nullptr, head ? head->entropy : nullptr),
+        "prologue");
+  else if (step_prologue(c, g0, n_layers_run))
+    TRY(launch_step_prologue(c, s, g0, c->layers[0].attn_norm, tile_qkv_rope(c, g0), sk_qkv_rows(c, g0) ? (g0.T + 15) / 16 : 0),
         "prologue");
   else TRY(launch_token_map(c, s, g0, n_layers_run > 0 && tile_qkv_rope(c, g0)), "token_map");
   StepGeom g = g0;
@@ -398,8 +406,8 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   const bool qkv_rope = !sk && tile_qkv_rope(c, g);   // (the token map has left the rows' K/V places)
   const int ss_groups = (f.d_model + 15) / 16;
   int n_ss = 1;      // partial sums of squares the current skinny-path GEMM input comes with
-  bool normed = false;  // the first layer's norm came with the embedding
-  if (!few) {           // (on the few-row paths run_forward's prologue launch has done both)
+  bool normed = !few && step_prologue(c, g, n_layers_run);   // the first layer's norm came with the embedding
+  if (!few && !normed) {   // (elsewhere run_forward's prologue launch has done both)
     TRY(launch_embed(c, s, g, n_layers_run > 0 ? c->layers[0].attn_norm : nullptr, &normed, qkv_mt), "embed");
     TRY(launch_rope_table(c, s, g), "rope_table");
   }

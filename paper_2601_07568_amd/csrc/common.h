@@ -121,6 +121,73 @@ struct RowStat {
   }
 };
 
+// What the first launch of a step leaves for the ones behind it, one workgroup per row.
+struct StepMap {
+  int B, Q, max_len, half;         // half: rotary pairs of a head
+  double log2_base;
+  const int32_t *prefix_len, *q_valid, *n_live;   // device values of the caller (the last two may be nullptr)
+  int32_t *len_safe, *q_valid_eff, *tok_seq, *tok_pos;
+  float *cs, *sn;
+  int4* loc;                       // [rows] where a row's K and V go (Workspace::kv_loc), or nullptr
+  KVView pool;                     // (loc: its table and page geometry)
+  int32_t* status;
+};
+// sequences that are part of the step
+__device__ inline int step_live(const StepMap& m) {
+  if (!m.n_live) return m.B;
+  const int nl = m.n_live[0];
+  return nl < 0 ? 0 : (nl > m.B ? m.B : nl);
+}
+// valid rows of sequence b (-1: not part of the step)
+__device__ inline int step_valid(const StepMap& m, int b, int nl) {
+  return b < nl ? (m.q_valid ? m.q_valid[b] : m.Q) : -1;
+}
+// Row t = blockIdx.x: its sequence, position (padding rows have none), rotary angles and, with loc, K/V place.  Workgroup 0
+// also checks the device-resident lengths: it writes the clamped copies, the live-row count and the status bit, exactly as
+// k_seq_check does; every workgroup derives its own sequence's values the same way.  bad: a shared word.
+__device__ inline void step_row_map(const StepMap& m, int t, int nl, int* bad) {
+  if (t == 0) {
+    if (threadIdx.x == 0) *bad = 0;
+    __syncthreads();
+    for (int b = threadIdx.x; b < m.B; b += blockDim.x) {
+      const int p = m.prefix_len[b];
+      const int pc = p < 0 ? 0 : (p > m.max_len ? m.max_len : p);
+      if (pc != p && b < nl) *bad = 1;
+      m.len_safe[b] = pc;
+      if (m.n_live) m.q_valid_eff[b] = step_valid(m, b, nl);
+    }
+    if (m.n_live && threadIdx.x == 0) m.status[2] = nl * m.Q;
+    __syncthreads();
+    if (threadIdx.x == 0 && *bad) atomicOr(m.status, DLLM_STATUS_BAD_LENGTH);
+  }
+  const int b = t / m.Q, j = t - b * m.Q;
+  const int p = m.prefix_len[b];
+  const int pc = p < 0 ? 0 : (p > m.max_len ? m.max_len : p);
+  const bool have_qv = m.n_live != nullptr || m.q_valid != nullptr;
+  const int pos = (have_qv && j >= step_valid(m, b, nl)) ? -1 : pc + j;
+  if (threadIdx.x == 0) {
+    m.tok_seq[t] = b;
+    m.tok_pos[t] = pos;
+    if (m.loc) {
+      int4 l = make_int4(-1, 0, -1, 0);
+      if (pos >= 0) {
+        const int pi = pos / m.pool.page_tokens;
+        const int page = pi < m.pool.max_pages ? m.pool.table[(int64_t)b * m.pool.max_pages + pi] : -1;
+        if (page >= 0 && page < m.pool.n_pages) { l.x = page; l.y = pos - pi * m.pool.page_tokens; }
+        else atomicOr(m.status, DLLM_STATUS_BAD_PAGE);
+      }
+      m.loc[t] = l;
+    }
+  }
+  for (int i = threadIdx.x; i < m.half; i += blockDim.x) {
+    const double theta = exp2(-(double)i / (double)m.half * m.log2_base);
+    double sv, cv;
+    sincos((double)pos * theta, &sv, &cv);
+    m.cs[t * m.half + i] = (float)cv;
+    m.sn[t * m.half + i] = (float)sv;
+  }
+}
+
 // Workspace map (byte offsets from the workspace base), fixed at dllm_create.
 struct Workspace {
   size_t status;       // int32[16]: [0] status bits, [1] number of LM-head rows
@@ -222,6 +289,11 @@ hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool 
 // the LM head's row list with the fixed outputs of the rows that are not masked, in one launch
 hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, int32_t* cand,
                               float* conf, float* entropy);
+// Steps of more rows than that on the matrix-core kernels: length checks, token map (with kv_loc as launch_token_map leaves
+// it), rotary table, embedding and the norm that reads it, in one launch
+bool step_prologue_usable(const dllm_ctx* c);
+hipError_t launch_step_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool kv_loc, int frag_mt);
+StepMap step_map(dllm_ctx* c, const StepGeom& g, bool kv_loc);
 // gain: of the norm that reads the embeddings, or nullptr; *normed: that norm has been applied in the same launch (frag_mt as below)
 hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed, int frag_mt = 0);
 hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g);

@@ -766,16 +766,24 @@ hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool 
 // the launch is a chain of memory round trips (as two passes over the row, the second re-reading what the first wrote,
 // it took 9.5 us at 128 rows of 4096; a trivial launch takes 4.6), so everything a thread needs - its part of the row, of
 // the open K shares of the last residual projection, of the gain - is requested before anything is used.
-// EMB: the rows come from the embedding table (the first norm of a forward): x is written, not read.
-template <int NV, bool EMB>
+// EMB: the rows come from the embedding table (the first norm of a forward): x is written, not read.  MAP: the launch is also
+// the step's first: step_row_map, which four launches (length check, token map, rotary table, embedding; 4.6 us each at least)
+// did one behind the other.
+template <int NV, bool EMB, bool MAP = false>
 __global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x, const bf16_t* gain, bf16_t* out,
                                                       const int32_t* rows, const int32_t* n_rows_dev, const float* delta,
                                                       int n_delta, int64_t delta_stride, float* rscale,
                                                       const int32_t* live_rows, const bf16_t* emb, const int32_t* tokens,
-                                                      int vocab, int32_t* status, float* mean_out, int ss_stride, int frag_mt) {
+                                                      int vocab, int32_t* status, float* mean_out, int ss_stride, int frag_mt, const StepMap m = StepMap()) {
   __shared__ float red[16];
   const int r = blockIdx.x;
-  const bool live = !live_rows || r < *live_rows;
+  bool live = !live_rows || r < *live_rows;
+  if constexpr (MAP) {
+    __shared__ int s_bad;
+    const int nl = step_live(m);
+    live = r < nl * m.Q;
+    step_row_map(m, r, nl, &s_bad);
+  }
   if (!EMB && !live) return;
   int src = r;
   if (rows) {
@@ -864,6 +872,36 @@ hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const voi
   else
     k_embed<float><<<g.T, 256, 0, s>>>(f.d_model, f.vocab, g.tokens, (const float*)c->tok_emb,
                                        WS(c, x, float), WS(c, status, int32_t));
+  return hipGetLastError();
+}
+
+StepMap step_map(dllm_ctx* c, const StepGeom& g, bool kv_loc) {
+  const dllm_config& f = c->cfg;
+  StepMap m;
+  m.B = g.B; m.Q = g.Q; m.max_len = g.max_kv - g.Q; m.half = f.head_dim / 2;
+  m.log2_base = log2((double)f.rope_base);
+  m.prefix_len = g.prefix_len; m.q_valid = g.q_valid; m.n_live = g.n_live;
+  m.len_safe = WS(c, len_safe, int32_t); m.q_valid_eff = WS(c, q_valid_eff, int32_t);
+  m.tok_seq = WS(c, tok_seq, int32_t); m.tok_pos = WS(c, tok_pos, int32_t);
+  m.cs = WS(c, rope_cos, float); m.sn = WS(c, rope_sin, float);
+  m.loc = kv_loc ? WS(c, kv_loc, int4) : nullptr;
+  m.pool = pool_view(c, g, 0);
+  m.status = WS(c, status, int32_t);
+  return m;
+}
+
+bool step_prologue_usable(const dllm_ctx* c) { return rmsnorm_row4_usable(c); }
+
+hipError_t launch_step_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool kv_loc, int frag_mt) {
+  const dllm_config& f = c->cfg;
+#define ROW4(NV) k_rmsnorm_row4<NV, true, true><<<g.T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,  \
+                     WS(c, xn, bf16_t), nullptr, nullptr, nullptr, 0, 0, WS(c, rscale, float), nullptr,                   \
+                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t), nullptr, 0, frag_mt, step_map(c, g, kv_loc))
+  if (f.d_model <= 2048) ROW4(2);
+  else if (f.d_model <= 4096) ROW4(4);
+  else if (f.d_model <= 8192) ROW4(8);
+  else ROW4(16);
+#undef ROW4
   return hipGetLastError();
 }
 

@@ -600,38 +600,21 @@ static void sk_row_scale(dllm_ctx* c, SkArgs& a, int n_ss) {
 }
 
 // Everything a denoise step of at most 64 rows needs before its first GEMM, in one launch of one workgroup per row:
-// the checks of the device-resident lengths (workgroup 0 writes the clamped copies, the live-row count and the status
-// bit, exactly as k_seq_check does; every workgroup derives its own sequence's values the same way), the row's
-// sequence and position (k_token_map), its rotary table entries (k_rope_table) and its embedding: x[t] = E[token[t]] in float, x * gain of the first norm in
-// fragment order as the first GEMM's input (bfloat16 models; the float kernels apply the gain themselves), the row's
+// step_row_map (lengths, token map, rotary table) and the row's embedding: x[t] = E[token[t]] in float, x * gain of the first
+// norm in fragment order as the first GEMM's input (bfloat16 models; the float kernels apply the gain themselves), the row's
 // sum of squares as its single partial.
 template <typename T>
-__global__ __launch_bounds__(256) void k_sk_prologue(int n_rows, int B, int Q, int max_len, int d, int vocab, int mt, int half,
-                                                     double log2_base, const int32_t* tokens, const int32_t* prefix_len,
-                                                     const int32_t* q_valid, const int32_t* n_live, const T* emb,
-                                                     const bf16_t* gain, float* x, bf16_t* xg, float* ss, int ss_stride,
-                                                     int32_t* len_safe, int32_t* q_valid_eff, int32_t* tok_seq,
-                                                     int32_t* tok_pos, float* cs, float* sn, int32_t* status,
-                                                     int32_t mask_id, int cap, int32_t* rows, int32_t* cand, float* conf,
+__global__ __launch_bounds__(256) void k_sk_prologue(const StepMap m, int n_rows, int d, int vocab, int mt, const int32_t* tokens,
+                                                     const T* emb, const bf16_t* gain, float* x, bf16_t* xg, float* ss,
+                                                     int ss_stride, int32_t mask_id, int cap, int32_t* rows, int32_t* cand, float* conf,
                                                      float* entropy) {
   __shared__ float red[4];
   __shared__ int s_bad;
-  const int t = blockIdx.x;
-  int nl = B;
-  if (n_live) { nl = n_live[0]; nl = nl < 0 ? 0 : (nl > B ? B : nl); }
+  const int t = blockIdx.x, Q = m.Q;
+  int32_t* const status = m.status;
+  const int nl = step_live(m);
+  step_row_map(m, t, nl, &s_bad);
   if (t == 0) {
-    if (threadIdx.x == 0) s_bad = 0;
-    __syncthreads();
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-      const int p = prefix_len[b];
-      const int pc = p < 0 ? 0 : (p > max_len ? max_len : p);
-      if (pc != p && b < nl) s_bad = 1;
-      len_safe[b] = pc;
-      if (n_live) q_valid_eff[b] = b < nl ? (q_valid ? q_valid[b] : Q) : -1;
-    }
-    if (n_live && threadIdx.x == 0) status[2] = nl * Q;
-    __syncthreads();
-    if (threadIdx.x == 0 && s_bad) atomicOr(status, DLLM_STATUS_BAD_LENGTH);
     // the rows of the LM head (k_mask_rows for a step of at most 64 rows: one wave, row r in lane r): the masked rows
     // that are not padding, in ascending order; every other row reports its own token with confidence 1
     if (cand && threadIdx.x < 64) {
@@ -639,8 +622,8 @@ __global__ __launch_bounds__(256) void k_sk_prologue(int n_rows, int B, int Q, i
       bool flag = false;
       if (r < n_rows) {
         const int b2 = r / Q, j2 = r - b2 * Q;
-        const bool hq = n_live != nullptr || q_valid != nullptr;
-        const int qv2 = n_live ? (b2 < nl ? (q_valid ? q_valid[b2] : Q) : -1) : (q_valid ? q_valid[b2] : Q);
+        const bool hq = m.n_live != nullptr || m.q_valid != nullptr;
+        const int qv2 = step_valid(m, b2, nl);
         const int tk = tokens[r];
         flag = !(hq && j2 >= qv2) && tk == mask_id;
         if (!flag) {
@@ -658,22 +641,6 @@ __global__ __launch_bounds__(256) void k_sk_prologue(int n_rows, int B, int Q, i
         status[1] = n;
       }
     }
-  }
-  // this row's sequence, position (padding rows have none) and rotary angles
-  const int b = t / Q, jrow = t - b * Q;
-  const int p = prefix_len[b];
-  const int pc = p < 0 ? 0 : (p > max_len ? max_len : p);
-  const bool have_qv = n_live != nullptr || q_valid != nullptr;
-  const int qve = n_live ? (b < nl ? (q_valid ? q_valid[b] : Q) : -1) : (q_valid ? q_valid[b] : Q);
-  const int pos = (have_qv && jrow >= qve) ? -1 : pc + jrow;
-  if (threadIdx.x == 0) { tok_seq[t] = b; tok_pos[t] = pos; }
-  for (int j = threadIdx.x; j < half; j += blockDim.x) {
-    const double theta = exp2(-(double)j / (double)half * log2_base);
-    const double ang = (double)pos * theta;
-    double sv, cv;
-    sincos(ang, &sv, &cv);
-    cs[t * half + j] = (float)cv;
-    sn[t * half + j] = (float)sv;
   }
   // embedding: x[t] = E[token[t]] (float), x * gain in fragment order, the row's sum of squares
   int tok = tokens[t];
@@ -718,15 +685,11 @@ __global__ __launch_bounds__(256) void k_sk_prologue(int n_rows, int B, int Q, i
 hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, int32_t* cand,
                               float* conf, float* entropy) {
   const dllm_config& f = c->cfg;
-  const bool live = g.n_live != nullptr;
 #define PROLOGUE(TYPE)                                                                                                   \
-  k_sk_prologue<TYPE><<<g.T, 256, 0, s>>>(g.T, g.B, g.Q, g.max_kv - g.Q, f.d_model, f.vocab, (g.T + 15) / 16, f.head_dim / 2, \
-                                    log2((double)f.rope_base), g.tokens, g.prefix_len, g.q_valid, live ? g.n_live : nullptr, \
+  k_sk_prologue<TYPE><<<g.T, 256, 0, s>>>(step_map(c, g, false), g.T, f.d_model, f.vocab, (g.T + 15) / 16, g.tokens,       \
                                     (const TYPE*)c->tok_emb, (const bf16_t*)gain, WSM(c, x, float), WSM(c, xn, bf16_t), \
-                                    WSM(c, ss, float), ss_row_stride(c), WSM(c, len_safe, int32_t), \
-                                    WSM(c, q_valid_eff, int32_t), WSM(c, tok_seq, int32_t), WSM(c, tok_pos, int32_t), \
-                                    WSM(c, rope_cos, float), WSM(c, rope_sin, float), WSM(c, status, int32_t), \
-                                    f.mask_id, (int)c->map.r_max, WSM(c, rows, int32_t), cand, conf, entropy)
+                                    WSM(c, ss, float), ss_row_stride(c), f.mask_id, (int)c->map.r_max,                   \
+                                    WSM(c, rows, int32_t), cand, conf, entropy)
   if (f.dtype == DLLM_BF16) PROLOGUE(bf16_t);
   else PROLOGUE(float);
 #undef PROLOGUE
