@@ -34,7 +34,7 @@ struct LgArgs {
   int k_per;               // RESID: K range of one split (multiple of LG_BK); gridDim.y splits
   int k_splits;            // tile kernel: number of K splits (its grid is flat)
   int group_m;             // tile kernel: most row tiles of a group (order of the work items)
-  int tn0;                 // tile kernel: its first column tile
+  int n_first;             // tile kernel: the column that its first column tile begins at
   float* delta;            // RESID: products of splits 1.. go to delta[(split - 1) * delta_stride + m * N + n]
   int64_t delta_stride;
   const int32_t* m_dev;    // optional device row count
@@ -352,7 +352,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   constexpr int TILE_N = SWIGLU ? BN / 2 : BN;                  // output features of a tile
   // gate and up tiles come in pairs; of an odd number the last holds 16 gate rows and the same 16 up rows
   constexpr bool ODD = SWIGLU && TN % 2 == 1;
-  static_assert((WM == 2 || ODD) && !(ODD && HALF), "other layouts of the waves are built for odd gate/up tiles alone");
+  constexpr bool RODD = EPI == LG_RESID && WM == 4;
+  static_assert((WM == 2 || ODD || RODD) && !((ODD || RODD) && HALF), "other layouts of the waves are built for odd tiles alone");
   static_assert(!STATS || TN % 2 == 0, "64 columns per partial");
   extern __shared__ __attribute__((aligned(1024))) unsigned char gt_smem[];
   unsigned char* const sA = gt_smem;
@@ -380,7 +381,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // chosen by the host's bound (4096 x 4096: three shares at 600 rows, one at 700), so it need not get them; and a
   // row's sums begin elsewhere when the rows of its call pass 256.
   const int k_rot = M <= 256 ? 11 : 0;
-  struct Item { int split, tm, tn, k_begin, k_end, k_first; bool ok, val; };
+  struct Item { int split, tm, n0, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
     Item t{0, 0, 0, 0, k_all, 0, false, false};
     const int item = gt_item(blockIdx.x, gridDim.x, it, n_items);
@@ -389,14 +390,14 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     const int tile = item - t.split * n_tiles;
     const int gi = tile / (gm_full * a.tiles_n), rem = tile - gi * gm_full * a.tiles_n;
     const int gm = tiles_m - gi * gm_full < gm_full ? tiles_m - gi * gm_full : gm_full;
-    t.tn = rem / gm;
-    t.tm = gi * gm_full + rem - t.tn * gm;
-    t.tn += a.tn0;
+    const int tn = rem / gm;
+    t.tm = gi * gm_full + rem - tn * gm;
+    t.n0 = tn * TILE_N + a.n_first;
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < k_all ? t.k_begin + a.k_per : k_all;
-    t.k_first = t.k_begin + ((SWIGLU ? t.tn * TILE_N / 1920 : t.tn * BN / 256) * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
+    t.k_first = t.k_begin + (t.n0 / (SWIGLU ? 1920 : 256) * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
     t.ok = true;
-    t.val = ROPE && t.tn * TILE_N >= N + a.N2;                  // a tile of the value projection
+    t.val = ROPE && t.n0 >= N + a.N2;                  // a tile of the value projection
     return t;
   };
   // descriptors that end with the matrix: rows of a tile past the last one are not read (nor, in the epilogue, written)
@@ -408,7 +409,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     return rsrc(a.A + (int64_t)t.tm * BM * K, (int64_t)rows * K * 2);
   };
   auto rsrc_w = [&](const Item& t) -> gt_rsrc {
-    const int n0 = t.tn * TILE_N;
+    const int n0 = t.n0;
     const bf16_t* base = a.W;
     int row = n0, rows = N - n0 < TILE_N ? N - n0 : TILE_N;
     if constexpr (QKV) {
@@ -433,7 +434,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // copies: instruction q of wave w fills LDS rows (w*C + q)*8 .. +7; lane l holds piece l%8 of row l/8
   const int l8 = lane >> 3, piece = (lane & 7) ^ (l8 >> 1);     // (odd q: the row's bit 3 flips bit 2 of the piece)
   // features between consecutive LDS rows of a tile
-  constexpr int FS = STATS || ODD ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
+  constexpr int FS = STATS || ODD || RODD ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
   const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = HALF ? vA0 + (piece < 4 ? 64 : -64) : vA0 ^ 64;
   const int vW0 = l8 * FS * K * 2 + piece * 16, vW1 = HALF ? vW0 + (piece < 4 ? 64 : -64) : vW0 ^ 64;
   const int out0 = piece < 4 ? 0 : 0x40000000, out1 = piece < 4 ? 0x40000000 : 0;   // HALF: added in the last stage (even, odd q)
@@ -447,7 +448,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   auto w_row = [&](int q) -> int {                              // weight row of the instruction's first LDS row
     if constexpr (ODD) return ((w & 1) * CW + q) * 8;
     const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
-    if constexpr (STATS) return R;
+    if constexpr (STATS || RODD) return R;
     // both members of a rotary pair (channels j and j + DH/2 of a head) in one lane, in tiles i and i + 2 (WIDE: two
     // neighbouring channels per lane) or in tiles 2g and 2g + 1
     else if constexpr (WIDE) return hw * 128 + (i >> 1) * 64 + 2 * c + (i & 1);
@@ -465,7 +466,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
 #pragma unroll
     for (int q = 0; q < CA; ++q) vA[q] = ((q & 1) ? vA1 : vA0) + q * 16 * K;
 #pragma unroll
-    for (int q = 0; q < CW; ++q) vW[q] = ((ODD ? (odd_lds(q) >> 3) & 1 : q & 1) ? vW1 : vW0) + w_row(q) * 2 * K;
+    for (int q = 0; q < CW; ++q) vW[q] = ((ODD ? (odd_lds(q) >> 3) & 1 : CW % 2 ? (w * CW + q) & 1 : q & 1) ? vW1 : vW0) + w_row(q) * 2 * K;
   }
   auto past = [&](int k, int q) -> int { return HALF && k + 64 > K ? ((q & 1) ? out1 : out0) : 0; };
   auto copy_a = [&](int slot, int q) {
@@ -576,7 +577,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
       sw = nw;
     }
 
-    const int m0 = cur.tm * BM, n0 = cur.tn * TILE_N, split = cur.split;
+    const int m0 = cur.tm * BM, n0 = cur.n0, split = cur.split;
     const int rows = M - m0 < BM ? M - m0 : BM;
     const gt_rsrc rr = rsrc(a.rscale + m0, (EPI != LG_RESID && a.rscale) ? (int64_t)rows * 4 : 0);
     if constexpr (STATS) {
@@ -825,6 +826,28 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
             __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, ro, ((lrow + odd) * N + n) * 2, (j * 32 + (e >> 2) * 8 + (e & 3)) * N * 2, 0);
         }
       }
+    } else if constexpr (RODD) {
+      // lane holds weight row l%32 of each tile: 32 lanes store a 128-byte line
+      char* const obase = (char*)(split == 0 ? (float*)a.C : a.delta + (int64_t)(split - 1) * a.delta_stride);
+      const gt_rsrc ro = rsrc(obase + (int64_t)m0 * N * 4, (int64_t)rows * N * 4);
+      const int lrow = wm * 32 * TM + h * 4;
+#pragma unroll
+      for (int j = 0; j < TM; ++j)
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+          __builtin_amdgcn_sched_barrier(0);
+          const int n = n0 + i * 32 + r, vo = (lrow * N + n) * 4;
+          if (n >= N) continue;
+          float xv[16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            xv[e] = 0.f;
+            if (split == 0) xv[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, vo, (j * 32 + (e >> 2) * 8 + (e & 3)) * N * 4, 0));
+          }
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(xv[e] + acc[i][j][e]), ro, vo, (j * 32 + (e >> 2) * 8 + (e & 3)) * N * 4, 0);
+        }
     } else {
       // lane holds weight rows TN*(l%32) .. of its tiles and, in register e, token row (e/4)*8 + (l/32)*4 + e%4
       const int n = n0 + (SWIGLU ? wn * 16 * TN + (TN / 2) * r : wn * 32 * TN + TN * r);
@@ -943,6 +966,7 @@ hipError_t init_gemm_tiles() {
 #define X(TM, TN, NA, NW) if (e == hipSuccess) e = gt_raise_lds<LG_SWIGLU, TM, TN, NA, NW, 4>();
   GT_ODD_KERNELS(X)
 #undef X
+  if (e == hipSuccess) e = gt_raise_lds<LG_RESID, 2, 7, 2, 3, 4>();
   gt_ready = e == hipSuccess;
   return e;
 }
@@ -950,17 +974,17 @@ hipError_t init_gemm_tiles() {
 // 18976, us, k_gemm_mfma / this kernel: 97 rows 658 / 432, 700 rows 1438 / 892, 3000 rows 5508 / 3226)
 static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 32 == 0 && K >= 128; }
 // of a mask of tiles (bit per GtTile) those that are built for this K
-static unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0xf2u; }
+static unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0x1f2u; }
 
-// the column tiles [tn0, tn0 + n_tn) of a product (n_tn 0: all of them)
+// n_tn column tiles of a product from column n_first on (n_tn 0: all that are left)
 template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2>
-static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 = 0, int n_tn = 0) {
+static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int n_first = 0, int n_tn = 0) {
   using G = GtGeom<TM, TN, NSA, NSW, WM>;
   constexpr int tile_n = EPI == LG_SWIGLU ? G::BN / 2 : G::BN;
   a.tiles_m = (a.M + G::BM - 1) / G::BM;
   constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128;
-  a.tiles_n = n_tn ? n_tn : (qkv ? (a.N + 2 * a.N2) / G::BN : (a.N + tile_n - 1) / tile_n) - tn0;
-  a.tn0 = tn0;
+  a.tiles_n = n_tn ? n_tn : qkv ? (a.N + 2 * a.N2) / G::BN : (a.N - n_first + tile_n - 1) / tile_n;
+  a.n_first = n_first;
   a.k_splits = k_splits;
   const int k_all = (a.K + 63) / 64 * 64;
   if (k_splits == 1) a.k_per = k_all;
@@ -991,16 +1015,16 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int tn0 =
 // 96), 300 rows 101 / 84 (128 x 160); 37888 x 3584: 65 rows 61.7 / 53.3 and 128 rows 67.3 / 58.4 (128 x 160), 211 rows
 // 83.5 / 71.8 and 256 rows 87.6 / 74.9 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its weights are all from
 // memory and two thirds of the CUs ask for them.
-enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_N = 8 };
+enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_256x224 = 8, GT_N = 9 };
 constexpr unsigned GT_ODD_TILES = 0xf0u;
 struct GtPlan { GtTile tile; int splits, k_per; double us; };
 // NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile that its widths allow
 // fold_us_per_share: what each share behind the first costs (written here, read by the kernel that adds it)
 static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok, double fold_us_per_share) {
-  static const int bm[GT_N] = {256, 128, 128, 128, 128, 128, 256, 256}, bn[GT_N] = {256, 256, 128, 64, 96, 160, 96, 160};
+  static const int bm[GT_N] = {256, 128, 128, 128, 128, 128, 256, 256, 256}, bn[GT_N] = {256, 256, 128, 64, 96, 160, 96, 160, 224};
   // (up to 256 rows a 128-row tile waits for its weights, which no other row tile has brought in)
   const double unit[GT_N] = {1.0, M <= 128 && (width_ok & GT_ODD_TILES) ? 0.68 : 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22,
-                             M <= 128 ? 0.39 : 0.45, M <= 128 ? 0.60 : 0.45, 0.54, 0.80};
+                             M <= 128 ? 0.39 : 0.45, M <= 128 ? 0.60 : 0.45, 0.54, 0.80, 0.90};
   GtPlan best{GT_128x128, 1, K, 1e30};
   for (int c = 0; c < GT_N; ++c) {
     if (!((gt_built(K, width_ok) >> c) & 1u)) continue;
@@ -1076,7 +1100,7 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
   a.delta = (float*)(c->ws + c->map.delta);
   a.delta_stride = c->map.lg_delta_stride;
   if (gt_usable(M, K)) {
-    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, 0xfu, 1.0 + 8.0 * M * (double)N / 4.0e6);
+    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, 0x10fu, 1.0 + 8.0 * M * (double)N / 4.0e6);
     a.k_per = p.k_per;
     *n_delta = p.splits - 1;
     const int n_tn = gt_whole_rounds(M, N, K, 0x6u, p.us);
@@ -1085,12 +1109,13 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
       a.k_per = K;
       const hipError_t e = gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, 1, 0, n_tn);
       if (e != hipSuccess) return e;
-      return gt_plan(M, N - n_tn * 256, K, 1, 0x6u, 0.0).tile == GT_128x256 ? gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, 1, n_tn)
-                                                                            : gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, 1, 2 * n_tn);
+      return gt_plan(M, N - n_tn * 256, K, 1, 0x6u, 0.0).tile == GT_128x256 ? gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, 1, n_tn * 256)
+                                                                            : gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, 1, n_tn * 256);
     }
     switch (p.tile) {
       case GT_256x256: return gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, p.splits);
       case GT_128x256: return gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, p.splits);
+      case GT_256x224: return gt_launch<LG_RESID, 2, 7, 2, 3, 4>(s, a, p.splits);
       case GT_128x128: return gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, p.splits);
       default: return gt_launch<LG_RESID, 2, 1, 3, 4>(s, a, p.splits);
     }
@@ -1192,6 +1217,19 @@ hipError_t launch_gemm_qkv(hipStream_t s, const void* A, const void* Wq, const v
   return lg_launch<LG_QKV>(s, a);
 }
 
+// gate/up from feature f_first on
+static hipError_t gt_launch_swiglu(hipStream_t s, const LgArgs& a, GtTile tile, int f_first) {
+  switch (tile) {
+    case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, f_first);
+    case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a, 1, f_first);
+    case GT_128x96: return gt_launch<LG_SWIGLU, 1, 3, 5, 5, 4>(s, a, 1, f_first);
+    case GT_128x160: return gt_launch<LG_SWIGLU, 1, 5, 4, 4, 4>(s, a, 1, f_first);
+    case GT_256x96: return gt_launch<LG_SWIGLU, 2, 3, 3, 3, 4>(s, a, 1, f_first);
+    case GT_256x160: return gt_launch<LG_SWIGLU, 2, 5, 3, 3, 4>(s, a, 1, f_first);
+    default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a, 1, f_first);
+  }
+}
+
 // h[M,F] = silu(A Wg^T) * (A Wu^T), bfloat16 row-major
 hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, const void* Wu, void* H, int M, int F,
                               int K, const float* rscale, const int32_t* m_dev) {
@@ -1202,22 +1240,13 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wg; a.W2 = (const bf16_t*)Wu; a.C = H; a.M = M; a.N = F; a.K = K;
   if (gt_usable(M, K)) {
     const GtPlan p = gt_plan(M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0);
-    const int n_tn = gt_whole_rounds(M, 2 * F, K, 0x6u, p.us);
+    const unsigned rest_ok = 0x6u | GT_ODD_TILES;
+    const int n_tn = gt_whole_rounds(M, 2 * F, K, rest_ok, p.us);
     if (n_tn > 0) {
       const hipError_t e = gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, 0, n_tn);
-      if (e != hipSuccess) return e;
-      return gt_plan(M, 2 * F - n_tn * 256, K, 1, 0x6u, 0.0).tile == GT_128x256 ? gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a, 1, n_tn)
-                                                                                : gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a, 1, 2 * n_tn);
+      return e != hipSuccess ? e : gt_launch_swiglu(s, a, gt_plan(M, 2 * F - n_tn * 256, K, 1, rest_ok, 0.0).tile, n_tn * 128);
     }
-    switch (p.tile) {
-      case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a);
-      case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a);
-      case GT_128x96: return gt_launch<LG_SWIGLU, 1, 3, 5, 5, 4>(s, a);
-      case GT_128x160: return gt_launch<LG_SWIGLU, 1, 5, 4, 4, 4>(s, a);
-      case GT_256x96: return gt_launch<LG_SWIGLU, 2, 3, 3, 3, 4>(s, a);
-      case GT_256x160: return gt_launch<LG_SWIGLU, 2, 5, 3, 3, 4>(s, a);
-      default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a);
-    }
+    return gt_launch_swiglu(s, a, p.tile, 0);
   }
   return lg_launch<LG_SWIGLU>(s, a);
 }
