@@ -89,8 +89,13 @@ __device__ __forceinline__ void attn_softmax_block(f32x4 (&s)[2][QT], int k0, in
   }
 }
 
-template <int DH, int QT>
-__global__ __launch_bounds__(256) void k_attn_step(const AttnArgs a) {
+// WPS: waves per SIMD that the registers allow.  Left to itself the compiler takes 340 for heads of 128 channels and with
+// them the second wave of a SIMD, whose loads fill the time that the first one's products and round trips leave (us, one /
+// two waves, 32 key heads: 8 sequences of 700 keys 37.5 / 30.1 = 2.9 TB/s, 16 of 2048 126 / 117, one of 1024 14.7 / 14.6; 64
+// rows, one of 1237 keys 22.2 / 18.8).  One wave where several row groups of a workgroup read the same keys through long
+// units: their shared lines last longer in the L1 (64 rows, 8 sequences of up to 4096 keys 185 / 196).
+template <int DH, int QT, int WPS>
+__global__ __launch_bounds__(256, WPS) void k_attn_step(const AttnArgs a) {
   constexpr int KK = DH / 32;   // k-steps of Q K^T
   constexpr int DT = DH / 16;   // 16-row tiles of O^T
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -899,8 +904,8 @@ static bool attn_merge_ready = false;
 constexpr int DL_LDS_MAX = 160 * 1024;          // ring of k_attn_dl plus its copy of a sequence's page ids
 hipError_t init_attn_kernels() {
   if (attn_merge_ready) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute((const void*)k_attn_step<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_attn_step<64, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+  hipError_t e = hipFuncSetAttribute((const void*)k_attn_step<128, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_attn_step<64, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
 #define DL_ATTR(DHV, PG)                                                                                          \
   if (e == hipSuccess)                                                                                            \
     e = hipFuncSetAttribute((const void*)k_attn_dl<DHV, PG>, hipFuncAttributeMaxDynamicSharedMemorySize, DL_LDS_MAX)
@@ -934,7 +939,16 @@ hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const
   // attention is a few MB), so give every unit about two 32-key blocks, within the partial buffer
   int64_t want = 2048 / ((int64_t)g.B * f.n_kv_heads * n_rg);
   if (want < 1) want = 1;
-  int64_t by_work = staged ? (nkb + 7) / 8 : (nkb + 1) / 2;   // staged kernel: at least four 64-key blocks per unit
+  int64_t by_work = staged ? (nkb + 7) / 8 : (nkb + 1) / 2;   // staged kernel: at least four 64-key blocks per unit ...
+  if (staged && by_work > 1) {   // (a single unit needs no combine)
+    // ... or two, or one, where that still leaves CUs without a workgroup (kernel + combine, us, four / two / one, 4 key heads of
+    // 7: 512 keys 17.3 + 4.8 / 15.5 + 4.8 / 13.7 + 4.8 in 12 / 20 / 36 workgroups, 2048 keys 19.7 + 4.8 / 16.7 + 5.3 / 15.6 + 7.2
+    // in 36 / 68 / 132, 8000 keys 22.0 + 6.1 / 20.9 + 10.0 / - in 128 / 252, 4 sequences of 2048 22.6 + 6.4 / 31.5 + 9.1 / - in
+    // 144 / 272)
+    const int64_t per_unit = (int64_t)n_chunks * g.B * f.n_kv_heads;
+    if ((nkb + 1) / 2 * per_unit <= 64) by_work = (nkb + 1) / 2;
+    else if ((nkb + 3) / 4 * per_unit <= 128) by_work = (nkb + 3) / 4;
+  }
   int64_t by_space = c->map.attn_rows / ((int64_t)g.T * f.n_q_heads);
   int64_t units = want < by_work ? want : by_work;
   if (units > by_space) units = by_space;
@@ -943,7 +957,9 @@ hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const
   // one row group per KV head (a batch-1 block on a multi-head model): four units share a workgroup and
   // merge their partial results in LDS, which leaves a quarter of the partials to write and re-read
   int kspl = 1;
-  if (!staged && n_rg == 1 && attn_merge_ready && units >= 4) {
+  // (also where more than 512 such workgroups are a second round: 32 sequences of 1024 keys, 32 key heads, as two single-wave
+  // units with their combine 126 + 16 us, as one workgroup of four waves 129)
+  if (!staged && n_rg == 1 && attn_merge_ready && by_work >= 4) {
     kspl = 4;
     int64_t parts = (nkb + 2 * kspl - 1) / (2 * kspl);
     if (parts * kspl > want) parts = want / kspl;
@@ -983,8 +999,9 @@ hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const
 #undef ATTN_DL
   } else {
     const size_t lds = kspl > 1 ? (size_t)kspl * (2 * QT * 16 * sizeof(float) + (size_t)(f.head_dim / 16) * QT * 64 * 16) : 0;
-    if (f.head_dim == 128) k_attn_step<128, QT><<<grid, threads, lds, s>>>(a);
-    else k_attn_step<64, QT><<<grid, threads, lds, s>>>(a);
+    if (f.head_dim == 64) k_attn_step<64, QT, 2><<<grid, threads, lds, s>>>(a);
+    else if (n_rg_wg > 1 && nkb >= 16 * units) k_attn_step<128, QT, 1><<<grid, threads, lds, s>>>(a);
+    else k_attn_step<128, QT, 2><<<grid, threads, lds, s>>>(a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_parts == 1) return e;
