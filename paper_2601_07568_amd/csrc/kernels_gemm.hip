@@ -292,7 +292,8 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(const LgArgs a) {
 
 // ------------------------------------------------------------------------------------------
 // The same products for more than 64 token rows.  A workgroup of 4 waves, one per SIMD, owns a tile of 64*TM token
-// rows x 64*TN weight rows, each wave a quarter of it as TM x TN products of 32 x 32 x 16.  Both operands stay
+// rows x 64*TN weight rows (WM = 4, all waves along the token rows: 128*TM x 32*TN), each wave a quarter of it as TM x TN
+// products of 32 x 32 x 16.  Both operands stay
 // row-major in memory and are copied straight into LDS (no register pass) in 64-deep K stages: 64 bfloat16 values are
 // one 128-byte cache line, so a copy instruction fetches 8 whole lines.  (With 32-deep stages every copy asked for
 // half lines: twice the requests to the L2 for the same bytes, 34 M against 17 M on a 1024 x 37888 x 3584 product, and
@@ -1009,12 +1010,14 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int n_fir
 // Over 200 layers of 128 .. 8192 channels and 96 .. 16384 rows, 257 .. 511 among them, what it picks takes 0.47 .. 0.98 of the
 // time of the 32-deep kernels that were here before.
 //
-// The odd widths are gate/up's alone: one round of one tile per CU decides there up to about 500 rows, and 128 and 256
-// columns seldom make one (256 CUs; 24576 gate and up rows: 256 tiles of 96, 37888: 237 of 160).  Measured, the best of the
+// Odd widths for gate/up: one round of one tile per CU decides there up to about 500 rows, and 128 and 256 columns
+// seldom make one (256 CUs; 24576 gate and up rows: 256 tiles of 96, 37888: 237 of 160).  Measured, the best of the
 // even tiles / these, us: 24576 x 4096: 128 rows 47.9 / 44.2 (128 x 96), 211 rows 59.3 / 56.9 and 256 rows 61.5 / 59.8 (256 x
 // 96), 300 rows 101 / 84 (128 x 160); 37888 x 3584: 65 rows 61.7 / 53.3 and 128 rows 67.3 / 58.4 (128 x 160), 211 rows
 // 83.5 / 71.8 and 256 rows 87.6 / 74.9 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its weights are all from
-// memory and two thirds of the CUs ask for them.
+// memory and two thirds of the CUs ask for them.  Behind whole rounds: 1024 x 10240 x 3584 as 160 tiles of 128 x 256 57, as 256
+// of 128 x 160 47.  One for residual projections, 256 x 224 at 0.90: 1024 x 3584 x 18944 in four K shares is 224 tiles of 256 x
+// 256 or 256 of these, 132 / 123.
 enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_256x224 = 8, GT_N = 9 };
 constexpr unsigned GT_ODD_TILES = 0xf0u;
 struct GtPlan { GtTile tile; int splits, k_per; double us; };
