@@ -336,12 +336,13 @@ static bool large_mfma(const dllm_ctx* c) {
   return c->cfg.dtype == DLLM_BF16 && c->kernel_mode == 0 && c->cfg.d_ff % 4 == 0 && c->cfg.vocab % 4 == 0;
 }
 
-// Steps of 65 .. 128 rows: the q/k/v product with its rotary embedding and K/V write still comes from the packed weights
-// (the other products are quicker on the tile kernel).  12288 x 4096, us, the split tile product + the rotary kernel behind
-// it / this one: 128 rows 32 + 16 / 35, 96 rows 30 on this one, 80 rows 28; at 256 rows a workgroup's accumulators no
-// longer fit its registers.
+// Steps of 65 .. 128 rows: the q/k/v product with its rotary embedding and K/V write is still the weight-streaming
+// kernel's, on the weights as given (the other products are quicker on the tile kernel).  us, the split tile product + the
+// rotary kernel behind it / this one (from packed weights): 12288 x 4096: 128 rows 31 + 16 / 44 (40), 96 rows 29 + 15 / 37 (34),
+// 80 rows 27 + 14 / 35 (32); 4608 x 3584: 128 rows 14.5 + 15 / 28.5 (24.5), 72 rows 12.5 + 15 / 22.5 (18.5); at 256 rows a
+// workgroup's accumulators no longer fit its registers.  (d_model: what the norm in front of it takes, which lays out its input.)
 static bool sk_qkv_rows(const dllm_ctx* c, const StepGeom& g) {
-  return mfma_supported(c) && large_mfma(c) && g.Q > 0 && g.T > SK_MAX_ROWS && g.T <= SK_QKV_ROWS;
+  return large_mfma(c) && c->cfg.d_model <= 16384 && g.Q > 0 && g.T > SK_MAX_ROWS && g.T <= SK_QKV_ROWS;
 }
 // the q/k/v product of many rows with the rotary embedding in it
 static bool tile_qkv_rope(const dllm_ctx* c, const StepGeom& g) {

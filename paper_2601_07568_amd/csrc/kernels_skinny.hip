@@ -8,6 +8,9 @@
 // The epilogue of the summed tile is the fusion point: residual add, rotary embedding + KV-cache
 // write, SiLU*up, or the softmax statistics of the LM head (the logits never reach memory).
 //
+// The q/k/v product takes up to 128 rows.  Above 64 it reads the weights as the caller gave them (row-major) and not the packed
+// copy, as every other product of such a step does: who changes a weight in place packs again for steps of few rows only.
+//
 #include "mfma_common.h"
 
 namespace dllm {
@@ -18,7 +21,7 @@ struct SkArgs {
   const bf16_t* X;          // activations [M, K], fragment order
   const int32_t* n_lm_rows; // optional device count: the kernel does nothing if it is zero
   int M, K;
-  const bf16_t* W0;         // main weight / Wq / W_gate / lm_head   (all in packed fragment order)
+  const bf16_t* W0;         // main weight / Wq / W_gate / lm_head   (packed fragment order; QKV of more than 64 rows: row-major)
   const bf16_t* W1;         // Wk / W_up
   const bf16_t* W2;         // Wv
   int N0, N1, N2;           // rows of W0, W1, W2
@@ -69,17 +72,22 @@ struct SkFrag {
 
 // Both operands are in fragment order: step u (32 k-elements) of weight tile t is the KiB at
 // wt[t] + u*64 units, of activation tile m the KiB at xf + (u*MT + m)*64 units (lane offset folded
-// into the pointers), so every load instruction of the wave is contiguous.
-template <int NT, int MT, int JB, bool TAIL>
+// into the pointers), so every load instruction of the wave is contiguous.  RM: row-major weights, 64 bytes of each of
+// the tile's 16 rows.
+template <int NT, int MT, int JB, bool TAIL, bool RM>
 __device__ inline void sk_load(SkFrag<NT, MT, JB>& f, const u32x4* const (&wt)[NT], const u32x4* xf, int stage, int g,
                                int K) {
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
     const int u = stage * JB + j;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) f.a[t][j] = wt[t][u * 64];   // packed weights are zero beyond K
-    // the activation buffer is not: beyond K it holds whatever was there, and 0 * NaN is NaN
+    // packed weights are zero beyond K; the activation buffer is not (it holds whatever was there, and 0 * NaN is NaN), and
+    // a row-major matrix may end there
     const bool ok = !TAIL || (u * 32 + g * 8 + 8 <= K);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (!RM || ok) f.a[t][j] = wt[t][u * (RM ? 4 : 64)];
+      else f.a[t][j] = u32x4{0, 0, 0, 0};
+    }
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       if (ok) f.b[t][j] = xf[(u * MT + t) * 64];
@@ -148,6 +156,7 @@ __device__ inline void sk_tile_rows(const SkArgs& a, int wg, const bf16_t* (&wba
 template <int NT, int MT, int NW, int EPI, int JB, int TPC, int D, int WPS>
 __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   constexpr bool SCALED = (EPI != SK_RESID);
+  constexpr bool RM = MT > 4;                           // the weights as the caller gave them, not the packed copy
   constexpr int RPW = (MT * 16 + NW - 1) / NW;          // rows per wave when the row scales are summed
   // partial tiles go through LDS in chunks of TPC weight tiles and MC activation tiles
   constexpr int NCH = NT / TPC, MCH = NW * TPC * MT <= 144 ? 1 : 2, MC = (MT + MCH - 1) / MCH;
@@ -176,6 +185,11 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   const u32x4* wt[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
+    if constexpr (RM) {
+      const int row = row0[t] + c < nrows[t] ? row0[t] + c : nrows[t] - 1;
+      wt[t] = (const u32x4*)(wbase[t] + (int64_t)row * K + g * 8);
+      continue;
+    }
     int rt = row0[t] >> 4;
     const int rt_max = (nrows[t] + 15) / 16 - 1;
     rt = rt < rt_max ? rt : rt_max;
@@ -284,7 +298,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   const int n_full = K / SKB;                         // stages that need no tail guard
   const int ws = __builtin_amdgcn_readfirstlane(w);   // wave index as a scalar
   const int n_w = n_full > ws ? (n_full - ws + NW - 1) / NW : 0;
-#define SK_LD(F, I) sk_load<NT, MT, JB, false>(F, wt, xf, ws + (I) * NW, g, K)
+#define SK_LD(F, I) sk_load<NT, MT, JB, false, RM>(F, wt, xf, ws + (I) * NW, g, K)
 #define SK_MM(F) sk_mma<NT, MT, JB>(F, acc)
   if (n_w == 0) {
     fetch_pages();
@@ -325,7 +339,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
 #undef SK_MM
   if (n_full * SKB < K && ws == n_full % NW) {   // ragged last stage
     SkFrag<NT, MT, JB> ft;
-    sk_load<NT, MT, JB, true>(ft, wt, xf, n_full, g, K);
+    sk_load<NT, MT, JB, true, RM>(ft, wt, xf, n_full, g, K);
     sk_mma<NT, MT, JB>(ft, acc);
   }
 
@@ -714,7 +728,7 @@ hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int laye
   SkArgs a = sk_base(c->ws + c->map.xn, g.T, f.d_model);
   if (g.T > SK_MAX_ROWS) a.rscale = WSM(c, rscale, float);
   else sk_row_scale(c, a, n_ss);
-  const dllm_layer_w& P = c->packed_layers[layer];
+  const dllm_layer_w& P = g.T > SK_MAX_ROWS ? c->layers[layer] : c->packed_layers[layer];
   a.W0 = (const bf16_t*)P.wq; a.W1 = (const bf16_t*)P.wk; a.W2 = (const bf16_t*)P.wv;
   a.N0 = f.n_q_heads * f.head_dim; a.N1 = a.N2 = f.n_kv_heads * f.head_dim;
   a.out_bf16 = WSM(c, q, bf16_t);
