@@ -309,6 +309,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(const LgArgs a) {
 // The activations are the first operand, so a lane holds one weight row and consecutive registers hold token rows;
 // the weight rows of a wave are dealt to its tiles (LDS row i*32 + c holds feature TN*c + i) so that a lane's TN tiles
 // are TN consecutive features: a row's stores are whole cache lines.  (LMSTATS: weights first, a lane holds one token.)
+constexpr int GT_APART_ROWS = 256;   // up to this many real rows the column tiles start their sums apart (item_at)
 typedef __amdgpu_buffer_rsrc_t gt_rsrc;
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 #define GT_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
@@ -377,11 +378,12 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // stages apart instead.  With more rows the activations no longer stay in the L2, which the column tiles share only in step.
   // (128 rows: 24576 x 4096 53.6 -> 51.7 us, 12288 x 4096 33.5 -> 30.9; a whole pass of 128 rows 782 -> 746 us.)  By the rows
   // there are and not the host's bound, by weight rows and not tiles (gate/up: by 1920 features, which tiles of every width end
-  // at; per tile 43.9 us and so 44.9 for 128 x 24576 x 4096 on 128 x 96 tiles, 59.7 and 58.9 at 256 rows): where a call with a device-resident total gets the
+  // at; per tile 43.9 us and so 44.9 for 128 x 24576 x 4096 on 128 x 96 tiles, 59.7 and 58.9 at 256 rows; tiles that would lie across
+  // the groups are left to calls that never start apart, gt_starts_apart): where a call with a device-resident total gets the
   // same K split and the same q/k/v form as the sized call, it sums in the same order whatever its tiles.  Those two are
   // chosen by the host's bound (4096 x 4096: three shares at 600 rows, one at 700), so it need not get them; and a
   // row's sums begin elsewhere when the rows of its call pass 256.
-  const int k_rot = M <= 256 ? 11 : 0;
+  const int k_rot = M <= GT_APART_ROWS ? 11 : 0;
   struct Item { int split, tm, n0, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
     Item t{0, 0, 0, 0, k_all, 0, false, false};
@@ -1019,7 +1021,11 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int n_fir
 // of 128 x 160 47.  One for residual projections, 256 x 224 at 0.90: 1024 x 3584 x 18944 in four K shares is 224 tiles of 256 x
 // 256 or 256 of these, 132 / 123.
 enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_256x224 = 8, GT_N = 9 };
-constexpr unsigned GT_ODD_TILES = 0xf0u;
+constexpr unsigned GT_ODD_TILES = 0xf0u, GT_RESID_TILES = 0xfu, GT_RESID_224 = 0x100u;
+// Column tiles of the call may start their sums apart: every tile has to lie inside one group of columns with a common start.
+// Residual tiles of 224 weight rows (groups of 256; in groups of 1792, which they would fit, the other tiles take 0.2 .. 0.6 us
+// more of 12 .. 50 at 72 .. 256 rows) and odd gate/up tiles that do not begin at column 0 (groups of 1920) do not.
+static bool gt_starts_apart(int M, const int32_t* m_dev) { return M <= GT_APART_ROWS || m_dev != nullptr; }
 struct GtPlan { GtTile tile; int splits, k_per; double us; };
 // NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile that its widths allow
 // fold_us_per_share: what each share behind the first costs (written here, read by the kernel that adds it)
@@ -1103,7 +1109,8 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
   a.delta = (float*)(c->ws + c->map.delta);
   a.delta_stride = c->map.lg_delta_stride;
   if (gt_usable(M, K)) {
-    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, 0x10fu, 1.0 + 8.0 * M * (double)N / 4.0e6);
+    const unsigned tiles_ok = GT_RESID_TILES | (gt_starts_apart(M, a.m_dev) ? 0u : GT_RESID_224);
+    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, tiles_ok, 1.0 + 8.0 * M * (double)N / 4.0e6);
     a.k_per = p.k_per;
     *n_delta = p.splits - 1;
     const int n_tn = gt_whole_rounds(M, N, K, 0x6u, p.us);
@@ -1243,7 +1250,7 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wg; a.W2 = (const bf16_t*)Wu; a.C = H; a.M = M; a.N = F; a.K = K;
   if (gt_usable(M, K)) {
     const GtPlan p = gt_plan(M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0);
-    const unsigned rest_ok = 0x6u | GT_ODD_TILES;
+    const unsigned rest_ok = 0x6u | (gt_starts_apart(M, m_dev) ? 0u : GT_ODD_TILES);
     const int n_tn = gt_whole_rounds(M, 2 * F, K, rest_ok, p.us);
     if (n_tn > 0) {
       const hipError_t e = gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, 0, n_tn);

@@ -117,6 +117,59 @@ def test_columns_behind_the_whole_rounds(ms, B, Q):
     run(ms, [5 + b % 3 for b in range(B)], Q)
 
 
+def device_weights(ms, seed):
+    """Seeded weights made on the device (wide layers): ({name: tensor}, [{name: tensor} per layer])."""
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(seed)
+
+    def mat(rows, cols, std=0.02):
+        return torch.randn(rows, cols, generator=gen, device=dev).mul_(std).to(torch.bfloat16)
+
+    one = torch.ones(ms.d_model, dtype=torch.bfloat16, device=dev)
+    d, dq, dkv, f = ms.d_model, ms.n_q_heads * ms.head_dim, ms.n_kv_heads * ms.head_dim, ms.d_ff
+    g = {"tok_emb": mat(ms.vocab, d), "lm_head": mat(ms.vocab, d, 0.02 * ms.lm_head_scale), "final_norm": one}
+    layers = [{"attn_norm": one, "wq": mat(dq, d), "wk": mat(dkv, d), "wv": mat(dkv, d), "wo": mat(d, dq), "mlp_norm": one,
+               "w_gate": mat(f, d), "w_up": mat(f, d), "w_down": mat(d, f)} for _ in range(ms.n_layers)]
+    return g, layers
+
+
+# 200 real rows behind a capacity of 1024.  The down projection of 3072 -> 4160 channels has three K shares at either size and
+# sums whose starts go by 256 columns; gate/up of 37888 weight rows is whole rounds of 256 x 256 tiles and a rest that begins
+# inside a group of 1920 features with a common start, and the down projection behind it has four shares again.  (One head of
+# 64 channels: the q/k/v product takes the same form at either size.  Sums in another order round otherwise in about one of
+# 10^4 bfloat16 numbers: of the seeds of the second case about every other one showed 64 features that were summed so.)
+@pytest.mark.parametrize("d,ff,seed", [(4160, 3072, 4), (1024, 18944, 0)], ids=["down", "gate-up"])
+def test_device_resident_total_sums_like_the_sized_call_whatever_its_tiles(d, ff, seed):
+    """The tiles are chosen by the host's bound, where a sum starts by the rows there are: dllm_refresh_cache_dev with a
+    capacity far above the total is dllm_refresh_cache of the total, bit for bit."""
+    ms = synth.ModelShape(2, d, 1, 1, 64, ff, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"device-total-{d}-{ff}")
+    lens, cap, Q, pt = [120, 80], 1024, 16, 32
+    total, B, mp = sum(lens), len(lens), 4
+    w = device_weights(ms, seed)
+    out = []
+    for n in (total, cap):
+        eng = binding.Engine(ms, None, page_tokens=pt, max_pages_per_seq=mp, n_pages=B * mp, max_batch=B, max_q=64, max_tokens=cap,
+                             device_weights=w)
+        toks = np.full(n, 3, dtype=np.int32)
+        toks[:total] = np.concatenate([np.concatenate([synth.random_tokens(ms, 60 + b, k - Q), synth.masked_block(ms, 70 + b, Q, Q)])
+                                       for b, k in enumerate(lens)])
+        cu, table = eng.i32([0, lens[0], total]), eng.i32(H.identity_table(eng, B))
+        ncommit = eng.i32([k - Q for k in lens])
+        cand = torch.zeros(n, dtype=torch.int32, device=eng.device)
+        conf, ent = (torch.zeros(n, dtype=torch.float32, device=eng.device) for _ in range(2))
+        if n == total:
+            eng.refresh_cache(eng.i32(toks), cu, table, ncommit, cand, conf, ent, total_tokens=n, max_seqlen=max(lens))
+        else:
+            eng.refresh_cache_dev(eng.i32(toks), cu, table, ncommit, cand, conf, ent, max_seqlen=max(lens))
+        assert eng.read_status() == 0
+        out.append([eng.kv_pool.clone(), cand[:total], conf[:total], ent[:total]])
+        eng.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    assert (out[0][2][-Q:] > 0.0).all()                     # the rows in flight are reported
+
+
 @pytest.mark.parametrize("ms", [EDGE, LONG], ids=["head-dim-64", "head-dim-128"])
 @pytest.mark.parametrize("lens,n_cache,pt", [([129, 70, 31], [129, 64, 0], 32), ([67], [66], 24), ([300, 3, 5, 150], [299, 3, 2, 150], 64)])
 def test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt):
