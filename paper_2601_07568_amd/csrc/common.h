@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include "../../include/dllm.h"
+#include "launch_plan.h"
 
 namespace dllm {
 
@@ -264,7 +265,6 @@ inline size_t kv_slab_elems(const dllm_config& c) {
 // floats between the rows of ws.ss: room for a partial sum of squares per 16 columns of d_model
 inline int ss_row_stride(const dllm_ctx* c) { return ((c->cfg.d_model + 15) / 16 + 3) / 4 * 4; }
 constexpr int LM_TILE_N = 512;      // vocabulary columns per LM-head partial
-constexpr int ATTN_MAX_SPLITS = 64;
 
 // ---- launchers implemented in kernels_generic.hip (any shape, both dtypes) -------------------
 struct StepGeom {           // which tokens a forward runs over

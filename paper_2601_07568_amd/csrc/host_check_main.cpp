@@ -1,7 +1,7 @@
 // Host-side exercise of the C ABI for a sanitizer build (AddressSanitizer + UndefinedBehaviorSanitizer on the host
 // code only): every entry point is driven through its argument validation, the workspace map and the context
 // life cycle with device pointers that are never dereferenced on the host, and the order in which the tile kernel's copies
-// and products run through their work (gemm_ring.h) is checked.  No GPU is needed: nothing is launched.
+// and products run through their work (gemm_ring.h) and the attention's launch (launch_plan.h) are checked.  No GPU is needed: nothing is launched.
 // Exit status 0 = every call returned what it should; the sanitizers abort the process on a finding.
 #include <stdio.h>
 #include <stdlib.h>
@@ -10,6 +10,7 @@
 #include <vector>
 #include "../../include/dllm.h"
 #include "gemm_ring.h"
+#include "launch_plan.h"
 
 static int failures = 0;
 #define EXPECT(call, want)                                                            \
@@ -68,7 +69,39 @@ static int ring_errors(int ring, int nsw, int stages, int n_items, int slots) {
   return errors;
 }
 
+// The attention launch over sizes: what it asks for fits, and the staged kernel takes every call of at least four row groups
+// over pages that are a power of two of at least 8 tokens, however long its sequences, as long as the partials of enough units
+// have room.  Returns the number of plans that break this.
+static int attn_plan_errors() {
+  using namespace dllm;
+  int errors = 0;
+  const int heads[][2] = {{28, 4}, {32, 32}, {32, 8}, {7, 1}};
+  const int kvs[] = {1, 64, 97, 2048, 8192, 65536, 65537, 70032, 140032, 300032, 524288};
+  for (const auto& h : heads)
+    for (int dh = 64; dh <= 128; dh += 64)
+      for (int B = 1; B <= 512; B *= 8)
+        for (int Q = 0; Q <= 128; Q += 32)
+          for (int pt = 8; pt <= 256; pt *= 2)
+            for (int kv : kvs) {
+              if (kv < Q || (Q == 0 && (int64_t)B * kv > 1 << 20)) continue;
+              const int T = Q > 0 ? B * Q : B * kv;
+              int64_t rows = (int64_t)T * h[0] * 8;           // (the workspace holds eight units, and 65536 rows at least)
+              if (rows < 65536) rows = 65536;
+              const AttnPlan p = attn_plan(dh, h[0], h[1], B, Q, T, kv, pt, rows, true);
+              const int groups = ((Q > 0 ? Q : kv) * (h[0] / h[1]) + 31) / 32;
+              const int blocks = (kv + 63) / 64, per_unit = (blocks + p.units - 1) / p.units;
+              const bool ok = p.units >= 1 && p.units <= ATTN_MAX_SPLITS && p.units % p.kspl == 0 &&
+                              (p.units == p.kspl || (int64_t)(p.units / p.kspl) * T * h[0] <= rows) &&
+                              p.lds <= (size_t)DL_LDS_MAX && p.n_rg_wg * p.n_chunks >= groups && p.staged == (groups >= 4) &&
+                              (!p.staged || Q == 0 || (p.pg_cap >= per_unit * (pt < 64 ? 64 / pt : 1) &&
+                                                       p.lds >= (size_t)DL_NB * dh * 256 + 4 * (size_t)p.pg_cap));
+              if (!ok && errors++ < 5) printf("attention plan: heads %d/%d x %d, B %d, Q %d, %d keys, pages of %d\n", h[0], h[1], dh, B, Q, kv, pt);
+            }
+  return errors;
+}
+
 int main() {
+  EXPECT(attn_plan_errors(), 0);
   const int rings[][2] = {{2, 3}, {3, 4}, {4, 5}, {3, 3}, {4, 4}, {5, 5}};
   for (const auto& r : rings)
     for (int stages = 2; stages <= 8; ++stages)

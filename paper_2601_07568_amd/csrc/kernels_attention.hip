@@ -30,7 +30,7 @@ struct AttnArgs {
   int n_parts;              // partials per row = workgroups along the keys
   int n_rg_wg;              // row groups per workgroup
   int pt_shift;             // log2(page_tokens) if that is a power of two (0 for the packed scratch), else -1
-  int pg_cap;               // k_attn_dl: page ids of a sequence that its LDS copy of the block table holds
+  int pg_cap;               // k_attn_dl: page ids of a unit's blocks that its LDS copy of the block table holds
   float scale_log2;         // log2(e) / sqrt(DH)
   float* part_o;            // [T*Hq, n_units, DH]
   float* part_ml;           // [T*Hq, n_units, 2]
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(512) void k_attn_combine(const float* part_o, const
 // 128-byte lines, its 16-byte pieces xor-ed with the row so that the 16 lanes an LDS read serves at a time touch every
 // bank once.  NB = 4 buffers form a ring: two blocks are in flight while the products read three (below); the only
 // wait on memory is "the next block has landed", once per block, together with the barrier that frees the oldest
-// buffer.  The page ids of the sequence lie in LDS; keys past the sequence end are read as they lie in the page (or
+// buffer.  The page ids of the unit's blocks lie in LDS; keys past the sequence end are read as they lie in the page (or
 // workspace), their scores are masked and their V^T columns zeroed in LDS before use, as are those of keys whose page
 // id is not addressable.
 //
@@ -457,7 +457,6 @@ template <typename T>
 __device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
 template <typename T, typename U>
 __device__ __forceinline__ void pin(T& x, U& y) { asm volatile("" : "+v"(x), "+v"(y)); }
-constexpr int DL_NB = 4;
 // PG: 0 packed scratch; 1 paged, a 64-key block lies inside a page; 2 paged, smaller pages (a power of two of at least 8)
 template <int DH, int PG>
 __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
@@ -489,14 +488,16 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
   const int64_t pcol = PG ? 0 : kv.cu_pad[b];
   uint32_t bad = 0;
   const int nkb = (kv_len + 63) >> 6;
+  const int n_own = unit < nkb ? (nkb - 1 - unit) / a.n_units + 1 : 0;   // the unit's blocks: unit, unit + n_units, ..
 
   int np = 0;
   const int32_t* const table = PG ? kv.table + (int64_t)b * kv.max_pages : nullptr;
   if constexpr (PG != 0) {
     np = (kv_len + pt - 1) >> sh;
-    np = np < a.pg_cap ? np : a.pg_cap;
     np = np < kv.max_pages ? np : kv.max_pages;
   }
+  const int ids_sh = PG == 2 ? 6 - sh : 0;                     // log2 of the page ids of a block
+  const int n_ids = PG == 0 ? 0 : n_own << ids_sh < a.pg_cap ? n_own << ids_sh : a.pg_cap;
 
   // this lane's source offsets (bytes from the block's K or V^T base) for the wave's copies; with small pages the
   // key (from the block's first) and the offset from its page's K row or V^T column
@@ -520,10 +521,12 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
     if constexpr (PG == 2) fkey[i] = key;
   }
   uint32_t badbuf = 0;                                        // buffers with keys from a page id out of range
-  auto page_of = [&](int kb64) -> int {
+  // own: 0, 1, .. of the unit's blocks; past the last one it is the last one
+  auto clampo = [&](int own) { return own < n_own ? own : n_own - 1; };
+  auto block_of = [&](int own) { return unit + clampo(own) * a.n_units; };
+  auto page_of = [&](int own) -> int {
     if constexpr (PG != 1) return 0;
-    const int pi = (kb64 << 6) >> sh;
-    return pi < np ? s_pg[pi] : -1;
+    return s_pg[clampo(own)];
   };
   // The block being copied, as a descriptor that ends with it.  (The form of the copies that goes through a flat address
   // makes the compiler wait for all LDS reads wherever it waits for one; small pages, whose keys lie wherever their page
@@ -555,12 +558,12 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
       rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(wave_k ? kslab + kb : vslab + vb), 0, bytes, 0x00020000);
     }
   };
-  auto copy = [&](int kb64, int buf, int i) {
+  auto copy = [&](int own, int buf, int i) {
     void* const dst = dl_smem + buf * BLK + (w * FPW + i) * 1024;
     if constexpr (PG == 2) {
-      const int key = (kb64 << 6) + fkey[i], pi = key >> sh;
-      const int page = s_pg[pi < np ? pi : 0];
-      const bool ok = pi < np && (uint32_t)page < (uint32_t)kv.n_pages;
+      const int key = (block_of(own) << 6) + fkey[i];
+      const int page = s_pg[(clampo(own) << ids_sh) + (fkey[i] >> sh)];
+      const bool ok = (uint32_t)page < (uint32_t)kv.n_pages;
       if (!ok && key < kv_len) { bad = 1; badbuf |= 1u << buf; }
       const int64_t rows = (((int64_t)(ok ? page : 0) * kv.n_kv_heads + kvh) << sh);
       const bf16_t* p = src + rows * DH + (wave_k ? (key & (pt - 1)) * DH : (key & (pt - 1))) + foff[i];
@@ -569,22 +572,23 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, foff[i], 0, 0, 0);
     }
   };
-  const int last = unit < nkb ? unit + ((nkb - 1 - unit) / a.n_units) * a.n_units : unit;
-  auto clampb = [&](int kb) { return kb <= last ? kb : last; };
   // the ring's first blocks (past the end: repeats of the last block into buffers nobody reads); their page ids come
   // straight from the table, so that the copies are on their way before anything else is waited for
   auto first_blocks = [&]() {
 #pragma unroll
     for (int j = 0; j < NB - 1; ++j) {
-      const int kb = clampb(unit + j * a.n_units), pi = (kb << 6) >> sh;
+      const int kb = block_of(j), pi = (kb << 6) >> sh;
       copy_base(kb, j, PG == 1 && pi < np ? table[pi] : -1);
 #pragma unroll
-      for (int i = 0; i < FPW; ++i) copy(kb, j, i);
+      for (int i = 0; i < FPW; ++i) copy(j, j, i);
     }
   };
-  if (PG != 2 && unit < nkb) first_blocks();
+  if (PG != 2 && n_own > 0) first_blocks();
   if constexpr (PG != 0)
-    for (int i = tid; i < np; i += nthr) s_pg[i] = table[i];
+    for (int i = tid; i < n_ids; i += nthr) {
+      const int pi = (((unit + (i >> ids_sh) * a.n_units) << 6) >> sh) + (i & ((1 << ids_sh) - 1));
+      s_pg[i] = pi < np ? table[pi] : -1;
+    }
 
   u32x4 qf[KK];               // B operand: column r = the lane's query
   int64_t row_out;            // its (token * Hq + head), -1 if beyond R
@@ -607,11 +611,12 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
   __syncthreads();                                            // page ids are in LDS
 
   // zeroes the V^T columns of keys past the sequence end and of keys without a page
-  auto fix_tail = [&](int kb64, int buf) {
+  auto fix_tail = [&](int own, int buf) {
+    const int kb64 = unit + own * a.n_units;
     bool any = (kb64 << 6) + 64 > kv_len;
     if constexpr (PG == 1) any |= (badbuf >> buf) & 1u;
     if constexpr (PG == 2) {
-      for (int p = (kb64 << 6) >> sh; p <= ((kb64 << 6) + 63) >> sh; ++p) any |= p >= np || (uint32_t)s_pg[p] >= (uint32_t)kv.n_pages;
+      for (int p = 0; p < 1 << ids_sh; ++p) any |= (uint32_t)s_pg[(own << ids_sh) + p] >= (uint32_t)kv.n_pages;
     }
     if (!any) return;
     u32x4* vb = (u32x4*)(dl_smem + buf * BLK + NKF * 1024);
@@ -620,8 +625,7 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
       int valid = kv_len - key;
       if constexpr (PG == 1) valid = ((badbuf >> buf) & 1u) ? 0 : valid;
       if constexpr (PG == 2) {
-        const int pi = key >> sh;
-        if (pi >= np || (uint32_t)s_pg[pi] >= (uint32_t)kv.n_pages) valid = 0;
+        if ((uint32_t)s_pg[(own << ids_sh) + ((key & 63) >> sh)] >= (uint32_t)kv.n_pages) valid = 0;
       }
       if (valid < 8) {
         u32x4 v = vb[q];
@@ -794,14 +798,14 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
 
-  if (unit < nkb) {          // (a unit without keys still writes its empty partial below)
+  if (n_own > 0) {           // (a unit without keys still writes its empty partial below)
     if (PG == 2) first_blocks();
-    int pg_next = page_of(clampb(unit + (NB - 1) * a.n_units));
+    int pg_next = page_of(NB - 1);
     // the first block has landed; with everything in front of it (PG 2), or with the q loads that were issued behind it
     if constexpr (PG == 2) __builtin_amdgcn_s_waitcnt(DL_VMCNT(2 * FPW));
     else __builtin_amdgcn_s_waitcnt(DL_VMCNT(0));
     __builtin_amdgcn_s_barrier();
-    fix_tail(unit, 0);        // read behind the barrier inside the loop
+    fix_tail(0, 0);           // read behind the barrier inside the loop
     int buf = 0;
     float mx = -DEV_INF;
     if (active) {
@@ -818,11 +822,12 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
 #pragma unroll
       for (int d = 0; d < DT; ++d) v0[d] = u32x4{0, 0, 0, 0};
     }
-    for (int kb = unit; kb < nkb; kb += a.n_units) {
+    for (int own = 0; own < n_own; ++own) {
+      const int kb = unit + own * a.n_units;
       const int nbuf = buf == 0 ? NB - 1 : buf - 1;            // (buf + NB - 1) % NB: the buffer of the block before
       const int buf1 = buf + 1 == NB ? 0 : buf + 1;
-      const int kn = clampb(kb + (NB - 1) * a.n_units);
-      if (kb != unit) fix_tail(kb, buf);
+      const int kn = block_of(own + NB - 1);
+      if (own > 0) fix_tail(own, buf);
       // (the counts are exact only while the loop issues no other vector memory instruction: no spills to scratch,
       // which the build's resource report shows)
       auto turn = [&]() {
@@ -832,15 +837,15 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
       };
       if (active) {
         settle(sc, mx, kb << 6, pb);
-        mx = half_step(I1{}, I1{}, I0{}, I0{}, sc, sn, pa, pb, [&]() { turn(); k_addr(buf1); v_addr(buf); }, [&](int i) { copy(kn, nbuf, i); });
-        pg_next = page_of(clampb(kb + NB * a.n_units));
+        mx = half_step(I1{}, I1{}, I0{}, I0{}, sc, sn, pa, pb, [&]() { turn(); k_addr(buf1); v_addr(buf); }, [&](int i) { copy(own + NB - 1, nbuf, i); });
+        pg_next = page_of(own + NB);
         settle(sn, mx, (kb << 6) + 32, pa);
         mx = half_step(I0{}, I0{}, I1{}, I1{}, sn, sc, pb, pa, [&]() {}, [&](int) {});
       } else {
         turn();
 #pragma unroll
-        for (int i = 0; i < FPW; ++i) copy(kn, nbuf, i);
-        pg_next = page_of(clampb(kb + NB * a.n_units));
+        for (int i = 0; i < FPW; ++i) copy(own + NB - 1, nbuf, i);
+        pg_next = page_of(own + NB);
       }
       buf = buf1;
     }
@@ -901,7 +906,6 @@ bool attn_step_supported(const dllm_ctx* c, const StepGeom& g) {
 // Attention of a denoise step (paged pool) or of a no-cache forward (packed scratch).
 // merging four waves' partial results takes a little more LDS than a kernel gets by default
 static bool attn_merge_ready = false;
-constexpr int DL_LDS_MAX = 160 * 1024;          // ring of k_attn_dl plus its copy of a sequence's page ids
 hipError_t init_attn_kernels() {
   if (attn_merge_ready) return hipSuccess;
   hipError_t e = hipFuncSetAttribute((const void*)k_attn_step<128, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
@@ -917,56 +921,8 @@ hipError_t init_attn_kernels() {
 
 hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const KVView& kv, bool frag_out) {
   const dllm_config& f = c->cfg;
-  const int G = f.n_q_heads / f.n_kv_heads;
-  const int max_q = g.Q > 0 ? g.Q : g.max_kv;                 // most query rows of a sequence
-  const int R = max_q * G;
+  const AttnPlan p = attn_plan(f.head_dim, f.n_q_heads, f.n_kv_heads, g.B, g.Q, g.T, g.max_kv, f.page_tokens, c->map.attn_rows, attn_merge_ready);
   constexpr int QT = 2;
-  const int n_rg = (R + 16 * QT - 1) / (16 * QT);
-  int pt_shift = 0;
-  if (g.Q > 0) {
-    pt_shift = -1;
-    for (int sft = 3; sft < 31; ++sft) if (f.page_tokens == (1 << sft)) pt_shift = sft;
-  }
-  // many rows per KV head: K and V staged in LDS, up to 8 row groups per workgroup, if the ring and the page ids fit
-  const int pg_cap = g.Q > 0 ? (g.max_kv + f.page_tokens - 1) / f.page_tokens : 0;
-  const size_t dl_lds = (size_t)DL_NB * (f.head_dim / 4) * 1024 + (size_t)pg_cap * sizeof(int32_t);
-  const bool staged = n_rg >= 4 && pt_shift >= 0 && attn_merge_ready && dl_lds <= (size_t)DL_LDS_MAX;
-  const int rg_cap = staged ? 8 : 4;                           // the register-direct kernel runs at most 4 waves
-  const int n_rg_wg = n_rg < rg_cap ? n_rg : rg_cap;
-  const int n_chunks = (n_rg + n_rg_wg - 1) / n_rg_wg;
-  const int nkb = (g.max_kv + 31) / 32;
-  // units along the keys: short dependent chains matter more than partial traffic here (a step's
-  // attention is a few MB), so give every unit about two 32-key blocks, within the partial buffer
-  int64_t want = 2048 / ((int64_t)g.B * f.n_kv_heads * n_rg);
-  if (want < 1) want = 1;
-  int64_t by_work = staged ? (nkb + 7) / 8 : (nkb + 1) / 2;   // staged kernel: at least four 64-key blocks per unit ...
-  if (staged && by_work > 1) {   // (a single unit needs no combine)
-    // ... or two, or one, where that still leaves CUs without a workgroup (kernel + combine, us, four / two / one, 4 key heads of
-    // 7: 512 keys 17.3 + 4.8 / 15.5 + 4.8 / 13.7 + 4.8 in 12 / 20 / 36 workgroups, 2048 keys 19.7 + 4.8 / 16.7 + 5.3 / 15.6 + 7.2
-    // in 36 / 68 / 132, 8000 keys 22.0 + 6.1 / 20.9 + 10.0 / - in 128 / 252, 4 sequences of 2048 22.6 + 6.4 / 31.5 + 9.1 / - in
-    // 144 / 272)
-    const int64_t per_unit = (int64_t)n_chunks * g.B * f.n_kv_heads;
-    if ((nkb + 1) / 2 * per_unit <= 64) by_work = (nkb + 1) / 2;
-    else if ((nkb + 3) / 4 * per_unit <= 128) by_work = (nkb + 3) / 4;
-  }
-  int64_t by_space = c->map.attn_rows / ((int64_t)g.T * f.n_q_heads);
-  int64_t units = want < by_work ? want : by_work;
-  if (units > by_space) units = by_space;
-  if (units > ATTN_MAX_SPLITS) units = ATTN_MAX_SPLITS;
-  if (units < 1) units = 1;                                   // a single unit needs no partial buffer
-  // one row group per KV head (a batch-1 block on a multi-head model): four units share a workgroup and
-  // merge their partial results in LDS, which leaves a quarter of the partials to write and re-read
-  int kspl = 1;
-  // (also where more than 512 such workgroups are a second round: 32 sequences of 1024 keys, 32 key heads, as two single-wave
-  // units with their combine 126 + 16 us, as one workgroup of four waves 129)
-  if (!staged && n_rg == 1 && attn_merge_ready && by_work >= 4) {
-    kspl = 4;
-    int64_t parts = (nkb + 2 * kspl - 1) / (2 * kspl);
-    if (parts * kspl > want) parts = want / kspl;
-    if (parts > by_space) parts = by_space;
-    if (parts < 1) parts = 1;
-    units = parts * kspl;
-  }
   AttnArgs a;
   a.q = WSM(c, q, bf16_t);
   a.prefix_len = g.prefix_len;
@@ -976,32 +932,31 @@ hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const
   a.out_mt = frag_out ? (g.T + 15) / 16 : 0;
   a.kv = kv;
   a.Q = g.Q; a.Hq = f.n_q_heads; a.Hkv = f.n_kv_heads; a.B = g.B;
-  a.n_units = (int)units; a.kspl = kspl; a.n_rg_wg = n_rg_wg;
-  a.n_parts = (int)(units / kspl);
-  a.pt_shift = pt_shift;
+  a.n_units = p.units; a.kspl = p.kspl; a.n_rg_wg = p.n_rg_wg;
+  a.n_parts = p.units / p.kspl;
+  a.pt_shift = p.pt_shift;
+  a.pg_cap = p.pg_cap;
   a.scale_log2 = 1.4426950408889634f / sqrtf((float)f.head_dim);
   a.part_o = WSM(c, attn_part, float);
   a.part_ml = a.part_o + (size_t)c->map.attn_rows * f.head_dim;
   a.status = WSM(c, status, int32_t);
-  dim3 grid((unsigned)(units / kspl), n_chunks, g.B * f.n_kv_heads);
-  const int threads = 64 * n_rg_wg * kspl;
-  if (staged) {
-    a.pg_cap = pg_cap;
-    const int pg = g.Q == 0 ? 0 : (pt_shift >= 6 ? 1 : 2);
+  dim3 grid((unsigned)a.n_parts, p.n_chunks, g.B * f.n_kv_heads);
+  const int threads = 64 * p.n_rg_wg * p.kspl;
+  if (p.staged) {
+    const int pg = g.Q == 0 ? 0 : (p.pt_shift >= 6 ? 1 : 2);
 #define ATTN_DL(DHV)                                                            \
   do {                                                                          \
-    if (pg == 0) k_attn_dl<DHV, 0><<<grid, 512, dl_lds, s>>>(a);                \
-    else if (pg == 1) k_attn_dl<DHV, 1><<<grid, 512, dl_lds, s>>>(a);           \
-    else k_attn_dl<DHV, 2><<<grid, 512, dl_lds, s>>>(a);                        \
+    if (pg == 0) k_attn_dl<DHV, 0><<<grid, 512, p.lds, s>>>(a);                 \
+    else if (pg == 1) k_attn_dl<DHV, 1><<<grid, 512, p.lds, s>>>(a);            \
+    else k_attn_dl<DHV, 2><<<grid, 512, p.lds, s>>>(a);                         \
   } while (0)
     if (f.head_dim == 128) ATTN_DL(128);
     else ATTN_DL(64);
 #undef ATTN_DL
   } else {
-    const size_t lds = kspl > 1 ? (size_t)kspl * (2 * QT * 16 * sizeof(float) + (size_t)(f.head_dim / 16) * QT * 64 * 16) : 0;
-    if (f.head_dim == 64) k_attn_step<64, QT, 2><<<grid, threads, lds, s>>>(a);
-    else if (n_rg_wg > 1 && nkb >= 16 * units) k_attn_step<128, QT, 1><<<grid, threads, lds, s>>>(a);
-    else k_attn_step<128, QT, 2><<<grid, threads, lds, s>>>(a);
+    if (f.head_dim == 64) k_attn_step<64, QT, 2><<<grid, threads, p.lds, s>>>(a);
+    else if (p.n_rg_wg > 1 && (g.max_kv + 31) / 32 >= 16 * p.units) k_attn_step<128, QT, 1><<<grid, threads, p.lds, s>>>(a);
+    else k_attn_step<128, QT, 2><<<grid, threads, p.lds, s>>>(a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_parts == 1) return e;

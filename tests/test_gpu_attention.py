@@ -61,3 +61,31 @@ def test_key_block_edges_growing_scores_and_nan_slots(name, Q, pt, ramp):
         assert err <= tol, (lens[b], err)
     assert eng.read_status() == 0
     eng.close()
+
+
+@pytest.mark.parametrize("B", [1, 293])
+def test_more_page_ids_than_a_workgroup_keeps(B):
+    """One sequence of 66000 keys in pages of 8 (8250 page ids, of which LDS holds 8192 beside the ring), alone and first of
+    many short ones, where it would be a single unit along the keys.  The pages repeat: a pool of 64 stands for all of them."""
+    ms, Q, pt, n = SHAPES["g7-128"], 32, 8, 66000
+    w = synth.Weights(ms, 4)
+    lens = [n] + [40] * (B - 1)
+    mp, pool, own = (n + Q) // pt, 64, Q // pt
+    rng = np.random.default_rng(23)
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=pool + B * own, max_batch=B, max_q=Q, max_tokens=0)
+    table = rng.integers(0, pool, (B, mp)).astype(np.int32)
+    for b, k in enumerate(lens):
+        table[b, k // pt:k // pt + own] = pool + b * own + np.arange(own)
+    eng.kv_pool.view(torch.bfloat16).fill_(float("nan"))
+    k, v = (ST(rng.standard_normal((pool, ms.n_kv_heads, pt, ms.head_dim))) for _ in range(2))
+    for which, x in ((0, k), (1, v)):
+        eng.kv_slab(0, which)[:pool] = torch.as_tensor(np.asarray(x)).to(eng.device, torch.bfloat16)
+    blks = [synth.masked_block(ms, 30 + b, Q, Q // 2) for b in range(B)]
+    hidden = eng.debug_hidden(eng.i32(np.stack(blks)), eng.i32(lens), eng.i32(table), 1, max_prefix_len=n).cpu().numpy()
+    for b in {0, B // 2, B - 1}:
+        cache = [[np.asarray(x)[table[b, :lens[b] // pt]].transpose(0, 2, 1, 3).reshape(lens[b], ms.n_kv_heads, ms.head_dim)] for x in (k, v)]
+        _, x = O.forward_cached(w, blks[b], *cache, widen=W, store=ST, want_logits=False)
+        err = H.rel_err_rows(hidden[b], x).max()
+        assert err <= H.logit_tol("bf16", 1, "store"), (b, err)
+    assert eng.read_status() == 0
+    eng.close()
