@@ -340,9 +340,10 @@ static bool large_mfma(const dllm_ctx* c) {
 // kernel's, on the weights as given (the other products are quicker on the tile kernel).  us, the split tile product + the
 // rotary kernel behind it / this one (from packed weights): 12288 x 4096: 128 rows 31 + 16 / 44 (40), 96 rows 29 + 15 / 37 (34),
 // 80 rows 27 + 14 / 35 (32); 4608 x 3584: 128 rows 14.5 + 15 / 28.5 (24.5), 72 rows 12.5 + 15 / 22.5 (18.5); at 256 rows a
-// workgroup's accumulators no longer fit its registers.  (d_model: what the norm in front of it takes, which lays out its input.)
+// workgroup's accumulators no longer fit its registers.  (step_prologue_usable: the step's first launch, which lays out the first
+// layer's input.)
 static bool sk_qkv_rows(const dllm_ctx* c, const StepGeom& g) {
-  return large_mfma(c) && c->cfg.d_model <= 16384 && g.Q > 0 && g.T > SK_MAX_ROWS && g.T <= SK_QKV_ROWS;
+  return large_mfma(c) && step_prologue_usable(c) && g.Q > 0 && g.T > SK_MAX_ROWS && g.T <= SK_QKV_ROWS;
 }
 // the q/k/v product of many rows with the rotary embedding in it
 static bool tile_qkv_rope(const dllm_ctx* c, const StepGeom& g) {
@@ -409,7 +410,7 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
   int n_ss = 1;      // partial sums of squares the current skinny-path GEMM input comes with
   bool normed = !few && step_prologue(c, g, n_layers_run);   // the first layer's norm came with the embedding
   if (!few && !normed) {   // (elsewhere run_forward's prologue launch has done both)
-    TRY(launch_embed(c, s, g, n_layers_run > 0 ? c->layers[0].attn_norm : nullptr, &normed, qkv_mt), "embed");
+    TRY(launch_embed(c, s, g, n_layers_run > 0 ? c->layers[0].attn_norm : nullptr, &normed), "embed");
     TRY(launch_rope_table(c, s, g), "rope_table");
   }
   int pending = 0;   // open residual sums (K splits of the last residual projection) not yet added to x

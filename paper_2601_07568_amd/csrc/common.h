@@ -294,8 +294,8 @@ hipError_t launch_sk_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, con
 bool step_prologue_usable(const dllm_ctx* c);
 hipError_t launch_step_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool kv_loc, int frag_mt);
 StepMap step_map(dllm_ctx* c, const StepGeom& g, bool kv_loc);
-// gain: of the norm that reads the embeddings, or nullptr; *normed: that norm has been applied in the same launch (frag_mt as below)
-hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed, int frag_mt = 0);
+// gain: of the norm that reads the embeddings, or nullptr; *normed: that norm has been applied in the same launch
+hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed);
 hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g);
 // out[T or n_rows, d] = rmsnorm(x[row]) * gain; rows == nullptr: identity row map, n = T
 // frag_mt > 0: write in fragment order for frag_mt 16-row tiles (bfloat16 only)

@@ -835,8 +835,9 @@ __global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x
     if (!live) continue;
     const float g0 = bf16_to_f32((bf16_t)(gq[k].x & 0xffff)), g1 = bf16_to_f32((bf16_t)(gq[k].x >> 16));
     const float g2 = bf16_to_f32((bf16_t)(gq[k].y & 0xffff)), g3 = bf16_to_f32((bf16_t)(gq[k].y >> 16));
-    *(frag_mt > 0 ? (uint2*)(out + frag_offset(r, 4 * i, frag_mt)) : orow + i) = make_uint2((uint32_t)f32_to_bf16(v[k].x * g0) | ((uint32_t)f32_to_bf16(v[k].y * g1) << 16),
-                         (uint32_t)f32_to_bf16(v[k].z * g2) | ((uint32_t)f32_to_bf16(v[k].w * g3) << 16));
+    uint2* const o = frag_mt > 0 ? (uint2*)(out + frag_offset(r, 4 * i, frag_mt)) : orow + i;
+    *o = make_uint2((uint32_t)f32_to_bf16(v[k].x * g0) | ((uint32_t)f32_to_bf16(v[k].y * g1) << 16),
+                    (uint32_t)f32_to_bf16(v[k].z * g2) | ((uint32_t)f32_to_bf16(v[k].w * g3) << 16));
   }
   if (!live) return;
   ss = block_sum(ss, red);
@@ -851,14 +852,14 @@ __global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x
 // one workgroup of 256 threads holds a row in registers
 static bool rmsnorm_row4_usable(const dllm_ctx* c) { return IS_BF16(c) && c->cfg.d_model % 4 == 0 && c->cfg.d_model <= 16384; }
 
-hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed, int frag_mt) {
+hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool* normed) {
   const dllm_config& f = c->cfg;
   *normed = false;
   if (gain && rmsnorm_row4_usable(c)) {
     *normed = true;
 #define ROW4(NV) k_rmsnorm_row4<NV, true><<<g.T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,      \
                      WS(c, xn, bf16_t), nullptr, nullptr, nullptr, 0, 0, WS(c, rscale, float), c->rows_dev,               \
-                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t), nullptr, 0, frag_mt)
+                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t), nullptr, 0, 0)
     if (f.d_model <= 2048) ROW4(2);
     else if (f.d_model <= 4096) ROW4(4);
     else if (f.d_model <= 8192) ROW4(8);
@@ -948,8 +949,9 @@ hipError_t launch_rmsnorm(dllm_ctx* c, hipStream_t s, const void* gain, int T, c
   }
   else if (IS_BF16(c))
     k_rmsnorm<bf16_t><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,
-                                        WS(c, xn, bf16_t), rows, n_rows_dev, 0, WS(c, delta, float), n_delta,
+                                        WS(c, xn, bf16_t), rows, n_rows_dev, frag_mt, WS(c, delta, float), n_delta,
                                         c->map.lg_delta_stride, WS(c, rscale, float), rows ? nullptr : c->rows_dev);
+  else if (frag_mt > 0) return hipErrorInvalidValue;   // (bfloat16 operands only)
   else
     k_rmsnorm<float><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const float*)gain,
                                        WS(c, xn, float), rows, n_rows_dev, 0, nullptr, 0, 0, nullptr,
