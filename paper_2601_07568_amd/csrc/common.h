@@ -373,6 +373,7 @@ hipError_t launch_sk_head_rows(dllm_ctx* c, hipStream_t s, int max_rows);
 hipError_t launch_gemm_mfma(hipStream_t s, const void* A, const void* W, void* C, int M, int N, int K, Epi epi,
                             const float* rscale = nullptr, const int32_t* m_dev = nullptr);
 hipError_t init_attn_kernels();   // once per process (raises a kernel's LDS limit)
+int device_cus();              // compute units, as init_gemm_tiles found them (a multiple of 8; 256 before)
 hipError_t init_gemm_tiles();  // once per process, before the first large GEMM (raises the kernels' LDS limits)
 hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, const void* W, float* x, int M, int N, int K,
                                    int* n_delta);

@@ -309,7 +309,6 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(const LgArgs a) {
 // The activations are the first operand, so a lane holds one weight row and consecutive registers hold token rows;
 // the weight rows of a wave are dealt to its tiles (LDS row i*32 + c holds feature TN*c + i) so that a lane's TN tiles
 // are TN consecutive features: a row's stores are whole cache lines.  (LMSTATS: weights first, a lane holds one token.)
-constexpr int GT_APART_ROWS = 256;   // up to this many real rows the column tiles start their sums apart (item_at)
 typedef __amdgpu_buffer_rsrc_t gt_rsrc;
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 #define GT_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
@@ -933,7 +932,7 @@ template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF = false, int WM =
 __global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW, HALF, WM>(a); }
 
 // Rings above the default LDS limit of a kernel: raised once per process.
-static bool gt_ready = false;
+static bool gt_ready = false;   // (the tiles: launch_plan.h)
 static int gt_cus = 256;
 #define GT_KERNELS(X)                                                                                   \
   X(LG_SWIGLU, 4, 4, 2, 3) X(LG_SWIGLU, 2, 4, 2, 3) X(LG_SWIGLU, 2, 2, 4, 5)                            \
@@ -956,6 +955,8 @@ static hipError_t gt_raise_lds() {
       e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   return e;
 }
+int device_cus() { return gt_cus; }
+
 hipError_t init_gemm_tiles() {
   if (gt_ready) return hipSuccess;
   int dev = 0, cus = 0;
@@ -976,8 +977,6 @@ hipError_t init_gemm_tiles() {
 // more rows than the weight-streaming kernels take, K in whole or half 64-deep stages (two layers of 3616 channels, d_ff
 // 18976, us, k_gemm_mfma / this kernel: 97 rows 658 / 432, 700 rows 1438 / 892, 3000 rows 5508 / 3226)
 static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 32 == 0 && K >= 128; }
-// of a mask of tiles (bit per GtTile) those that are built for this K
-static unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0x1f2u; }
 
 // n_tn column tiles of a product from column n_first on (n_tn 0: all that are left)
 template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2>
@@ -1003,67 +1002,6 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int n_fir
   if (a.K != k_all) return hipErrorInvalidValue;
   k_gemm_tile<EPI, TM, TN, NSA, NSW, false, WM><<<wgs, 256, G::LDS, s>>>(a);
   return hipGetLastError();
-}
-
-// Which tile: the estimate counts rounds of one workgroup per CU in units of a 256 x 256 tile's time.  A 128 x 256 tile
-// costs 0.6 of it (half the products, three quarters of the bytes), a 128 x 128 one 0.33 (copies and products take
-// equally long), a 128 x 64 one 0.22, a 256 x 160 one 0.80, a 256 x 96 one 0.54, a 128 x 160 one 0.45.  Measured against each other (K = 3584 .. 18944, us): 1024 x 37888: 271 / 286 /
-// 297; 256 x 24576: 85 / 55 / 61; 128 x 24576: 85 / 50 / 39; 1024 x 3584 x 3584: 48 (4 K shares) / 38 (2) / 42.
-// Over 200 layers of 128 .. 8192 channels and 96 .. 16384 rows, 257 .. 511 among them, what it picks takes 0.47 .. 0.98 of the
-// time of the 32-deep kernels that were here before.
-//
-// Odd widths for gate/up: one round of one tile per CU decides there up to about 500 rows, and 128 and 256 columns
-// seldom make one (256 CUs; 24576 gate and up rows: 256 tiles of 96, 37888: 237 of 160).  Measured, the best of the
-// even tiles / these, us: 24576 x 4096: 128 rows 47.9 / 44.2 (128 x 96), 211 rows 59.3 / 56.9 and 256 rows 61.5 / 59.8 (256 x
-// 96), 300 rows 101 / 84 (128 x 160); 37888 x 3584: 65 rows 61.7 / 53.3 and 128 rows 67.3 / 58.4 (128 x 160), 211 rows
-// 83.5 / 71.8 and 256 rows 87.6 / 74.9 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its weights are all from
-// memory and two thirds of the CUs ask for them.  Behind whole rounds: 1024 x 10240 x 3584 as 160 tiles of 128 x 256 57, as 256
-// of 128 x 160 47.  One for residual projections, 256 x 224 at 0.90: 1024 x 3584 x 18944 in four K shares is 224 tiles of 256 x
-// 256 or 256 of these, 132 / 123.
-enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_256x224 = 8, GT_N = 9 };
-constexpr unsigned GT_ODD_TILES = 0xf0u, GT_RESID_TILES = 0xfu, GT_RESID_224 = 0x100u;
-// Column tiles of the call may start their sums apart: every tile has to lie inside one group of columns with a common start.
-// Residual tiles of 224 weight rows (groups of 256; in groups of 1792, which they would fit, the other tiles take 0.2 .. 0.6 us
-// more of 12 .. 50 at 72 .. 256 rows) and odd gate/up tiles that do not begin at column 0 (groups of 1920) do not.
-static bool gt_starts_apart(int M, const int32_t* m_dev) { return M <= GT_APART_ROWS || m_dev != nullptr; }
-struct GtPlan { GtTile tile; int splits, k_per; double us; };
-// NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile that its widths allow
-// fold_us_per_share: what each share behind the first costs (written here, read by the kernel that adds it)
-static GtPlan gt_plan(int M, int NW, int K, int max_splits, unsigned width_ok, double fold_us_per_share) {
-  static const int bm[GT_N] = {256, 128, 128, 128, 128, 128, 256, 256, 256}, bn[GT_N] = {256, 256, 128, 64, 96, 160, 96, 160, 224};
-  // (up to 256 rows a 128-row tile waits for its weights, which no other row tile has brought in)
-  const double unit[GT_N] = {1.0, M <= 128 && (width_ok & GT_ODD_TILES) ? 0.68 : 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22,
-                             M <= 128 ? 0.39 : 0.45, M <= 128 ? 0.60 : 0.45, 0.54, 0.80, 0.90};
-  GtPlan best{GT_128x128, 1, K, 1e30};
-  for (int c = 0; c < GT_N; ++c) {
-    if (!((gt_built(K, width_ok) >> c) & 1u)) continue;
-    const int tiles = ((M + bm[c] - 1) / bm[c]) * ((NW + bn[c] - 1) / bn[c]);
-    for (int sp = 1; sp <= max_splits; ++sp) {
-      if (sp > 1 && (K / sp < 512 || tiles * sp > gt_cus)) break;    // shares long enough to pay for fill and drain
-      const int k_per = ((K + sp - 1) / sp + 63) / 64 * 64;
-      const int n_sp = (K + k_per - 1) / k_per;
-      if (n_sp != sp) continue;
-      const double rounds = (double)((tiles * sp + gt_cus - 1) / gt_cus);
-      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain
-      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + 4.0) + (sp - 1) * fold_us_per_share;
-      if (t < best.us) best = GtPlan{(GtTile)c, sp, k_per, t};
-    }
-  }
-  return best;
-}
-
-// A last round of 256 x 256 tiles that fills few of the CUs takes as long as a whole one.  Returns how many column tiles
-// the whole rounds hold (0: none, or not worth it) when those and then the remaining columns as a launch of smaller
-// tiles, which spread over the chip, are estimated shorter than `one_us`, all columns in one launch.  The second launch
-// costs its boundary and a fill of its own, 6 us.  (592 tiles of a 1024 x 37888 x 3584 product: 256 -> 185 + 55 us;
-// 15348 x 3584 products of K = 3584 and 18944, 840 tiles: 1075 -> 1007 us on average.  The cut in
-// one launch, its remainder as a second loop of the same kernel, costs the main loop registers: 313 us.)
-static int gt_whole_rounds(int M, int NW, int K, unsigned rest_ok, double one_us) {
-  const int tiles_m = (M + 255) / 256, tiles_n = (NW + 255) / 256, rounds = tiles_m * tiles_n / gt_cus;
-  const int n_tn = rounds * gt_cus / tiles_m;
-  if (rounds < 1 || n_tn < 1 || n_tn >= tiles_n) return 0;
-  const double us = rounds * (1.6 * (K / 64) + 4.0) + gt_plan(M, NW - n_tn * 256, K, 1, rest_ok, 0.0).us + 6.0;
-  return us < one_us ? n_tn : 0;
 }
 
 template <int EPI>
@@ -1109,25 +1047,19 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
   a.delta = (float*)(c->ws + c->map.delta);
   a.delta_stride = c->map.lg_delta_stride;
   if (gt_usable(M, K)) {
-    const unsigned tiles_ok = GT_RESID_TILES | (gt_starts_apart(M, a.m_dev) ? 0u : GT_RESID_224);
-    const GtPlan p = gt_plan(M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, tiles_ok, 1.0 + 8.0 * M * (double)N / 4.0e6);
-    a.k_per = p.k_per;
-    *n_delta = p.splits - 1;
-    const int n_tn = gt_whole_rounds(M, N, K, 0x6u, p.us);
-    if (n_tn > 0) {
-      *n_delta = 0;
-      a.k_per = K;
-      const hipError_t e = gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, 1, 0, n_tn);
+    const GtForm f = gt_resid_form(gt_cus, M, N, K, can_split ? LG_MAX_DELTA + 1 : 1, gt_starts_apart(M, a.m_dev != nullptr));
+    a.k_per = f.k_per;
+    *n_delta = f.splits - 1;
+    if (f.n_tn > 0) {
+      const hipError_t e = gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, 1, 0, f.n_tn);
       if (e != hipSuccess) return e;
-      return gt_plan(M, N - n_tn * 256, K, 1, 0x6u, 0.0).tile == GT_128x256 ? gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, 1, n_tn * 256)
-                                                                            : gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, 1, n_tn * 256);
     }
-    switch (p.tile) {
-      case GT_256x256: return gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, p.splits);
-      case GT_128x256: return gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, p.splits);
-      case GT_256x224: return gt_launch<LG_RESID, 2, 7, 2, 3, 4>(s, a, p.splits);
-      case GT_128x128: return gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, p.splits);
-      default: return gt_launch<LG_RESID, 2, 1, 3, 4>(s, a, p.splits);
+    switch (f.tile) {
+      case GT_256x256: return gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, f.splits);
+      case GT_128x256: return gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, f.splits, f.n_tn * 256);
+      case GT_256x224: return gt_launch<LG_RESID, 2, 7, 2, 3, 4>(s, a, f.splits);
+      case GT_128x128: return gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, f.splits, f.n_tn * 256);
+      default: return gt_launch<LG_RESID, 2, 1, 3, 4>(s, a, f.splits);
     }
   }
   const int tiles = ((M + 127) / 128) * ((N + LG_BN - 1) / LG_BN);
@@ -1156,7 +1088,7 @@ hipError_t launch_gemm_qkv_split(dllm_ctx* c, hipStream_t s, const void* A, cons
   a.m_dev = c->rows_dev;
   // a tile belongs to one of the projections; the buffers of a split product cover lg_delta_rows rows
   const unsigned width_ok = (dq % 256 == 0 && dkv % 256 == 0 ? 0x3u : 0u) | (dq % 128 == 0 && dkv % 128 == 0 ? 0x4u : 0u) | 0x8u;
-  const GtPlan p = gt_plan(M, dq + 2 * dkv, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, width_ok, 1.0 + 8.0 * M * (dq + 2.0 * dkv) / 4.0e6);
+  const GtPlan p = gt_plan(gt_cus, M, dq + 2 * dkv, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, width_ok, 1.0 + 8.0 * M * (dq + 2.0 * dkv) / 4.0e6);
   a.k_per = p.k_per;
   a.delta = (float*)(c->ws + c->map.qkvp);
   a.delta_stride = c->map.qkvp_stride;
@@ -1185,8 +1117,8 @@ bool gemm_qkv_rope_wins(const dllm_ctx* c, int M) {
   const dllm_config& f = c->cfg;
   const int dq = f.n_q_heads * f.head_dim, dkv = f.n_kv_heads * f.head_dim, nw = dq + 2 * dkv, K = f.d_model;
   const bool w256 = dq % 256 == 0 && dkv % 256 == 0;
-  const GtPlan fused = gt_plan(M, nw, K, 1, (w256 && f.head_dim == 128 ? 0x1u : 0u) | 0x4u, 0.0);
-  const GtPlan split = gt_plan(M, nw, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, (w256 ? 0x3u : 0u) | 0xcu, 0.0);
+  const GtPlan fused = gt_plan(gt_cus, M, nw, K, 1, (w256 && f.head_dim == 128 ? 0x1u : 0u) | 0x4u, 0.0);
+  const GtPlan split = gt_plan(gt_cus, M, nw, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, (w256 ? 0x3u : 0u) | 0xcu, 0.0);
   return fused.us <= split.us + 10.0 + (4.0 * split.splits + 2.0) * M * (double)nw / 2.5e6;
 }
 hipError_t launch_gemm_qkv_rope(dllm_ctx* c, hipStream_t s, const void* A, const void* Wq, const void* Wk, const void* Wv,
@@ -1205,7 +1137,7 @@ hipError_t launch_gemm_qkv_rope(dllm_ctx* c, hipStream_t s, const void* A, const
   a.pool_k = (bf16_t*)pool.k; a.pool_v = (bf16_t*)pool.v; a.page_tokens = pool.page_tokens;
   if (pack) { a.pack_k = (bf16_t*)pack->k; a.pack_v = (bf16_t*)pack->v; a.tpad = pack->tpad; }
   const bool dh64 = f.head_dim == 64, w256 = dq % 256 == 0 && dkv % 256 == 0 && !dh64;
-  const GtPlan p = gt_plan(M, dq + 2 * dkv, K, 1, (w256 ? 0x1u : 0u) | 0x4u, 0.0);
+  const GtPlan p = gt_plan(gt_cus, M, dq + 2 * dkv, K, 1, (w256 ? 0x1u : 0u) | 0x4u, 0.0);
   if (p.tile == GT_256x256) return gt_launch<LG_ROPE128, 4, 4, 2, 3>(s, a);
   // one tile per CU: the deep ring; more: two workgroups per CU
   if (((M + 127) / 128) * ((dq + 2 * dkv) / 128) <= gt_cus)
@@ -1249,14 +1181,12 @@ hipError_t launch_gemm_swiglu(hipStream_t s, const void* A, const void* Wg, cons
   a.m_dev = m_dev;
   a.A = (const bf16_t*)A; a.W = (const bf16_t*)Wg; a.W2 = (const bf16_t*)Wu; a.C = H; a.M = M; a.N = F; a.K = K;
   if (gt_usable(M, K)) {
-    const GtPlan p = gt_plan(M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0);
-    const unsigned rest_ok = 0x6u | (gt_starts_apart(M, m_dev) ? 0u : GT_ODD_TILES);
-    const int n_tn = gt_whole_rounds(M, 2 * F, K, rest_ok, p.us);
-    if (n_tn > 0) {
-      const hipError_t e = gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, 0, n_tn);
-      return e != hipSuccess ? e : gt_launch_swiglu(s, a, gt_plan(M, 2 * F - n_tn * 256, K, 1, rest_ok, 0.0).tile, n_tn * 128);
+    const GtForm f = gt_swiglu_form(gt_cus, M, F, K, gt_starts_apart(M, m_dev != nullptr));
+    if (f.n_tn > 0) {
+      const hipError_t e = gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, 0, f.n_tn);
+      if (e != hipSuccess) return e;
     }
-    return gt_launch_swiglu(s, a, p.tile, 0);
+    return gt_launch_swiglu(s, a, f.tile, f.n_tn * 128);
   }
   return lg_launch<LG_SWIGLU>(s, a);
 }

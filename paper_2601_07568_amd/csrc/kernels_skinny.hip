@@ -744,7 +744,7 @@ hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int laye
   // Value tiles in workgroups of their own where all then still run at once (few key heads: 128 pair tiles and 32 value
   // tiles took 128 workgroups of three tiles, most of them with one to throw away: 16.0 -> 13.1 us at 32 rows of 3584,
   // 21.4 -> 19.0 at 64, 27.8 -> 24.3 at 128).
-  if (apart <= 256) return sk_launch_mt<2, SK_NW, SK_QKV>(s, a, apart);
+  if (apart <= device_cus()) return sk_launch_mt<2, SK_NW, SK_QKV>(s, a, apart);
   return sk_launch_mt<3, SK_NW, SK_QKV>(s, a, n_pairs > n_vt ? n_pairs : n_vt);
 }
 
@@ -761,9 +761,9 @@ hipError_t launch_sk_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_
   // the weights at 32 rows and twice as many at 64, and although the L2 serves them their time adds to the stream's (a
   // stream of 200 MB from memory with 0 / 200 / 400 / 800 MB from the L2 beside it: 32 / 37 / 46 / 64 us).  F = 12288,
   // K = 4096, us, one pair / three: 32 rows 40.0 / 38.1, 48 rows 46.4 / 40.4, 64 rows 59.2 / 42.4; F = 18944, K = 3584: 57.1 /
-  // 55.1, -, 82.1 / 68.3; 16 rows 36.3 / 36.7 and 48.1 / 51.3, hence one there; and one where three would leave CUs idle.
+  // 55.1, -, 82.1 / 68.3; 16 rows 36.3 / 36.7 and 48.1 / 51.3, hence one there; and one where three would leave more than a quarter of the CUs idle.
   const int pairs = (f.d_ff + 15) / 16;
-  if (M > 16 && pairs >= 3 * 192) return sk_launch_mt<6, SK_NW, SK_SWIGLU>(s, a, (pairs + 2) / 3);
+  if (M > 16 && pairs >= 3 * (device_cus() * 3 / 4)) return sk_launch_mt<6, SK_NW, SK_SWIGLU>(s, a, (pairs + 2) / 3);
   return sk_launch_mt<2, SK_NW, SK_SWIGLU>(s, a, pairs);
 }
 

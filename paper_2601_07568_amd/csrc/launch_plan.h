@@ -84,4 +84,88 @@ inline AttnPlan attn_plan(int head_dim, int n_q_heads, int n_kv_heads, int B, in
   return p;
 }
 
+// ---- products of more than 64 rows (k_gemm_tile)
+// Up to this many real rows the column tiles start their sums apart, in groups of 256 columns (gate/up: of 1920 features).
+constexpr int GT_APART_ROWS = 256;
+// Column tiles of the call may start their sums apart: every tile has to lie inside one group.  Residual tiles of 224 weight rows
+// (in groups of 1792, which they would fit, the other tiles take 0.2 .. 0.6 us more of 12 .. 50 at 72 .. 256 rows) and odd
+// gate/up tiles that do not begin at column 0 do not.  device_rows: the rows there are come from the device, M bounds them
+inline bool gt_starts_apart(int M, bool device_rows) { return M <= GT_APART_ROWS || device_rows; }
+
+// Which tile (token rows x weight rows): the estimate counts rounds of one workgroup per CU in units of a 256 x 256 tile's time.
+// A 128 x 256 tile costs 0.6 of it (half the products, three quarters of the bytes), a 128 x 128 one 0.33 (copies and products
+// take equally long), a 128 x 64 one 0.22, a 256 x 160 one 0.80, a 256 x 96 one 0.54, a 128 x 160 one 0.45.  Measured against
+// each other (K = 3584 .. 18944, us): 1024 x 37888: 271 / 286 / 297; 256 x 24576: 85 / 55 / 61; 128 x 24576: 85 / 50 / 39; 1024 x
+// 3584 x 3584: 48 (4 K shares) / 38 (2) / 42.
+// Over 200 layers of 128 .. 8192 channels and 96 .. 16384 rows, 257 .. 511 among them, what it picks takes 0.47 .. 0.98 of the
+// time of the 32-deep kernels that were here before.
+//
+// Odd widths for gate/up: one round of one tile per CU decides there up to about 500 rows, and 128 and 256 columns
+// seldom make one (256 CUs; 24576 gate and up rows: 256 tiles of 96, 37888: 237 of 160).  Measured, the best of the
+// even tiles / these, us: 24576 x 4096: 128 rows 47.9 / 44.2 (128 x 96), 211 rows 59.3 / 56.9 and 256 rows 61.5 / 59.8 (256 x
+// 96), 300 rows 101 / 84 (128 x 160); 37888 x 3584: 65 rows 61.7 / 53.3 and 128 rows 67.3 / 58.4 (128 x 160), 211 rows
+// 83.5 / 71.8 and 256 rows 87.6 / 74.9 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its weights are all from
+// memory and two thirds of the CUs ask for them (residual projections of 12288 and 14336 channels, whose plan that decides as
+// well, take the same time with either).  Behind whole rounds: 1024 x 10240 x 3584 as 160 tiles of 128 x 256 57, as 256
+// of 128 x 160 47.  One for residual projections, 256 x 224 at 0.90: 1024 x 3584 x 18944 in four K shares is 224 tiles of 256 x
+// 256 or 256 of these, 132 / 123.
+enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_256x224 = 8, GT_N = 9 };
+constexpr unsigned GT_ODD_TILES = 0xf0u, GT_RESID_TILES = 0xfu, GT_RESID_224 = 0x100u, GT_REST_TILES = 0x6u;
+// of a mask of tiles (bit per GtTile) those that are built for this K
+inline unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0x1f2u; }
+struct GtPlan { GtTile tile; int splits, k_per; double us; };
+// NW: weight rows of the product; max_splits 1: no K split; width_ok: bit per tile that its widths allow
+// fold_us_per_share: what each share behind the first costs (written here, read by the kernel that adds it)
+inline GtPlan gt_plan(int cus, int M, int NW, int K, int max_splits, unsigned width_ok, double fold_us_per_share) {
+  static const int bm[GT_N] = {256, 128, 128, 128, 128, 128, 256, 256, 256}, bn[GT_N] = {256, 256, 128, 64, 96, 160, 96, 160, 224};
+  // (up to 256 rows a 128-row tile waits for its weights, which no other row tile has brought in)
+  const double unit[GT_N] = {1.0, M <= 128 ? 0.68 : 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22,
+                             M <= 128 ? 0.39 : 0.45, M <= 128 ? 0.60 : 0.45, 0.54, 0.80, 0.90};
+  GtPlan best{GT_128x128, 1, K, 1e30};
+  for (int c = 0; c < GT_N; ++c) {
+    if (!((gt_built(K, width_ok) >> c) & 1u)) continue;
+    const int tiles = ((M + bm[c] - 1) / bm[c]) * ((NW + bn[c] - 1) / bn[c]);
+    for (int sp = 1; sp <= max_splits; ++sp) {
+      if (sp > 1 && (K / sp < 512 || tiles * sp > cus)) break;    // shares long enough to pay for fill and drain
+      const int k_per = ((K + sp - 1) / sp + 63) / 64 * 64;
+      const int n_sp = (K + k_per - 1) / k_per;
+      if (n_sp != sp) continue;
+      const double rounds = (double)((tiles * sp + cus - 1) / cus);
+      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain
+      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + 4.0) + (sp - 1) * fold_us_per_share;
+      if (t < best.us) best = GtPlan{(GtTile)c, sp, k_per, t};
+    }
+  }
+  return best;
+}
+
+// A last round of 256 x 256 tiles that fills few of the CUs takes as long as a whole one.  Returns how many column tiles
+// the whole rounds hold (0: none, or not worth it) when those and then the remaining columns as a launch of smaller
+// tiles, which spread over the chip, are estimated shorter than `one_us`, all columns in one launch.  The second launch
+// costs its boundary and a fill of its own, 6 us.  (592 tiles of a 1024 x 37888 x 3584 product: 256 -> 185 + 47 us.  The cut in
+// one launch, its remainder as a second loop of the same kernel, costs the main loop registers: 313 us.)
+inline int gt_whole_rounds(int cus, int M, int NW, int K, unsigned rest_ok, double one_us) {
+  const int tiles_m = (M + 255) / 256, tiles_n = (NW + 255) / 256, rounds = tiles_m * tiles_n / cus;
+  const int n_tn = rounds * cus / tiles_m;
+  if (rounds < 1 || n_tn < 1 || n_tn >= tiles_n) return 0;
+  const double us = rounds * (1.6 * (K / 64) + 4.0) + gt_plan(cus, M, NW - n_tn * 256, K, 1, rest_ok, 0.0).us + 6.0;
+  return us < one_us ? n_tn : 0;
+}
+
+// What a product launches: n_tn column tiles of 256 x 256 in whole rounds (0: none), the columns behind them in `tile`; without
+// whole rounds the sum over K may be in several shares of k_per.
+struct GtForm { GtTile tile; int splits, k_per, n_tn; };
+inline GtForm gt_form(int cus, int M, int NW, int K, const GtPlan& p, unsigned rest_ok) {
+  const int n_tn = gt_whole_rounds(cus, M, NW, K, rest_ok, p.us);
+  if (n_tn == 0) return GtForm{p.tile, p.splits, p.k_per, 0};
+  return GtForm{gt_plan(cus, M, NW - n_tn * 256, K, 1, rest_ok, 0.0).tile, 1, K, n_tn};
+}
+inline GtForm gt_resid_form(int cus, int M, int N, int K, int max_splits, bool starts_apart) {
+  const unsigned ok = GT_RESID_TILES | (starts_apart ? 0u : GT_RESID_224);
+  return gt_form(cus, M, N, K, gt_plan(cus, M, N, K, max_splits, ok, 1.0 + 8.0 * M * (double)N / 4.0e6), GT_REST_TILES);
+}
+inline GtForm gt_swiglu_form(int cus, int M, int F, int K, bool starts_apart) {
+  return gt_form(cus, M, 2 * F, K, gt_plan(cus, M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0), GT_REST_TILES | (starts_apart ? 0u : GT_ODD_TILES));
+}
+
 }  // namespace dllm
