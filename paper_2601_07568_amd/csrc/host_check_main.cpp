@@ -2,6 +2,7 @@
 // code only): every entry point is driven through its argument validation, the workspace map and the context
 // life cycle with device pointers that are never dereferenced on the host, and the order in which the tile kernel's copies
 // and products run through their work (gemm_ring.h) and the attention's launch (launch_plan.h) are checked.  No GPU is needed: nothing is launched.
+// With arguments it says instead which tiles products of given sizes get.
 // Exit status 0 = every call returned what it should; the sanitizers abort the process on a finding.
 #include <stdio.h>
 #include <stdlib.h>
@@ -100,7 +101,24 @@ static int attn_plan_errors() {
   return errors;
 }
 
-int main() {
+// "form" then (kind, rows, columns, K, starts_apart) for each product: what it launches on 256 CUs, a line each.  kind "gate-up"
+// (columns: features) or "resid" (at most four K shares): [whole rounds' column tiles +] tile [/ K shares].
+static int print_forms(int n, char** v) {
+  using namespace dllm;
+  static const char* const name[GT_N] = {"256x256", "128x256", "128x128", "128x64", "128x96", "128x160", "256x96", "256x160", "256x224"};
+  for (int i = 0; i + 4 < n; i += 5) {
+    const int M = atoi(v[i + 1]), N = atoi(v[i + 2]), K = atoi(v[i + 3]);
+    const bool apart = atoi(v[i + 4]) != 0;
+    const GtForm f = strcmp(v[i], "resid") == 0 ? gt_resid_form(256, M, N, K, 4, apart) : gt_swiglu_form(256, M, N, K, apart);
+    if (f.n_tn > 0) printf("%d+%s\n", f.n_tn, name[f.tile]);
+    else if (f.splits > 1) printf("%s/%d\n", name[f.tile], f.splits);
+    else printf("%s\n", name[f.tile]);
+  }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1 && strcmp(argv[1], "form") == 0) return print_forms(argc - 2, argv + 2);
   EXPECT(attn_plan_errors(), 0);
   const int rings[][2] = {{2, 3}, {3, 4}, {4, 5}, {3, 3}, {4, 4}, {5, 5}};
   for (const auto& r : rings)

@@ -180,14 +180,31 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
 
 
-def test_host_side_code_under_address_and_undefined_behaviour_sanitizers():
+@pytest.fixture(scope="module")
+def host_check():
+    return build.build_host_check()
+
+
+def test_gpu_tests_reach_the_tiles_that_they_name(host_check):
+    """The launches that the tile tests' products get, by the library's own rules (256 compute units), are the ones that the
+    tests are written for: what the rules learn later must not leave a tile, a remainder or a K split untested unnoticed."""
+    import subprocess
+    from tests import test_gpu_gemm_tiles as tiles
+    forms = tiles.FORMS
+    args = [str(x) for kind, rows, cols, k, _ in forms for x in (kind, rows, cols, k, int(rows <= 256))]
+    r = subprocess.run([host_check, "form", *args], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr[-2000:]
+    got = r.stdout.split()
+    assert got == [f[-1] for f in forms], [(f, g) for f, g in zip(forms, got) if f[-1] != g]
+
+
+def test_host_side_code_under_address_and_undefined_behaviour_sanitizers(host_check):
     """The library's host code (argument validation, workspace map, context life cycle, launch geometry up to the
     first launch) compiled with AddressSanitizer + UndefinedBehaviorSanitizer on the host side only and driven by
     csrc/host_check_main.cpp through every entry point, without a GPU: the sanitizers abort on a finding, the
     driver counts wrong return codes, and stages and tiles that the tile kernel's copies would fetch out of order."""
     import subprocess
-    exe = build.build_host_check()
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    r = subprocess.run([host_check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
     assert "host check: 0 failure(s)" in r.stdout
     assert "ERROR: AddressSanitizer" not in r.stderr and "runtime error" not in r.stderr

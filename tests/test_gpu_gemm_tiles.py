@@ -20,7 +20,7 @@ EDGE = synth.ModelShape(1, 576, 8, 2, 64, 1088, 1500, 1499, dtype="bf16", lm_hea
 LONG = synth.ModelShape(1, 256, 2, 2, 128, 4160, 700, 699, dtype="bf16", lm_head_scale=8.0, name="tile-long-k")
 
 
-def run(ms, lens, Q, seed=5, pt=32):
+def run(ms, lens, Q, seed=5, pt=32, head=True):
     w = synth.Weights(ms, seed)
     B = len(lens)
     mp = (max(lens) + Q + pt - 1) // pt
@@ -42,6 +42,8 @@ def run(ms, lens, Q, seed=5, pt=32):
         ck, cv = O.prefill(w, seqs[b], widen=W, store=ST)
         logits, x = O.forward_cached(w, blks[b], ck, cv, widen=W, store=ST)
         assert H.rel_err_rows(hidden[b], x).max() <= tol, (b, H.rel_err_rows(hidden[b], x).max())
+        if not head:
+            continue
         r = {"logits": logits, "cand": O.confidence(logits, ms.mask_id)[0]}
         H.check_step_outputs(ms, r, blks[b] == ms.mask_id, cand.cpu().numpy()[b], conf.cpu().numpy()[b],
                              ent.cpu().numpy()[b], "bf16")
@@ -106,14 +108,62 @@ def test_k_of_half_a_stage_more(ms, lens, Q):
     run(ms, lens, Q)
 
 
+# Gate/up in tiles of 96 and 160 weight rows: (d, ff, (sequences, rows), form).  Every width ends inside a tile; sums of two or
+# three stages (shorter than the rings) and of nine (longer); one row tile and two, the last of them nearly empty or not.
+ODD_TILES = [
+    (128, 2048, (1, 65), "128x96"), (576, 2056, (1, 128), "128x96"),
+    (192, 16392, (1, 65), "128x160"), (576, 5448, (3, 100), "128x160"),
+    (128, 10248, (1, 150), "256x96"), (576, 5128, (4, 100), "256x96"),
+    (128, 16392, (1, 255), "256x160"), (576, 8200, (4, 100), "256x160"),
+    # 410 items on 256 places
+    (192, 16392, (4, 100), "256x160"),
+]
+
+
+@pytest.mark.parametrize("d,ff,rows,form", ODD_TILES)
+def test_gate_up_in_odd_tiles(d, ff, rows, form):
+    ms = synth.ModelShape(1, d, 2, 2, 64, ff, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"odd-{form}-{d}-{ff}")
+    run(ms, [5 + b for b in range(rows[0])], rows[1])
+
+
+# Residual projections in tiles of 224 weight rows: (d, heads, ff, (sequences, rows), form of O, form of down), all with a width
+# that ends inside a tile: K of two stages and of twelve, more items than places (330 on 256); three K shares of unequal length
+RESID_224 = [
+    (2200, 2, 768, (83, 99), "256x224", "256x224"),
+    (4616, 2, 4160, (8, 97), "128x256", "256x224/3"),
+]
+
+
+@pytest.mark.parametrize("d,heads,ff,rows,o,down", RESID_224)
+def test_residual_projections_in_tiles_of_224(d, heads, ff, rows, o, down):
+    """(The residual stream alone: with thousands of rows some sequence has a handful of near ties, whose gap lies inside twice the
+    logit tolerance and binds no candidate, and one in nine of them fell the other way.)"""
+    ms = synth.ModelShape(1, d, heads, 1, 64, ff, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"resid-224-{d}-{ff}")
+    run(ms, [5 + b % 3 for b in range(rows[0])], rows[1], head=False)
+
+
+# Whole rounds of 256 x 256 gate/up tiles and the columns behind them in smaller ones: (d, ff, (sequences, rows), form)
+RESTS = [
+    (512, 21776, (1, 257), "128+128x128"), (768, 23216, (1, 257), "128+128x256"), (512, 21856, (1, 257), "128+128x160"),
+    (768, 11096, (8, 97), "64+256x96"),
+]
+
+
+@pytest.mark.parametrize("d,ff,rows,form", RESTS)
+def test_gate_up_behind_whole_rounds(d, ff, rows, form):
+    ms = synth.ModelShape(1, d, 2, 2, 64, ff, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"rest-{form}")
+    run(ms, [5 + b for b in range(rows[0])], rows[1])
+
+
 @pytest.mark.parametrize("ms,B,Q", [
-    # gate and up of 1016 rows: 64 column tiles of 256 in one whole round, two and a half left
+    # gate and up of 1016 rows: 256 x 160 tiles, 428 items on 256 places
     (synth.ModelShape(1, 768, 2, 2, 64, 8512, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-ff"), 8, 127),
     # down of 8217 rows: 7 of the 8 column tiles in one whole round, the last row tile of 25 rows
     (synth.ModelShape(1, 2048, 2, 1, 64, 768, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-out"), 83, 99),
 ], ids=["gate-up", "down"])
 def test_columns_behind_the_whole_rounds(ms, B, Q):
-    """Products whose last columns are a launch of smaller tiles behind whole rounds of 256 x 256 ones."""
+    """A product whose last columns are a launch of smaller tiles behind whole rounds of 256 x 256 ones, and one as wide that
+    is a launch of odd tiles."""
     run(ms, [5 + b % 3 for b in range(B)], Q)
 
 
@@ -298,3 +348,12 @@ def test_rows_that_are_not_finite_stay_to_themselves(ms, Q):
     assert torch.isnan(conf[1][masked]).all() and torch.isfinite(out[0][1]).all()
     assert ((cand[1] >= 0) & (cand[1] < ms.vocab)).all() and (cand[1][masked] != ms.mask_id).all()
     eng.close()
+
+
+# (kind, rows, columns, K, form) of the products that the tests above are written for: tests/test_abi_host.py holds them against
+# the library's own rules
+FORMS = ([("gate-up", b * q, ff, d, form) for d, ff, (b, q), form in ODD_TILES + RESTS] +
+         [("resid", b * q, d, heads * 64, o) for d, heads, ff, (b, q), o, down in RESID_224] +
+         [("resid", b * q, d, ff, down) for d, heads, ff, (b, q), o, down in RESID_224] +
+         [("gate-up", 8 * 127, 8512, 768, "256x160"), ("resid", 83 * 99, 2048, 768, "7+128x128"),
+          ("gate-up", 8 * 127, 8544, 800, "64+128x128")])

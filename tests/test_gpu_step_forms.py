@@ -40,12 +40,11 @@ def test_qkv_of_65_to_128_rows(ms, B, Q):
     run(ms, [40 + 9 * b for b in range(B)], Q)
 
 
-# gate/up in tiles of 96 and 160 weight rows: 24704 rows end inside a tile of either (on 256 CUs the first is taken for them up
-# to 256 rows), 37888 rows take the second; a sum of three stages is shorter than its ring, one of eight longer.  300 rows: a
-# second row tile, two items for some workgroups
+# wide gate/up products over row counts on both sides of 128 and 256: 24704 weight rows in tiles of an even number of 32, 37888 in
+# odd ones up to 256 rows (every odd tile, its remainders and its rests: test_gpu_gemm_tiles.py)
 @pytest.mark.parametrize("rows", [(1, 65), (1, 128), (3, 43), (1, 160), (2, 128), (3, 100)])
 @pytest.mark.parametrize("d,ff", [(192, 12352), (512, 12352), (192, 18944)])
-def test_gate_up_in_odd_tiles(d, ff, rows):
+def test_wide_gate_up(d, ff, rows):
     run(shape(d, 2, 2, 64, ff), [5 + b for b in range(rows[0])], rows[1])
 
 
