@@ -438,7 +438,11 @@ __global__ __launch_bounds__(512) void k_attn_combine(const float* part_o, const
 // takes the exponentials of half u, its matrix instructions are the scores of half u+1 and V^T P^T of half u-1, one
 // product and a few vector instructions in turn (sched_barrier keeps the order), LDS reads 4 .. 8 products ahead.
 // (us, the kernel before it with 16 x 16 x 32 products / this one: 32 sequences of up to 8192 keys, 4 key heads of 7 x 32
-// rows 219 / 191; 8 prompts of up to 2048 tokens, 4 key heads 902 / 665; 1184 tokens, 32 heads 75 / 67.  The chip's clock
+// rows 219 / 191; 8 prompts of up to 2048 tokens, 4 key heads 902 / 665; 1184 tokens, 32 heads 75 / 67.  With four to six row
+// groups the other waves only copy, and one workgroup of eight waves a CU still beats the two of four waves that were there:
+// 32 heads, 128 rows of one sequence with 901 keys 19.6 / 16.7, 8 sequences of 128 rows 103 / 76 with 2048 keys, 37 / 35 with 300,
+// 8 of 104 rows 58 / 47; 5 and 6 groups 85 / 71 and 68 / 55; 8 key heads of 4 x 32 rows, 32 sequences of 1024 keys 62 / 48; 8
+// prompts of 128, 160, 256 tokens 16.2 / 14.3, 21.5 / 19.0, 27.1 / 25.8.)  (The chip's clock
 // follows the products' power: 24 of them on random operands, with as many vector instructions as here between them,
 // take two waves of a SIMD 0.94 us, on zeros 0.70.)
 //
@@ -520,7 +524,7 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
     foff[i] = PG == 2 ? off : off * 2;                        // (small pages: elements)
     if constexpr (PG == 2) fkey[i] = key;
   }
-  uint32_t badbuf = 0;                                        // buffers with keys from a page id out of range
+  uint32_t badbuf = 0;                                        // PG 1: buffers with keys from a page id out of range
   // own: 0, 1, .. of the unit's blocks; past the last one it is the last one
   auto clampo = [&](int own) { return own < n_own ? own : n_own - 1; };
   auto block_of = [&](int own) { return unit + clampo(own) * a.n_units; };
@@ -550,7 +554,6 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
       vb = (int64_t)kvh * DH * kv.tpad + pcol + k0;
     } else {
       kb = vb = 0;
-      badbuf &= ~(1u << buf);
     }
     if constexpr (PG == 2) src = wave_k ? kslab : vslab;
     else {
@@ -564,7 +567,7 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
       const int key = (block_of(own) << 6) + fkey[i];
       const int page = s_pg[(clampo(own) << ids_sh) + (fkey[i] >> sh)];
       const bool ok = (uint32_t)page < (uint32_t)kv.n_pages;
-      if (!ok && key < kv_len) { bad = 1; badbuf |= 1u << buf; }
+      if (!ok && key < kv_len) bad = 1;
       const int64_t rows = (((int64_t)(ok ? page : 0) * kv.n_kv_heads + kvh) << sh);
       const bf16_t* p = src + rows * DH + (wave_k ? (key & (pt - 1)) * DH : (key & (pt - 1))) + foff[i];
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
@@ -894,6 +897,7 @@ __device__ __forceinline__ void attn_dl_body(const AttnArgs& a) {
   if (bad) atomicOr(a.status, DLLM_STATUS_BAD_PAGE);
 }
 
+// (a kernel of its own around the body: as a kernel's own code it leaves the host without the launch stub)
 template <int DH, int PG>
 __global__ __launch_bounds__(512) void k_attn_dl(const AttnArgs a) { attn_dl_body<DH, PG>(a); }
 
