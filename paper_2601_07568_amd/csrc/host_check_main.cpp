@@ -102,14 +102,14 @@ static int attn_plan_errors() {
 }
 
 // "form" then (kind, rows, columns, K, starts_apart) for each product: what it launches on 256 CUs, a line each.  kind "gate-up"
-// (columns: features) or "resid" (at most four K shares): [whole rounds' column tiles +] tile [/ K shares].
+// (columns: features) or "resid" (at most four K shares, one above 2048 rows): [whole rounds' column tiles +] tile [/ K shares].
 static int print_forms(int n, char** v) {
   using namespace dllm;
   static const char* const name[GT_N] = {"256x256", "128x256", "128x128", "128x64", "128x96", "128x160", "256x96", "256x160", "256x224"};
   for (int i = 0; i + 4 < n; i += 5) {
     const int M = atoi(v[i + 1]), N = atoi(v[i + 2]), K = atoi(v[i + 3]);
     const bool apart = atoi(v[i + 4]) != 0;
-    const GtForm f = strcmp(v[i], "resid") == 0 ? gt_resid_form(256, M, N, K, 4, apart) : gt_swiglu_form(256, M, N, K, apart);
+    const GtForm f = strcmp(v[i], "resid") == 0 ? gt_resid_form(256, M, N, K, M <= 2048 ? 4 : 1, apart) : gt_swiglu_form(256, M, N, K, apart);
     if (f.n_tn > 0) printf("%d+%s\n", f.n_tn, name[f.tile]);
     else if (f.splits > 1) printf("%s/%d\n", name[f.tile], f.splits);
     else printf("%s\n", name[f.tile]);

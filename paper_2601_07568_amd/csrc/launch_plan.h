@@ -100,17 +100,19 @@ inline bool gt_starts_apart(int M, bool device_rows) { return M <= GT_APART_ROWS
 // Over 200 layers of 128 .. 8192 channels and 96 .. 16384 rows, 257 .. 511 among them, what it picks takes 0.47 .. 0.98 of the
 // time of the 32-deep kernels that were here before.
 //
-// Odd widths for gate/up: one round of one tile per CU decides there up to about 500 rows, and 128 and 256 columns
-// seldom make one (256 CUs; 24576 gate and up rows: 256 tiles of 96, 37888: 237 of 160).  Measured, the best of the
-// even tiles / these, us: 24576 x 4096: 128 rows 47.9 / 44.2 (128 x 96), 211 rows 59.3 / 56.9 and 256 rows 61.5 / 59.8 (256 x
-// 96), 300 rows 101 / 84 (128 x 160); 37888 x 3584: 65 rows 61.7 / 53.3 and 128 rows 67.3 / 58.4 (128 x 160), 211 rows
-// 83.5 / 71.8 and 256 rows 87.6 / 74.9 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its weights are all from
-// memory and two thirds of the CUs ask for them (residual projections of 12288 and 14336 channels, whose plan that decides as
-// well, take the same time with either).  Behind whole rounds: 1024 x 10240 x 3584 as 160 tiles of 128 x 256 57, as 256
-// of 128 x 160 47.  One for residual projections, 256 x 224 at 0.90: 1024 x 3584 x 18944 in four K shares is 224 tiles of 256 x
-// 256 or 256 of these, 132 / 123.
+// Odd widths for gate/up: one round of one tile per CU decides there up to about 300 rows, and 128 and 256 columns
+// seldom make one (256 CUs; 24576 gate and up rows: 256 tiles of 96, 37888: 237 of 160).  Measured in turn, what is taken
+// without odd tiles / with them, us: 24576 x 4096: 66 rows 41.4 / 38.9 and 128 rows 48.0 / 43.3 (128 x 96), 200 rows 60.0 / 56.6
+// and 256 rows 61.3 / 58.7 (256 x 96), 270 rows 87.9 / 79.0 (128 x 160); 37888 x 3584: 100 rows 65.6 / 56.3 and 128 rows 67.7 /
+// 58.6 (128 x 160), 228 rows 85.2 / 73.6 and 256 rows 86.4 / 74.2 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its
+// weights are all from memory and two thirds of the CUs ask for them (residual projections of 12288 and 14336 channels, whose
+// plan that decides as well, take the same time with either).  A 256 x 96 tile has 3.5 us more beside its products (128 x 256 /
+// 256 x 96 in one round: K = 1024 16.4 / 17.6, 2048 26.1 / 26.8, 4096 55.5 / 51.7).
+// Over 17 widths of 2048 .. 28672 features, five K of 1024 .. 8192 and 66 .. 16384 rows, in turn: where the odd tiles change the
+// launch it takes 0.74 .. 1.007 of the time without them, 0.92 on average; the residual tile of 224, over ten widths and ten K,
+// 0.72 .. 1.018, 0.945 on average.
 enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_256x224 = 8, GT_N = 9 };
-constexpr unsigned GT_ODD_TILES = 0xf0u, GT_RESID_TILES = 0xfu, GT_RESID_224 = 0x100u, GT_REST_TILES = 0x6u;
+constexpr unsigned GT_ODD_TILES = 0xf0u, GT_ODD_256 = 0xc0u, GT_RESID_TILES = 0xfu, GT_RESID_224 = 0x100u, GT_REST_TILES = 0x6u;
 // of a mask of tiles (bit per GtTile) those that are built for this K
 inline unsigned gt_built(int K, unsigned tiles) { return K % 64 == 0 ? tiles : tiles & ~0x1f2u; }
 struct GtPlan { GtTile tile; int splits, k_per; double us; };
@@ -131,8 +133,8 @@ inline GtPlan gt_plan(int cus, int M, int NW, int K, int max_splits, unsigned wi
       const int n_sp = (K + k_per - 1) / k_per;
       if (n_sp != sp) continue;
       const double rounds = (double)((tiles * sp + cus - 1) / cus);
-      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain
-      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + 4.0) + (sp - 1) * fold_us_per_share;
+      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain (256 x 96: above)
+      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + (c == GT_256x96 ? 7.5 : 4.0)) + (sp - 1) * fold_us_per_share;
       if (t < best.us) best = GtPlan{(GtTile)c, sp, k_per, t};
     }
   }
@@ -142,7 +144,7 @@ inline GtPlan gt_plan(int cus, int M, int NW, int K, int max_splits, unsigned wi
 // A last round of 256 x 256 tiles that fills few of the CUs takes as long as a whole one.  Returns how many column tiles
 // the whole rounds hold (0: none, or not worth it) when those and then the remaining columns as a launch of smaller
 // tiles, which spread over the chip, are estimated shorter than `one_us`, all columns in one launch.  The second launch
-// costs its boundary and a fill of its own, 6 us.  (592 tiles of a 1024 x 37888 x 3584 product: 256 -> 185 + 47 us.  The cut in
+// costs its boundary and a fill of its own, 6 us.  (592 tiles of a 1024 x 37888 x 3584 product: 256 -> 225 us.  The cut in
 // one launch, its remainder as a second loop of the same kernel, costs the main loop registers: 313 us.)
 inline int gt_whole_rounds(int cus, int M, int NW, int K, unsigned rest_ok, double one_us) {
   const int tiles_m = (M + 255) / 256, tiles_n = (NW + 255) / 256, rounds = tiles_m * tiles_n / cus;
@@ -155,17 +157,36 @@ inline int gt_whole_rounds(int cus, int M, int NW, int K, unsigned rest_ok, doub
 // What a product launches: n_tn column tiles of 256 x 256 in whole rounds (0: none), the columns behind them in `tile`; without
 // whole rounds the sum over K may be in several shares of k_per.
 struct GtForm { GtTile tile; int splits, k_per, n_tn; };
-inline GtForm gt_form(int cus, int M, int NW, int K, const GtPlan& p, unsigned rest_ok) {
-  const int n_tn = gt_whole_rounds(cus, M, NW, K, rest_ok, p.us);
+// pays: the tiles that the columns behind whole rounds are estimated in, rest: those that they may get
+inline GtForm gt_form(int cus, int M, int NW, int K, const GtPlan& p, unsigned pays, unsigned rest) {
+  const int n_tn = gt_whole_rounds(cus, M, NW, K, pays, p.us);
   if (n_tn == 0) return GtForm{p.tile, p.splits, p.k_per, 0};
-  return GtForm{gt_plan(cus, M, NW - n_tn * 256, K, 1, rest_ok, 0.0).tile, 1, K, n_tn};
+  return GtForm{gt_plan(cus, M, NW - n_tn * 256, K, 1, rest, 0.0).tile, 1, K, n_tn};
 }
+// Residual projections: 256 x 224 at 0.90, in the place of 256 x 256 tiles alone (1024 x 3584 x 18944 in four K shares is 224 tiles
+// of 256 x 256 or 256 of these, 142 / 138; 2304 x 4096 x 12288 234 / 206).  The estimate makes smaller tiles and fewer shares
+// look dearer than they are: 1536 x 4096 x 4096 as 128 x 256 tiles 57, as two shares of 256 x 224 70; 1552 x 3584 x 3584 45 / 61; 6810
+// x 3584 x 3584 157 / 168.
 inline GtForm gt_resid_form(int cus, int M, int N, int K, int max_splits, bool starts_apart) {
-  const unsigned ok = GT_RESID_TILES | (starts_apart ? 0u : GT_RESID_224);
-  return gt_form(cus, M, N, K, gt_plan(cus, M, N, K, max_splits, ok, 1.0 + 8.0 * M * (double)N / 4.0e6), GT_REST_TILES);
+  const double fold = 1.0 + 8.0 * M * (double)N / 4.0e6;
+  GtPlan p = gt_plan(cus, M, N, K, max_splits, GT_RESID_TILES, fold);
+  if (!starts_apart && p.tile == GT_256x256) {
+    const GtPlan q = gt_plan(cus, M, N, K, p.splits, GT_RESID_224, fold);
+    if (q.us < p.us) p = q;
+  }
+  return gt_form(cus, M, N, K, p, GT_REST_TILES, GT_REST_TILES);
 }
+// Gate/up.  Odd tiles of 128 rows are for one or two row tiles; a third that is a quarter full still pays (24576 x 4096 in 256 x
+// 256 tiles takes 88 whatever the rows, in 128 x 160 79 at 270 rows, 86 at 320, 92 at 356, 97 at 384; x 5120 104 and 99 / 112
+// at 270 / 320), a full one only in the place of 128 x 256 tiles (384 x 11008 x 2048 29.4 / 25.9).  Whole rounds have to pay with
+// a rest of even or 256-row tiles (one launch of 256 x 256 / whole rounds and 128 x 160: 1152 x 22016 x 4096 183 / 190, 1664 x 24576 x
+// 4096 282 / 285; and 256 x 160: 3044 x 24576 x 4096 465 / 455); a rest that is there anyway takes any (1424 x 24576 x 4096 with
+// 128 x 256 250, with 128 x 160 241; 1024 x 37888 x 3584 235 / 225).
 inline GtForm gt_swiglu_form(int cus, int M, int F, int K, bool starts_apart) {
-  return gt_form(cus, M, 2 * F, K, gt_plan(cus, M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0), GT_REST_TILES | (starts_apart ? 0u : GT_ODD_TILES));
+  GtPlan p = gt_plan(cus, M, 2 * F, K, 1, 0x7u | (M <= 288 ? GT_ODD_TILES : GT_ODD_256), 0.0);
+  if (M <= 384 && p.tile == GT_128x256) p = gt_plan(cus, M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0);
+  return gt_form(cus, M, 2 * F, K, p, GT_REST_TILES | (starts_apart ? 0u : GT_ODD_256),
+                 GT_REST_TILES | (starts_apart ? 0u : GT_ODD_TILES));
 }
 
 }  // namespace dllm

@@ -109,14 +109,15 @@ def test_k_of_half_a_stage_more(ms, lens, Q):
 
 
 # Gate/up in tiles of 96 and 160 weight rows: (d, ff, (sequences, rows), form).  Every width ends inside a tile; sums of two or
-# three stages (shorter than the rings) and of nine (longer); one row tile and two, the last of them nearly empty or not.
+# three stages (shorter than the rings; 256 x 96 is taken from 37 stages on) and of nine (longer); one row tile and two, the last
+# of them nearly empty or not.
 ODD_TILES = [
     (128, 2048, (1, 65), "128x96"), (576, 2056, (1, 128), "128x96"),
     (192, 16392, (1, 65), "128x160"), (576, 5448, (3, 100), "128x160"),
-    (128, 10248, (1, 150), "256x96"), (576, 5128, (4, 100), "256x96"),
+    (2432, 10264, (1, 150), "256x96"), (2432, 10264, (2, 100), "256x96"),
     (128, 16392, (1, 255), "256x160"), (576, 8200, (4, 100), "256x160"),
-    # 410 items on 256 places
-    (192, 16392, (4, 100), "256x160"),
+    # 410 and 411 items on 256 places
+    (192, 16392, (4, 100), "256x160"), (2432, 10912, (1, 257), "128x160"),
 ]
 
 
@@ -130,7 +131,7 @@ def test_gate_up_in_odd_tiles(d, ff, rows, form):
 # that ends inside a tile: K of two stages and of twelve, more items than places (330 on 256); three K shares of unequal length
 RESID_224 = [
     (2200, 2, 768, (83, 99), "256x224", "256x224"),
-    (4616, 2, 4160, (8, 97), "128x256", "256x224/3"),
+    (4680, 2, 3136, (8, 97), "128x256", "256x224/3"),
 ]
 
 
@@ -144,8 +145,8 @@ def test_residual_projections_in_tiles_of_224(d, heads, ff, rows, o, down):
 
 # Whole rounds of 256 x 256 gate/up tiles and the columns behind them in smaller ones: (d, ff, (sequences, rows), form)
 RESTS = [
-    (512, 21776, (1, 257), "128+128x128"), (768, 23216, (1, 257), "128+128x256"), (512, 21856, (1, 257), "128+128x160"),
-    (768, 11096, (8, 97), "64+256x96"),
+    (512, 21776, (1, 257), "128+128x128"), (768, 23216, (1, 257), "128+128x256"), (768, 21880, (1, 257), "128+128x160"),
+    (2432, 11096, (8, 97), "64+256x96"), (2432, 12312, (8, 127), "64+256x160"),
 ]
 
 
@@ -350,10 +351,19 @@ def test_rows_that_are_not_finite_stay_to_themselves(ms, Q):
     eng.close()
 
 
+# Products that took a tile they are slower in (us, the form below / that one): odd 128-row tiles at nearly three row tiles
+# (89 / 97), 256 x 96 at a short K (17 / 19), whole rounds for the sake of a rest of 128 x 160 (183 / 190), and residual projections
+# in K shares of 256 x 224 where one launch of smaller tiles does (57 / 70, 45 / 61, 158 / 168, 56 / 75).
+KEPT = [
+    ("gate-up", 384, 12288, 4096, "256x256"), ("gate-up", 1000, 2752, 1024, "128x256"), ("gate-up", 1152, 11008, 4096, "256x256"),
+    ("resid", 1536, 4096, 4096, "128x256"), ("resid", 1552, 3584, 3584, "128x256"), ("resid", 6810, 3584, 3584, "128x256"),
+    ("resid", 1424, 2048, 8192, "128x128"),
+]
+
 # (kind, rows, columns, K, form) of the products that the tests above are written for: tests/test_abi_host.py holds them against
 # the library's own rules
 FORMS = ([("gate-up", b * q, ff, d, form) for d, ff, (b, q), form in ODD_TILES + RESTS] +
          [("resid", b * q, d, heads * 64, o) for d, heads, ff, (b, q), o, down in RESID_224] +
          [("resid", b * q, d, ff, down) for d, heads, ff, (b, q), o, down in RESID_224] +
          [("gate-up", 8 * 127, 8512, 768, "256x160"), ("resid", 83 * 99, 2048, 768, "7+128x128"),
-          ("gate-up", 8 * 127, 8544, 800, "64+128x128")])
+          ("gate-up", 8 * 127, 8544, 800, "64+128x128")] + KEPT)
