@@ -3,6 +3,7 @@
 // bfloat16 shapes the matrix-core kernels do not take; the small bookkeeping kernels (token map, rotary
 // table, row compaction, statistics merge, unmask) are shared by both.
 #include "common.h"
+#include <type_traits>
 #include <math.h>
 
 namespace dllm {
@@ -769,12 +770,16 @@ hipError_t launch_token_map(dllm_ctx* c, hipStream_t s, const StepGeom& g, bool 
 // EMB: the rows come from the embedding table (the first norm of a forward): x is written, not read.  MAP: the launch is also
 // the step's first: step_row_map, which four launches (length check, token map, rotary table, embedding; 4.6 us each at least)
 // did one behind the other.
-template <int NV, bool EMB, bool MAP = false>
+// FRAG: x * gain in fragment order for frag_mt 16-row tiles.  (MAP and FRAG are forms of their own: with the layout chosen at run
+// time and the map's arguments in every form a launch of 100 .. 256 rows took 0.4 .. 0.6 us more of 6.5 .. 8.6.)
+struct NoMap {};
+template <int NV, bool EMB, bool MAP = false, bool FRAG = false>
 __global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x, const bf16_t* gain, bf16_t* out,
                                                       const int32_t* rows, const int32_t* n_rows_dev, const float* delta,
                                                       int n_delta, int64_t delta_stride, float* rscale,
                                                       const int32_t* live_rows, const bf16_t* emb, const int32_t* tokens,
-                                                      int vocab, int32_t* status, float* mean_out, int ss_stride, int frag_mt, const StepMap m = StepMap()) {
+                                                      int vocab, int32_t* status, float* mean_out, int ss_stride, int frag_mt = 0,
+                                                      const std::conditional_t<MAP, StepMap, NoMap> m = {}) {
   __shared__ float red[16];
   const int r = blockIdx.x;
   bool live = !live_rows || r < *live_rows;
@@ -835,7 +840,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm_row4(int d, float eps, float* x
     if (!live) continue;
     const float g0 = bf16_to_f32((bf16_t)(gq[k].x & 0xffff)), g1 = bf16_to_f32((bf16_t)(gq[k].x >> 16));
     const float g2 = bf16_to_f32((bf16_t)(gq[k].y & 0xffff)), g3 = bf16_to_f32((bf16_t)(gq[k].y >> 16));
-    uint2* const o = frag_mt > 0 ? (uint2*)(out + frag_offset(r, 4 * i, frag_mt)) : orow + i;
+    uint2* const o = FRAG ? (uint2*)(out + frag_offset(r, 4 * i, frag_mt)) : orow + i;
     *o = make_uint2((uint32_t)f32_to_bf16(v[k].x * g0) | ((uint32_t)f32_to_bf16(v[k].y * g1) << 16),
                     (uint32_t)f32_to_bf16(v[k].z * g2) | ((uint32_t)f32_to_bf16(v[k].w * g3) << 16));
   }
@@ -859,7 +864,7 @@ hipError_t launch_embed(dllm_ctx* c, hipStream_t s, const StepGeom& g, const voi
     *normed = true;
 #define ROW4(NV) k_rmsnorm_row4<NV, true><<<g.T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,      \
                      WS(c, xn, bf16_t), nullptr, nullptr, nullptr, 0, 0, WS(c, rscale, float), c->rows_dev,               \
-                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t), nullptr, 0, 0)
+                     (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t), nullptr, 0)
     if (f.d_model <= 2048) ROW4(2);
     else if (f.d_model <= 4096) ROW4(4);
     else if (f.d_model <= 8192) ROW4(8);
@@ -895,14 +900,16 @@ bool step_prologue_usable(const dllm_ctx* c) { return rmsnorm_row4_usable(c); }
 
 hipError_t launch_step_prologue(dllm_ctx* c, hipStream_t s, const StepGeom& g, const void* gain, bool kv_loc, int frag_mt) {
   const dllm_config& f = c->cfg;
-#define ROW4(NV) k_rmsnorm_row4<NV, true, true><<<g.T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,  \
+#define ROW4F(NV, FRAG) k_rmsnorm_row4<NV, true, true, FRAG><<<g.T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,  \
                      WS(c, xn, bf16_t), nullptr, nullptr, nullptr, 0, 0, WS(c, rscale, float), nullptr,                   \
                      (const bf16_t*)c->tok_emb, g.tokens, f.vocab, WS(c, status, int32_t), nullptr, 0, frag_mt, step_map(c, g, kv_loc))
+#define ROW4(NV) do { if (frag_mt > 0) ROW4F(NV, true); else ROW4F(NV, false); } while (0)
   if (f.d_model <= 2048) ROW4(2);
   else if (f.d_model <= 4096) ROW4(4);
   else if (f.d_model <= 8192) ROW4(8);
   else ROW4(16);
 #undef ROW4
+#undef ROW4F
   return hipGetLastError();
 }
 
@@ -937,15 +944,17 @@ hipError_t launch_rmsnorm(dllm_ctx* c, hipStream_t s, const void* gain, int T, c
                           const int32_t* n_rows_dev, int frag_mt, int n_delta, bool keep_mean) {
   const dllm_config& f = c->cfg;
   if (rmsnorm_row4_usable(c)) {
-#define ROW4(NV) k_rmsnorm_row4<NV, false><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,        \
+#define ROW4F(NV, FRAG) k_rmsnorm_row4<NV, false, false, FRAG><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,        \
                      WS(c, xn, bf16_t), rows, n_rows_dev, WS(c, delta, float), n_delta, c->map.lg_delta_stride,           \
                      WS(c, rscale, float), rows ? nullptr : c->rows_dev, nullptr, nullptr, 0, nullptr,           \
                      keep_mean ? WS(c, ss, float) : nullptr, ss_row_stride(c), frag_mt)
+#define ROW4(NV) do { if (frag_mt > 0) ROW4F(NV, true); else ROW4F(NV, false); } while (0)
     if (f.d_model <= 2048) ROW4(2);
     else if (f.d_model <= 4096) ROW4(4);
     else if (f.d_model <= 8192) ROW4(8);
     else ROW4(16);
 #undef ROW4
+#undef ROW4F
   }
   else if (IS_BF16(c))
     k_rmsnorm<bf16_t><<<T, 256, 0, s>>>(f.d_model, f.rms_eps, WS(c, x, float), (const bf16_t*)gain,
