@@ -506,11 +506,12 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
 
 // Pipeline of a form.  What a wave has in flight beyond two stages brings nothing (D 3 -> 4 .. 8: -1 .. +5 % where the
 // registers last, up to twice the time where they do not), so stages are as short and as few as keep a wave's registers
-// in its share: 8 waves of 6 tiles x 64 rows with two stages (178 registers) 42.4 us where 4 waves with three take 47.1.
+// in its share: 8 waves of 6 tiles x 64 rows with two stages (178 registers) 42.4 us where 4 waves with three take 47.1; gate/up
+// of 16 rows in stages of two steps / one: 8192 x 2048 14.1 / 12.7, 5504 x 2048 11.0 / 9.6, 12288 x 4096 37.2 / 37.3.
 template <int NT, int MT, int NW, int EPI>
 struct SkCfg {
   static constexpr bool WIDE = EPI == SK_SWIGLU && NT == 6;
-  static constexpr int JB = (MT >= 3 || (EPI == SK_SWIGLU && MT == 2) || (EPI == SK_QKV && NT == 2)) ? 1 : 2;
+  static constexpr int JB = (MT >= 3 || (EPI == SK_SWIGLU && MT <= 2) || (EPI == SK_QKV && NT == 2)) ? 1 : 2;
   static constexpr int D = (WIDE && MT >= 3) || (EPI == SK_SWIGLU && MT == 4) || (EPI == SK_QKV && MT >= 7) ? 2
                            : (EPI == SK_QKV && NT == 2 && MT <= 2) ? 5 : 3;
   static constexpr int TPC = EPI == SK_SWIGLU ? 2 : NT;
@@ -761,9 +762,12 @@ hipError_t launch_sk_swiglu(dllm_ctx* c, hipStream_t s, int layer, int M, int n_
   // the weights at 32 rows and twice as many at 64, and although the L2 serves them their time adds to the stream's (a
   // stream of 200 MB from memory with 0 / 200 / 400 / 800 MB from the L2 beside it: 32 / 37 / 46 / 64 us).  F = 12288,
   // K = 4096, us, one pair / three: 32 rows 40.0 / 38.1, 48 rows 46.4 / 40.4, 64 rows 59.2 / 42.4; F = 18944, K = 3584: 57.1 /
-  // 55.1, -, 82.1 / 68.3; 16 rows 36.3 / 36.7 and 48.1 / 51.3, hence one there; and one where three would leave more than a quarter of the CUs idle.
-  const int pairs = (f.d_ff + 15) / 16;
-  if (M > 16 && pairs >= 3 * (device_cus() * 3 / 4)) return sk_launch_mt<6, SK_NW, SK_SWIGLU>(s, a, (pairs + 2) / 3);
+  // 55.1, -, 82.1 / 68.3; 16 rows 36.3 / 36.7 and 48.1 / 51.3, hence one there.  A workgroup of three fills its CU: up to 48 rows
+  // they have to be one round that leaves no more than a quarter of the CUs idle (d_ff 14336 is 299 of them, 13824 288: 32 rows 50 /
+  // 61 and 64 / 73, 48 rows 58 / 68 and 74 / 83; 28672 597: 177 / 183); at 64 rows the activations cost more than a last
+  // round does (75 / 73, 94 / 91; 246 / 212).
+  const int pairs = (f.d_ff + 15) / 16, wgs = (pairs + 2) / 3, cus = device_cus();
+  if (M > 16 && wgs >= cus * 3 / 4 && (M > 48 || wgs <= cus)) return sk_launch_mt<6, SK_NW, SK_SWIGLU>(s, a, wgs);
   return sk_launch_mt<2, SK_NW, SK_SWIGLU>(s, a, pairs);
 }
 
