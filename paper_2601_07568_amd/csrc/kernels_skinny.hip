@@ -724,6 +724,17 @@ hipError_t launch_sk_f32(dllm_ctx* c, hipStream_t s, const void* A, const void* 
 
 // fused q/k/v projection of a denoise step: rotary embedding on q and k, q to the workspace,
 // k and v into the in-flight pages of the pool
+// workgroups of the q/k/v product with the value tiles apart from the rotary pairs, two to a workgroup; and of the form taken
+static int sk_qkv_apart(const dllm_ctx* c) {
+  const dllm_config& f = c->cfg;
+  return (f.n_q_heads + f.n_kv_heads) * (f.head_dim / 32) + (f.n_kv_heads * (f.head_dim / 16) + 1) / 2;
+}
+int sk_qkv_grid(const dllm_ctx* c) {
+  const dllm_config& f = c->cfg;
+  const int apart = sk_qkv_apart(c), pairs = (f.n_q_heads + f.n_kv_heads) * (f.head_dim / 32), values = f.n_kv_heads * (f.head_dim / 16);
+  return apart <= device_cus() ? apart : pairs > values ? pairs : values;
+}
+
 hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int layer, const KVView& pool, int n_ss) {
   const dllm_config& f = c->cfg;
   SkArgs a = sk_base(c->ws + c->map.xn, g.T, f.d_model);
@@ -741,12 +752,12 @@ hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int laye
   a.tok_seq = WSM(c, tok_seq, int32_t); a.tok_pos = WSM(c, tok_pos, int32_t);
   a.pool_k = (bf16_t*)pool.k; a.pool_v = (bf16_t*)pool.v; a.pool = pool;
   a.status = WSM(c, status, int32_t);
-  const int n_pairs = a.n_q_wg + a.n_k_wg, n_vt = (a.N2 + 15) / 16, apart = n_pairs + (n_vt + 1) / 2;
   // Value tiles in workgroups of their own where all then still run at once (few key heads: 128 pair tiles and 32 value
   // tiles took 128 workgroups of three tiles, most of them with one to throw away: 16.0 -> 13.1 us at 32 rows of 3584,
   // 21.4 -> 19.0 at 64, 27.8 -> 24.3 at 128).
-  if (apart <= device_cus()) return sk_launch_mt<2, SK_NW, SK_QKV>(s, a, apart);
-  return sk_launch_mt<3, SK_NW, SK_QKV>(s, a, n_pairs > n_vt ? n_pairs : n_vt);
+  const int grid = sk_qkv_grid(c);
+  if (sk_qkv_apart(c) <= device_cus()) return sk_launch_mt<2, SK_NW, SK_QKV>(s, a, grid);
+  return sk_launch_mt<3, SK_NW, SK_QKV>(s, a, grid);
 }
 
 // h[M,F] = silu(xn Wg^T) * (xn Wu^T), written in fragment order for the down projection
