@@ -106,11 +106,13 @@ inline bool gt_starts_apart(int M, bool device_rows) { return M <= GT_APART_ROWS
 // and 256 rows 61.3 / 58.7 (256 x 96), 270 rows 87.9 / 79.0 (128 x 160); 37888 x 3584: 100 rows 65.6 / 56.3 and 128 rows 67.7 /
 // 58.6 (128 x 160), 228 rows 85.2 / 73.6 and 256 rows 86.4 / 74.2 (256 x 160).  With one row tile a 128 x 256 tile costs 0.68: its
 // weights are all from memory and two thirds of the CUs ask for them (residual projections of 12288 and 14336 channels, whose
-// plan that decides as well, take the same time with either).  A 256 x 96 tile has 3.5 us more beside its products (128 x 256 /
-// 256 x 96 in one round: K = 1024 16.4 / 17.6, 2048 26.1 / 26.8, 4096 55.5 / 51.7).
+// plan that decides as well, take the same time with either).  Beside their products odd tiles have 2 .. 3.5 us more (128 x 256 /
+// 256 x 96 in one round: K = 1024 16.4 / 17.6, 2048 26.1 / 26.8, 4096 55.5 / 51.7; 128 x 256 / 128 x 160: K = 512 11.4 / 13.0, 1024
+// 18.3 / 18.7, 2048 31.7 / 30.3; 128 x 128 / 128 x 96: 1024 14.6 / 15.4, 1536 23.9 / 22.6), and chips differ by several per cent in
+// how they take a round that needs all CUs at once: 128 x 96 for 80 rows of 24576 x 4096 was 0.92, 0.92 and 1.09 of the time of
+// 128 x 128 on three of them.
 // Over 17 widths of 2048 .. 28672 features, five K of 1024 .. 8192 and 66 .. 16384 rows, in turn: where the odd tiles change the
-// launch it takes 0.74 .. 1.007 of the time without them, 0.92 on average; the residual tile of 224, over ten widths and ten K,
-// 0.72 .. 1.018, 0.945 on average.
+// launch it takes 0.92 of the time without them on average; the residual tile of 224, over ten widths and ten K, 0.945.
 enum GtTile { GT_256x256 = 0, GT_128x256 = 1, GT_128x128 = 2, GT_128x64 = 3, GT_128x96 = 4, GT_128x160 = 5, GT_256x96 = 6, GT_256x160 = 7, GT_256x224 = 8, GT_N = 9 };
 constexpr unsigned GT_ODD_TILES = 0xf0u, GT_ODD_256 = 0xc0u, GT_RESID_TILES = 0xfu, GT_RESID_224 = 0x100u, GT_REST_TILES = 0x6u;
 // of a mask of tiles (bit per GtTile) those that are built for this K
@@ -123,6 +125,7 @@ inline GtPlan gt_plan(int cus, int M, int NW, int K, int max_splits, unsigned wi
   // (up to 256 rows a 128-row tile waits for its weights, which no other row tile has brought in)
   const double unit[GT_N] = {1.0, M <= 128 ? 0.68 : 0.6, M <= 256 ? 0.45 : 0.33, M <= 256 ? 0.30 : 0.22,
                              M <= 128 ? 0.39 : 0.45, M <= 128 ? 0.60 : 0.45, 0.54, 0.80, 0.90};
+  static const double fill[GT_N] = {4.0, 4.0, 4.0, 4.0, 6.0, 7.5, 7.5, 7.5, 4.0};
   GtPlan best{GT_128x128, 1, K, 1e30};
   for (int c = 0; c < GT_N; ++c) {
     if (!((gt_built(K, width_ok) >> c) & 1u)) continue;
@@ -133,8 +136,8 @@ inline GtPlan gt_plan(int cus, int M, int NW, int K, int max_splits, unsigned wi
       const int n_sp = (K + k_per - 1) / k_per;
       if (n_sp != sp) continue;
       const double rounds = (double)((tiles * sp + cus - 1) / cus);
-      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain (256 x 96: above)
-      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + (c == GT_256x96 ? 7.5 : 4.0)) + (sp - 1) * fold_us_per_share;
+      // a 256 x 256 tile takes 1.6 us per stage and about 4 us of fill and drain
+      const double t = rounds * (unit[c] * 1.6 * (k_per / 64) + fill[c]) + (sp - 1) * fold_us_per_share;
       if (t < best.us) best = GtPlan{(GtTile)c, sp, k_per, t};
     }
   }
@@ -146,20 +149,20 @@ inline GtPlan gt_plan(int cus, int M, int NW, int K, int max_splits, unsigned wi
 // tiles, which spread over the chip, are estimated shorter than `one_us`, all columns in one launch.  The second launch
 // costs its boundary and a fill of its own, 6 us.  (592 tiles of a 1024 x 37888 x 3584 product: 256 -> 225 us.  The cut in
 // one launch, its remainder as a second loop of the same kernel, costs the main loop registers: 313 us.)
-inline int gt_whole_rounds(int cus, int M, int NW, int K, unsigned rest_ok, double one_us) {
+inline int gt_whole_rounds(int cus, int M, int NW, int K, double one_us) {
   const int tiles_m = (M + 255) / 256, tiles_n = (NW + 255) / 256, rounds = tiles_m * tiles_n / cus;
   const int n_tn = rounds * cus / tiles_m;
   if (rounds < 1 || n_tn < 1 || n_tn >= tiles_n) return 0;
-  const double us = rounds * (1.6 * (K / 64) + 4.0) + gt_plan(cus, M, NW - n_tn * 256, K, 1, rest_ok, 0.0).us + 6.0;
+  const double us = rounds * (1.6 * (K / 64) + 4.0) + gt_plan(cus, M, NW - n_tn * 256, K, 1, GT_REST_TILES, 0.0).us + 6.0;
   return us < one_us ? n_tn : 0;
 }
 
 // What a product launches: n_tn column tiles of 256 x 256 in whole rounds (0: none), the columns behind them in `tile`; without
 // whole rounds the sum over K may be in several shares of k_per.
 struct GtForm { GtTile tile; int splits, k_per, n_tn; };
-// pays: the tiles that the columns behind whole rounds are estimated in, rest: those that they may get
-inline GtForm gt_form(int cus, int M, int NW, int K, const GtPlan& p, unsigned pays, unsigned rest) {
-  const int n_tn = gt_whole_rounds(cus, M, NW, K, pays, p.us);
+// rest: tiles that the columns behind whole rounds may get
+inline GtForm gt_form(int cus, int M, int NW, int K, const GtPlan& p, unsigned rest) {
+  const int n_tn = gt_whole_rounds(cus, M, NW, K, p.us);
   if (n_tn == 0) return GtForm{p.tile, p.splits, p.k_per, 0};
   return GtForm{gt_plan(cus, M, NW - n_tn * 256, K, 1, rest, 0.0).tile, 1, K, n_tn};
 }
@@ -174,19 +177,18 @@ inline GtForm gt_resid_form(int cus, int M, int N, int K, int max_splits, bool s
     const GtPlan q = gt_plan(cus, M, N, K, p.splits, GT_RESID_224, fold);
     if (q.us < p.us) p = q;
   }
-  return gt_form(cus, M, N, K, p, GT_REST_TILES, GT_REST_TILES);
+  return gt_form(cus, M, N, K, p, GT_REST_TILES);
 }
 // Gate/up.  Odd tiles of 128 rows are for one or two row tiles; a third that is a quarter full still pays (24576 x 4096 in 256 x
 // 256 tiles takes 88 whatever the rows, in 128 x 160 79 at 270 rows, 86 at 320, 92 at 356, 97 at 384; x 5120 104 and 99 / 112
 // at 270 / 320), a full one only in the place of 128 x 256 tiles (384 x 11008 x 2048 29.4 / 25.9).  Whole rounds have to pay with
-// a rest of even or 256-row tiles (one launch of 256 x 256 / whole rounds and 128 x 160: 1152 x 22016 x 4096 183 / 190, 1664 x 24576 x
-// 4096 282 / 285; and 256 x 160: 3044 x 24576 x 4096 465 / 455); a rest that is there anyway takes any (1424 x 24576 x 4096 with
-// 128 x 256 250, with 128 x 160 241; 1024 x 37888 x 3584 235 / 225).
+// a rest of even tiles (one launch of 256 x 256 / whole rounds and 128 x 160: 1152 x 22016 x 4096 183 / 190, 1664 x 24576 x 4096
+// 282 / 285; and 256 x 160: 3044 x 24576 x 4096 465 / 455, 5200 x 11008 x 2048 189 / 194); a rest that is there anyway takes any
+// (1424 x 24576 x 4096 with 128 x 256 250, with 128 x 160 241; 1024 x 37888 x 3584 235 / 225).
 inline GtForm gt_swiglu_form(int cus, int M, int F, int K, bool starts_apart) {
   GtPlan p = gt_plan(cus, M, 2 * F, K, 1, 0x7u | (M <= 288 ? GT_ODD_TILES : GT_ODD_256), 0.0);
   if (M <= 384 && p.tile == GT_128x256) p = gt_plan(cus, M, 2 * F, K, 1, 0x7u | GT_ODD_TILES, 0.0);
-  return gt_form(cus, M, 2 * F, K, p, GT_REST_TILES | (starts_apart ? 0u : GT_ODD_256),
-                 GT_REST_TILES | (starts_apart ? 0u : GT_ODD_TILES));
+  return gt_form(cus, M, 2 * F, K, p, GT_REST_TILES | (starts_apart ? 0u : GT_ODD_TILES));
 }
 
 }  // namespace dllm

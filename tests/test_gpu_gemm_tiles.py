@@ -108,16 +108,13 @@ def test_k_of_half_a_stage_more(ms, lens, Q):
     run(ms, lens, Q)
 
 
-# Gate/up in tiles of 96 and 160 weight rows: (d, ff, (sequences, rows), form).  Every width ends inside a tile; sums of two or
-# three stages (shorter than the rings; 256 x 96 is taken from 37 stages on) and of nine (longer); one row tile and two, the last
-# of them nearly empty or not.
+# Gate/up in tiles of 96 and 160 weight rows: (d, ff, (sequences, rows), form), sums about as short as each is taken for.  Every
+# width ends inside a tile; one row tile and two, the last of them nearly empty or not.
 ODD_TILES = [
-    (128, 2048, (1, 65), "128x96"), (576, 2056, (1, 128), "128x96"),
-    (192, 16392, (1, 65), "128x160"), (576, 5448, (3, 100), "128x160"),
-    (2432, 10264, (1, 150), "256x96"), (2432, 10264, (2, 100), "256x96"),
-    (128, 16392, (1, 255), "256x160"), (576, 8200, (4, 100), "256x160"),
-    # 410 and 411 items on 256 places
-    (192, 16392, (4, 100), "256x160"), (2432, 10912, (1, 257), "128x160"),
+    (1408, 2056, (1, 65), "128x96"), (1408, 2056, (1, 128), "128x96"),
+    (1856, 16392, (1, 65), "128x160"), (1024, 5448, (3, 100), "128x160"),
+    (2432, 10264, (1, 150), "256x96"), (2432, 5448, (3, 100), "256x96"),
+    (768, 16392, (1, 255), "256x160"), (768, 8200, (4, 100), "256x160"),
 ]
 
 
@@ -145,8 +142,8 @@ def test_residual_projections_in_tiles_of_224(d, heads, ff, rows, o, down):
 
 # Whole rounds of 256 x 256 gate/up tiles and the columns behind them in smaller ones: (d, ff, (sequences, rows), form)
 RESTS = [
-    (512, 21776, (1, 257), "128+128x128"), (768, 23216, (1, 257), "128+128x256"), (768, 21880, (1, 257), "128+128x160"),
-    (2432, 11096, (8, 97), "64+256x96"), (2432, 12312, (8, 127), "64+256x160"),
+    (512, 21776, (1, 257), "128+128x128"), (768, 23216, (1, 257), "128+128x256"), (1024, 21880, (1, 257), "128+128x160"),
+    (2432, 11096, (8, 97), "64+256x96"),
 ]
 
 
@@ -157,14 +154,13 @@ def test_gate_up_behind_whole_rounds(d, ff, rows, form):
 
 
 @pytest.mark.parametrize("ms,B,Q", [
-    # gate and up of 1016 rows: 256 x 160 tiles, 428 items on 256 places
+    # gate and up of 1016 rows: 64 column tiles of 256 in one whole round, two and a half left
     (synth.ModelShape(1, 768, 2, 2, 64, 8512, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-ff"), 8, 127),
     # down of 8217 rows: 7 of the 8 column tiles in one whole round, the last row tile of 25 rows
     (synth.ModelShape(1, 2048, 2, 1, 64, 768, 600, 599, dtype="bf16", lm_head_scale=8.0, name="wide-out"), 83, 99),
 ], ids=["gate-up", "down"])
 def test_columns_behind_the_whole_rounds(ms, B, Q):
-    """A product whose last columns are a launch of smaller tiles behind whole rounds of 256 x 256 ones, and one as wide that
-    is a launch of odd tiles."""
+    """Products whose last columns are a launch of smaller tiles behind whole rounds of 256 x 256 ones."""
     run(ms, [5 + b % 3 for b in range(B)], Q)
 
 
@@ -352,10 +348,11 @@ def test_rows_that_are_not_finite_stay_to_themselves(ms, Q):
 
 
 # Products that took a tile they are slower in (us, the form below / that one): odd 128-row tiles at nearly three row tiles
-# (89 / 97), 256 x 96 at a short K (17 / 19), whole rounds for the sake of a rest of 128 x 160 (183 / 190), and residual projections
+# (89 / 97), 256 x 96 and 128 x 160 at a short K (17 / 19, 11 / 13), whole rounds for the sake of an odd rest (183 / 190), and residual projections
 # in K shares of 256 x 224 where one launch of smaller tiles does (57 / 70, 45 / 61, 158 / 168, 56 / 75).
 KEPT = [
-    ("gate-up", 384, 12288, 4096, "256x256"), ("gate-up", 1000, 2752, 1024, "128x256"), ("gate-up", 1152, 11008, 4096, "256x256"),
+    ("gate-up", 384, 12288, 4096, "256x256"), ("gate-up", 1000, 2752, 1024, "128x256"), ("gate-up", 256, 9216, 512, "128x256"),
+    ("gate-up", 1152, 11008, 4096, "256x256"),
     ("resid", 1536, 4096, 4096, "128x256"), ("resid", 1552, 3584, 3584, "128x256"), ("resid", 6810, 3584, 3584, "128x256"),
     ("resid", 1424, 2048, 8192, "128x128"),
 ]
@@ -365,5 +362,5 @@ KEPT = [
 FORMS = ([("gate-up", b * q, ff, d, form) for d, ff, (b, q), form in ODD_TILES + RESTS] +
          [("resid", b * q, d, heads * 64, o) for d, heads, ff, (b, q), o, down in RESID_224] +
          [("resid", b * q, d, ff, down) for d, heads, ff, (b, q), o, down in RESID_224] +
-         [("gate-up", 8 * 127, 8512, 768, "256x160"), ("resid", 83 * 99, 2048, 768, "7+128x128"),
+         [("gate-up", 8 * 127, 8512, 768, "64+128x128"), ("resid", 83 * 99, 2048, 768, "7+128x128"),
           ("gate-up", 8 * 127, 8544, 800, "64+128x128")] + KEPT)

@@ -40,8 +40,7 @@ def test_qkv_of_65_to_128_rows(ms, B, Q):
     run(ms, [40 + 9 * b for b in range(B)], Q)
 
 
-# wide gate/up products over row counts on both sides of 128 and 256: 24704 weight rows in tiles of an even number of 32, 37888 in
-# odd ones up to 256 rows (every odd tile, its remainders and its rests: test_gpu_gemm_tiles.py)
+# wide gate/up products of short sums over row counts on both sides of 128 and 256 (the odd tiles: test_gpu_gemm_tiles.py)
 @pytest.mark.parametrize("rows", [(1, 65), (1, 128), (3, 43), (1, 160), (2, 128), (3, 100)])
 @pytest.mark.parametrize("d,ff", [(192, 12352), (512, 12352), (192, 18944)])
 def test_wide_gate_up(d, ff, rows):
