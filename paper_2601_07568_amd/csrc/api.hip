@@ -338,11 +338,11 @@ static bool large_mfma(const dllm_ctx* c) {
 
 // Steps of 65 .. 128 rows: the q/k/v product with its rotary embedding and K/V write is still the weight-streaming
 // kernel's, on the weights as given (the other products are quicker on the tile kernel), as long as its workgroups are one
-// round (15360 x 5120 with 320 of them: 84 / 108 at 66 rows, 94 / 134 at 128; 10240 x 8192 with 288: 104 / 138, 110 / 167).  us, the split tile product + the
-// rotary kernel behind it / this one (from packed weights): 12288 x 4096: 128 rows 31 + 16 / 44 (40), 96 rows 29 + 15 / 37 (34),
-// 80 rows 27 + 14 / 35 (32); 4608 x 3584: 128 rows 14.5 + 15 / 28.5 (24.5), 72 rows 12.5 + 15 / 22.5 (18.5); at 256 rows a
-// workgroup's accumulators no longer fit its registers.  (step_prologue_usable: the step's first launch, which lays out the first
-// layer's input.)
+// round.  us, the split tile product + the rotary kernel behind it / this one (from packed weights): 12288 x 4096: 128 rows 31 +
+// 16 / 44 (40), 96 rows 29 + 15 / 37 (34), 80 rows 27 + 14 / 35 (32); 4608 x 3584: 128 rows 14.5 + 15 / 28.5 (24.5), 72 rows 12.5 +
+// 15 / 22.5 (18.5).  With a second round: 15360 x 5120 (320 workgroups) 66 rows 84 / (108), 128 rows 94 / (134); 10240 x 8192 (288)
+// 104 / (138), 110 / (167).  At 256 rows a workgroup's accumulators no longer fit its registers.  (step_prologue_usable: the
+// step's first launch, which lays out the first layer's input.)
 static bool sk_qkv_rows(const dllm_ctx* c, const StepGeom& g) {
   return large_mfma(c) && step_prologue_usable(c) && g.Q > 0 && g.T > SK_MAX_ROWS && g.T <= SK_QKV_ROWS && sk_qkv_grid(c) <= device_cus();
 }

@@ -358,8 +358,8 @@ bool mfma_supported(const dllm_ctx* c);
 size_t packed_weight_bytes(int N, int K);
 hipError_t launch_pack_weight(hipStream_t s, const void* W, void* P, int N, int K);
 constexpr int SK_MAX_ROWS = 64;   // the skinny (weight-streaming) kernels take at most this many rows
-int sk_qkv_grid(const dllm_ctx* c);   // workgroups of their q/k/v product
 constexpr int SK_QKV_ROWS = 128;  // ... their q/k/v product this many (above SK_MAX_ROWS on the weights as given)
+int sk_qkv_grid(const dllm_ctx* c);   // workgroups of that product
 KVView attention_view(dllm_ctx* c, const StepGeom& g, int layer);
 // n_ss: partial sums of squares per row the GEMM input comes with (1 after the embedding, d_model / 64 after a
 // residual projection)
