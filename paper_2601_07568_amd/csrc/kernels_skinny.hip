@@ -2,7 +2,7 @@
 //
 // Skinny GEMM (at most 64 activation rows): the step is bound by streaming each weight once from
 // HBM, so a workgroup owns a few 16-row tiles of the weight matrix for the whole K extent, its
-// waves split K among themselves in interleaved stages of one or two 32-element steps, every load
+// waves split K among themselves in interleaved stages of one to four 32-element steps, every load
 // of a wave is a contiguous KiB of the packed weights or of the activations straight into registers
 // (one or two stages ahead), and the partial tiles are summed through LDS in a fixed order.
 // The epilogue of the summed tile is the fusion point: residual add, rotary embedding + KV-cache
@@ -58,9 +58,7 @@ struct SkArgs {
 };
 
 constexpr int SK_KB = 128;  // k-elements per block: 4 matrix instructions deep
-constexpr int SK_NW = 8;    // waves of a workgroup (they split K among themselves)
-constexpr int SK_NW_RESID = 16;   // ... of a residual projection's (one 16-row weight tile per workgroup: the bytes in
-                                  // flight come from the waves)
+constexpr int SK_NW = 8;    // waves of a workgroup (they split K among themselves; the LM head's have four)
 
 // One pipeline stage: JB matrix-instruction steps (JB*32 k-elements) of NT weight tiles and MT
 // activation tiles.
@@ -77,17 +75,24 @@ struct SkFrag {
 template <int NT, int MT, int JB, bool TAIL, bool RM>
 __device__ inline void sk_load(SkFrag<NT, MT, JB>& f, const u32x4* const (&wt)[NT], const u32x4* xf, int stage, int g,
                                int K) {
+  // (all weights of the stage in front of its activations: see SkCfg)
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
     const int u = stage * JB + j;
-    // packed weights are zero beyond K; the activation buffer is not (it holds whatever was there, and 0 * NaN is NaN), and
-    // a row-major matrix may end there
+    // packed weights are zero beyond K; a row-major matrix may end there
     const bool ok = !TAIL || (u * 32 + g * 8 + 8 <= K);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       if (!RM || ok) f.a[t][j] = wt[t][u * (RM ? 4 : 64)];
       else f.a[t][j] = u32x4{0, 0, 0, 0};
     }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < JB; ++j) {
+    const int u = stage * JB + j;
+    // (the activation buffer holds whatever was there beyond K, and 0 * NaN is NaN)
+    const bool ok = !TAIL || (u * 32 + g * 8 + 8 <= K);
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       if (ok) f.b[t][j] = xf[(u * MT + t) * 64];
@@ -174,7 +179,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   if (a.n_lm_rows && *a.n_lm_rows <= 0) return;
   if (M <= 0) return;
 
-  float xres = 0.f, gres = 0.f;                         // RESID: the thread's element of x and of the next gain
+  constexpr int RIT = EPI == SK_RESID ? (MT * 256 + NW * 64 - 1) / (NW * 64) : 1;
+  float xres[RIT], gres[RIT];                           // RESID: the thread's elements of x and of the next gain
 
   const bf16_t* wbase[NT];
   int row0[NT], nrows[NT];
@@ -197,12 +203,15 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   }
   const u32x4* xf = (const u32x4*)a.X + lane;   // rows >= M of the last tile hold stale data: their columns are dropped
   if constexpr (EPI == SK_RESID) {
-    // the element this thread will update (items beyond the first, with more than 1024 / 256 row tiles, load late)
-    const int m = tid >> 8, iq = (tid >> 6) & 3;
-    const int tok = m * 16 + c, n = row0[0] + 4 * g + iq;
-    const bool ok = m < MT && tok < M && n < a.N0;
-    xres = a.x[ok ? (int64_t)tok * a.N0 + n : 0];
-    gres = bf16_to_f32(a.gain_next[ok ? n : 0]);
+    // the elements this thread will update
+#pragma unroll
+    for (int k = 0; k < RIT; ++k) {
+      const int item = tid + k * NW * 64, m = item >> 8, iq = (item >> 6) & 3;
+      const int tok = m * 16 + c, n = row0[0] + 4 * g + iq;
+      const bool ok = m < MT && tok < M && n < a.N0;
+      xres[k] = a.x[ok ? (int64_t)tok * a.N0 + n : 0];
+      gres[k] = bf16_to_f32(a.gain_next[ok ? n : 0]);
+    }
   }
   // QKV: what a thread's epilogue items need besides the sums - the rows' positions, their rotary factors - is requested
   // before the weights, the pages of their cache slots (which depend on the positions) behind the first weights: a wave
@@ -365,7 +374,10 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   if constexpr (EPI == SK_RESID) {
     // ---- residual projection: x += tile; next GEMM's input x * gain; sums of squares of the 16 columns per row
     static_assert(EPI != SK_RESID || NT == 1, "a residual projection's workgroup owns one 16-row weight tile");
-    for (int item = tid; item < MT * 256; item += NW * 64) {
+#pragma unroll
+    for (int k = 0; k < RIT; ++k) {
+      const int item = tid + k * NW * 64;
+      if (item >= MT * 256) break;
       const int m = item >> 8, iq = (item >> 6) & 3, ln = item & 63;
       const int tok = m * 16 + (ln & 15);
       const int n = row0[0] + 4 * (ln >> 4) + iq;
@@ -374,8 +386,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
       for (int ww = 0; ww < NW; ++ww) sum += red[ww][0][m][iq][ln];
       float sq = 0.f;
       if (tok < M && n < a.N0) {
-        const float v = (item == tid ? xres : a.x[(int64_t)tok * a.N0 + n]) + sum;
-        const float gn = item == tid ? gres : bf16_to_f32(a.gain_next[n]);
+        const float v = xres[k] + sum, gn = gres[k];
         a.x[(int64_t)tok * a.N0 + n] = v;
         a.xg_out[frag_offset(tok, n, MT)] = f32_to_bf16(v * gn);
         sq = v * v;
@@ -504,20 +515,27 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
   }   // chunks
 }
 
-// Pipeline of a form.  What a wave has in flight beyond two stages brings nothing (D 3 -> 4 .. 8: -1 .. +5 % where the
-// registers last, up to twice the time where they do not), so stages are as short and as few as keep a wave's registers
-// in its share: 8 waves of 6 tiles x 64 rows with two stages (178 registers) 42.4 us where 4 waves with three take 47.1; gate/up
-// of 16 rows in stages of two steps / one: 8192 x 2048 14.1 / 12.7, 5504 x 2048 11.0 / 9.6, 12288 x 4096 37.2 / 37.3.
+// Pipeline of a form.  What bounds a workgroup beside the memory itself is how much its CU can have outstanding: about 32 KB,
+// whatever the registers could hold, and loads come back in the order in which they were issued.  So a CU reads 58 GB/s from
+// memory, 149 from the L2, and 58 of both mixed: an activation load (from the L2) behind a weight load (from memory) takes as long.
+// Stages are therefore as long as the registers allow with two of them in flight, and ask for all their weights first: then
+// the activations behind them come at the L2's pace.  (Short stages, weights and activations in turn / these, us: residual 32 rows of
+// 4096 x 12288 25.6 / 24.8, 64 rows 34.9 / 33.7, 16 rows of 2048 x 2048 8.6 / 7.0; q/k/v 12288 x 4096 64 rows 28.3 / 26.8, 96 rows
+// 34.6 / 32.1; 4608 x 3584 32 rows 13.3 / 12.6; LM head 126464 x 4096 32 rows 191 / 186, 48 rows 203 / 194.)  More stages than two
+// in flight bring nothing; registers beyond a wave's share cost up to twice the time.  Gate/up of 16 rows in stages of two steps / one:
+// 8192 x 2048 14.1 / 12.7, 5504 x 2048 11.0 / 9.6, 12288 x 4096 37.2 / 37.3; six tiles x 32 rows two / one 37.3 / 36.4.
 template <int NT, int MT, int NW, int EPI>
 struct SkCfg {
-  static constexpr bool WIDE = EPI == SK_SWIGLU && NT == 6;
-  static constexpr int JB = (MT >= 3 || (EPI == SK_SWIGLU && MT <= 2) || (EPI == SK_QKV && NT == 2)) ? 1 : 2;
-  static constexpr int D = (WIDE && MT >= 3) || (EPI == SK_SWIGLU && MT == 4) || (EPI == SK_QKV && MT >= 7) ? 2
-                           : (EPI == SK_QKV && NT == 2 && MT <= 2) ? 5 : 3;
+  static constexpr bool HEAD = EPI == SK_LMSTATS || EPI == SK_F32;
+  static constexpr int JB = EPI == SK_RESID ? 4
+                            : EPI == SK_QKV ? (NT == 2 ? (MT <= 4 ? 4 : 2) : MT == 8 ? 1 : 2)
+                            : HEAD          ? (MT == 1 ? 4 : 2)
+                                            : MT >= 3 || EPI == SK_SWIGLU ? 1 : 2;
+  static constexpr int D = EPI == SK_RESID ? (MT <= 2 ? 3 : 2) : EPI == SK_QKV ? (NT == 3 && MT <= 2 ? 3 : 2) : HEAD ? 2 : MT == 4 ? 2 : 3;
   static constexpr int TPC = EPI == SK_SWIGLU ? 2 : NT;
   // waves per SIMD that the registers are to allow: two 8-wave workgroups per CU for the narrow gate/up form, so that one
   // workgroup's prologue and reduction overlap the other's streaming
-  static constexpr int WPS = NW == 16 || (EPI == SK_SWIGLU && NT == 2) ? 4 : (NW == 4 && MT <= 2) ? 1 : 2;
+  static constexpr int WPS = EPI == SK_SWIGLU && NT == 2 ? 4 : (NW == 4 && MT <= 2) ? 1 : 2;
 };
 template <int NT, int MT, int NW, int EPI>
 static hipError_t sk_go(hipStream_t s, const SkArgs& a, int grid) {
@@ -588,7 +606,7 @@ static SkArgs sk_base(const void* X, int M, int K) {
   return a;
 }
 
-// Residual projection x += A * W^T: one workgroup of 16 waves per 16-column tile, the waves split K.  Its epilogue
+// Residual projection x += A * W^T: one workgroup of 8 waves per 16-column tile, the waves split K.  Its epilogue
 // prepares the next GEMM's input (x * gain_next in fragment order, sums of squares per row): no RMSNorm launch.
 // A workgroup re-reads all of A from the L2 (twice its weight bytes); that costs less than exchanging partial
 // products between workgroups would (two memory round trips at the end of every launch).
@@ -602,7 +620,7 @@ hipError_t launch_sk_resid(dllm_ctx* c, hipStream_t s, const void* A, const void
   a.xg_out = WSM(c, xn, bf16_t);
   a.ss_out = WSM(c, ss, float);
   a.ss_stride = ss_row_stride(c);
-  return sk_launch_mt<1, SK_NW_RESID, SK_RESID>(s, a, (N + 15) / 16);
+  return sk_launch_mt<1, SK_NW, SK_RESID>(s, a, (N + 15) / 16);
 }
 
 // the GEMM input comes with n_ss partial sums of squares per row
