@@ -30,7 +30,8 @@ __host__ __device__ __forceinline__ int gt_item(int wg, int n_wg, int it, int n_
 // Workgroups of a launch over n_items items, `slots` of which the chip holds at a time.  Copies run up to nsw - 1 stages
 // ahead and a workgroup knows one item ahead.  Items of fewer than nsw stages would need more: the cursor would come to
 // the next item's end while the one in front of it is still being multiplied, and fetch that item a second time in place
-// of the one behind it.  Such launches have a workgroup per item, so that no copies run on into a next one.
+// of the one behind it.  Such launches have a workgroup per item, so that no copies run on into a next one.  (Weights of two stages
+// together: nsw is one more than the ring.)
 __host__ __device__ inline int gt_workgroups(int n_items, int slots, int stages, int nsw) {
   return n_items < slots || stages < nsw ? (n_items + 7) / 8 * 8 : slots;
 }

@@ -34,12 +34,13 @@ static dllm_config tiny_cfg() {
 // Every workgroup's copies are issued as the kernel issues them - ring - 1 stages in front of its first item, then one per
 // stage, each followed by a step of the cursor that knows the item behind the one being multiplied and no other - and the
 // stage a copy fetched has to be the one that is multiplied from its buffer.  Returns the number of wrong stages and of
-// items that are not multiplied exactly once.
-static int ring_errors(int ring, int nsw, int stages, int n_items, int slots) {
+// items that are not multiplied exactly once.  pair 1, 2: copies of two stages together, for items of `stages` (even) +
+// 2 * (i % 3) stages, as early as the kernel issues them (in the stage in front of every other one) or as late (in that one).
+static int ring_errors(int ring, int nsw, int stages, int n_items, int slots, int pair = 0) {
   struct It { int id, k_first, k_begin, k_end; bool ok; };
-  const int n_wg = dllm::gt_workgroups(n_items, slots, stages, nsw);
+  const int n_wg = dllm::gt_workgroups(n_items, slots, stages, nsw + (pair ? 1 : 0));
   auto item = [&](int wg, int it) {
-    const int id = dllm::gt_item(wg, n_wg, it, n_items), n = stages + (id < 0 ? 0 : id) % 3;
+    const int id = dllm::gt_item(wg, n_wg, it, n_items), n = stages + (id < 0 ? 0 : id) % 3 * (pair ? 2 : 1);
     return It{id, (id < 0 ? 0 : id) % n * 64, 0, n * 64, id >= 0};
   };
   int errors = 0;
@@ -54,10 +55,10 @@ static int ring_errors(int ring, int nsw, int stages, int n_items, int slots) {
       copied.push_back({from, k});
       GT_ADVANCE(k, first, begin, end, nxt, from = nxt.id);
     };
-    for (int s = 0; s < ring - 1; ++s) copy();
+    for (int s = 0; s < (pair == 0 ? ring - 1 : pair == 1 ? ring : ring - 2); ++s) copy();
     for (size_t at = 0;;) {
       for (int s = 0, n = cur.k_end / 64; s < n; ++s, ++at) {
-        copy();
+        for (int c = 0; c < (pair == 0 ? 1 : s % 2 == pair % 2 ? 2 : 0); ++c) copy();
         if (copied[at] != std::make_pair(cur.id, (cur.k_first / 64 + s) % n * 64)) ++errors;
       }
       ++seen[cur.id];
@@ -102,13 +103,20 @@ static int attn_plan_errors() {
 }
 
 // "form" then (kind, rows, columns, K, starts_apart) for each product: what it launches on 256 CUs, a line each.  kind "gate-up"
-// (columns: features) or "resid" (at most four K shares, one above 2048 rows): [whole rounds' column tiles +] tile [/ K shares].
+// (columns: features) or "resid" (at most four K shares, one above 2048 rows): [whole rounds' column tiles +] tile [/ K shares];
+// "qkv:query heads:key heads:channels" (columns: not read): the fused kernel's tile, or "split".
 static int print_forms(int n, char** v) {
   using namespace dllm;
   static const char* const name[GT_N] = {"256x256", "128x256", "128x128", "128x64", "128x96", "128x160", "256x96", "256x160", "256x224"};
   for (int i = 0; i + 4 < n; i += 5) {
     const int M = atoi(v[i + 1]), N = atoi(v[i + 2]), K = atoi(v[i + 3]);
     const bool apart = atoi(v[i + 4]) != 0;
+    int hq, hkv, dh;
+    if (sscanf(v[i], "qkv:%d:%d:%d", &hq, &hkv, &dh) == 3) {
+      const bool fused = gt_qkv_fused(256, M, hq * dh, hkv * dh, dh, K, M <= 2048 ? 3 : 1);
+      printf("%s\n", fused ? name[gt_rope_plan(256, M, hq * dh, hkv * dh, dh, K).tile] : "split");
+      continue;
+    }
     const GtForm f = strcmp(v[i], "resid") == 0 ? gt_resid_form(256, M, N, K, M <= 2048 ? 4 : 1, apart) : gt_swiglu_form(256, M, N, K, apart);
     if (f.n_tn > 0) printf("%d+%s\n", f.n_tn, name[f.tile]);
     else if (f.splits > 1) printf("%s/%d\n", name[f.tile], f.splits);
@@ -120,12 +128,14 @@ static int print_forms(int n, char** v) {
 int main(int argc, char** argv) {
   if (argc > 1 && strcmp(argv[1], "form") == 0) return print_forms(argc - 2, argv + 2);
   EXPECT(attn_plan_errors(), 0);
-  const int rings[][2] = {{2, 3}, {3, 4}, {4, 5}, {3, 3}, {4, 4}, {5, 5}};
+  const int rings[][2] = {{2, 3}, {3, 4}, {4, 5}, {4, 6}, {3, 3}, {4, 4}};
   for (const auto& r : rings)
     for (int stages = 2; stages <= 8; ++stages)
       for (int n_items = 1; n_items <= 48; ++n_items) {       // on 8 places: up to six items after each other
         EXPECT(ring_errors(r[0], r[1], stages, n_items, 8), 0);
         EXPECT(ring_errors(r[1], r[1], stages, n_items, 8), 0);
+        if (r[1] >= 4 && stages % 2 == 0)
+          for (int pair = 1; pair <= 2; ++pair) EXPECT(ring_errors(r[1], r[1], stages, n_items, 8, pair), 0);
       }
   void* const p = (void*)0x3000;          // stands for device memory; the host never reads it
   int32_t* const ip = (int32_t*)p;

@@ -1,6 +1,7 @@
 // bfloat16 matrix-core (MFMA) kernels for gfx950: GEMMs over many token rows.
 #include "mfma_common.h"
 #include "gemm_ring.h"
+#include <type_traits>
 
 // ==========================================================================================
 // Large-M bfloat16 GEMM on the matrix cores: C[M,N] = A[M,K] * W[N,K]^T (both K-contiguous).
@@ -20,7 +21,7 @@ constexpr int LG_BN = 128, LG_BK = 64;
 // 16-byte columns of a slice) write 16 different bank groups instead of two.
 __device__ __forceinline__ int lg_swz(int g, int ks) { return (4 * g) ^ (2 * ks); }
 enum LgEpi { LG_STORE = 0, LG_STORE_F32 = 1, LG_RESID = 2, LG_SWIGLU = 3, LG_LMSTATS = 4, LG_QKV = 5, LG_ROPE64 = 6, LG_ROPE128 = 7,
-             LG_LMSTATS_X = 8 };   // (tile kernel: LMSTATS with expf)
+             LG_LMSTATS_X = 8, LG_ROPE_ODD = 9 };   // (tile kernel: LMSTATS with expf)
 
 struct LgArgs {
   const bf16_t* A;
@@ -44,7 +45,8 @@ struct LgArgs {
   float* part;             // LMSTATS: [rows, n_parts, 4]
   int n_parts;
   int32_t mask_id;
-  // ROPE64 / ROPE128 (q/k/v product of heads of 64 / 128 channels, rotary embedding and K/V write in the epilogue)
+  // ROPE64 / ROPE128 (q/k/v product of heads of 64 / 128 channels, rotary embedding and K/V write in the epilogue), ROPE_ODD
+  int dh;                  // ROPE_ODD: channels of a head, a multiple of 32
   const float* rope_cos;   // [M, dh/2]
   const float* rope_sin;
   const int4* loc;         // [M] where a row's K and V go: pool page (-1: not cached), slot, packed column (-1: none)
@@ -313,40 +315,58 @@ typedef __amdgpu_buffer_rsrc_t gt_rsrc;
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 #define GT_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
 
-// WM: waves along the token rows (the others lie along the weight rows)
-template <int TM, int TN, int NSA, int NSW, int WM = 2>
+// WM: waves along the token rows (the others lie along the weight rows).  WB 2: the weights of two stages are asked for
+// together, every other stage, in front of that stage's activations.  A CU has about 32 KB outstanding and gets them back in order
+// (58 GB/s from memory, 149 GB/s from the L2, 54 .. 59 where the two alternate), so activations that the L2 holds wait less often
+// for weights in front of them (us, WB 1 / 2: down 256 x 4096 x 12288 in four shares of 128 x 128 39.3 / 36.5, q/k/v 256 x 12288 x 4096
+// in 128 x 96 44.1 / 42.7, gate/up 256 x 24576 x 4096 in 256 x 96 57.8 / 56.1; no gain in 128 x 64 and 128 x 160).  The loop over
+// stages goes by pairs: an item begins with a pair.
+template <int TM, int TN, int NSA, int NSW, int WM = 2, int WB = 1>
 struct GtGeom {
   static_assert(NSA >= 2 && NSA <= NSW, "the weights run at least as far ahead as the activations");
+  static_assert(WB == 1 || (WB == 2 && NSW >= 4), "a pair of stages lands before the first of them is needed");
   static constexpr int BM = 32 * WM * TM, BN = 32 * (4 / WM) * TN, A_BYTES = BM * 128, W_BYTES = BN * 128;
   static constexpr int CA = BM / 32, CW = BN / 32;              // copies of a wave and stage (8 rows x 128 bytes each)
   static constexpr int LDS = NSA * A_BYTES + NSW * W_BYTES;
   static constexpr int PER_CU = LDS <= 80 * 1024 ? 2 : 1;       // workgroups that fit a CU
   static constexpr int NPOS = 4 * TM * TN;                      // products of a wave and stage
   static constexpr int PB = 3 * TM * TN;                        // the barrier comes behind this product
-  // copy c of a stage's group (activations first) goes behind this product, counted on from the barrier that frees
-  // its buffers; positions past the stage's end wrap into the next stage
-  static constexpr int raw_pos(int c) { return PB + 1 + c * (NPOS - 1) / (CA + CW); }
-  static constexpr int pos(int c) { return raw_pos(c) % NPOS; }
-  static constexpr int early() {                                // copies of a group in front of its own stage
-    int n = 0;
-    for (int c = 0; c < CA + CW; ++c) n += raw_pos(c) < NPOS;
-    return n;
+  // The copies of group s are issued between the barrier of stage s - 1, which frees that stage's buffers, and the barrier of stage
+  // s: the activations of stage s - 1 + NSA and, WB 1, the weights of stage s - 1 + NSW behind them; WB 2, in front of them in
+  // groups of even phase the weights of stages s - 2 + NSW and s - 1 + NSW.
+  static constexpr int n(int ph) { return WB == 1 ? CA + CW : ph == 0 ? CA + 2 * CW : CA; }
+  // copy c of a group goes behind this product, counted on from the beginning of stage s - 1
+  static constexpr int raw_pos(int ph, int c) { return PB + 1 + c * (NPOS - 1) / n(ph); }
+  static constexpr int early(int ph) {                          // copies of a group in front of its own stage
+    int k = 0;
+    for (int c = 0; c < n(ph); ++c) k += raw_pos(ph, c) < NPOS;
+    return k;
   }
-  // copies issued behind those of stage s+1 that may still be in flight at the barrier in front of stage s+1
-  static constexpr int FLY_A = CW + (NSA - 2) * (CA + CW), FLY_W = (NSW - 2) * (CA + CW);
-  static constexpr int IN_FLIGHT = FLY_A < FLY_W ? FLY_A : FLY_W;
-  static_assert(IN_FLIGHT < 64, "what the memory counter holds");
+  // copies issued behind those of stage s + 1 that may still be in flight at the barrier of stage s (of phase ph)
+  static constexpr int behind(int ph, int groups) {             // all copies of the last `groups` groups up to group s
+    int k = 0;
+    for (int g = 0; g < groups; ++g) k += n((ph + g) & 1);
+    return k;
+  }
+  static constexpr int in_flight(int ph) {
+    const int fa = (WB == 1 ? CW : 0) + behind(ph, NSA - 2);
+    const bool first = ((ph + NSW - 3) & 1) == 0;               // stage s + 1 is the first of its pair, in group s + 3 - NSW
+    const int fw = WB == 1 ? behind(ph, NSW - 2) : first ? CW + CA + behind(ph, NSW - 3) : CA + behind(ph, NSW - 2);
+    return fa < fw ? fa : fw;
+  }
+  static_assert(in_flight(0) < 64 && in_flight(1) < 64, "what the memory counter holds");
 };
 
 // HALF: K is 32 more than a multiple of 64.  The last stage's upper 32 come from past the end of the row, so their copies
 // are sent out of the descriptor, which leaves zeros in LDS.  A form of its own: it takes 19 .. 21 instructions more per stage
 // (128 x 128: 146 for 125).
-template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF, int WM>
+template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF, int WM, int WB>
 __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
-  using G = GtGeom<TM, TN, NSA, NSW, WM>;
+  using G = GtGeom<TM, TN, NSA, NSW, WM, WB>;
   constexpr int BM = G::BM, BN = G::BN, CA = G::CA, CW = G::CW;
   constexpr bool SWIGLU = EPI == LG_SWIGLU, STATS = EPI == LG_LMSTATS || EPI == LG_LMSTATS_X, ROPE = EPI == LG_ROPE64 || EPI == LG_ROPE128;
   constexpr bool QKV = EPI == LG_QKV || ROPE;
+  constexpr bool ROPT = EPI == LG_ROPE_ODD;
   constexpr int DH = EPI == LG_ROPE64 ? 64 : 128;
   constexpr bool WIDE = EPI == LG_ROPE128 && TN == 4;           // a wave's weight rows are one whole head of 128 channels
   static_assert(!ROPE || (TM == TN && TN % 2 == 0), "value tiles swap the operands; rotary pairs share a lane");
@@ -354,7 +374,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // gate and up tiles come in pairs; of an odd number the last holds 16 gate rows and the same 16 up rows
   constexpr bool ODD = SWIGLU && TN % 2 == 1;
   constexpr bool RODD = EPI == LG_RESID && WM == 4;
-  static_assert((WM == 2 || ODD || RODD) && !((ODD || RODD) && HALF), "other layouts of the waves are built for odd tiles alone");
+  static_assert((WM == 2 || ODD || RODD || ROPT) && !((ODD || RODD || ROPT) && HALF), "other layouts of the waves are built for odd tiles alone");
   static_assert(!STATS || TN % 2 == 0, "64 columns per partial");
   extern __shared__ __attribute__((aligned(1024))) unsigned char gt_smem[];
   unsigned char* const sA = gt_smem;
@@ -397,7 +417,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     t.n0 = tn * TILE_N + a.n_first;
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < k_all ? t.k_begin + a.k_per : k_all;
-    t.k_first = t.k_begin + (t.n0 / (SWIGLU ? 1920 : 256) * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
+    t.k_first = t.k_begin + (t.n0 / (SWIGLU ? 1920 : ROPT ? 3840 : 256) * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
     t.ok = true;
     t.val = ROPE && t.n0 >= N + a.N2;                  // a tile of the value projection
     return t;
@@ -410,7 +430,9 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     const int rows = M - t.tm * BM < BM ? M - t.tm * BM : BM;
     return rsrc(a.A + (int64_t)t.tm * BM * K, (int64_t)rows * K * 2);
   };
-  auto rsrc_w = [&](const Item& t) -> gt_rsrc {
+  // ROPE_ODD: the rows of two copies may lie apart, so a descriptor covers one copy of 8 rows, or two of the same 16
+  constexpr int ND = !ROPT ? 1 : CW % 2 ? CW : CW / 2, DC = CW / ND;   // descriptors of a wave, copies of each
+  auto rsrc_w = [&](const Item& t, int d = 0) -> gt_rsrc {
     const int n0 = t.n0;
     const bf16_t* base = a.W;
     int row = n0, rows = N - n0 < TILE_N ? N - n0 : TILE_N;
@@ -419,6 +441,22 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
       // the tile width, so a tile belongs to one of them)
       if (n0 >= N) { base = n0 < N + a.N2 ? a.W2 : a.W3; row = n0 < N + a.N2 ? n0 - N : n0 - N - a.N2; }
       rows = BN;
+    }
+    if constexpr (ROPT) {
+      // stacked as above, in groups of 32 rows: 16 channels of a head of q or k and the 16 that they rotate with, half a head on;
+      // or 32 value channels
+      const int R = n0 + (w * CW + d * DC) * 8, half = a.dh >> 1;
+      rows = DC * 8;
+      if (R >= N + a.N2) {
+        base = a.W3;
+        row = R - N - a.N2;
+        if (row >= a.N2) row = rows = 0;                        // behind the last column
+      } else {
+        row = R & ~31;
+        if (R >= N) { base = a.W2; row -= N; }
+        const int head = row / a.dh;
+        row = head * a.dh + ((row - head * a.dh) >> 1) + (R & 15) + (R & 16 ? half : 0);
+      }
     }
     if constexpr (SWIGLU) {
       if (ODD ? w >> 1 : w & 1) base = a.W2;                    // a wave copies gate rows or up rows
@@ -430,13 +468,18 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   int it_next = 1;
   Item nxt = item_at(it_next);
   gt_rsrc ra = rsrc_a(cur), rw = rsrc_w(cur), rna = rsrc_a(nxt.ok ? nxt : cur), rnw = rsrc_w(nxt.ok ? nxt : cur);
+  gt_rsrc rwd[ND];                                              // (ROPE_ODD: one item a workgroup)
+  if constexpr (ROPT) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d) rwd[d] = rsrc_w(cur, d);
+  }
   int ka = cur.k_first, kw = cur.k_first, kba = cur.k_begin, kbw = cur.k_begin, kea = cur.k_end, kew = cur.k_end;
   int ksa = ka, ksw = kw;                                       // where the item's stages begin and, having wrapped, end
 
   // copies: instruction q of wave w fills LDS rows (w*C + q)*8 .. +7; lane l holds piece l%8 of row l/8
   const int l8 = lane >> 3, piece = (lane & 7) ^ (l8 >> 1);     // (odd q: the row's bit 3 flips bit 2 of the piece)
   // features between consecutive LDS rows of a tile
-  constexpr int FS = STATS || ODD || RODD ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
+  constexpr int FS = STATS || ODD || RODD || ROPT ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
   const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = HALF ? vA0 + (piece < 4 ? 64 : -64) : vA0 ^ 64;
   const int vW0 = l8 * FS * K * 2 + piece * 16, vW1 = HALF ? vW0 + (piece < 4 ? 64 : -64) : vW0 ^ 64;
   const int out0 = piece < 4 ? 0 : 0x40000000, out1 = piece < 4 ? 0x40000000 : 0;   // HALF: added in the last stage (even, odd q)
@@ -449,6 +492,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   };
   auto w_row = [&](int q) -> int {                              // weight row of the instruction's first LDS row
     if constexpr (ODD) return ((w & 1) * CW + q) * 8;
+    if constexpr (ROPT) return q % DC * 8;                      // (the rest is in the descriptor)
     const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
     if constexpr (STATS || RODD) return R;
     // both members of a rotary pair (channels j and j + DH/2 of a head) in one lane, in tiles i and i + 2 (WIDE: two
@@ -476,11 +520,30 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
                                              16, (VO ? vA[q] : (q & 1) ? vA1 : vA0) + past(ka, q), VO ? ka * 2 : ka * 2 + q * 16 * K, 0, 0);
   };
   auto copy_w = [&](int slot, int q) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (ODD ? odd_lds(q) * 128 : (w * CW + q) * 1024)),
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ROPT ? rwd[q / DC] : rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (ODD ? odd_lds(q) * 128 : (w * CW + q) * 1024)),
                                              16, (VO ? vW[q] : (q & 1) ? vW1 : vW0) + past(kw, q), VO ? kw * 2 : kw * 2 + w_row(q) * 2 * K, 0, 0);
   };
   auto adv_a = [&]() { GT_ADVANCE(ka, ksa, kba, kea, nxt, ra = rna); };
   auto adv_w = [&]() { GT_ADVANCE(kw, ksw, kbw, kew, nxt, rw = rnw); };
+  // copy c of a group of phase ph, in its own stage or in the stage before (`early`); sa, sw: buffers of the stage that issues it
+  auto issue = [&](int ph, int c, bool early, int sa, int sw) {
+    const int a_slot = early ? sa : sa == 0 ? NSA - 1 : sa - 1;
+    const int w1 = sw == 0 ? NSW - 1 : sw - 1, w2 = w1 == 0 ? NSW - 1 : w1 - 1;
+    if constexpr (WB == 1) {
+      if (c < CA) copy_a(a_slot, c);
+      else copy_w(w1, c - CA);
+    } else {
+      const int nw = ph == 0 ? 2 * CW : 0;
+      if (c < nw) {
+        const int second = c >= CW;
+        copy_w(early ? (second ? sw : w1) : (second ? w1 : w2), c - second * CW);
+        if (c == CW - 1 || c == 2 * CW - 1) adv_w();
+      } else {
+        copy_a(a_slot, c - nw);
+        if (c == nw + CA - 1) adv_a();
+      }
+    }
+  };
 #pragma unroll
   for (int s = 0; s < NSW - 1; ++s) {
     if (s < NSA - 1) {
@@ -488,16 +551,18 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
       for (int q = 0; q < CA; ++q) copy_a(s, q);
       adv_a();
     }
+    if (s < NSW - WB) {
 #pragma unroll
-    for (int q = 0; q < CW; ++q) copy_w(s, q);
-    adv_w();
+      for (int q = 0; q < CW; ++q) copy_w(s, q);
+      adv_w();
+    }
   }
-  constexpr int EARLY = G::early();
-  static_assert(EARLY < CA, "the copies in front of their own stage are activations, not all of them");
+  constexpr int EARLY = G::early(0);
+  static_assert(WB == 2 || EARLY < CA, "the copies in front of their own stage are activations, not all of them");
 #pragma unroll
-  for (int q = 0; q < EARLY; ++q) copy_a(NSA - 1, q);
+  for (int q = 0; q < EARLY; ++q) issue(0, q, true, NSA - 1, NSW - 1);
   // stage 0 is in: all but the copies behind it
-  constexpr int FILL = (NSA - 1) * CA + (NSW - 1) * CW + EARLY - (CA + CW);
+  constexpr int FILL = (NSA - 1) * CA + (NSW - WB) * CW + EARLY - (CA + CW);
   static_assert(FILL < 64, "what the memory counter holds");
   __builtin_amdgcn_s_waitcnt(GT_VMCNT(FILL));
   __builtin_amdgcn_s_barrier();
@@ -528,9 +593,9 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
     // K ranges are multiples of 64: at least two stages, and where another item follows at least NSW (gt_workgroups)
     const int ns = (cur.k_end - cur.k_begin) / 64;
-    for (int st = 0; st < ns; ++st) {
+    auto stage = [&](auto phase, int st) __attribute__((always_inline)) {
+      constexpr int PH = decltype(phase)::value;
       const int na = sa + 1 == NSA ? 0 : sa + 1, nw = sw + 1 == NSW ? 0 : sw + 1;
-      const int fa_slot = sa == 0 ? NSA - 1 : sa - 1, fw_slot = sw == 0 ? NSW - 1 : sw - 1;   // the stage before: free
       const unsigned char *bA = sA + sa * G::A_BYTES, *bW = sW + sw * G::W_BYTES;
       const unsigned char *cA = sA + na * G::A_BYTES, *cW = sW + nw * G::W_BYTES;
       // the last item's loads and stores are not to count among the copies
@@ -559,24 +624,38 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
             if (p == G::PB) {
               // this wave's copies of the next stage are in and its reads of this one are back (lgkmcnt(0)); behind the
               // barrier everybody's are
-              __builtin_amdgcn_s_waitcnt(GT_VMCNT(G::IN_FLIGHT) & 0xF0FF);
+              __builtin_amdgcn_s_waitcnt(GT_VMCNT(G::in_flight(PH)) & 0xF0FF);
               __builtin_amdgcn_s_barrier();
             }
 #pragma unroll
             for (int n = 0; n < TM + TN; ++n)
               if (n * (TM * TN) / (TM + TN) == idx) rd(b ^ 1, n, pa, pw);
 #pragma unroll
-            for (int c = 0; c < CA + CW; ++c)
-              if (G::pos(c) == p) {
-                if (c < CA) copy_a(p > G::PB ? sa : fa_slot, c);   // behind the barrier: into this stage's own buffer
-                else copy_w(fw_slot, c - CA);
-              }
+            for (int c = 0; c < G::n(PH); ++c)
+              if (G::raw_pos(PH, c) == p + G::NPOS || (WB == 1 && G::raw_pos(PH, c) == p)) issue(PH, c, p > G::PB, sa, sw);
+            if constexpr (WB == 2) {
+#pragma unroll
+              for (int c = 0; c < G::early(PH ^ 1); ++c)
+                if (G::raw_pos(PH ^ 1, c) == p) issue(PH ^ 1, c, true, sa, sw);
+            }
           }
-        if (G::pos(CA - 1) / (TM * TN) == ks) adv_a();
-        if (G::pos(CA + CW - 1) / (TM * TN) == ks) adv_w();
+        if constexpr (WB == 1) {
+          if (G::raw_pos(0, CA - 1) % G::NPOS / (TM * TN) == ks) adv_a();
+          if (G::raw_pos(0, CA + CW - 1) % G::NPOS / (TM * TN) == ks) adv_w();
+        }
       }
       sa = na;
       sw = nw;
+    };
+    if constexpr (WB == 1) {
+      for (int st = 0; st < ns; ++st) stage(std::integral_constant<int, 0>{}, st);
+    } else {
+      int st = 0;
+      for (; st + 1 < ns; st += 2) {
+        stage(std::integral_constant<int, 0>{}, st);
+        stage(std::integral_constant<int, 1>{}, st + 1);
+      }
+      if (st < ns) stage(std::integral_constant<int, 0>{}, st);
     }
 
     const int m0 = cur.tm * BM, n0 = cur.n0, split = cur.split;
@@ -791,6 +870,122 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
           }
         }
       }
+    } else if constexpr (ROPT) {
+      // One item a workgroup: the ring is free, and the sums go through it, 32 token rows of every wave at a time, so that a thread
+      // has 8 neighbouring channels of a token, and the 8 that they rotate with, or 8 tokens of a value channel, and stores 16
+      // bytes.  Groups of 32 weight rows allow any width: 256 x 12288 x 4096 in 256 tiles of 128 x 96 takes 42.7 us where 192 of
+      // 128 x 128 take 48.3, 1024 x 4608 x 3584 in 232 of 128 x 160 52.7 where 288 of 128 x 128 take 66.9.  (From the registers,
+      // where a lane has single channels: 2-byte stores, 45.9 and 57.5.  K in two shares, the last workgroup of a tile to come
+      // adding up the sums of both: 128 rows 43.0 -> 35.5, 8 of them for the exchange; the weight-streaming product takes 30 .. 39.)
+      constexpr int P = BN + 4;                                  // floats of a row (16-byte reads aligned, rows 4 banks apart)
+      static_assert(128 * P * 4 + BM * 20 <= G::LDS, "the rows of a pass, and all rows' factors and places");
+      float* const tile = (float*)gt_smem;
+      int4* const locs = (int4*)(gt_smem + 128 * P * 4);
+      float* const rss = (float*)(locs + BM);
+      const int pt = a.page_tokens, dh = a.dh, half = dh >> 1, gh = dh >> 5, nq = N >> 5, nk = a.N2 >> 5, hkv = a.N2 / dh, u0 = n0 >> 5;
+      __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));                   // the trailing copies
+      __syncthreads();
+      // row of the pass -> row of the tile
+      auto tok_of = [&](int lr, int j) -> int { return (lr >> 5) * 32 * TM + j * 32 + (lr & 31); };
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        // what the pass needs from memory is requested together, in front of the exchange
+        f32x4 cs[TN][2], sn[TN][2];
+        int4 l;
+        float rsv;
+        if (j == 0) {
+          const int m = m0 + (tid < rows ? tid : 0);
+          l = a.loc[m];
+          rsv = a.rscale ? a.rscale[m] : 1.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < TN; ++k) {
+          const int it = tid + k * 256, oct = it & 1, u = u0 + (it >> 1) % TN, t = tok_of((it >> 1) / TN, j);
+          const int uk = u < nq ? u : u - nq, ch = (uk % gh) * 16 + oct * 8;
+          const int64_t at = (int64_t)(m0 + (t < rows ? t : 0)) * half + ch;
+#pragma unroll
+          for (int e = 0; e < 2; ++e) { cs[k][e] = *(const f32x4*)(a.rope_cos + at + e * 4); sn[k][e] = *(const f32x4*)(a.rope_sin + at + e * 4); }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) tile[(wm * 32 + (e >> 2) * 8 + h * 4 + (e & 3)) * P + i * 32 + r] = acc[i][j][e];
+        if (j == 0 && tid < BM) {
+          locs[tid] = tid < rows ? l : make_int4(-1, 0, -1, 0);
+          rss[tid] = rsv;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < TN; ++k) {
+          const int it = tid + k * 256, oct = it & 1, i = (it >> 1) % TN, lr = (it >> 1) / TN, u = u0 + i, t = tok_of(lr, j);
+          if (u >= nq + nk || t >= rows) continue;
+          const bool is_q = u < nq;
+          const int uk = is_q ? u : u - nq, head = uk / gh, ch = (uk - head * gh) * 16 + oct * 8;
+          const float* const x = tile + lr * P + i * 32 + oct * 8;
+          const float rs = rss[t];
+          u32x4 lo, hi;
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const f32x4 x0 = *(const f32x4*)(x + e * 4) * rs, x1 = *(const f32x4*)(x + 16 + e * 4) * rs;
+            float a0[4], a1[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              a0[q] = x0[q] * cs[k][e][q] - x1[q] * sn[k][e][q];
+              a1[q] = x1[q] * cs[k][e][q] + x0[q] * sn[k][e][q];
+            }
+            lo[e * 2] = pack_bf16x2(a0[0], a0[1]); lo[e * 2 + 1] = pack_bf16x2(a0[2], a0[3]);
+            hi[e * 2] = pack_bf16x2(a1[0], a1[1]); hi[e * 2 + 1] = pack_bf16x2(a1[2], a1[3]);
+          }
+          if (is_q) {
+            bf16_t* const o = (bf16_t*)a.C + (int64_t)(m0 + t) * N + head * dh + ch;
+            *(u32x4*)o = lo;
+            *(u32x4*)(o + half) = hi;
+          } else {
+            const int4 kl = locs[t];
+            if (kl.x >= 0) {
+              bf16_t* const o = a.pool_k + (((int64_t)kl.x * hkv + head) * pt + kl.y) * dh + ch;
+              *(u32x4*)o = lo;
+              *(u32x4*)(o + half) = hi;
+            }
+            if (kl.z >= 0) {
+              bf16_t* const o = a.pack_k + ((int64_t)head * a.tpad + kl.z) * dh + ch;
+              *(u32x4*)o = lo;
+              *(u32x4*)(o + half) = hi;
+            }
+          }
+        }
+        // values: a thread has 8 tokens of a channel, stored together where they lie side by side
+        if (u0 + TN > nq + nk) {
+          for (int it = tid; it < 16 * TN * 32; it += 256) {
+            const int f0 = it % (TN * 32), lr = it / (TN * 32) * 8, u = u0 + (f0 >> 5), t = tok_of(lr, j), f = (u - nq - nk) * 32 + (f0 & 31);
+            if (u < nq + nk || u >= nq + 2 * nk || t >= rows) continue;
+            bf16_t v[8];
+            int4 vl[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { v[k] = f32_to_bf16(tile[(lr + k) * P + f0] * rss[t + k]); vl[k] = locs[t + k]; }
+            bool runp = vl[0].x >= 0, runk = vl[0].z >= 0;
+#pragma unroll
+            for (int k = 1; k < 8; ++k) {
+              runp = runp && vl[k].x == vl[0].x && vl[k].y == vl[0].y + k;
+              runk = runk && vl[k].z == vl[0].z + k;
+            }
+            if (runp) __builtin_memcpy(a.pool_v + ((int64_t)vl[0].x * a.N2 + f) * pt + vl[0].y, v, 16);
+            else {
+#pragma unroll
+              for (int k = 0; k < 8; ++k)
+                if (vl[k].x >= 0) a.pool_v[((int64_t)vl[k].x * a.N2 + f) * pt + vl[k].y] = v[k];
+            }
+            if (runk) __builtin_memcpy(a.pack_v + (int64_t)f * a.tpad + vl[0].z, v, 16);
+            else {
+#pragma unroll
+              for (int k = 0; k < 8; ++k)
+                if (vl[k].z >= 0) a.pack_v[(int64_t)f * a.tpad + vl[k].z] = v[k];
+            }
+          }
+        }
+      }
     } else if constexpr (ODD) {
       // Lane holds gate and up rows l%32 of tiles i and TN/2 + i; of the last tile the lanes with l%32 < 16 hold gate rows and the
       // others the up rows of the same features: two registers (two token rows) exchange their halves, and each lane has one row.
@@ -920,7 +1115,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
         }
       }
     }
-    if (!nxt.ok) break;
+    if (ROPT || !nxt.ok) break;
     cur = nxt;
     nxt = item_at(++it_next);
     if (nxt.ok) { rna = rsrc_a(nxt); rnw = rsrc_w(nxt); }
@@ -928,31 +1123,32 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   __builtin_amdgcn_s_waitcnt(GT_VMCNT(0));   // the trailing repeats must not outlive the workgroup
 }
 
-template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF = false, int WM = 2>
-__global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW, HALF, WM>(a); }
+template <int EPI, int TM, int TN, int NSA, int NSW, bool HALF = false, int WM = 2, int WB = 1>
+__global__ __launch_bounds__(256) void k_gemm_tile(const LgArgs a) { gemm_tile_body<EPI, TM, TN, NSA, NSW, HALF, WM, WB>(a); }
 
 // Rings above the default LDS limit of a kernel: raised once per process.
 static bool gt_ready = false;   // (the tiles: launch_plan.h)
 static int gt_cus = 256;
 #define GT_KERNELS(X)                                                                                   \
   X(LG_SWIGLU, 4, 4, 2, 3) X(LG_SWIGLU, 2, 4, 2, 3) X(LG_SWIGLU, 2, 2, 4, 5)                            \
-  X(LG_RESID, 4, 4, 2, 3) X(LG_RESID, 2, 4, 2, 3) X(LG_RESID, 2, 2, 4, 5) X(LG_RESID, 2, 1, 3, 4)       \
+  X(LG_RESID, 4, 4, 2, 3) X(LG_RESID, 2, 4, 2, 3) X(LG_RESID, 2, 1, 3, 4)       \
   X(LG_ROPE64, 2, 2, 4, 5) X(LG_ROPE64, 2, 2, 2, 3)                            \
   X(LG_ROPE128, 4, 4, 2, 3) X(LG_ROPE128, 2, 2, 4, 5) X(LG_ROPE128, 2, 2, 2, 3)                         \
   X(LG_QKV, 4, 4, 2, 3) X(LG_QKV, 2, 4, 2, 3) X(LG_QKV, 2, 2, 4, 5) X(LG_QKV, 2, 1, 3, 4)               \
   X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS_X, 4, 4, 2, 3) X(LG_LMSTATS_X, 2, 2, 4, 5)
 // gate/up in tiles of an odd number of 32 weight rows, all four waves along the token rows
-#define GT_ODD_KERNELS(X) X(1, 3, 5, 5) X(1, 5, 4, 4) X(2, 3, 3, 3) X(2, 5, 3, 3)
+#define GT_ODD_KERNELS(X) X(LG_SWIGLU, 1, 3, 4, 5, 2) X(LG_SWIGLU, 1, 5, 4, 4, 1) X(LG_SWIGLU, 2, 3, 3, 4, 2) X(LG_SWIGLU, 2, 5, 3, 3, 1) \
+  X(LG_ROPE_ODD, 1, 3, 4, 6, 2) X(LG_ROPE_ODD, 1, 5, 4, 4, 1) X(LG_ROPE_ODD, 2, 3, 3, 4, 2) X(LG_ROPE_ODD, 2, 5, 3, 3, 1)
 // the forms that are also built for K of 32 more than a multiple of 64
 template <int EPI, int TM, int TN>
-constexpr bool GT_HALF = (TM == TN || TN == 1) && EPI != LG_ROPE64 && EPI != LG_ROPE128;
-template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2>
+constexpr bool GT_HALF = (TM == TN || TN == 1) && EPI != LG_ROPE64 && EPI != LG_ROPE128 && EPI != LG_ROPE_ODD;
+template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2, int WB = 1>
 static hipError_t gt_raise_lds() {
-  constexpr int lds = GtGeom<TM, TN, NSA, NSW, WM>::LDS;
-  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, false, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  constexpr int lds = GtGeom<TM, TN, NSA, NSW, WM, WB>::LDS;
+  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, false, WM, WB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if constexpr (WM == 2 && GT_HALF<EPI, TM, TN>)
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      e = hipFuncSetAttribute((const void*)k_gemm_tile<EPI, TM, TN, NSA, NSW, true, WM, WB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   return e;
 }
 int device_cus() { return gt_cus; }
@@ -967,9 +1163,10 @@ hipError_t init_gemm_tiles() {
 #define X(E, TM, TN, NA, NW) if (e == hipSuccess) e = gt_raise_lds<E, TM, TN, NA, NW>();
   GT_KERNELS(X)
 #undef X
-#define X(TM, TN, NA, NW) if (e == hipSuccess) e = gt_raise_lds<LG_SWIGLU, TM, TN, NA, NW, 4>();
+#define X(E, TM, TN, NA, NW, WB) if (e == hipSuccess) e = gt_raise_lds<E, TM, TN, NA, NW, 4, WB>();
   GT_ODD_KERNELS(X)
 #undef X
+  if (e == hipSuccess) e = gt_raise_lds<LG_RESID, 2, 2, 4, 5, 2, 2>();
   if (e == hipSuccess) e = gt_raise_lds<LG_RESID, 2, 7, 2, 3, 4>();
   gt_ready = e == hipSuccess;
   return e;
@@ -979,28 +1176,32 @@ hipError_t init_gemm_tiles() {
 static bool gt_usable(int M, int K) { return gt_ready && M > 64 && K % 32 == 0 && K >= 128; }
 
 // n_tn column tiles of a product from column n_first on (n_tn 0: all that are left)
-template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2>
+template <int EPI, int TM, int TN, int NSA, int NSW, int WM = 2, int WB = 1>
 static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int n_first = 0, int n_tn = 0) {
-  using G = GtGeom<TM, TN, NSA, NSW, WM>;
+  using G = GtGeom<TM, TN, NSA, NSW, WM, WB>;
   constexpr int tile_n = EPI == LG_SWIGLU ? G::BN / 2 : G::BN;
   a.tiles_m = (a.M + G::BM - 1) / G::BM;
-  constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128;
-  a.tiles_n = n_tn ? n_tn : qkv ? (a.N + 2 * a.N2) / G::BN : (a.N - n_first + tile_n - 1) / tile_n;
+  constexpr bool qkv = EPI == LG_QKV || EPI == LG_ROPE64 || EPI == LG_ROPE128 || EPI == LG_ROPE_ODD;
+  a.tiles_n = n_tn ? n_tn : qkv ? (a.N + 2 * a.N2 + G::BN - 1) / G::BN : (a.N - n_first + tile_n - 1) / tile_n;
   a.n_first = n_first;
   a.k_splits = k_splits;
   const int k_all = (a.K + 63) / 64 * 64;
   if (k_splits == 1) a.k_per = k_all;
   a.group_m = 8;
   const int last_k = k_all - (k_splits - 1) * a.k_per;          // the last share is the shortest
-  const int wgs = gt_workgroups(a.tiles_m * a.tiles_n * k_splits, gt_cus * G::PER_CU, (last_k < a.k_per ? last_k : a.k_per) / 64, NSW);
+  const int n_items = a.tiles_m * a.tiles_n * k_splits;
+  int wgs = gt_workgroups(n_items, gt_cus * G::PER_CU, (last_k < a.k_per ? last_k : a.k_per) / 64, NSW + WB - 1);
+  // weights in pairs of stages: an item begins with a pair, so it may follow another only behind an even number of stages
+  if (WB == 2 && n_items > wgs && (a.k_per / 64 % 2 || last_k / 64 % 2)) wgs = (n_items + 7) / 8 * 8;
+  if (EPI == LG_ROPE_ODD && n_items > wgs) return hipErrorInvalidValue;   // its epilogue takes the ring's place
   if constexpr (WM == 2 && GT_HALF<EPI, TM, TN>) {
     if (a.K != k_all) {
-      k_gemm_tile<EPI, TM, TN, NSA, NSW, true><<<wgs, 256, G::LDS, s>>>(a);
+      k_gemm_tile<EPI, TM, TN, NSA, NSW, true, WM, WB><<<wgs, 256, G::LDS, s>>>(a);
       return hipGetLastError();
     }
   }
   if (a.K != k_all) return hipErrorInvalidValue;
-  k_gemm_tile<EPI, TM, TN, NSA, NSW, false, WM><<<wgs, 256, G::LDS, s>>>(a);
+  k_gemm_tile<EPI, TM, TN, NSA, NSW, false, WM, WB><<<wgs, 256, G::LDS, s>>>(a);
   return hipGetLastError();
 }
 
@@ -1058,7 +1259,7 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
       case GT_256x256: return gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, f.splits);
       case GT_128x256: return gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, f.splits, f.n_tn * 256);
       case GT_256x224: return gt_launch<LG_RESID, 2, 7, 2, 3, 4>(s, a, f.splits);
-      case GT_128x128: return gt_launch<LG_RESID, 2, 2, 4, 5>(s, a, f.splits, f.n_tn * 256);
+      case GT_128x128: return gt_launch<LG_RESID, 2, 2, 4, 5, 2, 2>(s, a, f.splits, f.n_tn * 256);
       default: return gt_launch<LG_RESID, 2, 1, 3, 4>(s, a, f.splits);
     }
   }
@@ -1108,18 +1309,11 @@ static bool qkv_rope_usable(const dllm_ctx* c, int M) {
   const dllm_config& f = c->cfg;
   return gt_usable(M, f.d_model) && f.d_model % 64 == 0 && (f.n_q_heads * f.head_dim) % 128 == 0 && (f.n_kv_heads * f.head_dim) % 128 == 0;
 }
-// Taken unless the split product and the rotary kernel behind it are quicker by the estimate (the rotary kernel: about
-// 10 us and its operands at 2.5 TB/s).  Measured, product + rotary
-// kernel against this one (us): 15348 rows x 4608 x 3584: 464 + 278 / 513; 1184 x 12288 x 4096: 107 + 38 / 128; 1024 x
-// 4608 x 3584: 42 + 21 / 61; 211 x 12288 x 4096: 43 + 13 / 48; 128 rows there: 33 + 15 / 52 (96 workgroups), not taken.
 bool gemm_qkv_rope_wins(const dllm_ctx* c, int M) {
   if (!qkv_rope_usable(c, M)) return false;
   const dllm_config& f = c->cfg;
-  const int dq = f.n_q_heads * f.head_dim, dkv = f.n_kv_heads * f.head_dim, nw = dq + 2 * dkv, K = f.d_model;
-  const bool w256 = dq % 256 == 0 && dkv % 256 == 0;
-  const GtPlan fused = gt_plan(gt_cus, M, nw, K, 1, (w256 && f.head_dim == 128 ? 0x1u : 0u) | 0x4u, 0.0);
-  const GtPlan split = gt_plan(gt_cus, M, nw, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1, (w256 ? 0x3u : 0u) | 0xcu, 0.0);
-  return fused.us <= split.us + 10.0 + (4.0 * split.splits + 2.0) * M * (double)nw / 2.5e6;
+  const int dq = f.n_q_heads * f.head_dim, dkv = f.n_kv_heads * f.head_dim, K = f.d_model;
+  return gt_qkv_fused(gt_cus, M, dq, dkv, f.head_dim, K, M <= c->map.lg_delta_rows ? LG_QKV_SPLITS : 1);
 }
 hipError_t launch_gemm_qkv_rope(dllm_ctx* c, hipStream_t s, const void* A, const void* Wq, const void* Wk, const void* Wv,
                                 int M, const KVView& pool, const KVView* pack) {
@@ -1136,8 +1330,16 @@ hipError_t launch_gemm_qkv_rope(dllm_ctx* c, hipStream_t s, const void* A, const
   a.loc = WSM(c, kv_loc, int4);
   a.pool_k = (bf16_t*)pool.k; a.pool_v = (bf16_t*)pool.v; a.page_tokens = pool.page_tokens;
   if (pack) { a.pack_k = (bf16_t*)pack->k; a.pack_v = (bf16_t*)pack->v; a.tpad = pack->tpad; }
-  const bool dh64 = f.head_dim == 64, w256 = dq % 256 == 0 && dkv % 256 == 0 && !dh64;
-  const GtPlan p = gt_plan(gt_cus, M, dq + 2 * dkv, K, 1, (w256 ? 0x1u : 0u) | 0x4u, 0.0);
+  a.dh = f.head_dim;
+  const bool dh64 = f.head_dim == 64;
+  const GtPlan p = gt_rope_plan(gt_cus, M, dq, dkv, f.head_dim, K);
+  switch (p.tile) {
+    case GT_128x96: return gt_launch<LG_ROPE_ODD, 1, 3, 4, 6, 4, 2>(s, a);
+    case GT_128x160: return gt_launch<LG_ROPE_ODD, 1, 5, 4, 4, 4>(s, a);
+    case GT_256x96: return gt_launch<LG_ROPE_ODD, 2, 3, 3, 4, 4, 2>(s, a);
+    case GT_256x160: return gt_launch<LG_ROPE_ODD, 2, 5, 3, 3, 4>(s, a);
+    default: break;
+  }
   if (p.tile == GT_256x256) return gt_launch<LG_ROPE128, 4, 4, 2, 3>(s, a);
   // one tile per CU: the deep ring; more: two workgroups per CU
   if (((M + 127) / 128) * ((dq + 2 * dkv) / 128) <= gt_cus)
@@ -1164,9 +1366,9 @@ static hipError_t gt_launch_swiglu(hipStream_t s, const LgArgs& a, GtTile tile, 
   switch (tile) {
     case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, f_first);
     case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a, 1, f_first);
-    case GT_128x96: return gt_launch<LG_SWIGLU, 1, 3, 5, 5, 4>(s, a, 1, f_first);
+    case GT_128x96: return gt_launch<LG_SWIGLU, 1, 3, 4, 5, 4, 2>(s, a, 1, f_first);
     case GT_128x160: return gt_launch<LG_SWIGLU, 1, 5, 4, 4, 4>(s, a, 1, f_first);
-    case GT_256x96: return gt_launch<LG_SWIGLU, 2, 3, 3, 3, 4>(s, a, 1, f_first);
+    case GT_256x96: return gt_launch<LG_SWIGLU, 2, 3, 3, 4, 4, 2>(s, a, 1, f_first);
     case GT_256x160: return gt_launch<LG_SWIGLU, 2, 5, 3, 3, 4>(s, a, 1, f_first);
     default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a, 1, f_first);
   }

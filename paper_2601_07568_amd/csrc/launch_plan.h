@@ -191,4 +191,30 @@ inline GtForm gt_swiglu_form(int cus, int M, int F, int K, bool starts_apart) {
   return gt_form(cus, M, 2 * F, K, p, GT_REST_TILES | (starts_apart ? 0u : GT_ODD_TILES));
 }
 
+// q/k/v with the rotary embedding and the K/V write in its epilogue.  Odd tiles only as one round: their epilogue needs the copies'
+// ring, so a workgroup has one tile.  us a stage and beside the stages, from 256 x 12288 x 4096 and 1024 x 4608 x 3584 (128 x 128 tiles / these: 48.3 / 42.7
+// and 66.9 / 52.7).
+inline GtPlan gt_rope_plan(int cus, int M, int dq, int dkv, int dh, int K) {
+  const int nw = dq + 2 * dkv;
+  GtPlan best = gt_plan(cus, M, nw, K, 1, (dq % 256 == 0 && dkv % 256 == 0 && dh == 128 ? 0x1u : 0u) | 0x4u, 0.0);
+  static const struct { GtTile t; int bm, bn; double stage, rest; } odd[4] = {
+      {GT_128x96, 128, 96, 0.53, 9.0}, {GT_128x160, 128, 160, 0.75, 10.0}, {GT_256x96, 256, 96, 0.84, 10.0}, {GT_256x160, 256, 160, 1.09, 11.0}};
+  for (const auto& o : odd) {
+    if ((M + o.bm - 1) / o.bm * ((nw + o.bn - 1) / o.bn) > cus) continue;
+    const double us = o.stage * (K / 64) + o.rest;
+    if (us < best.us) best = GtPlan{o.t, 1, K, us};
+  }
+  return best;
+}
+
+// ... taken unless the split product and the rotary kernel behind it are quicker by the estimate (the rotary kernel: about 10 us
+// and its operands at 2.5 TB/s).  Measured, product + rotary kernel against the fused one (us): 15348 rows x 4608 x 3584: 464 +
+// 278 / 513; 1184 x 12288 x 4096: 107 + 38 / 128; 1024 x 4608 x 3584: 42 + 21 / 53; 211 x 12288 x 4096: 43 + 13 / 41.
+inline bool gt_qkv_fused(int cus, int M, int dq, int dkv, int dh, int K, int max_splits) {
+  const int nw = dq + 2 * dkv;
+  const GtPlan fused = gt_rope_plan(cus, M, dq, dkv, dh, K);
+  const GtPlan split = gt_plan(cus, M, nw, K, max_splits, (dq % 256 == 0 && dkv % 256 == 0 ? 0x3u : 0u) | 0xcu, 0.0);
+  return fused.us <= split.us + 10.0 + (4.0 * split.splits + 2.0) * M * (double)nw / 2.5e6;
+}
+
 }  // namespace dllm

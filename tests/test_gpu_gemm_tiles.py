@@ -246,6 +246,30 @@ def test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt):
     eng.close()
 
 
+# q/k/v in tiles of 96 and 160 weight rows: (d, query heads, key heads, head width, prompts, cached of each, page, form).  Tiles lie
+# across the ends of q and k and end behind v; rows end inside a tile; runs of eight tokens end at a page's or a prompt's end.
+ODD_ROPE = [
+    (1792, 48, 8, 64, [129, 70, 31], [129, 64, 0], 24, "128x96"),
+    (1024, 64, 4, 64, [500, 3, 300, 190], [499, 3, 296, 150], 32, "128x160"),
+    (640, 72, 8, 128, [257, 143], [257, 100], 24, "256x96"),
+    (960, 72, 8, 128, [400, 299], [399, 299], 64, "256x160"),
+]
+
+
+@pytest.mark.parametrize("d,hq,hkv,dh,lens,n_cache,pt,form", ODD_ROPE, ids=[f[-1] for f in ODD_ROPE])
+def test_keys_and_values_written_from_odd_tiles(d, hq, hkv, dh, lens, n_cache, pt, form):
+    ms = synth.ModelShape(1, d, hq, hkv, dh, 256, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"odd-rope-{form}")
+    test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt)
+
+
+@pytest.mark.parametrize("i,seqs,Q", [(0, 3, 77), (0, 2, 115), (2, 4, 100)], ids=["128x96", "128x96-one-tile-nearly-empty", "256x96"])
+def test_steps_on_odd_rope_tiles(i, seqs, Q):
+    """Denoise steps on the same tiles: every row of q, and the rows' keys and values through the attention."""
+    d, hq, hkv, dh = ODD_ROPE[i][:4]
+    ms = synth.ModelShape(1, d, hq, hkv, dh, 256, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"odd-rope-step-{i}")
+    run(ms, [9 + 30 * b for b in range(seqs)], Q, head=False)
+
+
 @pytest.mark.parametrize("ms,lens,Q,n_masked", [(EDGE, [80], 32, 1), (EDGE, [75, 90], 32, 17), (LONG, [70], 64, 64)],
                          ids=["one-row", "seventeen-rows-k-576", "sixty-four-rows"])
 def test_few_head_rows_behind_a_forward_of_many(ms, lens, Q, n_masked):
@@ -363,4 +387,6 @@ FORMS = ([("gate-up", b * q, ff, d, form) for d, ff, (b, q), form in ODD_TILES +
          [("resid", b * q, d, heads * 64, o) for d, heads, ff, (b, q), o, down in RESID_224] +
          [("resid", b * q, d, ff, down) for d, heads, ff, (b, q), o, down in RESID_224] +
          [("gate-up", 8 * 127, 8512, 768, "64+128x128"), ("resid", 83 * 99, 2048, 768, "7+128x128"),
-          ("gate-up", 8 * 127, 8544, 800, "64+128x128")] + KEPT)
+          ("gate-up", 8 * 127, 8544, 800, "64+128x128")] + KEPT +
+         [(f"qkv:{hq}:{hkv}:{dh}", sum(lens), 0, d, form) for d, hq, hkv, dh, lens, n_cache, pt, form in ODD_ROPE] +
+         [("qkv:48:8:64", 231, 0, 1792, "128x96"), ("qkv:48:8:64", 230, 0, 1792, "128x96"), ("qkv:72:8:128", 400, 0, 640, "256x96")])
