@@ -72,7 +72,8 @@ static int ring_errors(int ring, int nsw, int stages, int n_items, int slots, in
 }
 
 // The attention launch over sizes: what it asks for fits, and the staged kernel takes every call of at least four row groups
-// over pages that are a power of two of at least 8 tokens, however long its sequences, as long as the partials of enough units
+// over pages that are a power of two of at least 8 tokens (but for short ones of few sequences with grouped queries), however long its
+// sequences, as long as the partials of enough units
 // have room.  Returns the number of plans that break this.
 static int attn_plan_errors() {
   using namespace dllm;
@@ -89,12 +90,15 @@ static int attn_plan_errors() {
               const int T = Q > 0 ? B * Q : B * kv;
               int64_t rows = (int64_t)T * h[0] * 8;           // (the workspace holds eight units, and 65536 rows at least)
               if (rows < 65536) rows = 65536;
-              const AttnPlan p = attn_plan(dh, h[0], h[1], B, Q, T, kv, pt, rows, true);
+              const AttnPlan p = attn_plan(256, dh, h[0], h[1], B, Q, T, kv, pt, rows, true);
               const int groups = ((Q > 0 ? Q : kv) * (h[0] / h[1]) + 31) / 32;
+              // (steps with grouped queries and at most a workgroup per CU may take the register kernel)
+              const bool few = Q > 0 && h[0] > h[1] && groups > 4 && (int64_t)B * h[1] * groups <= 256;
               const int blocks = (kv + 63) / 64, per_unit = (blocks + p.units - 1) / p.units;
-              const bool ok = p.units >= 1 && p.units <= ATTN_MAX_SPLITS && p.units % p.kspl == 0 &&
+              const bool ok = p.units >= 1 && p.units / p.kspl <= ATTN_MAX_SPLITS && p.units % p.kspl == 0 &&
                               (p.units == p.kspl || (int64_t)(p.units / p.kspl) * T * h[0] <= rows) &&
-                              p.lds <= (size_t)DL_LDS_MAX && p.n_rg_wg * p.n_chunks >= groups && p.staged == (groups >= 4) &&
+                              p.lds <= (size_t)DL_LDS_MAX && p.n_rg_wg * p.n_chunks >= groups && (p.staged ? groups >= 4 : groups < 4 || few) &&
+                              (p.staged || (p.n_rg_wg * p.kspl <= 4 && (p.kspl == 1 || p.n_rg_wg == 1))) &&
                               (!p.staged || Q == 0 || (p.pg_cap >= per_unit * (pt < 64 ? 64 / pt : 1) &&
                                                        p.lds >= (size_t)DL_NB * dh * 256 + 4 * (size_t)p.pg_cap));
               if (!ok && errors++ < 5) printf("attention plan: heads %d/%d x %d, B %d, Q %d, %d keys, pages of %d\n", h[0], h[1], dh, B, Q, kv, pt);

@@ -174,6 +174,25 @@ __global__ __launch_bounds__(256, WPS) void k_attn_step(const AttnArgs a) {
       }
     }
   };
+  // pages that are multiples of 32 tokens: a block lies inside one, so all lanes share the page and the slot of the block's
+  // first key (a division per block instead of three per lane and block)
+  auto issue_in_page = [&](int kb, int page, Blk& blk) {
+    const int k0 = kb << 5, slot0 = k0 - k0 / pt * pt, left = kv_len - 1 - k0;
+    const bool ok = (uint32_t)page < (uint32_t)kv.n_pages;
+    bad |= !ok;
+    blk.pbad = !ok;
+    const int64_t ph = (int64_t)(ok ? page : 0) * kv.n_kv_heads + kvh;
+    const bf16_t* kp = kslab + (ph * pt + slot0) * DH + g * 8;
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt) {
+      const int off = 8 * (c >> 2) + (c & 3) + 4 * tt;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) blk.kf[tt][kk] = *(const u32x4*)(kp + (off < left ? off : left) * DH + kk * 32);
+    }
+    const bf16_t* vp = vslab + (ph * DH + c) * pt + slot0 + (8 * g <= left ? 8 * g : left & ~7);
+#pragma unroll
+    for (int d = 0; d < DT; ++d) blk.vf[d] = *(const u32x4*)(vp + (int64_t)d * 16 * pt);
+  };
   auto issue = [&](int kb, const int (&pg)[3], Blk& blk) {
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
@@ -253,23 +272,20 @@ __global__ __launch_bounds__(256, WPS) void k_attn_step(const AttnArgs a) {
     // wave's first two blocks are requested before the sequence length is known (the table row has max_pages
     // entries whatever the length), one memory round trip less in front of the K/V loads; later pairs' ids are
     // requested a pair ahead.
-    auto block_page = [&](int kb, int (&pg)[3]) {
+    auto block_page = [&](int kb) -> int {
       const int pi = (kb << 5) / pt;
       const int v = table[pi < kv.max_pages ? pi : kv.max_pages - 1];
-      pg[0] = pg[1] = pg[2] = pi < kv.max_pages ? v : -1;
+      return pi < kv.max_pages ? v : -1;
     };
-    int pga[3], pgb[3];
-    block_page(unit, pga);
-    block_page(unit + a.n_units, pgb);
+    int pga = block_page(unit), pgb = block_page(unit + a.n_units);
     for (int kb = unit; kb < nkb; kb += 2 * a.n_units) {
       const int kb2 = kb + a.n_units;
       const bool two = kb2 < nkb;
       Blk ba, bb;
-      issue(kb, pga, ba);
-      if (two) issue(kb2, pgb, bb);
-      else issue(kb, pga, bb);                    // a repeat of the first block's loads: no branch around a load
-      block_page(kb + 2 * a.n_units, pga);
-      block_page(kb2 + 2 * a.n_units, pgb);
+      issue_in_page(kb, pga, ba);
+      issue_in_page(two ? kb2 : kb, two ? pgb : pga, bb);   // (a repeat of the first block's loads: no branch around a load)
+      pga = block_page(kb + 2 * a.n_units);
+      pgb = block_page(kb2 + 2 * a.n_units);
       compute(kb, ba);
       if (two) compute(kb2, bb);
     }
@@ -925,7 +941,7 @@ hipError_t init_attn_kernels() {
 
 hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const KVView& kv, bool frag_out) {
   const dllm_config& f = c->cfg;
-  const AttnPlan p = attn_plan(f.head_dim, f.n_q_heads, f.n_kv_heads, g.B, g.Q, g.T, g.max_kv, f.page_tokens, c->map.attn_rows, attn_merge_ready);
+  const AttnPlan p = attn_plan(device_cus(), f.head_dim, f.n_q_heads, f.n_kv_heads, g.B, g.Q, g.T, g.max_kv, f.page_tokens, c->map.attn_rows, attn_merge_ready);
   constexpr int QT = 2;
   AttnArgs a;
   a.q = WSM(c, q, bf16_t);

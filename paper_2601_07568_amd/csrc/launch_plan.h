@@ -20,7 +20,7 @@ struct AttnPlan {
 };
 // Q: query rows of a sequence, 0: no-cache forward (max_kv: the longest sequence); T: rows of the call; part_rows: (token,
 // head, unit) rows that the buffer of partial results holds; raised: the kernels may use more LDS than by default
-inline AttnPlan attn_plan(int head_dim, int n_q_heads, int n_kv_heads, int B, int Q, int T, int max_kv, int page_tokens,
+inline AttnPlan attn_plan(int cus, int head_dim, int n_q_heads, int n_kv_heads, int B, int Q, int T, int max_kv, int page_tokens,
                           int64_t part_rows, bool raised) {
   AttnPlan p{};
   const int G = n_q_heads / n_kv_heads;
@@ -40,10 +40,43 @@ inline AttnPlan attn_plan(int head_dim, int n_q_heads, int n_kv_heads, int B, in
   const int64_t ids_fit = (int64_t)(DL_LDS_MAX - ring) / sizeof(int32_t);
   const int64_t least = ids_blk > 0 ? (n_blk + ids_fit / ids_blk - 1) / (ids_fit / ids_blk) : 1;
   p.staged = n_rg >= 4 && p.pt_shift >= 0 && raised && least <= most;
+  const int nkb = (max_kv + 31) / 32;
+  // Denoise steps whose row groups leave the CUs room: a workgroup per row group (they meet in the L2), and as many along the keys
+  // as fill one round, each on a CU of its own, whose 32 KB of outstanding loads set the pace.  One wave alone up to eight blocks
+  // each, or where the row groups fill the chip twice; else four waves, which merge their results in LDS (3 us).  One round and no
+  // combine kernel where there are many sequences.  (All row groups of a key head in one workgroup, units of two blocks in up to
+  // 512 workgroups / this, attention + combine, us, 32 key heads: one sequence of 512 keys 14.7 / 10.6, 1024 15.8 / 13.4, 4096 30.0 /
+  // 25.5; 8 of 100 / 400 / 700 keys 18.3 / 11.8, 26.1 / 20.5, 33.7 / 25.3; 16 of 2048 118 / 96; 32 of 64 / 250 39.3 / 19.7, 44.9 / 34.9; 64
+  // rows: one of 1237 23.0 / 20.6, of 5000 56.2 / 37.8, 4 of 1500 55.4 / 39.9, 8 of 1500 86.3 / 66.3.  Not where a second round would
+  // hold a few workgroups of long sequences: 3 sequences of 2500 keys and 80 rows 78.9 / 90.4.)
+  const int64_t groups = (int64_t)B * n_kv_heads * n_rg;
+  const bool few_groups = groups <= cus || groups >= 2 * cus - cus / 4 || nkb <= 32;
+  int64_t parts = cus / groups < 1 ? 1 : cus / groups;
+  if (parts > (nkb + 1) / 2) parts = (nkb + 1) / 2;
+  if (parts >= 8) parts = parts / 8 * 8;                       // row groups of the same keys behind the same L2
+  if (parts > most) parts = most;
+  // Grouped queries: the staged kernel where a wave would have more than six blocks (4 key heads of 7, 32 rows, staged / this: one
+  // sequence of 600 keys 16.5 / 14.6, 2048 21.0 / 16.0, 4000 24.5 / 19.8, 8000 26.6 / 31.2; 2 of 1000 21.4 / 17.6, of 4000 27.3 / 27.9; 64
+  // rows, 2048 keys 25.7 / 21.0), and always for up to four row groups (16 rows 15.9 / 15.8; 128 rows of a model with as many
+  // key heads as heads 21.8 / 23.1, 39.6 / 43.4).
+  if (p.staged && Q > 0 && G > 1 && n_rg > 4 && groups <= cus && nkb <= 24 * parts) p.staged = false;
+  if (!p.staged && Q > 0 && raised && few_groups) {
+    // (seven or eight blocks in all: 4 sequences of 200 keys as two single waves 12.4, as four waves of one workgroup 11.7; pages
+    // that are no multiple of 32 tokens have longer chains per block: one sequence of 1000 keys in pages of 24 16.3 / 15.2)
+    const bool narrow = groups < 2 * cus - cus / 4;
+    const bool merge = narrow && parts <= 2 && (nkb == 7 || nkb == 8);
+    if (merge) parts = 1;
+    const int64_t per_wave = (nkb + parts - 1) / parts;
+    p.kspl = merge || (narrow && per_wave > (page_tokens % 32 == 0 ? 8 : 4)) ? 4 : 1;
+    p.n_rg_wg = 1;
+    p.n_chunks = n_rg;
+    p.units = (int)(parts * p.kspl);
+    if (p.kspl > 1) p.lds = (size_t)p.kspl * (2 * QT * 16 * sizeof(float) + (size_t)(head_dim / 16) * QT * 64 * 16);
+    return p;
+  }
   const int rg_cap = p.staged ? 8 : 4;                         // the register-direct kernel runs at most 4 waves
   p.n_rg_wg = n_rg < rg_cap ? n_rg : rg_cap;
   p.n_chunks = (n_rg + p.n_rg_wg - 1) / p.n_rg_wg;
-  const int nkb = (max_kv + 31) / 32;
   // units along the keys: short dependent chains matter more than partial traffic here (a step's
   // attention is a few MB), so give every unit about two 32-key blocks, within the partial buffer
   int64_t want = 2048 / ((int64_t)B * n_kv_heads * n_rg);
