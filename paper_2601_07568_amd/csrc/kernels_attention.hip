@@ -401,7 +401,7 @@ __global__ __launch_bounds__(512) void k_attn_combine(const float* part_o, const
       const float s0 = exp2f(ml.x - Mn), s1 = exp2f(ml.z - Mn);
       den = fmaf(ml.w, s1, ml.y * s0);
       num = fmaf(o1, s1, o0 * s0);
-    }
+    } else den = ml.y + ml.w;                           // empty units (0), or none but scores that are NaN (NaN)
   } else
   for (int u0 = 0; u0 < n_units; u0 += 8) {
     float mu[8], lu[8], ou[8];
@@ -417,7 +417,11 @@ __global__ __launch_bounds__(512) void k_attn_combine(const float* part_o, const
     float Mn = M;
 #pragma unroll
     for (int i = 0; i < 8; ++i) Mn = fmaxf(Mn, mu[i]);
-    if (Mn == -DEV_INF) continue;                       // nothing but empty units so far
+    if (Mn == -DEV_INF) {                               // nothing but empty units so far, or scores that are NaN
+#pragma unroll
+      for (int i = 0; i < 8; ++i) den += lu[i];
+      continue;
+    }
     const float r = exp2f(M - Mn);                      // exp2(-inf) = 0 on the first chunk
     num *= r;
     den *= r;
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(512) void k_attn_combine(const float* part_o, const
   }
   const int tok = (int)(row / Hq), head = (int)(row - (int64_t)tok * Hq);
   const int64_t at = mt > 0 ? frag_offset(tok, head * DH + d, mt) : row * DH + d;
-  o[at] = f32_to_bf16(den > 0.f ? num / den : 0.f);
+  o[at] = f32_to_bf16(den == 0.f ? 0.f : num / den);     // (NaN stays NaN: a key that is not finite shows in every row that sees it)
 }
 
 // ------------------------------------------------------------------------------------------

@@ -89,3 +89,61 @@ def test_more_page_ids_than_a_workgroup_keeps(B):
         assert err <= H.logit_tol("bf16", 1, "store"), (b, err)
     assert eng.read_status() == 0
     eng.close()
+
+
+def _many(lens, n):
+    return [lens[b % len(lens)] for b in range(n)]
+
+
+# (shape, rows, page, prefixes): a workgroup per row group, keys in parts of single waves and of four that merge, with one part and
+# several, and a part that a short sequence leaves empty; grouped queries with room for a workgroup per row group; and, with more
+# row groups than CUs, the staged kernel for seven to ten of them
+FORMS = {
+    "one-wave-64-parts": ("g1-128", 32, 64, [5000]),
+    "four-waves-8-parts": ("g1-64", 32, 64, [3000, 64, 700, 33, 2000, 0, 1500, 31]),
+    "four-waves-8-parts-page-24": ("g1-64", 32, 24, [3000, 64, 700, 33, 2000, 0, 1500, 31]),
+    "four-waves-1-part": ("g1-128", 32, 32, _many([200, 224, 0, 150, 31], 72)),
+    "one-wave-1-part": ("g1-128", 32, 32, _many([300, 31, 100], 230)),
+    "two-row-groups": ("g1-128", 64, 64, [1237, 5, 64]),
+    "two-row-groups-48": ("g1-128", 48, 96, [4000, 77]),
+    "three-row-groups": ("g1-64", 72, 128, [2500, 600, 9]),
+    "grouped-one-sequence": ("g7-128", 32, 64, [2048]),
+    "grouped-7500-keys": ("g7-64", 32, 64, [24000]),
+    "staged-7": ("g7-128", 32, 8, _many([480, 31, 33, 1500, 0], 40)),
+    "staged-7-64": ("g7-64", 32, 64, _many([480, 31, 33, 1500, 0], 40)),
+    "staged-8": ("g4-128", 64, 16, _many([63, 65, 700, 0], 17)),
+    "staged-10": ("g8-64", 40, 8, _many([23, 24, 88, 300], 30)),
+}
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_forms_of_the_launch(form, monkeypatch):
+    name, Q, pt, lens = FORMS[form]
+    monkeypatch.setitem(LENS, Q, lens)
+    test_key_block_edges_growing_scores_and_nan_slots(name, Q, pt, 20.0)
+
+
+@pytest.mark.parametrize("n", [70, 130, 500, 3000, 9000])
+@pytest.mark.parametrize("where", ["first", "last"])
+def test_a_key_that_is_not_a_number_shows_in_every_row_of_its_sequence(n, where):
+    """One NaN among the cached keys of the second of two sequences, in two, three, eight and more parts along the keys: all of that
+    sequence's rows become NaN, the other's stay as they are, bit for bit."""
+    ms, Q, pt = SHAPES["g1-128"], 32, 32
+    w = synth.Weights(ms, 5)
+    mp = (n + Q + pt - 1) // pt
+    out = []
+    for poison in (False, True):
+        eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=2 * mp, max_batch=2, max_q=Q, max_tokens=0)
+        gen = torch.Generator(device=eng.device)
+        gen.manual_seed(3)
+        eng.kv_pool.view(torch.bfloat16)[:].normal_(generator=gen)
+        if poison:
+            at = 0 if where == "first" else n - 1
+            eng.kv_slab(0, 0)[mp + at // pt, 0, at % pt, 5] = float("nan")
+            eng.kv_slab(0, 0)[mp + at // pt, 1, at % pt, 5] = float("nan")
+        q = np.stack([synth.masked_block(ms, 40 + b, Q, Q // 2) for b in range(2)])
+        out.append(eng.debug_hidden(eng.i32(q), eng.i32([n, n]), eng.i32(H.identity_table(eng, 2)), 1, max_prefix_len=n).clone())
+        assert eng.read_status() == 0
+        eng.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.isfinite(out[0]).all()
+    assert torch.isnan(out[1][1]).all()
