@@ -1131,14 +1131,15 @@ static bool gt_ready = false;   // (the tiles: launch_plan.h)
 static int gt_cus = 256;
 #define GT_KERNELS(X)                                                                                   \
   X(LG_SWIGLU, 4, 4, 2, 3) X(LG_SWIGLU, 2, 4, 2, 3) X(LG_SWIGLU, 2, 2, 4, 5)                            \
-  X(LG_RESID, 4, 4, 2, 3) X(LG_RESID, 2, 4, 2, 3) X(LG_RESID, 2, 1, 3, 4)       \
+  X(LG_RESID, 4, 4, 2, 3) X(LG_RESID, 2, 4, 2, 3) X(LG_RESID, 2, 2, 4, 5) X(LG_RESID, 2, 1, 3, 4)       \
   X(LG_ROPE64, 2, 2, 4, 5) X(LG_ROPE64, 2, 2, 2, 3)                            \
   X(LG_ROPE128, 4, 4, 2, 3) X(LG_ROPE128, 2, 2, 4, 5) X(LG_ROPE128, 2, 2, 2, 3)                         \
   X(LG_QKV, 4, 4, 2, 3) X(LG_QKV, 2, 4, 2, 3) X(LG_QKV, 2, 2, 4, 5) X(LG_QKV, 2, 1, 3, 4)               \
   X(LG_LMSTATS, 4, 4, 2, 3) X(LG_LMSTATS_X, 4, 4, 2, 3) X(LG_LMSTATS_X, 2, 2, 4, 5)
 // gate/up in tiles of an odd number of 32 weight rows, all four waves along the token rows
-#define GT_ODD_KERNELS(X) X(LG_SWIGLU, 1, 3, 4, 5, 2) X(LG_SWIGLU, 1, 5, 4, 4, 1) X(LG_SWIGLU, 2, 3, 3, 4, 2) X(LG_SWIGLU, 2, 5, 3, 3, 1) \
-  X(LG_ROPE_ODD, 1, 3, 4, 6, 2) X(LG_ROPE_ODD, 1, 5, 4, 4, 1) X(LG_ROPE_ODD, 2, 3, 3, 4, 2) X(LG_ROPE_ODD, 2, 5, 3, 3, 1)
+#define GT_ODD_KERNELS(X) X(LG_SWIGLU, 1, 3, 5, 5, 1) X(LG_SWIGLU, 1, 3, 4, 6, 2) X(LG_SWIGLU, 1, 5, 4, 4, 1) X(LG_SWIGLU, 2, 3, 3, 3, 1) X(LG_SWIGLU, 2, 3, 3, 4, 2) \
+  X(LG_SWIGLU, 2, 5, 3, 3, 1) X(LG_ROPE_ODD, 1, 3, 5, 5, 1) X(LG_ROPE_ODD, 1, 3, 4, 6, 2) X(LG_ROPE_ODD, 1, 5, 4, 4, 1) X(LG_ROPE_ODD, 2, 3, 3, 3, 1) \
+  X(LG_ROPE_ODD, 2, 3, 3, 4, 2) X(LG_ROPE_ODD, 2, 5, 3, 3, 1)
 // the forms that are also built for K of 32 more than a multiple of 64
 template <int EPI, int TM, int TN>
 constexpr bool GT_HALF = (TM == TN || TN == 1) && EPI != LG_ROPE64 && EPI != LG_ROPE128 && EPI != LG_ROPE_ODD;
@@ -1205,6 +1206,17 @@ static hipError_t gt_launch(hipStream_t s, LgArgs a, int k_splits = 1, int n_fir
   return hipGetLastError();
 }
 
+// Weights in pairs of stages where the last row tile is at least half full.  With a nearly empty one the pairs lose what they gain
+// elsewhere: its workgroups run ahead and bring the weights in for the others (down 12288 -> 4096, us, one stage / two: 256 rows 39.3 /
+// 36.5, 400 rows 83.7 / 90.6, 900 rows 92.2 / 99.4, 1400 rows 217 / 198; gate/up 24576 x 4096 in 256 x 96: 300 rows 88.2 / 92.0, 500
+// rows 107.8 / 101.2; 128 x 96: 128 rows 42.6 / 40.5).
+template <int EPI, int TM, int TN, int WM, int NSA, int NSW, int NSA2, int NSW2>
+static hipError_t gt_launch_fill(hipStream_t s, const LgArgs& a, int k_splits = 1, int n_first = 0) {
+  constexpr int BM = 32 * WM * TM;
+  if ((a.M - 1) % BM + 1 >= BM / 2) return gt_launch<EPI, TM, TN, NSA2, NSW2, WM, 2>(s, a, k_splits, n_first);
+  return gt_launch<EPI, TM, TN, NSA, NSW, WM>(s, a, k_splits, n_first);
+}
+
 template <int EPI>
 static hipError_t lg_launch(hipStream_t s, LgArgs a, int k_splits = 1) {
   // 128-row tiles, two workgroups per CU (a 256-row form of this kernel, one workgroup per CU, measured
@@ -1259,7 +1271,7 @@ hipError_t launch_gemm_resid_split(dllm_ctx* c, hipStream_t s, const void* A, co
       case GT_256x256: return gt_launch<LG_RESID, 4, 4, 2, 3>(s, a, f.splits);
       case GT_128x256: return gt_launch<LG_RESID, 2, 4, 2, 3>(s, a, f.splits, f.n_tn * 256);
       case GT_256x224: return gt_launch<LG_RESID, 2, 7, 2, 3, 4>(s, a, f.splits);
-      case GT_128x128: return gt_launch<LG_RESID, 2, 2, 4, 5, 2, 2>(s, a, f.splits, f.n_tn * 256);
+      case GT_128x128: return gt_launch_fill<LG_RESID, 2, 2, 2, 4, 5, 4, 5>(s, a, f.splits, f.n_tn * 256);
       default: return gt_launch<LG_RESID, 2, 1, 3, 4>(s, a, f.splits);
     }
   }
@@ -1334,9 +1346,9 @@ hipError_t launch_gemm_qkv_rope(dllm_ctx* c, hipStream_t s, const void* A, const
   const bool dh64 = f.head_dim == 64;
   const GtPlan p = gt_rope_plan(gt_cus, M, dq, dkv, f.head_dim, K);
   switch (p.tile) {
-    case GT_128x96: return gt_launch<LG_ROPE_ODD, 1, 3, 4, 6, 4, 2>(s, a);
+    case GT_128x96: return gt_launch_fill<LG_ROPE_ODD, 1, 3, 4, 5, 5, 4, 6>(s, a);
     case GT_128x160: return gt_launch<LG_ROPE_ODD, 1, 5, 4, 4, 4>(s, a);
-    case GT_256x96: return gt_launch<LG_ROPE_ODD, 2, 3, 3, 4, 4, 2>(s, a);
+    case GT_256x96: return gt_launch_fill<LG_ROPE_ODD, 2, 3, 4, 3, 3, 3, 4>(s, a);
     case GT_256x160: return gt_launch<LG_ROPE_ODD, 2, 5, 3, 3, 4>(s, a);
     default: break;
   }
@@ -1366,9 +1378,9 @@ static hipError_t gt_launch_swiglu(hipStream_t s, const LgArgs& a, GtTile tile, 
   switch (tile) {
     case GT_256x256: return gt_launch<LG_SWIGLU, 4, 4, 2, 3>(s, a, 1, f_first);
     case GT_128x256: return gt_launch<LG_SWIGLU, 2, 4, 2, 3>(s, a, 1, f_first);
-    case GT_128x96: return gt_launch<LG_SWIGLU, 1, 3, 4, 5, 4, 2>(s, a, 1, f_first);
+    case GT_128x96: return gt_launch_fill<LG_SWIGLU, 1, 3, 4, 5, 5, 4, 6>(s, a, 1, f_first);
     case GT_128x160: return gt_launch<LG_SWIGLU, 1, 5, 4, 4, 4>(s, a, 1, f_first);
-    case GT_256x96: return gt_launch<LG_SWIGLU, 2, 3, 3, 4, 4, 2>(s, a, 1, f_first);
+    case GT_256x96: return gt_launch_fill<LG_SWIGLU, 2, 3, 4, 3, 3, 3, 4>(s, a, 1, f_first);
     case GT_256x160: return gt_launch<LG_SWIGLU, 2, 5, 3, 3, 4>(s, a, 1, f_first);
     default: return gt_launch<LG_SWIGLU, 2, 2, 4, 5>(s, a, 1, f_first);
   }
