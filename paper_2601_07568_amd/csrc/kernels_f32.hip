@@ -52,9 +52,9 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
   __shared__ float red[NW][NT][MT][4][64];
   __shared__ float rs[MT * 16];
   __shared__ float aux[EPI == S32_LMSTATS ? MT * 4 * 16 * 4 : (EPI == S32_RESID ? MT * 4 * 64 : 1)];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
-  const int wg = blockIdx.x, K = a.K, M = a.M;
+  const int wg = blockIdx.x, K = a.K, M = a.M, t0 = blockIdx.y * MT * 16;   // t0: the workgroup's first row
   if (EPI == S32_LMSTATS && a.n_lm_rows && *a.n_lm_rows <= 0) return;
 
   // the tiles' first weight rows
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
   }
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
-    int r = m * 16 + c; r = r < M ? r : M - 1;
+    int r = t0 + m * 16 + c; r = r < M ? r : M - 1;
     xp[m] = a.X + (int64_t)r * K + g * 4;
   }
   const float* gp = a.gain ? a.gain + g * 4 : nullptr;
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
   float xres = 0.f, pcs = 0.f, psn = 0.f;
   int ppos = -1, ppage = -1;
   {
-    const int m = tid >> 8, iq = (tid >> 6) & 3, tok = m * 16 + c;
+    const int m = tid >> 8, iq = (tid >> 6) & 3, tok = t0 + m * 16 + c;
     if (EPI == S32_RESID) {
       const int n = row0[0] + 4 * g + iq;
       xres = a.x[m < MT && tok < M && n < a.N0 ? (int64_t)tok * a.N0 + n : 0];
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
   if (a.ss_in) {
 #pragma unroll
     for (int q = 0; q < RPW; ++q) {
-      const int row = w * RPW + q < M ? w * RPW + q : M - 1;
+      const int row = t0 + w * RPW + q < M ? t0 + w * RPW + q : M - 1;
       const float v = a.ss_in[(int64_t)row * a.ss_stride + (lane < a.n_ss ? lane : a.n_ss - 1)];
       ssv[q] = lane < a.n_ss ? v : 0.f;
     }
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
 #pragma unroll
       for (int q = 0; q < RPW; ++q)
         for (int p = 64 + lane; p < a.n_ss; p += 64)
-          ssv[q] += a.ss_in[(int64_t)(w * RPW + q < M ? w * RPW + q : M - 1) * a.ss_stride + p];
+          ssv[q] += a.ss_in[(int64_t)(t0 + w * RPW + q < M ? t0 + w * RPW + q : M - 1) * a.ss_stride + p];
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1)
@@ -164,7 +164,8 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
     }
     if (first) { first = false; row_factors(); }
 #pragma unroll
-    for (int u = 0; u < UN; ++u)
+    for (int u = 0; u < UN; ++u) {
+      if (s0 + u * NW >= n_steps) break;                   // (a product of zeros takes as long as another)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -173,6 +174,7 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
 #pragma unroll
           for (int t = 0; t < NT; ++t) acc[t][m] = mfma4(fw[u][t][e], b, acc[t][m]);
         }
+    }
   }
   if (first) row_factors();                                // a wave without a step of its own still sums its rows
   // sum the waves' partial tiles in wave order
@@ -186,10 +188,10 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
 
   for (int item = tid; item < MT * 256; item += NW * 64) {
     const int m = item >> 8, i = (item >> 6) & 3, ln = item & 63;
-    const int tok = m * 16 + (ln & 15), fr = 4 * (ln >> 4) + i;     // row inside the 16-row tile
+    const int tok = t0 + m * 16 + (ln & 15), fr = 4 * (ln >> 4) + i;     // row inside the 16-row tile
     const bool tok_ok = tok < M;
     float val[NT];
-    const float rsc = a.ss_in ? rs[tok] : 1.0f;
+    const float rsc = a.ss_in ? rs[tok - t0] : 1.0f;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       float s = 0.f;
@@ -279,12 +281,12 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int lg = 0; lg < 4; ++lg) sq += aux[(m * 4 + i) * 64 + lg * 16 + cc];
-      a.ss_out[(int64_t)tid * a.ss_stride + wg] = sq;
+      a.ss_out[(int64_t)(t0 + tid) * a.ss_stride + wg] = sq;
     }
   }
   if constexpr (EPI == S32_LMSTATS) {
     __syncthreads();
-    if (tid < MT * 16 && tid < M) {
+    if (tid < MT * 16 && t0 + tid < M) {
       const int m = tid >> 4, cc = tid & 15;
       RowStat st;
       st.init();
@@ -293,13 +295,22 @@ __global__ __launch_bounds__(S32_NW * 64) void k_s32(const S32Args a) {
         const float* p = aux + ((m * 4 + i) * 16 + cc) * 4;
         st.merge(p[0], __float_as_int(p[1]), p[2], p[3]);
       }
-      *(f32x4*)(a.part + ((int64_t)tid * a.n_parts + wg) * 4) = f32x4{st.m, __int_as_float(st.idx), st.s, st.t};
+      *(f32x4*)(a.part + ((int64_t)(t0 + tid) * a.n_parts + wg) * 4) = f32x4{st.m, __int_as_float(st.idx), st.s, st.t};
     }
   }
 }
 
+// Where the weight tiles leave CUs idle every 16 rows get a workgroup of their own: a step of the 256-wide model is 64 weight
+// tiles at most, and their products, sums and epilogues are as long as their rows are many (the float products of a CU's matrix
+// cores run one after the other: 64 x 32 outputs of K = 256 take 1.7 us).  32 rows, together / apart, us: residual 6.3 / 4.5, gate/up
+// 8.7 / 6.2, q/k/v 8.4 / 7.7, LM head 10.9 / 8.6.
 template <int NT, int EPI>
 static hipError_t s32_launch(hipStream_t s, const S32Args& a, int grid) {
+  const int row_tiles = (a.M + 15) / 16;
+  if (row_tiles > 1 && grid * row_tiles <= device_cus()) {
+    k_s32<NT, 1, EPI><<<dim3(grid, row_tiles), S32_NW * 64, 0, s>>>(a);
+    return hipGetLastError();
+  }
   switch ((a.M + 15) / 16) {
     case 1: k_s32<NT, 1, EPI><<<grid, S32_NW * 64, 0, s>>>(a); break;
     case 2: k_s32<NT, 2, EPI><<<grid, S32_NW * 64, 0, s>>>(a); break;
