@@ -501,8 +501,13 @@ static int run_forward_inner(dllm_ctx* c, hipStream_t s, const StepGeom& g, int 
     }
   }
   if (hidden_out) {
-    if (pending) { TRY(launch_fold_delta(c, s, T, pending, false), "fold_delta"); pending = 0; }
-    TRY(launch_copy_f32(s, WSP(c, x, float), hidden_out, (size_t)T * f.d_model), "copy_hidden");
+    // (nothing reads the residual stream behind it: a call has one output)
+    if (pending && ((uintptr_t)hidden_out & 15) == 0) TRY(launch_fold_delta(c, s, T, pending, hidden_out), "fold_delta");
+    else {
+      if (pending) TRY(launch_fold_delta(c, s, T, pending, WSP(c, x, float)), "fold_delta");
+      TRY(launch_copy_f32(s, WSP(c, x, float), hidden_out, (size_t)T * f.d_model), "copy_hidden");
+    }
+    pending = 0;
   }
   if (logits_out) {
     if (sk) {

@@ -303,7 +303,7 @@ hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g);
 // keep_mean (at most 64 rows, d_model as sk_head_supported allows it): also leave the rows' mean squares in ws.ss
 hipError_t launch_rmsnorm(dllm_ctx* c, hipStream_t s, const void* gain, int T, const int32_t* rows,
                           const int32_t* n_rows_dev, int frag_mt, int n_delta, bool keep_mean = false);
-hipError_t launch_fold_delta(dllm_ctx* c, hipStream_t s, int T, int n_delta, bool frag_path);
+hipError_t launch_fold_delta(dllm_ctx* c, hipStream_t s, int T, int n_delta, float* out);
 constexpr int LG_QKV_SPLITS = 3;       // large path: most K splits of the fused q/k/v product
 constexpr int LG_MAX_DELTA = 3;        // large path: a residual projection is split over K at most 4 ways
 constexpr int LG_DELTA_ROWS = 2048;    // ... and only when the token count leaves the chip underfilled

@@ -381,6 +381,30 @@ __global__ __launch_bounds__(256, WPS) void k_attn_step(const AttnArgs a) {
   if (bad) atomicOr(a.status, DLLM_STATUS_BAD_PAGE);
 }
 
+// The merge of two partial results a row, for many rows: four channels a lane (a lane per channel, 28672 rows of 128: 7168
+// workgroups of a few loads each, 13.4 us, 8.5 so).
+template <int DH>
+__global__ __launch_bounds__(256) void k_attn_combine2(const float* part_o, const float* part_ml, bf16_t* o, int Hq, int mt, int64_t n_rows) {
+  constexpr int LR = DH / 4;                            // lanes of a row
+  const int64_t row = (int64_t)blockIdx.x * (256 / LR) + threadIdx.x / LR;
+  if (row >= n_rows) return;
+  const int d = threadIdx.x % LR * 4;
+  const float4 ml = *(const float4*)(part_ml + row * 4);               // (m0, l0, m1, l1)
+  const f32x4 o0 = *(const f32x4*)(part_o + row * 2 * DH + d), o1 = *(const f32x4*)(part_o + (row * 2 + 1) * DH + d);
+  const float Mn = fmaxf(ml.x, ml.z);
+  float s0 = 0.f, s1 = 0.f, den = ml.y + ml.w;          // two empty units: 0; none but scores that are NaN: NaN
+  if (Mn > -DEV_INF) {
+    s0 = exp2f(ml.x - Mn); s1 = exp2f(ml.z - Mn);
+    den = fmaf(ml.w, s1, ml.y * s0);
+  }
+  float v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = den == 0.f ? 0.f : (Mn > -DEV_INF ? fmaf(o1[i], s1, o0[i] * s0) : 0.f) / den;
+  const int tok = (int)(row / Hq), head = (int)(row - (int64_t)tok * Hq);
+  const int64_t at = mt > 0 ? frag_offset(tok, head * DH + d, mt) : row * DH + d;
+  *(uint2*)(o + at) = make_uint2((uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16), (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16));
+}
+
 // merges the units' partials of one (token, head) row and stores the normalised output
 // (fragment order of the [T, Hq*DH] matrix: it is the activation operand of the output projection)
 template <int DH>
@@ -985,6 +1009,11 @@ hipError_t launch_attn_step(dllm_ctx* c, hipStream_t s, const StepGeom& g, const
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_parts == 1) return e;
   const int rows = g.T * f.n_q_heads;
+  if (a.n_parts == 2 && rows >= 4096) {
+    if (f.head_dim == 128) k_attn_combine2<128><<<(rows + 7) / 8, 256, 0, s>>>(a.part_o, a.part_ml, a.o, f.n_q_heads, a.out_mt, rows);
+    else k_attn_combine2<64><<<(rows + 15) / 16, 256, 0, s>>>(a.part_o, a.part_ml, a.o, f.n_q_heads, a.out_mt, rows);
+    return hipGetLastError();
+  }
   if (f.head_dim == 128)
     k_attn_combine<128><<<(rows + 3) / 4, 512, 0, s>>>(a.part_o, a.part_ml, a.n_parts, a.o, f.n_q_heads, a.out_mt, rows);
   else

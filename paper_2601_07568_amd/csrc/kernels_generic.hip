@@ -950,18 +950,26 @@ hipError_t launch_rope_table(dllm_ctx* c, hipStream_t s, const StepGeom& g) {
   return hipGetLastError();
 }
 
-__global__ void k_fold_delta(int64_t n, float* x, const float* delta, int n_delta, int64_t delta_stride) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float v = x[i];
-  for (int sd = 0; sd < n_delta; ++sd) v += delta[sd * delta_stride + i];
-  x[i] = v;
+// out = x and the open K splits of the last residual projection, in split order.  d_model is a multiple of 4 where there are any.
+template <int ND>
+__global__ __launch_bounds__(256) void k_fold_delta(int64_t n4, const float4* x, const float4* delta, int64_t stride4, float4* out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  float4 v = x[i], dv[ND];
+#pragma unroll
+  for (int sd = 0; sd < ND; ++sd) dv[sd] = delta[sd * stride4 + i];
+#pragma unroll
+  for (int sd = 0; sd < ND; ++sd) { v.x += dv[sd].x; v.y += dv[sd].y; v.z += dv[sd].z; v.w += dv[sd].w; }
+  out[i] = v;
 }
 
-hipError_t launch_fold_delta(dllm_ctx* c, hipStream_t s, int T, int n_delta, bool frag_path) {
-  const int64_t n = (int64_t)T * c->cfg.d_model;
-  k_fold_delta<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, WS(c, x, float), WS(c, delta, float), n_delta,
-                                                          frag_path ? c->map.delta_stride : c->map.lg_delta_stride);
+hipError_t launch_fold_delta(dllm_ctx* c, hipStream_t s, int T, int n_delta, float* out) {
+  const int64_t n4 = (int64_t)T * c->cfg.d_model / 4, stride4 = c->map.lg_delta_stride / 4;
+  const float4 *x = WS(c, x, float4), *delta = WS(c, delta, float4);
+  const unsigned grid = (unsigned)((n4 + 255) / 256);
+  if (n_delta == 1) k_fold_delta<1><<<grid, 256, 0, s>>>(n4, x, delta, stride4, (float4*)out);
+  else if (n_delta == 2) k_fold_delta<2><<<grid, 256, 0, s>>>(n4, x, delta, stride4, (float4*)out);
+  else k_fold_delta<3><<<grid, 256, 0, s>>>(n4, x, delta, stride4, (float4*)out);
   return hipGetLastError();
 }
 

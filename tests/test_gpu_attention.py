@@ -113,6 +113,10 @@ FORMS = {
     "staged-7-64": ("g7-64", 32, 64, _many([480, 31, 33, 1500, 0], 40)),
     "staged-8": ("g4-128", 64, 16, _many([63, 65, 700, 0], 17)),
     "staged-10": ("g8-64", 40, 8, _many([23, 24, 88, 300], 30)),
+    # two parts of at least 4096 (token, head) rows
+    "two-parts-4096-rows": ("g1-128", 32, 32, _many([60, 31, 0, 33], 64)),
+    "two-parts-4096-rows-64": ("g8-64", 32, 32, _many([60, 31, 0, 33], 16)),
+    "staged-two-parts": ("g7-128", 32, 32, _many([400, 31, 255, 0], 37)),
 }
 
 
@@ -147,3 +151,25 @@ def test_a_key_that_is_not_a_number_shows_in_every_row_of_its_sequence(n, where)
         eng.close()
     assert torch.equal(out[0][0], out[1][0]) and torch.isfinite(out[0]).all()
     assert torch.isnan(out[1][1]).all()
+
+
+def test_a_key_that_is_not_a_number_among_many_rows_of_two_parts():
+    """As above for 64 sequences of 60 keys, two parts each (4096 rows to merge)."""
+    ms, Q, pt, n, B = SHAPES["g1-128"], 32, 32, 60, 64
+    w = synth.Weights(ms, 5)
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=3, n_pages=3 * B, max_batch=B, max_q=Q, max_tokens=0)
+    gen = torch.Generator(device=eng.device)
+    gen.manual_seed(3)
+    eng.kv_pool.view(torch.bfloat16)[:].normal_(generator=gen)
+    q = eng.i32(np.stack([synth.masked_block(ms, 40 + b, Q, Q // 2) for b in range(B)]))
+    table, pre = eng.i32(H.identity_table(eng, B)), eng.i32([n] * B)
+    good = eng.debug_hidden(q, pre, table, 1, max_prefix_len=n).clone()
+    assert torch.isfinite(good).all()
+    for b, at in ((5, 0), (50, n - 1)):
+        for head in range(ms.n_kv_heads):
+            eng.kv_slab(0, 0)[3 * b + at // pt, head, at % pt, 7] = float("nan")
+    bad = eng.debug_hidden(q, pre, table, 1, max_prefix_len=n)
+    others = [b for b in range(B) if b not in (5, 50)]
+    assert torch.isnan(bad[[5, 50]]).all() and torch.equal(bad[others], good[others])
+    assert eng.read_status() == 0
+    eng.close()
