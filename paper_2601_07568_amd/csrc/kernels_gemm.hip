@@ -357,6 +357,13 @@ struct GtGeom {
   static_assert(in_flight(0) < 64 && in_flight(1) < 64, "what the memory counter holds");
 };
 
+// A rotary pair in the epilogue of every q/k/v tile.  Which product is rounded is written out: left to the compiler, even and odd
+// tiles differed in one of 10^5 channels.
+__device__ __forceinline__ void gt_rotate(float x, float y, float c, float s, float& lo, float& hi) {
+  lo = fmaf(x, c, -(y * s));
+  hi = fmaf(y, c, x * s);
+}
+
 // HALF: K is 32 more than a multiple of 64.  The last stage's upper 32 come from past the end of the row, so their copies
 // are sent out of the descriptor, which leaves zeros in LDS.  A form of its own: it takes 19 .. 21 instructions more per stage
 // (128 x 128: 146 for 125).
@@ -396,13 +403,16 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // channels: 4.5 against 6.4 TB/s of plain reads with rows of 8 KiB.  Neighbouring columns of 256 weight rows begin 11
   // stages apart instead.  With more rows the activations no longer stay in the L2, which the column tiles share only in step.
   // (128 rows: 24576 x 4096 53.6 -> 51.7 us, 12288 x 4096 33.5 -> 30.9; a whole pass of 128 rows 782 -> 746 us.)  By the rows
-  // there are and not the host's bound, by weight rows and not tiles (gate/up: by 1920 features, which tiles of every width end
-  // at; per tile 43.9 us and so 44.9 for 128 x 24576 x 4096 on 128 x 96 tiles, 59.7 and 58.9 at 256 rows; tiles that would lie across
-  // the groups are left to calls that never start apart, gt_starts_apart): where a call with a device-resident total gets the
-  // same K split and the same q/k/v form as the sized call, it sums in the same order whatever its tiles.  Those two are
+  // there are and not the host's bound, by weight rows and not tiles (gate/up: by 1920 features, q/k/v with the rotary embedding:
+  // by 3840 rows, which tiles of every width end at; gate/up per tile 43.9 us and so 44.9 for 128 x 24576 x 4096 on 128 x 96 tiles,
+  // 59.7 and 58.9 at 256 rows; tiles that would lie across the groups are left to calls that never start apart, gt_starts_apart):
+  // where a call with a device-resident total gets the same K split and the same q/k/v form as the sized call, it sums in the same
+  // order whatever its tiles.  Those two are
   // chosen by the host's bound (4096 x 4096: three shares at 600 rows, one at 700), so it need not get them; and a
   // row's sums begin elsewhere when the rows of its call pass 256.
   const int k_rot = M <= GT_APART_ROWS ? 11 : 0;
+  constexpr int GROUP = SWIGLU ? GT_APART_SWIGLU : ROPE || ROPT ? GT_APART_ROPE : GT_APART_COLS;
+  static_assert(GROUP % TILE_N == 0 || RODD, "no tile lies across two groups");
   struct Item { int split, tm, n0, k_begin, k_end, k_first; bool ok, val; };
   auto item_at = [&](int it) -> Item {
     Item t{0, 0, 0, 0, k_all, 0, false, false};
@@ -417,7 +427,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     t.n0 = tn * TILE_N + a.n_first;
     t.k_begin = t.split * a.k_per;
     t.k_end = t.k_begin + a.k_per < k_all ? t.k_begin + a.k_per : k_all;
-    t.k_first = t.k_begin + (t.n0 / (SWIGLU ? 1920 : ROPT ? 3840 : 256) * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
+    t.k_first = t.k_begin + (t.n0 / GROUP * k_rot) % ((t.k_end - t.k_begin) / 64) * 64;
     t.ok = true;
     t.val = ROPE && t.n0 >= N + a.N2;                  // a tile of the value projection
     return t;
@@ -826,8 +836,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
             for (int g = 0; g < G2; ++g) {
               const float x = (WIDE ? acc[g][j][e] : acc[2 * g][j][e]) * rs, y = (WIDE ? acc[g + 2][j][e] : acc[2 * g + 1][j][e]) * rs;
               const float c = cs[e][WIDE ? g : 0], s = sn[e][WIDE ? g : 0];
-              lo[g] = x * c - y * s;
-              hi[g] = y * c + x * s;
+              gt_rotate(x, y, c, s, lo[g], hi[g]);
             }
             if (is_q) {
               const int so = row * N * 2;
@@ -932,8 +941,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
             float a0[4], a1[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              a0[q] = x0[q] * cs[k][e][q] - x1[q] * sn[k][e][q];
-              a1[q] = x1[q] * cs[k][e][q] + x0[q] * sn[k][e][q];
+              gt_rotate(x0[q], x1[q], cs[k][e][q], sn[k][e][q], a0[q], a1[q]);
             }
             lo[e * 2] = pack_bf16x2(a0[0], a0[1]); lo[e * 2 + 1] = pack_bf16x2(a0[2], a0[3]);
             hi[e * 2] = pack_bf16x2(a1[0], a1[1]); hi[e * 2 + 1] = pack_bf16x2(a1[2], a1[3]);

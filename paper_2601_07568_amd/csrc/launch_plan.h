@@ -118,8 +118,9 @@ inline AttnPlan attn_plan(int cus, int head_dim, int n_q_heads, int n_kv_heads, 
 }
 
 // ---- products of more than 64 rows (k_gemm_tile)
-// Up to this many real rows the column tiles start their sums apart, in groups of 256 columns (gate/up: of 1920 features).
-constexpr int GT_APART_ROWS = 256;
+// Up to this many real rows the column tiles start their sums apart, in groups of 256 columns (gate/up: of 1920 features, q/k/v
+// with the rotary embedding: of 3840).
+constexpr int GT_APART_ROWS = 256, GT_APART_COLS = 256, GT_APART_SWIGLU = 1920, GT_APART_ROPE = 3840;
 // Column tiles of the call may start their sums apart: every tile has to lie inside one group.  Residual tiles of 224 weight rows
 // (in groups of 1792, which they would fit, the other tiles take 0.2 .. 0.6 us more of 12 .. 50 at 72 .. 256 rows) and odd
 // gate/up tiles that do not begin at column 0 do not.  device_rows: the rows there are come from the device, M bounds them

@@ -191,7 +191,16 @@ def test_device_resident_total_sums_like_the_sized_call_whatever_its_tiles(d, ff
     """The tiles are chosen by the host's bound, where a sum starts by the rows there are: dllm_refresh_cache_dev with a
     capacity far above the total is dllm_refresh_cache of the total, bit for bit."""
     ms = synth.ModelShape(2, d, 1, 1, 64, ff, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"device-total-{d}-{ff}")
-    lens, cap, Q, pt = [120, 80], 1024, 16, 32
+    sized, device = sized_and_device_total(ms, [120, 80], 1024, seed)
+    for a, b in zip(sized, device):
+        assert torch.equal(a, b)
+    assert (sized[2][-16:] > 0.0).all()                     # the rows in flight are reported
+
+
+def sized_and_device_total(ms, lens, cap, seed):
+    """Pool, candidates, confidences and entropies of dllm_refresh_cache over prompts of these lengths, and of
+    dllm_refresh_cache_dev with the same ones behind a capacity."""
+    Q, pt = 16, 32
     total, B, mp = sum(lens), len(lens), 4
     w = device_weights(ms, seed)
     out = []
@@ -212,9 +221,29 @@ def test_device_resident_total_sums_like_the_sized_call_whatever_its_tiles(d, ff
         assert eng.read_status() == 0
         out.append([eng.kv_pool.clone(), cand[:total], conf[:total], ent[:total]])
         eng.close()
-    for a, b in zip(*out):
-        assert torch.equal(a, b)
-    assert (out[0][2][-Q:] > 0.0).all()                     # the rows in flight are reported
+    return out
+
+
+# (d, query heads, key heads, head width, prompts, capacity, tile of the sized call, tile at the capacity): q/k/v with the rotary
+# embedding, K of eight to 28 stages
+ROPE_PAIRS = [
+    (640, 32, 32, 128, [100, 29], 263, "128x128", "128x160"),
+    (1792, 32, 16, 64, [120, 80], 263, "128x96", "128x128"),
+    (512, 16, 16, 128, [100, 29], 1500, "128x128", "256x256"),
+    (1792, 32, 2, 128, [100, 29], 2048, "128x96", "256x160"),
+]
+
+
+@pytest.mark.parametrize("d,hq,hkv,dh,lens,cap,sized,device", ROPE_PAIRS)
+def test_device_resident_total_rotates_like_the_sized_call(d, hq, hkv, dh, lens, cap, sized, device):
+    """As above where the q/k/v product takes another tile at the capacity: the first layer's keys and values, bit for bit, and
+    everything behind them where the residual projections have the same K shares at both sizes (the first case)."""
+    layers = 2 if d == 640 else 1
+    ms = synth.ModelShape(layers, d, hq, hkv, dh, 512, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"device-total-rope-{d}-{dh}")
+    a, b = sized_and_device_total(ms, lens, cap, 2)
+    assert torch.equal(a[0], b[0]) and int(a[0].count_nonzero()) > 0
+    if layers == 2:
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
 
 
 @pytest.mark.parametrize("ms", [EDGE, LONG], ids=["head-dim-64", "head-dim-128"])
@@ -389,4 +418,6 @@ FORMS = ([("gate-up", b * q, ff, d, form) for d, ff, (b, q), form in ODD_TILES +
          [("gate-up", 8 * 127, 8512, 768, "64+128x128"), ("resid", 83 * 99, 2048, 768, "7+128x128"),
           ("gate-up", 8 * 127, 8544, 800, "64+128x128")] + KEPT +
          [(f"qkv:{hq}:{hkv}:{dh}", sum(lens), 0, d, form) for d, hq, hkv, dh, lens, n_cache, pt, form in ODD_ROPE] +
-         [("qkv:48:8:64", 231, 0, 1792, "128x96"), ("qkv:48:8:64", 230, 0, 1792, "128x96"), ("qkv:72:8:128", 400, 0, 640, "256x96")])
+         [("qkv:48:8:64", 231, 0, 1792, "128x96"), ("qkv:48:8:64", 230, 0, 1792, "128x96"), ("qkv:72:8:128", 400, 0, 640, "256x96")] +
+         [(f"qkv:{hq}:{hkv}:{dh}", n, 0, d, form) for d, hq, hkv, dh, lens, cap, *forms in ROPE_PAIRS for n, form in zip((sum(lens), cap), forms)] +
+         [("resid", n, 640, k, form) for n in (129, 263) for k, form in ((4096, "128x64/4"), (512, "128x64"))])
