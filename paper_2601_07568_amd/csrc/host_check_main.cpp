@@ -108,7 +108,9 @@ static int attn_plan_errors() {
 
 // "form" then (kind, rows, columns, K, starts_apart) for each product: what it launches on 256 CUs, a line each.  kind "gate-up"
 // (columns: features) or "resid" (at most four K shares, one above 2048 rows): [whole rounds' column tiles +] tile [/ K shares];
-// "qkv:query heads:key heads:channels" (columns: not read): the fused kernel's tile, or "split".
+// "qkv:query heads:key heads:channels" (columns: not read): the fused kernel's tile, or "split"; "attn:query heads:key
+// heads:channels:page" (rows: sequences, columns: query rows of each, K: the longest prefix): "staged" or "waves" along the keys of
+// a workgroup, row groups of a workgroup x parts along the keys.
 static int print_forms(int n, char** v) {
   using namespace dllm;
   static const char* const name[GT_N] = {"256x256", "128x256", "128x128", "128x64", "128x96", "128x160", "256x96", "256x160", "256x224"};
@@ -119,6 +121,15 @@ static int print_forms(int n, char** v) {
     if (sscanf(v[i], "qkv:%d:%d:%d", &hq, &hkv, &dh) == 3) {
       const bool fused = gt_qkv_fused(256, M, hq * dh, hkv * dh, dh, K, M <= 2048 ? 3 : 1);
       printf("%s\n", fused ? name[gt_rope_plan(256, M, hq * dh, hkv * dh, dh, K).tile] : "split");
+      continue;
+    }
+    int page;
+    if (sscanf(v[i], "attn:%d:%d:%d:%d", &hq, &hkv, &dh, &page) == 4) {
+      int64_t part_rows = (int64_t)M * N * hq * 8;            // (an engine for just this call)
+      if (part_rows < 65536) part_rows = 65536;
+      const AttnPlan p = attn_plan(256, dh, hq, hkv, M, N, M * N, K + N, page, part_rows, true);
+      if (p.staged) printf("staged:%dx%d\n", p.n_rg_wg, p.units);
+      else printf("%d:%dx%d\n", p.kspl, p.n_rg_wg, p.units / p.kspl);
       continue;
     }
     const GtForm f = strcmp(v[i], "resid") == 0 ? gt_resid_form(256, M, N, K, M <= 2048 ? 4 : 1, apart) : gt_swiglu_form(256, M, N, K, apart);

@@ -340,14 +340,13 @@ __global__ __launch_bounds__(256, WPS) void k_attn_step(const AttnArgs a) {
     for (int t = 0; t < QT; ++t) {
       float mx = -DEV_INF;
       for (int ww = 0; ww < KS; ++ww) mx = fmaxf(mx, sm_m[(ww * QT + t) * 16 + c]);
+      // A wave whose maximum is -inf has no keys (sums of 0) or none but scores that are NaN, and its NaN sum stays: 0 * NaN.
+      const float base = mx > -DEV_INF ? mx : 0.f;
       float ls = 0.f;
-      for (int ww = 0; ww < KS; ++ww) {
-        const float mw = sm_m[(ww * QT + t) * 16 + c];
-        ls += mw > -DEV_INF ? sm_l[(ww * QT + t) * 16 + c] * exp2f(mw - mx) : 0.f;
-      }
+      for (int ww = 0; ww < KS; ++ww) ls = fmaf(sm_l[(ww * QT + t) * 16 + c], exp2f(sm_m[(ww * QT + t) * 16 + c] - base), ls);
       m_all[t] = mx;
       l_all[t] = ls;
-      const float f = m_run[t] > -DEV_INF ? exp2f(m_run[t] - mx) : 0.f;
+      const float f = exp2f(m_run[t] - base);
 #pragma unroll
       for (int d = 0; d < DT; ++d) sm_o[(w * DT * QT + d * QT + t) * 64 + lane] = oacc[d][t] * f;
     }

@@ -186,11 +186,11 @@ def host_check():
 
 
 def test_gpu_tests_reach_the_tiles_that_they_name(host_check):
-    """The launches that the tile tests' products get, by the library's own rules (256 compute units), are the ones that the
+    """The launches that the tile and attention tests get, by the library's own rules (256 compute units), are the ones that the
     tests are written for: what the rules learn later must not leave a tile, a remainder or a K split untested unnoticed."""
     import subprocess
-    from tests import test_gpu_gemm_tiles as tiles
-    forms = tiles.FORMS
+    from tests import test_gpu_attention as attention, test_gpu_gemm_tiles as tiles
+    forms = tiles.FORMS + attention.PLANS
     args = [str(x) for kind, rows, cols, k, _ in forms for x in (kind, rows, cols, k, int(rows <= 256))]
     r = subprocess.run([host_check, "form", *args], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr[-2000:]

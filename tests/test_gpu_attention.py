@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from oracle import dllm_oracle as O
-from paper_2601_07568_amd import synth
+from paper_2601_07568_amd import binding, synth
 from tests import harness as H
 
 pytestmark = pytest.mark.gpu
@@ -173,3 +173,56 @@ def test_a_key_that_is_not_a_number_among_many_rows_of_two_parts():
     assert torch.isnan(bad[[5, 50]]).all() and torch.equal(bad[others], good[others])
     assert eng.read_status() == 0
     eng.close()
+
+
+# Launches in which every score of a row is NaN, or every score but those of the block's own keys: single waves and four that merge,
+# one, two, up to eight and more parts along the keys, and the staged kernel: (shape, rows, page, prefixes, form as host_check prints it)
+ALL_NAN = {
+    "one-wave-1-part": ("g1-128", 32, 32, [30], "1:1x1"),
+    "one-wave-2-parts": ("g1-128", 32, 32, [70, 90], "1:1x2"),
+    "one-wave-8-parts": ("g1-128", 32, 64, [500], "1:1x8"),
+    "one-wave-32-parts": ("g1-128", 32, 64, [2000], "1:1x32"),
+    "four-waves-1-part": ("g1-128", 32, 32, _many([200, 150, 224], 72), "4:1x1"),
+    "four-waves-2-parts": ("g1-128", 32, 32, _many([600, 550], 50), "4:1x2"),
+    "four-waves-8-parts": ("g1-64", 32, 64, _many([3000, 2500], 8), "4:1x8"),
+    "four-waves-16-parts": ("g1-128", 32, 64, _many([5000, 4200], 8), "4:1x16"),
+    "two-parts-4096-rows": ("g1-128", 32, 32, _many([60, 40], 64), "1:1x2"),
+    "staged-1-unit": ("g7-128", 32, 8, _many([60, 50], 300), "staged:7x1"),
+    "staged-2-units": ("g7-128", 32, 32, _many([400, 300], 37), "staged:7x2"),
+    "staged-24-units": ("g4-128", 32, 16, [1500], "staged:4x24"),
+}
+
+
+@pytest.mark.parametrize("poison", ["query", "keys"])
+@pytest.mark.parametrize("form", ALL_NAN)
+def test_rows_without_a_score_that_is_a_number_are_nan(form, poison):
+    """A channel of the query projection that is NaN, or all cached keys: the rows come out NaN from every form of the launch, not
+    zero from those that take an attention part without a finite maximum for an empty one."""
+    name, Q, pt, lens, _ = ALL_NAN[form]
+    ms, B = SHAPES[name], len(lens)
+    w = synth.Weights(ms, 5)
+    mp = (max(lens) + Q + pt - 1) // pt
+    eng = H.make_engine(ms, w, page_tokens=pt, max_pages_per_seq=mp, n_pages=B * mp, max_batch=B, max_q=Q, max_tokens=0)
+    gen = torch.Generator(device=eng.device)
+    gen.manual_seed(3)
+    eng.kv_pool.view(torch.bfloat16)[:].normal_(generator=gen)
+    if poison == "keys":
+        eng.kv_slab(0, 0).fill_(float("nan"))
+    else:
+        eng.layers[0]["wq"][5::ms.head_dim] = float("nan")
+        off = (-eng.packed.data_ptr()) % 256
+        eng._check(binding.lib().dllm_pack_weights(eng.ctx, eng._stream(), eng.packed.data_ptr() + off, eng.packed.numel() - 256))
+    q = eng.i32(np.stack([synth.masked_block(ms, 40 + b, Q, Q // 2) for b in range(B)]))
+    hidden = eng.debug_hidden(q, eng.i32(lens), eng.i32(H.identity_table(eng, B)), 1, max_prefix_len=max(lens))
+    assert torch.isnan(hidden).all(), int(torch.isfinite(hidden).sum())
+    assert eng.read_status() == 0
+    eng.close()
+
+
+# (kind, sequences, rows of each, longest prefix, form): tests/test_abi_host.py holds them against the library's own rules
+def _planned(shape_name, Q, pt, lens, form):
+    ms = SHAPES[shape_name]
+    return f"attn:{ms.n_q_heads}:{ms.n_kv_heads}:{ms.head_dim}:{pt}", len(lens), Q, max(lens), form
+
+
+PLANS = [_planned(*f) for f in ALL_NAN.values()]
