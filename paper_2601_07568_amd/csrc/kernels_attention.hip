@@ -89,6 +89,10 @@ __device__ __forceinline__ void attn_softmax_block(f32x4 (&s)[2][QT], int k0, in
   }
 }
 
+// What partial results are brought to: their largest maximum, or any number if that is -inf.  Those parts have no keys (sums of 0)
+// or none but scores that are NaN; their factor is 0 either way, and their NaN sums stay NaN.
+__device__ __forceinline__ float attn_base(float mx) { return mx > -DEV_INF ? mx : 0.f; }
+
 // WPS: waves per SIMD that the registers allow.  Left to itself the compiler takes 340 for heads of 128 channels and with
 // them the second wave of a SIMD, whose loads fill the time that the first one's products and round trips leave (us, one /
 // two waves, 32 key heads: 8 sequences of 700 keys 37.5 / 30.1 = 2.9 TB/s, 16 of 2048 126 / 117, one of 1024 14.7 / 14.6; 64
@@ -340,8 +344,7 @@ __global__ __launch_bounds__(256, WPS) void k_attn_step(const AttnArgs a) {
     for (int t = 0; t < QT; ++t) {
       float mx = -DEV_INF;
       for (int ww = 0; ww < KS; ++ww) mx = fmaxf(mx, sm_m[(ww * QT + t) * 16 + c]);
-      // A wave whose maximum is -inf has no keys (sums of 0) or none but scores that are NaN, and its NaN sum stays: 0 * NaN.
-      const float base = mx > -DEV_INF ? mx : 0.f;
+      const float base = attn_base(mx);
       float ls = 0.f;
       for (int ww = 0; ww < KS; ++ww) ls = fmaf(sm_l[(ww * QT + t) * 16 + c], exp2f(sm_m[(ww * QT + t) * 16 + c] - base), ls);
       m_all[t] = mx;
@@ -390,15 +393,11 @@ __global__ __launch_bounds__(256) void k_attn_combine2(const float* part_o, cons
   const int d = threadIdx.x % LR * 4;
   const float4 ml = *(const float4*)(part_ml + row * 4);               // (m0, l0, m1, l1)
   const f32x4 o0 = *(const f32x4*)(part_o + row * 2 * DH + d), o1 = *(const f32x4*)(part_o + (row * 2 + 1) * DH + d);
-  const float Mn = fmaxf(ml.x, ml.z);
-  float s0 = 0.f, s1 = 0.f, den = ml.y + ml.w;          // two empty units: 0; none but scores that are NaN: NaN
-  if (Mn > -DEV_INF) {
-    s0 = exp2f(ml.x - Mn); s1 = exp2f(ml.z - Mn);
-    den = fmaf(ml.w, s1, ml.y * s0);
-  }
+  const float base = attn_base(fmaxf(ml.x, ml.z));
+  const float s0 = exp2f(ml.x - base), s1 = exp2f(ml.z - base), den = fmaf(ml.w, s1, ml.y * s0);
   float v[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = den == 0.f ? 0.f : (Mn > -DEV_INF ? fmaf(o1[i], s1, o0[i] * s0) : 0.f) / den;
+  for (int i = 0; i < 4; ++i) v[i] = den == 0.f ? 0.f : fmaf(o1[i], s1, o0[i] * s0) / den;
   const int tok = (int)(row / Hq), head = (int)(row - (int64_t)tok * Hq);
   const int64_t at = mt > 0 ? frag_offset(tok, head * DH + d, mt) : row * DH + d;
   *(uint2*)(o + at) = make_uint2((uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16), (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16));
@@ -412,45 +411,43 @@ __global__ __launch_bounds__(512) void k_attn_combine(const float* part_o, const
   const int64_t row = (int64_t)blockIdx.x * (512 / DH) + threadIdx.x / DH;
   if (row >= n_rows) return;
   const int d = threadIdx.x % DH;
-  // eight units at a time: their loads are independent and issued together, the running
-  // (max, numerator, denominator) is rescaled between chunks
+  // eight units at a time; the running (max, numerator, denominator) is rescaled between chunks.  The maxima are waited for in
+  // front of the sums and outputs: a wave that asks for all of them at once keeps others' small loads waiting (us, at once / maxima
+  // ahead / waited for: 16384 rows of 64 in four parts 7.5 / 7.2 / 6.6, 7168 of 128 in five 6.8 / 6.5 / 6.0, in nine 11.3 /
+  // 10.9 / 9.6)
   float M = -DEV_INF, num = 0.f, den = 0.f;
   if (n_units == 2) {                                   // the common case at large batch: no padded chunk of eight
     const int64_t slot = row * 2;
     const float4 ml = *(const float4*)(part_ml + slot * 2);            // (m0, l0, m1, l1)
     const float o0 = part_o[slot * DH + d], o1 = part_o[(slot + 1) * DH + d];
-    const float Mn = fmaxf(ml.x, ml.z);
-    if (Mn > -DEV_INF) {
-      const float s0 = exp2f(ml.x - Mn), s1 = exp2f(ml.z - Mn);
-      den = fmaf(ml.w, s1, ml.y * s0);
-      num = fmaf(o1, s1, o0 * s0);
-    } else den = ml.y + ml.w;                           // empty units (0), or none but scores that are NaN (NaN)
+    const float base = attn_base(fmaxf(ml.x, ml.z)), s0 = exp2f(ml.x - base), s1 = exp2f(ml.z - base);
+    den = fmaf(ml.w, s1, ml.y * s0);
+    num = fmaf(o1, s1, o0 * s0);
   } else
   for (int u0 = 0; u0 < n_units; u0 += 8) {
     float mu[8], lu[8], ou[8];
 #pragma unroll
+    for (int i = 0; i < 8; ++i) mu[i] = part_ml[(row * n_units + min(u0 + i, n_units - 1)) * 2];
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const bool ok = u0 + i < n_units;
-      const int64_t slot = row * n_units + (ok ? u0 + i : n_units - 1);
-      const float2 ml = *(const float2*)(part_ml + slot * 2);
-      mu[i] = ok ? ml.x : -DEV_INF;
-      lu[i] = ml.y;
+      const int64_t slot = row * n_units + min(u0 + i, n_units - 1);
+      lu[i] = part_ml[slot * 2 + 1];
       ou[i] = part_o[slot * DH + d];
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mu[i] = u0 + i < n_units ? mu[i] : -DEV_INF;
     float Mn = M;
 #pragma unroll
     for (int i = 0; i < 8; ++i) Mn = fmaxf(Mn, mu[i]);
-    if (Mn == -DEV_INF) {                               // nothing but empty units so far, or scores that are NaN
-#pragma unroll
-      for (int i = 0; i < 8; ++i) den += lu[i];
-      continue;
-    }
-    const float r = exp2f(M - Mn);                      // exp2(-inf) = 0 on the first chunk
+    const float base = attn_base(Mn), r = exp2f(M - base);   // exp2(-inf) = 0 on the first chunk
     num *= r;
     den *= r;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float sc = exp2f(mu[i] - Mn);               // 0 for empty units
+      const float sc = exp2f(mu[i] - base);             // 0 for empty units
       den = fmaf(lu[i], sc, den);
       num = fmaf(ou[i], sc, num);
     }
