@@ -225,16 +225,36 @@ inline GtForm gt_swiglu_form(int cus, int M, int F, int K, bool starts_apart) {
   return gt_form(cus, M, 2 * F, K, p, GT_REST_TILES | (starts_apart ? 0u : GT_ODD_TILES));
 }
 
-// q/k/v with the rotary embedding and the K/V write in its epilogue.  Odd tiles only as one round: their epilogue needs the copies'
-// ring, so a workgroup has one tile.  us a stage and beside the stages, from 256 x 12288 x 4096 and 1024 x 4608 x 3584 (128 x 128 tiles / these: 48.3 / 42.7
-// and 66.9 / 52.7).
+// q/k/v with the rotary embedding and the K/V write in its epilogue.  What a launch of a step takes, fitted over 13 widths of 1536
+// .. 12288 weight rows, eight K of 1024 .. 5120 and 136 .. 2560 rows (1656 shapes, cold weights; standard deviation 4 .. 9 %).  Odd
+// tiles, which are launched as one round only, with 1.5 us against them, so that what they are taken for is a gain.
+inline double gt_rope_us(int cus, GtTile t, int M, int nw, int K) {
+  const double s = K / 64;
+  const double n = (double)((M + 127) / 128 * ((nw + 127) / 128)) / cus;       // 128 x 128 tiles a CU
+  const bool few = M <= GT_APART_ROWS;
+  switch (t) {
+    case GT_256x256: return 1.07 * s + 19.0;
+    case GT_128x96: return (few ? 0.38 : 0.41) * s + 12.5;
+    case GT_128x160: return (few ? 0.53 : 0.59) * s + 16.5;
+    case GT_256x96: return few ? 0.58 * s + 15.5 : 0.57 * s + 19.5;
+    case GT_256x160: return few ? 0.73 * s + 23.5 : 0.72 * s + 30.5;
+    default: return n <= 1.0 ? (few ? 0.47 : 0.52) * s + 10.0 : n <= 2.0 ? (0.53 + 0.22 * n) * s + 9.5 : (0.64 + 0.33 * n) * s + 15.0;
+  }
+}
+// Odd tiles only as one round: their epilogue needs the copies' ring, so a workgroup has one tile.  `us` (a stage and beside the
+// stages, from 256 x 12288 x 4096 and 1024 x 4608 x 3584: 128 x 128 tiles / these 48.3 / 42.7 and 66.9 / 52.7) is on the scale of the
+// other plans; at short sums it makes odd tiles look cheaper than they are, and two even tiles a CU dearer (steps, even / odd:
+// 1600 x 3072 x 1024 23.1 / 28.7, 768 x 6144 x 2048 33.6 / 36.2), so they also have to be the quicker ones by gt_rope_us.  Of those 1656
+// shapes 517 take an odd tile, in 0.88 of the even one's time as steps and 0.85 as prefills on average; nine lose 2 .. 4 %.
 inline GtPlan gt_rope_plan(int cus, int M, int dq, int dkv, int dh, int K) {
   const int nw = dq + 2 * dkv;
-  GtPlan best = gt_plan(cus, M, nw, K, 1, (dq % 256 == 0 && dkv % 256 == 0 && dh == 128 ? 0x1u : 0u) | 0x4u, 0.0);
+  const GtPlan even = gt_plan(cus, M, nw, K, 1, (dq % 256 == 0 && dkv % 256 == 0 && dh == 128 ? 0x1u : 0u) | 0x4u, 0.0);
+  const double even_us = gt_rope_us(cus, even.tile, M, nw, K);
   static const struct { GtTile t; int bm, bn; double stage, rest; } odd[4] = {
       {GT_128x96, 128, 96, 0.53, 9.0}, {GT_128x160, 128, 160, 0.75, 10.0}, {GT_256x96, 256, 96, 0.84, 10.0}, {GT_256x160, 256, 160, 1.09, 11.0}};
+  GtPlan best = even;
   for (const auto& o : odd) {
-    if ((M + o.bm - 1) / o.bm * ((nw + o.bn - 1) / o.bn) > cus) continue;
+    if ((M + o.bm - 1) / o.bm * ((nw + o.bn - 1) / o.bn) > cus || gt_rope_us(cus, o.t, M, nw, K) > even_us) continue;
     const double us = o.stage * (K / 64) + o.rest;
     if (us < best.us) best = GtPlan{o.t, 1, K, us};
   }

@@ -225,12 +225,14 @@ def sized_and_device_total(ms, lens, cap, seed):
 
 
 # (d, query heads, key heads, head width, prompts, capacity, tile of the sized call, tile at the capacity): q/k/v with the rotary
-# embedding, K of eight to 28 stages
+# embedding, K of eight to 36 stages
 ROPE_PAIRS = [
-    (640, 32, 32, 128, [100, 29], 263, "128x128", "128x160"),
+    (1792, 36, 12, 64, [126, 124], 300, "128x96", "128x128"),
     (1792, 32, 16, 64, [120, 80], 263, "128x96", "128x128"),
     (512, 16, 16, 128, [100, 29], 1500, "128x128", "256x256"),
-    (1792, 32, 2, 128, [100, 29], 2048, "128x96", "256x160"),
+    (1792, 16, 16, 128, [100, 29], 1500, "128x96", "256x256"),
+    (1536, 32, 32, 64, [100, 29], 1500, "128x128", "256x160"),
+    (2304, 24, 8, 128, [120, 80], 1024, "128x96", "128x160"),
 ]
 
 
@@ -238,7 +240,7 @@ ROPE_PAIRS = [
 def test_device_resident_total_rotates_like_the_sized_call(d, hq, hkv, dh, lens, cap, sized, device):
     """As above where the q/k/v product takes another tile at the capacity: the first layer's keys and values, bit for bit, and
     everything behind them where the residual projections have the same K shares at both sizes (the first case)."""
-    layers = 2 if d == 640 else 1
+    layers = 2 if hq == 36 else 1
     ms = synth.ModelShape(layers, d, hq, hkv, dh, 512, 600, 599, dtype="bf16", lm_head_scale=8.0, name=f"device-total-rope-{d}-{dh}")
     a, b = sized_and_device_total(ms, lens, cap, 2)
     assert torch.equal(a[0], b[0]) and int(a[0].count_nonzero()) > 0
@@ -279,9 +281,9 @@ def test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt):
 # across the ends of q and k and end behind v; rows end inside a tile; runs of eight tokens end at a page's or a prompt's end.
 ODD_ROPE = [
     (1792, 48, 8, 64, [129, 70, 31], [129, 64, 0], 24, "128x96"),
-    (1024, 64, 4, 64, [500, 3, 300, 190], [499, 3, 296, 150], 32, "128x160"),
-    (640, 72, 8, 128, [257, 143], [257, 100], 24, "256x96"),
-    (960, 72, 8, 128, [400, 299], [399, 299], 64, "256x160"),
+    (2240, 68, 4, 64, [500, 3, 300, 190], [499, 3, 296, 150], 32, "128x160"),
+    (2560, 34, 2, 128, [257, 143, 650], [257, 100, 649], 24, "256x96"),
+    (1408, 72, 3, 128, [400, 299, 201], [399, 299, 0], 64, "256x160"),
 ]
 
 
@@ -291,7 +293,7 @@ def test_keys_and_values_written_from_odd_tiles(d, hq, hkv, dh, lens, n_cache, p
     test_keys_and_values_written_by_the_projection(ms, lens, n_cache, pt)
 
 
-@pytest.mark.parametrize("i,seqs,Q", [(0, 3, 77), (0, 2, 115), (2, 4, 100)], ids=["128x96", "128x96-one-tile-nearly-empty", "256x96"])
+@pytest.mark.parametrize("i,seqs,Q", [(0, 3, 77), (0, 2, 115), (2, 10, 105)], ids=["128x96", "128x96-one-tile-nearly-empty", "256x96"])
 def test_steps_on_odd_rope_tiles(i, seqs, Q):
     """Denoise steps on the same tiles: every row of q, and the rows' keys and values through the attention."""
     d, hq, hkv, dh = ODD_ROPE[i][:4]
@@ -418,6 +420,6 @@ FORMS = ([("gate-up", b * q, ff, d, form) for d, ff, (b, q), form in ODD_TILES +
          [("gate-up", 8 * 127, 8512, 768, "64+128x128"), ("resid", 83 * 99, 2048, 768, "7+128x128"),
           ("gate-up", 8 * 127, 8544, 800, "64+128x128")] + KEPT +
          [(f"qkv:{hq}:{hkv}:{dh}", sum(lens), 0, d, form) for d, hq, hkv, dh, lens, n_cache, pt, form in ODD_ROPE] +
-         [("qkv:48:8:64", 231, 0, 1792, "128x96"), ("qkv:48:8:64", 230, 0, 1792, "128x96"), ("qkv:72:8:128", 400, 0, 640, "256x96")] +
+         [("qkv:48:8:64", 231, 0, 1792, "128x96"), ("qkv:48:8:64", 230, 0, 1792, "128x96"), ("qkv:34:2:128", 1050, 0, 2560, "256x96")] +
          [(f"qkv:{hq}:{hkv}:{dh}", n, 0, d, form) for d, hq, hkv, dh, lens, cap, *forms in ROPE_PAIRS for n, form in zip((sum(lens), cap), forms)] +
-         [("resid", n, 640, k, form) for n in (129, 263) for k, form in ((4096, "128x64/4"), (512, "128x64"))])
+         [("resid", n, 1792, k, form) for n in (250, 300) for k, form in ((2304, "128x64/3"), (512, "128x64"))])
