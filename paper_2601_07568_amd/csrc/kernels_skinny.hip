@@ -524,22 +524,26 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
 // 34.6 / 32.1; 4608 x 3584 32 rows 13.3 / 12.6; LM head 126464 x 4096 32 rows 191 / 186, 48 rows 203 / 194.)  More stages than two
 // in flight bring nothing; registers beyond a wave's share cost up to twice the time.  Gate/up of 16 rows in stages of two steps / one:
 // 8192 x 2048 14.1 / 12.7, 5504 x 2048 11.0 / 9.6, 12288 x 4096 37.2 / 37.3; six tiles x 32 rows two / one 37.3 / 36.4.
-template <int NT, int MT, int NW, int EPI>
+// SHORT (q/k/v of at most 32 rows in two tiles a workgroup): stages of one step, four of them in flight.  The long stages give the
+// eight waves 1024 of K at a time, which where that leaves a rest is a round of half-idle waves, and beside a memory that nearly all CUs
+// ask shows (launch_sk_qkv).
+template <int NT, int MT, int NW, int EPI, bool SHORT = false>
 struct SkCfg {
   static constexpr bool HEAD = EPI == SK_LMSTATS || EPI == SK_F32;
-  static constexpr int JB = EPI == SK_RESID ? 4
+  static constexpr int JB = SHORT ? 1
+                            : EPI == SK_RESID ? 4
                             : EPI == SK_QKV ? (NT == 2 ? (MT <= 4 ? 4 : 2) : MT == 8 ? 1 : 2)
                             : HEAD          ? (MT == 1 ? 4 : 2)
                                             : MT >= 3 || EPI == SK_SWIGLU ? 1 : 2;
-  static constexpr int D = EPI == SK_RESID ? (MT <= 2 ? 3 : 2) : EPI == SK_QKV ? (NT == 3 && MT <= 2 ? 3 : 2) : HEAD ? 2 : MT == 4 ? 2 : 3;
+  static constexpr int D = SHORT ? 5 : EPI == SK_RESID ? (MT <= 2 ? 3 : 2) : EPI == SK_QKV ? (NT == 3 && MT <= 2 ? 3 : 2) : HEAD ? 2 : MT == 4 ? 2 : 3;
   static constexpr int TPC = EPI == SK_SWIGLU ? 2 : NT;
   // waves per SIMD that the registers are to allow: two 8-wave workgroups per CU for the narrow gate/up form, so that one
   // workgroup's prologue and reduction overlap the other's streaming
   static constexpr int WPS = EPI == SK_SWIGLU && NT == 2 ? 4 : (NW == 4 && MT <= 2) ? 1 : 2;
 };
-template <int NT, int MT, int NW, int EPI>
+template <int NT, int MT, int NW, int EPI, bool SHORT = false>
 static hipError_t sk_go(hipStream_t s, const SkArgs& a, int grid) {
-  using C = SkCfg<NT, MT, NW, EPI>;
+  using C = SkCfg<NT, MT, NW, EPI, SHORT>;
   k_skinny<NT, MT, NW, EPI, C::JB, C::TPC, C::D, C::WPS><<<grid, NW * 64, 0, s>>>(a);
   return hipGetLastError();
 }
@@ -774,7 +778,15 @@ hipError_t launch_sk_qkv(dllm_ctx* c, hipStream_t s, const StepGeom& g, int laye
   // tiles took 128 workgroups of three tiles, most of them with one to throw away: 16.0 -> 13.1 us at 32 rows of 3584,
   // 21.4 -> 19.0 at 64, 27.8 -> 24.3 at 128).
   const int grid = sk_qkv_grid(c);
-  if (sk_qkv_apart(c) <= device_cus()) return sk_launch_mt<2, SK_NW, SK_QKV>(s, a, grid);
+  if (sk_qkv_apart(c) <= device_cus()) {
+    // Short stages on more than 13/16 of the CUs where the long ones leave a rest of K (us, long / short at 16 and 32 rows: 216
+    // workgroups of K = 2304 10.0 / 8.9, 11.2 / 10.6; 240 of 2560 11.6 / 10.6, 13.4 / 12.4; 252 of 2688 12.1 / 11.2, 14.1 / 12.8 and of
+    // 3584 14.0 / 13.2, 16.0 / 15.4; 224 of 3584 13.3 / 12.7, 15.1 / 15.5; but 208 of 3328 12.2 / 12.3, 14.0 / 14.8, 144 of 1536 7.2 / 8.2, 8.2
+    // / 9.4, and without a rest 240 of 3072 12.1 / 11.7, 13.8 / 13.8, of 2048 10.2 / 10.1, 11.5 / 12.0).
+    if (g.T <= 32 && a.K % (4 * 32 * SK_NW) != 0 && grid > device_cus() * 13 / 16)
+      return g.T <= 16 ? sk_go<2, 1, SK_NW, SK_QKV, true>(s, a, grid) : sk_go<2, 2, SK_NW, SK_QKV, true>(s, a, grid);
+    return sk_launch_mt<2, SK_NW, SK_QKV>(s, a, grid);
+  }
   return sk_launch_mt<3, SK_NW, SK_QKV>(s, a, grid);
 }
 

@@ -34,6 +34,13 @@ def test_rows_of_a_step(ms, B, Q):
     run(ms, [40 + 9 * b for b in range(B)], Q)
 
 
+# 240 workgroups of the q/k/v product, value tiles apart, K that leaves a rest of 1024: short stages up to 32 rows; K without one
+@pytest.mark.parametrize("B,Q", [(1, 1), (1, 16), (1, 17), (4, 8), (3, 11)])
+@pytest.mark.parametrize("d,hq,hkv,dh", [(264, 40, 40, 64), (1096, 72, 24, 64), (2088, 20, 20, 128), (1024, 40, 40, 64)])
+def test_qkv_of_few_rows_on_nearly_all_compute_units(B, Q, d, hq, hkv, dh):
+    run(shape(d, hq, hkv, dh, 256), [40 + 9 * b for b in range(B)], Q)
+
+
 @pytest.mark.parametrize("B,Q", [(1, 65), (1, 80), (3, 27), (1, 96), (1, 111), (4, 32), (1, 129)])
 @pytest.mark.parametrize("ms", [DEEP, HEADS, GROUPED], ids=["deep", "heads", "grouped"])
 def test_qkv_of_65_to_128_rows(ms, B, Q):
