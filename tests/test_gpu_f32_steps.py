@@ -13,9 +13,15 @@ from tests import harness as H
 pytestmark = pytest.mark.gpu
 ODD = synth.ModelShape(2, 196, 4, 2, 64, 300, 1003, 1002, dtype="f32", lm_head_scale=8.0, name="odd-f32")
 WIDE = synth.ModelShape(1, 1040, 3, 1, 128, 2052, 515, 514, dtype="f32", lm_head_scale=8.0, name="wide-f32")
+# 130 workgroups of 16 residual or gate/up columns, 144 of rotary pairs, 129 of 64 vocabulary columns: with more than one row tile
+# more than the 256 compute units hold at a time, so a workgroup keeps all rows (narrower models have one for every 16 rows)
+BIG = synth.ModelShape(1, 2068, 32, 4, 128, 2068, 8250, 8249, dtype="f32", lm_head_scale=8.0, name="big-f32")
+BIG_64 = synth.ModelShape(1, 2080, 66, 33, 64, 4100, 8200, 8199, dtype="f32", lm_head_scale=8.0, name="big-f32-64")
 
 
-@pytest.mark.parametrize("ms,lens,Q,pt", [(ODD, [1], 1, 4), (ODD, [15, 16, 17], 7, 4), (ODD, [130], 64, 16), (ODD, [31], 33, 8),
+@pytest.mark.parametrize("ms,lens,Q,pt", [(BIG, [17], 17, 8), (BIG, [40], 32, 16), (BIG, [5, 0, 33], 16, 16), (BIG, [20, 64], 32, 32),
+                                          (BIG_64, [3], 32, 4), (BIG_64, [9], 33, 16), (BIG_64, [16, 2, 7], 17, 8),
+                                          (ODD, [1], 1, 4), (ODD, [15, 16, 17], 7, 4), (ODD, [130], 64, 16), (ODD, [31], 33, 8),
                                           (WIDE, [127, 1], 16, 16), (WIDE, [300], 48, 12), (WIDE, [0, 5], 32, 32)])
 def test_float_step_around_the_tiles(ms, lens, Q, pt):
     w = synth.Weights(ms, 4)
