@@ -74,7 +74,6 @@ static bool build_map(const dllm_config* c, Workspace* m) {
   m->q_valid_eff = take((size_t)c->max_batch * 4);
   m->rscale = take(t_max * 4);
   m->ss = take((size_t)64 * ((((size_t)c->d_model + 15) / 16 + 3) / 4 * 4) * 4);
-  m->delta_stride = (int64_t)SK_MAX_ROWS * c->d_model;
   m->lg_delta_rows = c->dtype == DLLM_BF16 ? (int64_t)(t_max < (size_t)LG_DELTA_ROWS ? t_max : (size_t)LG_DELTA_ROWS) : 0;
   m->lg_delta_stride = m->lg_delta_rows * c->d_model;
   {

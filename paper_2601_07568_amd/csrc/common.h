@@ -220,7 +220,6 @@ struct Workspace {
   size_t rscale;       // float [Tmax]                  row normalisation factors of the current GEMM input (bfloat16 models)
   size_t ss;           // float [64][d/16 rounded up to 4]   partial sums of squares of the rows of the skinny path's GEMM input
   size_t delta;        // float open residual sums of K-split residual projections: [LG_MAX_DELTA][lg_delta_rows, d]
-  int64_t delta_stride;
   int64_t lg_delta_rows, lg_delta_stride;   // large path: rows the buffer covers (0 = none), floats per split
   size_t qkvp;         // float [LG_QKV_SPLITS][lg_delta_rows, dq + 2 dkv]: K-split partial sums of the fused q/k/v product
   int64_t qkvp_stride;

@@ -440,8 +440,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     const int rows = M - t.tm * BM < BM ? M - t.tm * BM : BM;
     return rsrc(a.A + (int64_t)t.tm * BM * K, (int64_t)rows * K * 2);
   };
-  // ROPE_ODD: the rows of two copies may lie apart, so a descriptor covers one copy of 8 rows, or two of the same 16
-  constexpr int ND = !ROPT ? 1 : CW % 2 ? CW : CW / 2, DC = CW / ND;   // descriptors of a wave, copies of each
+  // ROPE_ODD: the rows of two copies may lie apart, so each copy of 8 rows has a descriptor of its own
+  constexpr int ND = ROPT ? CW : 1;
   auto rsrc_w = [&](const Item& t, int d = 0) -> gt_rsrc {
     const int n0 = t.n0;
     const bf16_t* base = a.W;
@@ -455,8 +455,8 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     if constexpr (ROPT) {
       // stacked as above, in groups of 32 rows: 16 channels of a head of q or k and the 16 that they rotate with, half a head on;
       // or 32 value channels
-      const int R = n0 + (w * CW + d * DC) * 8, half = a.dh >> 1;
-      rows = DC * 8;
+      const int R = n0 + (w * CW + d) * 8, half = a.dh >> 1;
+      rows = 8;
       if (R >= N + a.N2) {
         base = a.W3;
         row = R - N - a.N2;
@@ -502,7 +502,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   };
   auto w_row = [&](int q) -> int {                              // weight row of the instruction's first LDS row
     if constexpr (ODD) return ((w & 1) * CW + q) * 8;
-    if constexpr (ROPT) return q % DC * 8;                      // (the rest is in the descriptor)
+    if constexpr (ROPT) return 0;                               // (it is in the descriptor)
     const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
     if constexpr (STATS || RODD) return q * 8;                  // (w * BN / 4 is in the lanes' offsets: eight scalar registers less)
     // both members of a rotary pair (channels j and j + DH/2 of a head) in one lane, in tiles i and i + 2 (WIDE: two
@@ -530,7 +530,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
                                              16, (VO ? vA[q] : (q & 1) ? vA1 : vA0) + past(ka, q), VO ? ka * 2 : ka * 2 + q * 16 * K, 0, 0);
   };
   auto copy_w = [&](int slot, int q) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(ROPT ? rwd[q / DC] : rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (ODD ? odd_lds(q) * 128 : (w * CW + q) * 1024)),
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ROPT ? rwd[q] : rw, (__attribute__((address_space(3))) void*)(sW + slot * G::W_BYTES + (ODD ? odd_lds(q) * 128 : (w * CW + q) * 1024)),
                                              16, (VO ? vW[q] : (q & 1) ? vW1 : vW0) + past(kw, q), VO ? kw * 2 : kw * 2 + w_row(q) * 2 * K, 0, 0);
   };
   auto adv_a = [&]() { GT_ADVANCE(ka, ksa, kba, kea, nxt, ra = rna); };
