@@ -97,7 +97,8 @@ __device__ __forceinline__ float attn_base(float mx) { return mx > -DEV_INF ? mx
 // them the second wave of a SIMD, whose loads fill the time that the first one's products and round trips leave (us, one /
 // two waves, 32 key heads: 8 sequences of 700 keys 37.5 / 30.1 = 2.9 TB/s, 16 of 2048 126 / 117, one of 1024 14.7 / 14.6; 64
 // rows, one of 1237 keys 22.2 / 18.8).  One wave where several row groups of a workgroup read the same keys through long
-// units: their shared lines last longer in the L1 (64 rows, 8 sequences of up to 4096 keys 185 / 196).
+// units: their shared lines last longer in the L1 (a layer of 256 channels, one / two waves, 32 key heads, 64 rows: 6 sequences of
+// 2500 keys 158 / 169, of 6000 249 / 287, 5 of 4000 179 / 194; 80 rows, 3 of 5000 177 / 204).
 template <int DH, int QT, int WPS>
 __global__ __launch_bounds__(256, WPS) void k_attn_step(const AttnArgs a) {
   constexpr int KK = DH / 32;   // k-steps of Q K^T

@@ -61,10 +61,15 @@ inline AttnPlan attn_plan(int cus, int head_dim, int n_q_heads, int n_kv_heads, 
   // key heads as heads 21.8 / 23.1, 39.6 / 43.4).
   if (p.staged && Q > 0 && G > 1 && n_rg > 4 && groups <= cus && nkb <= 24 * parts) p.staged = false;
   if (!p.staged && Q > 0 && raised && few_groups) {
-    // (seven or eight blocks in all: 4 sequences of 200 keys as two single waves 12.4, as four waves of one workgroup 11.7; pages
-    // that are no multiple of 32 tokens have longer chains per block: one sequence of 1000 keys in pages of 24 16.3 / 15.2)
+    // Seven or eight blocks in all: four waves of one workgroup instead of one wave with all of them or two that need the combine
+    // kernel, as long as the workgroups are one round (a layer of 256 channels, us, single waves / this, 190 .. 220 keys: 32 key heads, 4
+    // sequences 54.4 / 53.7, 5 59.1 / 57.3, 8 62.9 / 61.2, but 10 78.0 / 78.7, 13 80.4 / 80.9; 16 key heads, 8 sequences 56.7 / 55.3, 16 60.8
+    // / 59.2, but 20 64.3 / 64.9; heads of 64 channels, 32 key heads, 4 sequences 47.3 / 45.3, 8 53.0 / 51.5, 10 54.9 / 54.9).  Longer ones
+    // have four waves by the rule below where a single wave would have more than eight blocks, the same launch; where there are two
+    // parts of up to eight each, two single waves gain over one workgroup as often as they lose.  Pages that are no multiple of 32
+    // tokens have longer chains per block: one sequence of 1000 keys in pages of 24 16.3 / 15.2.
     const bool narrow = groups < 2 * cus - cus / 4;
-    const bool merge = narrow && parts <= 2 && (nkb == 7 || nkb == 8);
+    const bool merge = groups <= cus && parts <= 2 && (nkb == 7 || nkb == 8);
     if (merge) parts = 1;
     const int64_t per_wave = (nkb + parts - 1) / parts;
     p.kspl = merge || (narrow && per_wave > (page_tokens % 32 == 0 ? 8 : 4)) ? 4 : 1;
@@ -83,10 +88,11 @@ inline AttnPlan attn_plan(int cus, int head_dim, int n_q_heads, int n_kv_heads, 
   if (want < 1) want = 1;
   int64_t by_work = p.staged ? (nkb + 7) / 8 : (nkb + 1) / 2;   // staged kernel: at least four 64-key blocks per unit ...
   if (p.staged && by_work > 1) {   // (a single unit needs no combine)
-    // ... or two, or one, where that still leaves CUs without a workgroup (kernel + combine, us, four / two / one, 4 key heads of
-    // 7: 512 keys 17.3 + 4.8 / 15.5 + 4.8 / 13.7 + 4.8 in 12 / 20 / 36 workgroups, 2048 keys 19.7 + 4.8 / 16.7 + 5.3 / 15.6 + 7.2
-    // in 36 / 68 / 132, 8000 keys 22.0 + 6.1 / 20.9 + 10.0 / - in 128 / 252, 4 sequences of 2048 22.6 + 6.4 / 31.5 + 9.1 / - in
-    // 144 / 272)
+    // ... or two, or one, where that still leaves CUs without a workgroup (a layer of 256 channels, us, four / two / one: 4 key
+    // heads of 7, 16 rows, 512 keys 32.7 / 31.7 / 31.6 in 12 / 20 / 36 workgroups, 1000 keys 33.9 / 31.6 / 31.9 in 16 / 32 / 64, 2048
+    // keys 35.2 / 34.3 / 36.3 in 36 / 68 / 132, 4 sequences of 2048 50.5 / 57.0 / 58.2 in 144 / 272 / 528; 8 key heads of 4, 32 rows, 512 keys
+    // 38.2 / 37.3 / 37.5, 1000 keys 40.0 / 39.1 / 40.6, 2048 keys 41.6 / 42.1 / 50.5; 128 rows of 32 key heads, 500 keys 60.7 / 59.0 /
+    // 66.5, which keeps four for its 96 workgroups, 1000 keys 60.5 / 69.4 / 71.5)
     const int64_t per_unit = (int64_t)p.n_chunks * B * n_kv_heads;
     if ((nkb + 1) / 2 * per_unit <= 64) by_work = (nkb + 1) / 2;
     else if ((nkb + 3) / 4 * per_unit <= 128) by_work = (nkb + 3) / 4;
@@ -94,11 +100,11 @@ inline AttnPlan attn_plan(int cus, int head_dim, int n_q_heads, int n_kv_heads, 
   int64_t units = want < by_work ? want : by_work;
   if (p.staged && units < least) units = least;
   if (units > most) units = most;
-  // one row group per KV head (a batch-1 block on a multi-head model): four units share a workgroup and
-  // merge their partial results in LDS, which leaves a quarter of the partials to write and re-read
+  // One row group per KV head, more of them than CUs but not two rounds, and long sequences (the others have returned above): four units share a workgroup and merge their partial results in LDS, which leaves a
+  // quarter of the partials to write and re-read, or none.  (A layer of 256 channels, us, units of single waves with their combine /
+  // this, 32 key heads: 9 sequences of 1100 / 2000 keys 120.2 / 117.7, 147.4 / 144.4, 10 124.5 / 118.7, 154.4 / 146.7, 13 136.7 / 123.5,
+  // 172.8 / 157.1; of 4000 keys 9 sequences 208.3 / 221.4, 10 221.7 / 225.5, 12 248.8 / 234.2.)
   p.kspl = 1;
-  // (also where more than 512 such workgroups are a second round: 32 sequences of 1024 keys, 32 key heads, as two single-wave
-  // units with their combine 126 + 16 us, as one workgroup of four waves 129)
   if (!p.staged && n_rg == 1 && raised && by_work >= 4) {
     p.kspl = 4;
     int64_t parts = (nkb + 2 * p.kspl - 1) / (2 * p.kspl);

@@ -97,32 +97,36 @@ def _many(lens, n):
 
 # (shape, rows, page, prefixes): a workgroup per row group, keys in parts of single waves and of four that merge, with one part and
 # several, and a part that a short sequence leaves empty; grouped queries with room for a workgroup per row group; and, with more
-# row groups than CUs, the staged kernel for seven to ten of them
+# row groups than CUs, the staged kernel for seven to ten of them; between one and two rounds of row groups long sequences in one
+# workgroup each.  Last: the form as host_check prints it
 FORMS = {
-    "one-wave-64-parts": ("g1-128", 32, 64, [5000]),
-    "four-waves-8-parts": ("g1-64", 32, 64, [3000, 64, 700, 33, 2000, 0, 1500, 31]),
-    "four-waves-8-parts-page-24": ("g1-64", 32, 24, [3000, 64, 700, 33, 2000, 0, 1500, 31]),
-    "four-waves-1-part": ("g1-128", 32, 32, _many([200, 224, 0, 150, 31], 72)),
-    "one-wave-1-part": ("g1-128", 32, 32, _many([300, 31, 100], 230)),
-    "two-row-groups": ("g1-128", 64, 64, [1237, 5, 64]),
-    "two-row-groups-48": ("g1-128", 48, 96, [4000, 77]),
-    "three-row-groups": ("g1-64", 72, 128, [2500, 600, 9]),
-    "grouped-one-sequence": ("g7-128", 32, 64, [2048]),
-    "grouped-7500-keys": ("g7-64", 32, 64, [24000]),
-    "staged-7": ("g7-128", 32, 8, _many([480, 31, 33, 1500, 0], 40)),
-    "staged-7-64": ("g7-64", 32, 64, _many([480, 31, 33, 1500, 0], 40)),
-    "staged-8": ("g4-128", 64, 16, _many([63, 65, 700, 0], 17)),
-    "staged-10": ("g8-64", 40, 8, _many([23, 24, 88, 300], 30)),
+    "one-wave-64-parts": ("g1-128", 32, 64, [5000], "1:1x64"),
+    "four-waves-8-parts": ("g1-64", 32, 64, [3000, 64, 700, 33, 2000, 0, 1500, 31], "4:1x8"),
+    "four-waves-8-parts-page-24": ("g1-64", 32, 24, [3000, 64, 700, 33, 2000, 0, 1500, 31], "4:1x8"),
+    "four-waves-1-part": ("g1-128", 32, 32, _many([200, 224, 0, 150, 31], 72), "4:1x1"),
+    "one-wave-1-part": ("g1-128", 32, 32, _many([300, 31, 100], 230), "1:1x1"),
+    "one-wave-1-part-second-round": ("g1-128", 32, 32, _many([200, 224, 0, 150, 31], 129), "1:1x1"),
+    "four-waves-1-part-long": ("g1-128", 32, 32, _many([1100, 3, 40, 0, 64], 150), "4:1x1"),
+    "two-row-groups-long": ("g1-128", 64, 64, _many([3300, 5, 64, 700], 75), "1:2x6"),
+    "two-row-groups": ("g1-128", 64, 64, [1237, 5, 64], "1:1x16"),
+    "two-row-groups-48": ("g1-128", 48, 96, [4000, 77], "1:1x32"),
+    "three-row-groups": ("g1-64", 72, 128, [2500, 600, 9], "4:1x8"),
+    "grouped-one-sequence": ("g7-128", 32, 64, [2048], "1:1x32"),
+    "grouped-7500-keys": ("g7-64", 32, 64, [24000], "4:1x32"),
+    "staged-7": ("g7-128", 32, 8, _many([480, 31, 33, 1500, 0], 40), "staged:7x6"),
+    "staged-7-64": ("g7-64", 32, 64, _many([480, 31, 33, 1500, 0], 40), "staged:7x6"),
+    "staged-8": ("g4-128", 64, 16, _many([63, 65, 700, 0], 17), "staged:8x3"),
+    "staged-10": ("g8-64", 40, 8, _many([23, 24, 88, 300], 30), "staged:8x2"),
     # two parts of at least 4096 (token, head) rows
-    "two-parts-4096-rows": ("g1-128", 32, 32, _many([60, 31, 0, 33], 64)),
-    "two-parts-4096-rows-64": ("g8-64", 32, 32, _many([60, 31, 0, 33], 16)),
-    "staged-two-parts": ("g7-128", 32, 32, _many([400, 31, 255, 0], 37)),
+    "two-parts-4096-rows": ("g1-128", 32, 32, _many([60, 31, 0, 33], 64), "1:1x2"),
+    "two-parts-4096-rows-64": ("g8-64", 32, 32, _many([60, 31, 0, 33], 16), "1:1x2"),
+    "staged-two-parts": ("g7-128", 32, 32, _many([400, 31, 255, 0], 37), "staged:7x2"),
 }
 
 
 @pytest.mark.parametrize("form", FORMS)
 def test_forms_of_the_launch(form, monkeypatch):
-    name, Q, pt, lens = FORMS[form]
+    name, Q, pt, lens, _ = FORMS[form]
     monkeypatch.setitem(LENS, Q, lens)
     test_key_block_edges_growing_scores_and_nan_slots(name, Q, pt, 20.0)
 
@@ -225,4 +229,4 @@ def _planned(shape_name, Q, pt, lens, form):
     return f"attn:{ms.n_q_heads}:{ms.n_kv_heads}:{ms.head_dim}:{pt}", len(lens), Q, max(lens), form
 
 
-PLANS = [_planned(*f) for f in ALL_NAN.values()]
+PLANS = [_planned(*f) for f in (*FORMS.values(), *ALL_NAN.values())]
