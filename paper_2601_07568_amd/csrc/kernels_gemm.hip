@@ -491,7 +491,7 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
   // features between consecutive LDS rows of a tile
   constexpr int FS = STATS || ODD || RODD || ROPT ? 1 : (ROPE ? (WIDE ? 2 : 1) : (SWIGLU ? TN / 2 : TN));
   const int vA0 = (w * (BM / 4) + l8) * K * 2 + piece * 16, vA1 = HALF ? vA0 + (piece < 4 ? 64 : -64) : vA0 ^ 64;
-  const int vW0 = ((STATS || RODD ? w * (BN / 4) : 0) + l8 * FS) * K * 2 + piece * 16, vW1 = HALF ? vW0 + (piece < 4 ? 64 : -64) : vW0 ^ 64;
+  const int vW0 = ((STATS ? w * (BN / 4) : 0) + l8 * FS) * K * 2 + piece * 16, vW1 = HALF ? vW0 + (piece < 4 ? 64 : -64) : vW0 ^ 64;
   const int out0 = piece < 4 ? 0 : 0x40000000, out1 = piece < 4 ? 0x40000000 : 0;   // HALF: added in the last stage (even, odd q)
   // ODD: waves 0 and 1 copy the gate rows, waves 2 and 3 the up rows, eight at a time in the order of the features; a wave's
   // first 4*(TN/2) eights are its whole tiles, the other two its half of the last
@@ -504,7 +504,10 @@ __device__ __forceinline__ void gemm_tile_body(const LgArgs& a) {
     if constexpr (ODD) return ((w & 1) * CW + q) * 8;
     if constexpr (ROPT) return 0;                               // (it is in the descriptor)
     const int R = w * (BN / 4) + q * 8, c = R & 31, i = (R >> 5) % TN, hw = R / (32 * TN);
-    if constexpr (STATS || RODD) return q * 8;                  // (w * BN / 4 is in the lanes' offsets: eight scalar registers less)
+    if constexpr (RODD) return R;
+    // (w * BN / 4 is in the lanes' offsets: eight scalar registers less.  512 rows of 126464 x 4096 533 -> 513 us; the 224-row residual
+    // tiles lose 0.4 % by it, 1012 -> 1017 us at 15348 x 3584 x 18944 and x 3584 on average)
+    if constexpr (STATS) return q * 8;
     // both members of a rotary pair (channels j and j + DH/2 of a head) in one lane, in tiles i and i + 2 (WIDE: two
     // neighbouring channels per lane) or in tiles 2g and 2g + 1
     else if constexpr (WIDE) return hw * 128 + (i >> 1) * 64 + 2 * c + (i & 1);
