@@ -521,7 +521,10 @@ __global__ __launch_bounds__(NW * 64, WPS) void k_skinny(const SkArgs a) {
 // Stages are therefore as long as the registers allow with two of them in flight, and ask for all their weights first: then
 // the activations behind them come at the L2's pace.  (Short stages, weights and activations in turn / these, us: residual 32 rows of
 // 4096 x 12288 25.6 / 24.8, 64 rows 34.9 / 33.7, 16 rows of 2048 x 2048 8.6 / 7.0; q/k/v 12288 x 4096 64 rows 28.3 / 26.8, 96 rows
-// 34.6 / 32.1; 4608 x 3584 32 rows 13.3 / 12.6; LM head 126464 x 4096 32 rows 191 / 186, 48 rows 203 / 194.)  More stages than two
+// 34.6 / 32.1; 4608 x 3584 32 rows 13.3 / 12.6; LM head 126464 x 4096 32 rows 191 / 186, 48 rows 203 / 194.  Three-tile q/k/v of
+// at most 32 rows had stages of two steps before; the order alone, in turn / weights first, whole layers of 4096 channels, 32 heads
+// and 12288 features at 8, 16, 24, 32, 48, 64 rows: 100.7 / 101.2, 102.0 / 102.7, 111.5 / 111.3, 112.9 / 112.7, 129.0 / 127.5, 144.6 /
+// 141.2; of 3072 and 5120 channels the second is the better one at every count.)  More stages than two
 // in flight bring nothing; registers beyond a wave's share cost up to twice the time.  Gate/up of 16 rows in stages of two steps / one:
 // 8192 x 2048 14.1 / 12.7, 5504 x 2048 11.0 / 9.6, 12288 x 4096 37.2 / 37.3; six tiles x 32 rows two / one 37.3 / 36.4.
 // SHORT (q/k/v of at most 32 rows in two tiles a workgroup): stages of one step, four of them in flight.  The long stages give the
